@@ -94,7 +94,8 @@ int64_t gvq_num_slices(const gvq_basis_t* h);
  * as samples of the *aggregated* gradient.  For every basis b the sample set is every
  * full slice of its range in each of the L gradients (a partial tail slice is not a
  * sample): mu_b = sample mean, C_b = covariance with normaliser 1/n, accumulated in
- * float64 from exact products; C_b is eigendecomposed in float64 (Jacobi rotations),
+ * float64 from exact products; C_b is eigendecomposed in float64 (Householder tridiagonal
+ * form, bisection, inverse iteration),
  * eigenvalues sorted in decreasing order, U_b = eigenvectors of the k largest, each
  * negated if needed so that its largest-magnitude entry (lowest index on ties) is
  * positive.  Results stay on the device inside the handle.  A basis whose range holds
@@ -114,8 +115,9 @@ int gvq_fit_basis_first_slice(gvq_basis_t* h, const void* const* grads, int L, v
 
 /*
  * Waits for `stream`'s work, then reports on the last fit: *max_sweeps (may be NULL)
- * receives the largest Jacobi sweep count over the bases.  Returns GVQ_ENOCONV if a basis
- * hit the sweep limit, GVQ_ENONFINITE if an eigenvalue is not finite (e.g. NaN/Inf in a
+ * receives the largest iteration count of the eigensolver over the bases (0: every covariance is
+ * zero).  Returns GVQ_ENOCONV if an
+ * eigenvector of a basis did not converge, GVQ_ENONFINITE if an eigenvalue is not finite (e.g. NaN/Inf in a
  * fit gradient), GVQ_ENOTFIT if no fit was run.
  */
 int gvq_fit_status(const gvq_basis_t* h, int* max_sweeps, void* stream);

@@ -69,7 +69,7 @@ int gvq_basis_destroy(gvq_basis_t* h)
 {
     if (!h) return GVQ_OK;
     (void)hipDeviceSynchronize();
-    void* dev[] = {h->d_offs, h->d_tile_block, h->d_U, h->d_Upc, h->d_Upd, h->d_Upb, h->d_Uws, h->d_Umu, h->d_mu, h->d_eig, h->d_cov, h->d_V, h->d_part, h->d_part2, h->d_mom, h->d_nsamp, h->d_bjA, h->d_bjQ, h->d_bjfro, h->d_jstate, h->d_ltile, h->d_sweeps, h->d_ksel, h->d_loss_slice, h->d_loss_part};
+    void* dev[] = {h->d_offs, h->d_tile_block, h->d_U, h->d_Upc, h->d_Upd, h->d_Upb, h->d_Uws, h->d_Umu, h->d_mu, h->d_eig, h->d_cov, h->d_eA, h->d_eT, h->d_eZ, h->d_eLU, h->d_part, h->d_part2, h->d_mom, h->d_nsamp, h->d_ltile, h->d_sweeps, h->d_ksel, h->d_loss_slice, h->d_loss_part};
     for (void* p : dev)
         if (p) (void)hipFree(p);
     for (gvq_plan& pl : h->plan) {
@@ -145,7 +145,7 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
             h->P = (int)wgs * streams;
             width = (size_t)gvq_moments_packed_width(d);
         }
-        const size_t B = (size_t)n_blocks, W = (size_t)d * d + d, n = (size_t)(d + (d & 1));
+        const size_t B = (size_t)n_blocks, W = (size_t)d * d + d;
         TRY(hipMalloc((void**)&h->d_offs, sizeof(int64_t) * (B + 1)));
         TRY(hipMalloc((void**)&h->d_U, sizeof(float) * B * d * k));
         TRY(hipMalloc((void**)&h->d_mu, sizeof(float) * B * d));
@@ -175,16 +175,10 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
         }
         TRY(hipMalloc((void**)&h->d_eig, sizeof(double) * B * d));
         TRY(hipMalloc((void**)&h->d_cov, sizeof(double) * B * d * d));
-        if (d > GVQ_LDS_EIGEN_MAX_D) {
-            const size_t np = (size_t)gvq_bj_padded(d);
-            TRY(hipMalloc((void**)&h->d_V, sizeof(double) * B * np * np));
-            TRY(hipMalloc((void**)&h->d_bjA, sizeof(double) * B * np * np));
-            TRY(hipMalloc((void**)&h->d_bjQ, sizeof(double) * B * gvq_bj_q_doubles(d)));
-            TRY(hipMalloc((void**)&h->d_bjfro, sizeof(double) * B * (1 + 2 * 32)));   // norm, then the check's partial sums
-            TRY(hipMalloc((void**)&h->d_jstate, sizeof(int) * B * 4));
-        } else {
-            TRY(hipMalloc((void**)&h->d_V, sizeof(double) * B * n * n));
-        }
+        TRY(hipMalloc((void**)&h->d_eA, sizeof(double) * B * (d + 1) * d));
+        TRY(hipMalloc((void**)&h->d_eT, sizeof(double) * B * 5 * d));
+        TRY(hipMalloc((void**)&h->d_eZ, sizeof(double) * B * k * d));
+        if (gvq_eigen_lu_doubles(d, k)) TRY(hipMalloc((void**)&h->d_eLU, sizeof(double) * B * gvq_eigen_lu_doubles(d, k)));
         if (part_doubles) {
             TRY(hipMalloc((void**)&h->d_part, sizeof(double) * B * part_doubles));
         } else {
@@ -192,7 +186,7 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
             TRY(hipMalloc((void**)&h->d_part2, sizeof(double) * B * (size_t)((h->P + 31) / 32) * width));
         }
         TRY(hipMalloc((void**)&h->d_mom, sizeof(double) * B * W));
-        TRY(hipMalloc((void**)&h->d_nsamp, sizeof(unsigned long long) * B));
+        TRY(hipMalloc((void**)&h->d_nsamp, sizeof(unsigned long long) * 2 * B));
         TRY(hipMalloc((void**)&h->d_sweeps, sizeof(int) * B));
         TRY(hipMalloc((void**)&h->d_ksel, sizeof(int) * B));
         TRY(hipMalloc((void**)&h->d_loss_slice, sizeof(float) * (size_t)S));

@@ -1,0 +1,833 @@
+// Eigensolver of the basis refresh (GradiVeQ Section 2, PCA paragraph: "applies SVD to obtain the eigen matrix U
+// and eigen vector s"), float64, any slice length and any number of bases side by side:
+//
+//   tridiagonal    A = Q T Q^T by Householder reflections.  Up to 128 rows one work-group holds the whole matrix in
+//                  its registers; a larger matrix is first cut down to its trailing 128 x 128 block by one launch
+//                  per column, spread over the chip.
+//   bisect         every eigenvalue of T by multisection on Sturm counts, a group of lanes per eigenvalue.
+//   inverse        the k wanted eigenvectors of T by inverse iteration from random vectors, one lane each.
+//   orthonormalise modified Gram-Schmidt over those k vectors (eigenvalues of the noise lie so close together that
+//                  their vectors come out of the iteration correct but not orthogonal to float64 precision).
+//   back           Q z for each of them.
+//   out            order, sign and conversion to the fp32 basis.
+//
+// It replaces Jacobi methods, which compute all d eigenvectors and need 12 - 14 sweeps over the matrix whatever k is:
+// d = 128 4.0 -> 0.5 ms, d = 768 (k = 96) 22 -> 5.6 ms.  What bounds it is the chain of dependent steps (d reflections,
+// each needing the whole of the one before), not arithmetic or memory.
+//
+// Every kernel returns at once for a basis whose matrix is zero (unit vectors, eigenvalues 0) or not finite
+// (eigenvalues NaN, reported by gvq_fit_status), which the largest |entry| says (EigenArgs::norm).
+#include "gvq_eigen.h"
+
+// ---- helpers ----------------------------------------------------------------------------------------------------
+
+template <int CTRL> __device__ __forceinline__ double dpp_move(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+#define DPP_XOR1 0xB1          // quad_perm [1,0,3,2]
+#define DPP_XOR2 0x4E          // quad_perm [2,3,0,1]
+#define DPP_HALF_MIRROR 0x141  // lane i of 8 -> 7 - i
+#define DPP_MIRROR 0x140       // lane i of 16 -> 15 - i
+#define DPP_ROR4 0x124
+#define DPP_ROR8 0x128
+
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Sum over the 64 lanes, the same bits in every lane.
+__device__ __forceinline__ double wave_sum(double v)
+{
+    v += dpp_move<DPP_XOR1>(v);
+    v += dpp_move<DPP_XOR2>(v);
+    v += dpp_move<DPP_HALF_MIRROR>(v);
+    v += dpp_move<DPP_MIRROR>(v);
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
+// 1/x to the last bit or two for normal x and 1/x: the hardware's approximation and two Newton steps.
+__device__ __forceinline__ double fast_rcp(double x)
+{
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return y;
+}
+
+#define EIG_E_FLOOR 1e-20     // smallest off-diagonal entry of T relative to the matrix: decoupled blocks stay coupled
+                              // by far less than rounding, which spares every recurrence its special cases
+#define EIG_PIVOT 2.3e-16     // smallest pivot relative to the matrix
+
+// Power of two that brings the largest entry below 1.
+__device__ __forceinline__ int eig_scale_exp(unsigned long long norm)
+{
+    return -(__builtin_amdgcn_frexp_exp(__longlong_as_double((long long)norm)));
+}
+
+// ---- covariance from the moments ----------------------------------------------------------------------------------
+
+// cov = G/n - mu mu^T, mu, and the largest |entry| (as the bits of a positive double: NaN and Inf sort above all).
+__global__ __launch_bounds__(256) void cov_kernel(const double* mom_all, const unsigned long long* nsamp, int d,
+                                                  double* cov_all, float* mu, unsigned long long* norm, int* sweeps)
+{
+    const int b = blockIdx.y;
+    const size_t W = (size_t)d * d + d;
+    const double* mom = mom_all + (size_t)b * W;
+    double* cov = cov_all + (size_t)b * d * d;
+    const double ns = (double)nsamp[b];
+    double big = 0.0, bad = 0.0;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < d * d; i += gridDim.x * 256) {
+        const int r = i / d, c = i - r * d;
+        // upper and lower halves of the Gram sum are bit-identical (same products, same order);
+        // true divisions: a constant gradient then gives exactly C = 0
+        const double v = ns > 0.0 ? mom[i] / ns - (mom[(size_t)d * d + r] / ns) * (mom[(size_t)d * d + c] / ns) : 0.0;
+        cov[i] = v;
+        big = fmax(big, fabs(v));
+        if (v != v) bad = v;   // fmax drops a NaN
+    }
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < d; i += gridDim.x * 256)
+        mu[(size_t)b * d + i] = ns > 0.0 ? (float)(mom[(size_t)d * d + i] / ns) : 0.0f;
+    eig_norm_max(bad != bad ? bad : big, norm + b);
+    if (blockIdx.x == 0 && threadIdx.x == 0) sweeps[b] = EIG_SOLVES;
+}
+
+// ---- tridiagonal ----------------------------------------------------------------------------------------------------
+//
+// Step i reflects the entries i+1.. of column i onto its first: H = I - tau v v^T with v[i+1] = 1, and A <- H A H is the
+// rank-two update A - v w^T - w v^T, w = p - (tau/2)(p.v) v, p = tau A v.  Row r of the working matrix is
+// a.A + (r+1) n; the reflector of step i goes to row i-1, which nobody needs any more.
+
+// One column of a matrix with more than 128 rows.  Every work-group repeats the O(n) part (the previous step's w, the
+// column, its reflector) and then takes eight rows: the rank-two update of the step before, in place, and their
+// entries of p for this step -- so a step is one launch, whose end is the only synchronisation it needs.  NE = number of
+// 64-column pieces of a row.  Bound by that chain (launch, two block-wide sums, one dot product: about 5 us a
+// column); its memory traffic is a few per cent of that.
+template <int NE>
+__global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
+{
+    __shared__ double vp[NE * 64], wp[NE * 64], vn[NE * 64], red[2][4], first;
+    const int b = blockIdx.y, n = a.n, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (eig_skip(a.norm[b])) return;
+    double* A = a.A + (size_t)b * a.A_stride;
+    const double* cur = i == 0 ? a.src + (size_t)b * a.src_stride : A + n;   // the matrix before the pending update
+    double* T = a.T + (size_t)b * 5 * a.t_ld;
+    const double* p_old = T + (size_t)(3 + ((i + 1) & 1)) * a.t_ld;
+    double* p_new = T + (size_t)(3 + (i & 1)) * a.t_ld;
+
+    // this wave's two rows, requested first
+    const int r0 = i + 1 + (blockIdx.x * 4 + wave) * 2;
+    double x[2][NE];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int q = 0; q < NE; ++q) {
+            const int c = 64 * q + lane;
+            x[u][q] = (r0 + u < n && c > i && c < n) ? cur[(size_t)(r0 + u) * n + c] : 0.0;
+        }
+
+    // column i (row i, the matrix is symmetric) with the previous step's update; at most four entries per thread
+    constexpr int NT = (NE + 3) / 4;
+    double col[NT], v[NT], p[NT];
+    double tau = 0.0, s = 0.0, pi = 0.0;
+    const double* v_old = A + (size_t)(i - 1) * n;   // not touched at i = 0
+    if (i > 0) { tau = T[2 * a.t_ld + i - 1]; pi = p_old[i]; }
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+        const int c = i + tid + 256 * u;
+        col[u] = c < n ? cur[(size_t)i * n + c] : 0.0;
+        v[u] = i > 0 && c < n ? v_old[c] : 0.0;
+        p[u] = i > 0 && c < n ? p_old[c] : 0.0;
+        s = fma(p[u], v[u], s);
+    }
+    s = wave_sum(s);
+    if (lane == 0) red[0][wave] = s;
+    __syncthreads();
+    s = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
+    const double half = 0.5 * tau * s, wi = pi - half;   // v[i] of the previous step is 1
+    double n2 = 0.0;
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+        const int c = i + tid + 256 * u;
+        const double w = fma(-half, v[u], p[u]);
+        if (i > 0) col[u] -= fma(v[u], wi, w);
+        if (c < n) { vp[c] = v[u]; wp[c] = w; }
+        if (c > i + 1) n2 = fma(col[u], col[u], n2);
+        if (c == i + 1) first = col[u];
+    }
+    n2 = wave_sum(n2);
+    if (lane == 0) red[1][wave] = n2;
+    __syncthreads();
+    n2 = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+    const double x0 = first;
+    double beta = x0, t = 0.0, sc = 0.0;
+    if (n2 > 0.0) {
+        beta = sqrt(fma(x0, x0, n2));
+        if (x0 > 0.0) beta = -beta;
+        t = (beta - x0) / beta;
+        sc = 1.0 / (x0 - beta);
+    }
+    double* R = A + (size_t)i * n;   // row i-1 of the matrix
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+        const int c = i + tid + 256 * u;
+        if (c >= n) continue;
+        const double h = c == i + 1 ? 1.0 : c > i ? col[u] * sc : 0.0;
+        vn[c] = h;
+        if (blockIdx.x == 0) {
+            if (c > i) R[c] = h;
+            else { T[i] = col[u]; T[a.t_ld + i] = beta; T[2 * a.t_ld + i] = t; }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int r = r0 + u;
+        if (r >= n) continue;   // uniform over the wave
+        const double vr = vp[r], wr = wp[r];
+        double dot = 0.0;
+#pragma unroll
+        for (int q = 0; q < NE; ++q) {
+            const int c = 64 * q + lane;
+            if (c <= i || c >= n) continue;
+            double y = x[u][q];
+            if (i > 0) y -= fma(vr, wp[c], wr * vp[c]);
+            A[(size_t)(r + 1) * n + c] = y;
+            dot = fma(y, vn[c], dot);
+        }
+        dot = wave_sum(dot);
+        if (lane == 0) p_new[r] = t * dot;
+    }
+}
+
+// The whole matrix (n <= 128), or what is left of a larger one from row i0 on, in the registers of one work-group:
+// thread (ti, tj) holds the 4 x 4 entries of rows 4 ti.. and columns 4 tj...  Per step: the column goes through LDS
+// (one barrier), every wave forms the reflector for itself, multiplies its tiles with it, sums over tj inside the wave,
+// the entries of p go through LDS (second barrier), update.  About 1000 cycles a step; the matrix never leaves the
+// registers (in LDS, 128 x 128 doubles would take 1000 cycles to read once).
+template <int TJ>
+__global__ __launch_bounds__(TJ * TJ) void tri_small_kernel(EigenArgs a, int i0)
+{
+    constexpr int N = 4 * TJ, PL = N > 64 ? N / 64 : 1;   // entries of a vector per lane
+    __shared__ double colb[2][N], pb[N];
+    const int b = blockIdx.x, n = a.n, nl = n - i0, tid = threadIdx.x, lane = tid & 63;
+    const int ti = tid / TJ, tj = tid % TJ;
+    if (eig_skip(a.norm[b])) return;
+    double* A = a.A + (size_t)b * a.A_stride;
+    const double* cur = i0 == 0 ? a.src + (size_t)b * a.src_stride : A + n;
+    double* T = a.T + (size_t)b * 5 * a.t_ld;
+
+    double x[4][4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int gr = i0 + 4 * ti + r, gc = i0 + 4 * tj + c;
+            x[r][c] = gr < n && gc < n ? cur[(size_t)gr * n + gc] : 0.0;
+        }
+    if (i0 > 0) {
+        // the update that the last of the steps before this kernel left pending
+        const double* p_old = T + (size_t)(3 + ((i0 + 1) & 1)) * a.t_ld;
+        const double* v_old = A + (size_t)(i0 - 1) * n;
+        const double tau = T[2 * a.t_ld + i0 - 1];
+        double s = 0.0;
+        for (int c = i0 + lane; c < n; c += 64) s = fma(p_old[c], v_old[c], s);
+        const double half = 0.5 * tau * wave_sum(s);
+        double vr[4], wr[4], vc[4], wc[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = i0 + 4 * ti + u, c = i0 + 4 * tj + u;
+            vr[u] = r < n ? v_old[r] : 0.0;
+            wr[u] = r < n ? fma(-half, vr[u], p_old[r]) : 0.0;
+            vc[u] = c < n ? v_old[c] : 0.0;
+            wc[u] = c < n ? fma(-half, vc[u], p_old[c]) : 0.0;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[r][c] -= fma(vr[r], wc[c], wr[r] * vc[c]);
+    }
+
+    __builtin_amdgcn_s_waitcnt(0);   // the reflectors overwrite rows of the matrix: every thread's loads have come back
+    __syncthreads();
+    for (int ib = 0; ib < nl; ib += 4) {
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            const int i = ib + cb;
+            if (i >= nl) break;
+            double* col = colb[cb & 1];
+            if (tj == ib / 4) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) col[4 * ti + r] = x[r][cb];
+            }
+            __syncthreads();
+            // nothing to reflect in the last two columns
+            if (i >= nl - 2) {
+                if (tid == 0) {
+                    T[i0 + i] = col[i];
+                    T[a.t_ld + i0 + i] = i + 1 < nl ? col[i + 1] : 0.0;
+                    T[2 * a.t_ld + i0 + i] = 0.0;
+                }
+                continue;
+            }
+            double xl[PL], n2 = 0.0;
+#pragma unroll
+            for (int u = 0; u < PL; ++u) {
+                const int c = PL * lane + u;
+                xl[u] = c < N ? col[c] : 0.0;   // entries past the matrix are zero
+                if (c > i + 1) n2 = fma(xl[u], xl[u], n2);
+            }
+            n2 = wave_sum(n2);
+            const double x0 = col[i + 1];
+            double beta = x0, t = 0.0, sc = 0.0;
+            if (n2 > 0.0) {
+                beta = sqrt(fma(x0, x0, n2));
+                if (x0 > 0.0) beta = -beta;
+                t = (beta - x0) / beta;
+                sc = 1.0 / (x0 - beta);
+            }
+            if (tid < 64) {
+#pragma unroll
+                for (int u = 0; u < PL; ++u) {
+                    const int c = PL * lane + u;
+                    if (c > i && c < nl) A[(size_t)(i0 + i) * n + i0 + c] = c == i + 1 ? 1.0 : xl[u] * sc;
+                }
+                if (lane == 0) {
+                    T[i0 + i] = col[i];
+                    T[a.t_ld + i0 + i] = beta;
+                    T[2 * a.t_ld + i0 + i] = t;
+                }
+            }
+            if (t == 0.0) continue;   // uniform over the work-group; the next column takes the other buffer
+            double vr[4], vc[4], y[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int r = 4 * ti + u, c = 4 * tj + u;
+                vr[u] = r == i + 1 ? 1.0 : r > i ? col[r] * sc : 0.0;
+                vc[u] = c == i + 1 ? 1.0 : c > i ? col[c] * sc : 0.0;
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                y[r] = x[r][0] * vc[0];
+#pragma unroll
+                for (int c = 1; c < 4; ++c) y[r] = fma(x[r][c], vc[c], y[r]);
+            }
+            // sum over tj; lane bit 0 keeps rows 0,1 or 2,3, bit 1 one of the two
+            {
+                const bool o1 = lane & 1, o2 = lane & 2;
+                const double s0 = o1 ? y[0] : y[2], s1 = o1 ? y[1] : y[3];
+                const double k0 = (o1 ? y[2] : y[0]) + dpp_move<DPP_XOR1>(s0);
+                const double k1 = (o1 ? y[3] : y[1]) + dpp_move<DPP_XOR1>(s1);
+                double z = (o2 ? k1 : k0) + dpp_move<DPP_XOR2>(o2 ? k0 : k1);
+                if (TJ >= 16) {
+                    z += dpp_move<DPP_ROR4>(z);
+                    z += dpp_move<DPP_ROR8>(z);
+                    if (TJ == 32) z += __shfl_xor(z, 16, 64);
+                } else {
+                    z += __shfl_xor(z, 4, 64);
+                }
+                if (tj < 4) pb[4 * ti + 2 * (lane & 1) + ((lane >> 1) & 1)] = t * z;
+            }
+            __syncthreads();
+            double s = 0.0;
+#pragma unroll
+            for (int u = 0; u < PL; ++u) {
+                const int c = PL * lane + u;
+                const double v = c == i + 1 ? 1.0 : c > i ? xl[u] * sc : 0.0;
+                if (c < N) s = fma(pb[c], v, s);
+            }
+            const double half = 0.5 * t * wave_sum(s);
+            double wr[4], wc[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                wr[u] = fma(-half, vr[u], pb[4 * ti + u]);
+                wc[u] = fma(-half, vc[u], pb[4 * tj + u]);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) x[r][c] -= fma(vr[r], wc[c], wr[r] * vc[c]);
+        }
+    }
+}
+
+// ---- eigenvalues of T -----------------------------------------------------------------------------------------------
+//
+// The number of eigenvalues below s is the number of sign changes in p_0 = 1, p_1 = d_0 - s, p_{i+1} = (d_i - s) p_i -
+// e_{i-1}^2 p_{i-1}.  The three-term form (one dependent fused multiply-add a step, rescaled every eight steps) is a
+// quarter of the latency of the quotient form with its division.  A group of `lanes` lanes cuts the interval of its
+// eigenvalue into lanes + 1 pieces per pass.  All eigenvalues start from one interval and follow one tree of cuts, so
+// they come out ordered.
+__global__ __launch_bounds__(256) void bisect_kernel(EigenArgs a)
+{
+    __shared__ double2 t[GVQ_MAX_D];   // d_i, e_{i-1}^2
+    __shared__ double bound[2];
+    const int b = blockIdx.y, n = a.n, tid = threadIdx.x;
+    const unsigned long long norm = a.norm[b];
+    double* eig = a.eig + (size_t)b * a.eig_ld;
+    const int g = blockIdx.x * (256 / a.lanes) + tid / a.lanes;   // this group's eigenvalue, in increasing order
+    const int l = tid % a.lanes;
+    if (blockIdx.x == 0)
+        for (int i = n + tid; i < a.eig_ld; i += 256) eig[i] = norm >= EIG_INF_BITS ? __longlong_as_double(-1ll) : 0.0;
+    if (eig_skip(norm)) {
+        if (l == 0 && g < n) eig[g] = norm ? __longlong_as_double(-1ll) : 0.0;   // NaN where the input was not finite
+        return;
+    }
+    const double* T = a.T + (size_t)b * 5 * a.t_ld;
+    const int ex = eig_scale_exp(norm);
+    double lo = 0.0, hi = 0.0;
+    for (int i = tid; i < n; i += 256) {
+        const double d = ldexp(T[i], ex);
+        const double e0 = i ? fmax(fabs(ldexp(T[a.t_ld + i - 1], ex)), EIG_E_FLOOR) : 0.0;
+        const double e1 = i + 1 < n ? fmax(fabs(ldexp(T[a.t_ld + i], ex)), EIG_E_FLOOR) : 0.0;
+        t[i] = make_double2(d, e0 * e0);
+        lo = fmin(lo, d - e0 - e1);
+        hi = fmax(hi, d + e0 + e1);
+    }
+    if (tid == 0) { bound[0] = 0.0; bound[1] = 0.0; }
+    __syncthreads();
+    // |bounds| as integers: positive doubles order like their bits
+    atomicMax((unsigned long long*)&bound[0], (unsigned long long)__double_as_longlong(fmax(-lo, 0.0)));
+    atomicMax((unsigned long long*)&bound[1], (unsigned long long)__double_as_longlong(fmax(hi, 0.0)));
+    __syncthreads();
+    const double slack = 1e-15 * (bound[0] + bound[1]) + 1e-18;
+    lo = -bound[0] - slack;
+    hi = bound[1] + slack;
+
+    const double step = 1.0 / (a.lanes + 1);
+    const int passes = a.lanes == 64 ? 9 : a.lanes == 16 ? 14 : 18;   // (lanes + 1)^passes > 2^54
+    for (int pass = 0; pass < passes; ++pass) {
+        const double w = (hi - lo) * step, s = fma(w, (double)(l + 1), lo);
+        double p0 = 1.0, p1 = t[0].x - s;
+        unsigned int below = (unsigned int)__double2hiint(p1) >> 31;
+        int i = 1;
+        for (; i + 8 <= n; i += 8) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const double2 q = t[i + u];
+                const double p2 = fma(q.x - s, p1, -(q.y * p0));
+                below += (unsigned int)(__double2hiint(p2) ^ __double2hiint(p1)) >> 31;
+                p0 = p1;
+                p1 = p2;
+            }
+            const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
+            p0 = ldexp(p0, -e);
+            p1 = ldexp(p1, -e);
+        }
+        for (; i < n; ++i) {
+            const double2 q = t[i];
+            const double p2 = fma(q.x - s, p1, -(q.y * p0));
+            below += (unsigned int)(__double2hiint(p2) ^ __double2hiint(p1)) >> 31;
+            p0 = p1;
+            p1 = p2;
+        }
+        // cut points with at most g eigenvalues below them are at or left of eigenvalue g
+        const unsigned long long left = __ballot(below <= (unsigned int)g);
+        const int cut = a.lanes == 64 ? __popcll(left)
+                                      : __popcll((left >> ((tid & 63) / a.lanes * a.lanes)) & ((1ull << a.lanes) - 1));
+        const double base = lo;
+        lo = cut > 0 ? fma(w, (double)cut, base) : base;
+        if (cut < a.lanes) hi = fma(w, (double)(cut + 1), base);
+    }
+    if (l == 0 && g < n) {
+        const double v = ldexp(0.5 * (lo + hi), -ex);
+        eig[n - 1 - g] = a.clamp && v < 0.0 ? 0.0 : v;
+    }
+}
+
+// ---- eigenvectors of T ------------------------------------------------------------------------------------------------
+//
+// One lane per vector: LU with partial pivoting of T - s I (s the eigenvalue), then two solves, the first with a random
+// right-hand side of U alone.  A solve multiplies what other eigenvectors contribute by (rounding / gap), so two leave
+// nothing of any whose eigenvalue can be told apart.  Vectors of eigenvalues that cannot are independent random
+// members of their common space, which the orthonormalisation sorts out.  NV vectors per work-group (one wave); the
+// factors sit in LDS up to n = 128, else in global memory, entry-major so that a step's access is one contiguous run.
+// Bound by the chain of dependent steps: n divisions and 3 n multiply-adds per vector.
+template <int NV, bool IN_LDS>
+__global__ __launch_bounds__(64) void inverse_kernel(EigenArgs a)
+{
+    extern __shared__ double lu_lds[];
+    __shared__ double td[IN_LDS ? GVQ_EIGEN_SMALL : GVQ_MAX_D], te[IN_LDS ? GVQ_EIGEN_SMALL : GVQ_MAX_D];
+    const int b = blockIdx.y, n = a.n, lane = threadIdx.x;
+    const unsigned long long norm = a.norm[b];
+    if (eig_skip(norm)) return;
+    const double* T = a.T + (size_t)b * 5 * a.t_ld;
+    const int ex = eig_scale_exp(norm);
+    for (int i = lane; i < n; i += 64) {
+        td[i] = ldexp(T[i], ex);
+        const double e = i + 1 < n ? ldexp(T[a.t_ld + i], ex) : 0.0;
+        te[i] = i + 1 < n && fabs(e) < EIG_E_FLOOR ? EIG_E_FLOOR : e;   // 0 past the last
+    }
+    __syncthreads();
+    double* base = IN_LDS ? lu_lds : a.lu + ((size_t)b * gridDim.x + blockIdx.x) * 5 * n * NV;
+    const size_t plane = (size_t)n * NV;
+    const int j = blockIdx.x * NV + lane;
+    if (lane < NV && j < a.k) {
+        double* ip = base + lane;        // 1 / pivot
+        double* u1 = ip + plane;         // U's first and second superdiagonal
+        double* u2 = u1 + plane;
+        double* lm = u2 + plane;         // multipliers
+        double* z = lm + plane;          // right-hand side, solution
+        const double s = ldexp(a.eig[(size_t)b * a.eig_ld + j], ex);
+        double c = td[0] - s, sup = te[0];
+#pragma unroll 4
+        for (int i = 0; i < n - 1; ++i) {
+            const double e = te[i], d1 = td[i + 1] - s, e1 = te[i + 1];
+            // no swap for an off-diagonal entry below rounding: the block ends here, and its pivot is what is floored
+            const bool swap = fabs(e) > fmax(fabs(c), EIG_PIVOT);
+            double piv = swap ? e : c;
+            if (fabs(piv) < EIG_PIVOT) piv = piv < 0.0 ? -EIG_PIVOT : EIG_PIVOT;
+            const double r = fast_rcp(piv), f = (swap ? c : e) * r;
+            ip[(size_t)i * NV] = r;
+            u1[(size_t)i * NV] = swap ? d1 : sup;
+            u2[(size_t)i * NV] = swap ? (i + 2 < n ? e1 : 1.0) : 0.0;   // non-zero marks a swap
+            lm[(size_t)i * NV] = f;
+            c = swap ? fma(-f, d1, sup) : fma(-f, sup, d1);
+            sup = swap ? -f * e1 : e1;
+        }
+        if (fabs(c) < EIG_PIVOT) c = c < 0.0 ? -EIG_PIVOT : EIG_PIVOT;
+        const double r_last = fast_rcp(c);
+
+        // Both sweeps work on blocks of eight steps: a block's operands are read before the block ahead of it is
+        // worked through, so that the chain waits for arithmetic only.
+        constexpr int K = 8;
+        double big = 1.0;
+        for (int solve = 0; solve < EIG_SOLVES; ++solve) {
+            double y = hash_unit((unsigned int)(n - 1), (unsigned int)j);
+            if (solve > 0) {
+                // forward, on the first solution scaled to its largest entry
+                const double sc = 1.0 / big;
+                double zc[K], lc[K], uc[K], zn[K], ln[K], un[K];
+                auto fetch = [&](int i, double (&zz)[K], double (&ll)[K], double (&uu)[K]) {
+#pragma unroll
+                    for (int u = 0; u < K; ++u) {
+                        const int at = i + u < n - 1 ? i + u : n - 2;
+                        zz[u] = z[(size_t)(at + 1) * NV];
+                        ll[u] = lm[(size_t)at * NV];
+                        uu[u] = u2[(size_t)at * NV];
+                    }
+                };
+                y = z[0] * sc;
+                fetch(0, zc, lc, uc);
+                for (int i = 0; i < n - 1; i += K) {
+                    fetch(i + K, zn, ln, un);
+#pragma unroll
+                    for (int u = 0; u < K; ++u) {
+                        if (i + u >= n - 1) break;
+                        const double t = zc[u] * sc, f = lc[u];
+                        const bool swap = uc[u] != 0.0;
+                        z[(size_t)(i + u) * NV] = swap ? t : y;
+                        y = swap ? fma(-f, t, y) : fma(-f, y, t);
+                    }
+#pragma unroll
+                    for (int u = 0; u < K; ++u) { zc[u] = zn[u]; lc[u] = ln[u]; uc[u] = un[u]; }
+                }
+            }
+            // backward
+            double x2 = 0.0, x1 = y * r_last;
+            big = fabs(x1);
+            z[(size_t)(n - 1) * NV] = x1;
+            double rc[K], ac[K], bc[K], zc[K], rn[K], an[K], bn[K], zn[K];
+            auto fetch = [&](int i, double (&rr)[K], double (&aa)[K], double (&bb)[K], double (&zz)[K]) {
+#pragma unroll
+                for (int u = 0; u < K; ++u) {
+                    const int at = i - u > 0 ? i - u : 0;
+                    rr[u] = ip[(size_t)at * NV];
+                    aa[u] = u1[(size_t)at * NV];
+                    bb[u] = at == n - 2 ? 0.0 : u2[(size_t)at * NV];
+                    zz[u] = solve == 0 ? hash_unit((unsigned int)at, (unsigned int)j) : z[(size_t)at * NV];
+                }
+            };
+            fetch(n - 2, rc, ac, bc, zc);
+            for (int i = n - 2; i >= 0; i -= K) {
+                fetch(i - K, rn, an, bn, zn);
+#pragma unroll
+                for (int u = 0; u < K; ++u) {
+                    if (i - u < 0) break;
+                    const double v = fma(-ac[u], x1, fma(-bc[u], x2, zc[u])) * rc[u];
+                    z[(size_t)(i - u) * NV] = v;
+                    x2 = x1;
+                    x1 = v;
+                    big = fmax(big, fabs(v));
+                }
+#pragma unroll
+                for (int u = 0; u < K; ++u) { rc[u] = rn[u]; ac[u] = an[u]; bc[u] = bn[u]; zc[u] = zn[u]; }
+            }
+        }
+        // a converged vector grows by about 1 / (rounding) in the last solve
+        if (!(big > 1e9)) a.sweeps[b] = -1;
+        lm[0] = 1.0 / big;   // this vector's scale, for the copy below
+    }
+    __syncthreads();
+    for (int v = 0; v < NV; ++v) {
+        const int jv = blockIdx.x * NV + v;
+        if (jv >= a.k) break;
+        const double sc = base[3 * plane + v];
+        double* o = a.Z + (size_t)b * a.Z_stride + (size_t)jv * n;
+        for (int i = lane; i < n; i += 64) o[i] = base[4 * plane + (size_t)i * NV + v] * sc;
+    }
+}
+
+// ---- orthonormalise -----------------------------------------------------------------------------------------------------
+//
+// Modified Gram-Schmidt over k columns of length n, one work-group per basis, panels of 32 columns in registers (four
+// per wave, NE numbers per lane each).  A panel first sheds its components along the finished columns, then along its
+// own, column by column through LDS.
+template <int NE>
+__global__ __launch_bounds__(512) void orthonormalise_kernel(double* Z, size_t Z_stride, int k, int n,
+                                                             const unsigned long long* norm)
+{
+    __shared__ double q[2][NE * 64];
+    const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (eig_skip(norm[b])) return;
+    Z += (size_t)b * Z_stride;
+    for (int c0 = 0; c0 < k; c0 += 32) {
+        double x[4][NE];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                const int c = c0 + 8 * s + wave, i = 64 * e + lane;
+                x[s][e] = c < k && i < n ? Z[(size_t)c * n + i] : 0.0;
+            }
+        for (int done = 0; done < c0; ++done) {
+            double y[NE], dot[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int e = 0; e < NE; ++e) y[e] = 64 * e + lane < n ? Z[(size_t)done * n + 64 * e + lane] : 0.0;
+#pragma unroll
+            for (int e = 0; e < NE; ++e)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) dot[s] = fma(y[e], x[s][e], dot[s]);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                dot[s] = wave_sum(dot[s]);
+#pragma unroll
+                for (int e = 0; e < NE; ++e) x[s][e] = fma(-dot[s], y[e], x[s][e]);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            for (int w = 0; w < 8; ++w) {
+                const int c = c0 + 8 * s + w;
+                if (c >= k) break;   // uniform
+                double* buf = q[w & 1];
+                if (wave == w) {
+                    double n2 = 0.0;
+#pragma unroll
+                    for (int e = 0; e < NE; ++e) n2 = fma(x[s][e], x[s][e], n2);
+                    n2 = wave_sum(n2);
+                    const double inv = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
+#pragma unroll
+                    for (int e = 0; e < NE; ++e) {
+                        x[s][e] *= inv;
+                        buf[64 * e + lane] = x[s][e];
+                        if (64 * e + lane < n) Z[(size_t)c * n + 64 * e + lane] = x[s][e];
+                    }
+                }
+                __syncthreads();
+                double y[NE], dot[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int e = 0; e < NE; ++e) y[e] = buf[64 * e + lane];
+#pragma unroll
+                for (int e = 0; e < NE; ++e)
+#pragma unroll
+                    for (int s2 = 0; s2 < 4; ++s2)
+                        if (s2 >= s) dot[s2] = fma(y[e], x[s2][e], dot[s2]);
+#pragma unroll
+                for (int s2 = 0; s2 < 4; ++s2) {
+                    if (s2 < s || (s2 == s && wave <= w)) continue;
+                    const double f = wave_sum(dot[s2]);
+#pragma unroll
+                    for (int e = 0; e < NE; ++e) x[s2][e] = fma(-f, y[e], x[s2][e]);
+                }
+            }
+        }
+        __syncthreads();   // the finished panel is visible to every wave
+    }
+}
+
+// ---- back ---------------------------------------------------------------------------------------------------------------
+//
+// z <- H_0 H_1 ... H_{n-3} z, one wave per vector held in registers, the next reflector requested ahead.
+template <int NE>
+__global__ __launch_bounds__(256) void back_kernel(EigenArgs a)
+{
+    const int b = blockIdx.y, n = a.n, lane = threadIdx.x & 63;
+    const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (eig_skip(a.norm[b]) || j >= a.k) return;
+    const double* R = a.A + (size_t)b * a.A_stride;   // reflector i is row i (row i-1 of the matrix)
+    const double* tau = a.T + (size_t)b * 5 * a.t_ld + 2 * a.t_ld;
+    double* Z = a.Z + (size_t)b * a.Z_stride + (size_t)j * n;
+    double z[NE], v[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) z[e] = 64 * e + lane < n ? Z[64 * e + lane] : 0.0;
+    auto fetch = [&](int i) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const int c = 64 * e + lane;
+            v[e] = i >= 0 && c > i && c < n ? R[(size_t)i * n + c] : 0.0;
+        }
+    };
+    fetch(n - 3);
+    for (int i = n - 3; i >= 0; --i) {
+        double cur[NE], dot = 0.0;
+        const double t = tau[i];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) cur[e] = v[e];
+        fetch(i - 1);
+        if (t == 0.0) continue;   // its vector was not written
+#pragma unroll
+        for (int e = 0; e < NE; ++e) dot = fma(cur[e], z[e], dot);
+        dot = t * wave_sum(dot);
+#pragma unroll
+        for (int e = 0; e < NE; ++e) z[e] = fma(-dot, cur[e], z[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+        if (64 * e + lane < n) Z[64 * e + lane] = z[e];
+}
+
+// ---- out ----------------------------------------------------------------------------------------------------------------
+//
+// U = the k columns of Z as float, each negated if needed so that its largest-magnitude entry (lowest index on ties) is
+// positive; unit vectors for a zero matrix, NaN for one that is not finite.  One wave per column.
+__global__ __launch_bounds__(256) void basis_out_kernel(const double* Z, size_t Z_stride, int k, int d,
+                                                        const unsigned long long* norm, float* U, int* sweeps)
+{
+    const int b = blockIdx.y, lane = threadIdx.x & 63, c = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (c >= k) return;
+    U += (size_t)b * d * k;
+    const unsigned long long nb = norm[b];
+    if (eig_skip(nb)) {
+        for (int i = lane; i < d; i += 64) U[(size_t)i * k + c] = nb ? __int_as_float(0x7FC00000) : i == c ? 1.f : 0.f;
+        if (c == 0 && lane == 0) sweeps[b] = nb ? -1 : 0;
+        return;
+    }
+    const double* z = Z + (size_t)b * Z_stride + (size_t)c * d;
+    double big = -1.0;
+    int arg = GVQ_MAX_D;
+    bool neg = false;
+    for (int i = lane; i < d; i += 64) {
+        const double v = z[i], m = fabs(v);
+        if (m > big) { big = m; arg = i; neg = v < 0.0; }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        const double m = __shfl_xor(big, o, 64);
+        const int at = __shfl_xor(arg, o, 64);
+        const int ng = __shfl_xor((int)neg, o, 64);
+        if (m > big || (m == big && at < arg)) { big = m; arg = at; neg = ng != 0; }
+    }
+    for (int i = lane; i < d; i += 64) U[(size_t)i * k + c] = (float)(neg ? -z[i] : z[i]);
+}
+
+// ======================================================================================
+size_t gvq_eigen_lu_doubles(int d, int k)   // per basis
+{
+    return d <= GVQ_EIGEN_SMALL ? 0 : (size_t)((k + 63) / 64) * 5 * d * 64;
+}
+
+template <template <int> class F, typename... Args>
+static void by_pieces(int n, Args... args)
+{
+    if (n <= 128) F<2>::go(args...);
+    else if (n <= 256) F<4>::go(args...);
+    else if (n <= 512) F<8>::go(args...);
+    else if (n <= 768) F<12>::go(args...);
+    else F<16>::go(args...);
+}
+template <int NE> struct go_step {
+    static void go(dim3 grid, EigenArgs a, int i, hipStream_t st) { hipLaunchKernelGGL((tri_step_kernel<NE>), grid, dim3(256), 0, st, a, i); }
+};
+template <int NE> struct go_ortho {
+    static void go(double* Z, size_t stride, int k, int n, int B, const unsigned long long* norm, hipStream_t st)
+    {
+        hipLaunchKernelGGL((orthonormalise_kernel<NE>), dim3(B), dim3(512), 0, st, Z, stride, k, n, norm);
+    }
+};
+template <int NE> struct go_back {
+    static void go(dim3 grid, EigenArgs a, hipStream_t st) { hipLaunchKernelGGL((back_kernel<NE>), grid, dim3(256), 0, st, a); }
+};
+
+int gvq_launch_orthonormalise(const gvq_basis* h, double* Z, size_t Z_stride, int k, int n, hipStream_t st)
+{
+    by_pieces<go_ortho>(n, Z, Z_stride, k, n, h->B, (const unsigned long long*)(h->d_nsamp + h->B), st);
+    GVQ_HIP(hipGetLastError());
+    return GVQ_OK;
+}
+
+int gvq_launch_sym_eigen(const gvq_basis* h, EigenArgs a, bool ortho, hipStream_t st)
+{
+    const int n = a.n, B = h->B, i0 = n > GVQ_EIGEN_SMALL ? n - GVQ_EIGEN_SMALL : 0;
+    for (int i = 0; i < i0; ++i) {
+        by_pieces<go_step>(n, dim3((unsigned)((n - 1 - i + 7) / 8), B), a, i, st);
+        GVQ_HIP(hipGetLastError());
+    }
+    if (n - i0 <= 32) hipLaunchKernelGGL((tri_small_kernel<8>), dim3(B), dim3(64), 0, st, a, i0);
+    else if (n - i0 <= 64) hipLaunchKernelGGL((tri_small_kernel<16>), dim3(B), dim3(256), 0, st, a, i0);
+    else hipLaunchKernelGGL((tri_small_kernel<32>), dim3(B), dim3(1024), 0, st, a, i0);
+    GVQ_HIP(hipGetLastError());
+    // a wave per eigenvalue while that leaves the chip's 1024 SIMDs a handful each, fewer lanes for many small matrices
+    a.lanes = (int64_t)n * B <= 4096 ? 64 : (int64_t)n * B <= 65536 ? 16 : 8;
+    hipLaunchKernelGGL(bisect_kernel, dim3((unsigned)((n * a.lanes + 255) / 256), B), dim3(256), 0, st, a);
+    GVQ_HIP(hipGetLastError());
+    if (n <= GVQ_EIGEN_SMALL) {
+        const size_t lds = sizeof(double) * 5 * n * 16;
+        static gvq_once_per_device once;
+        if (once.first(h->device))
+            GVQ_HIP(hipFuncSetAttribute((const void*)(inverse_kernel<16, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)(sizeof(double) * 5 * GVQ_EIGEN_SMALL * 16)));
+        hipLaunchKernelGGL((inverse_kernel<16, true>), dim3((unsigned)((a.k + 15) / 16), B), dim3(64), lds, st, a);
+    } else {
+        hipLaunchKernelGGL((inverse_kernel<64, false>), dim3((unsigned)((a.k + 63) / 64), B), dim3(64), 0, st, a);
+    }
+    GVQ_HIP(hipGetLastError());
+    if (ortho) {
+        const int rc = gvq_launch_orthonormalise(h, a.Z, a.Z_stride, a.k, n, st);
+        if (rc != GVQ_OK) return rc;
+    }
+    if (n > 2) {
+        by_pieces<go_back>(n, dim3((unsigned)((a.k + 3) / 4), B), a, st);
+        GVQ_HIP(hipGetLastError());
+    }
+    return GVQ_OK;
+}
+
+EigenArgs gvq_eigen_args(const gvq_basis* h)
+{
+    EigenArgs a;
+    const size_t d = (size_t)h->d;
+    a.n = h->d; a.k = h->k;
+    a.src = h->d_cov; a.src_stride = d * d;
+    a.A = h->d_eA; a.A_stride = (d + 1) * d;
+    a.T = h->d_eT; a.t_ld = h->d;
+    a.norm = h->d_nsamp + h->B;
+    a.eig = h->d_eig; a.eig_ld = h->d;
+    a.Z = h->d_eZ; a.Z_stride = (size_t)h->k * d;
+    a.lu = h->d_eLU; a.lanes = 64; a.clamp = 0; a.sweeps = h->d_sweeps;
+    return a;
+}
+
+int gvq_launch_basis_out(const gvq_basis* h, hipStream_t st)
+{
+    hipLaunchKernelGGL(basis_out_kernel, dim3((unsigned)((h->k + 3) / 4), h->B), dim3(256), 0, st, h->d_eZ,
+                       (size_t)h->k * h->d, h->k, h->d, h->d_nsamp + h->B, h->d_U, h->d_sweeps);
+    GVQ_HIP(hipGetLastError());
+    return GVQ_OK;
+}
+
+int gvq_launch_eigen(const gvq_basis* h, bool from_moments, hipStream_t st)
+{
+    if (from_moments) {
+        int g = (int)(((int64_t)h->d * h->d + 1023) / 1024);
+        if (g > 256) g = 256;
+        hipLaunchKernelGGL(cov_kernel, dim3(g, h->B), dim3(256), 0, st, h->d_mom, h->d_nsamp, h->d, h->d_cov, h->d_mu,
+                           h->d_nsamp + h->B, h->d_sweeps);
+        GVQ_HIP(hipGetLastError());
+    }
+    const int rc = gvq_launch_sym_eigen(h, gvq_eigen_args(h), true, st);
+    return rc != GVQ_OK ? rc : gvq_launch_basis_out(h, st);
+}

@@ -2,8 +2,7 @@
 //   1. moments:  per basis, sum x and sum x x^T over the sample slices, in float64
 //                (fp32/bf16 inputs widen exactly and their products are exact in float64);
 //   2. reduce:   fixed-order sum of the per-workgroup partials (bit-reproducible);
-//   3. eigen:    mu = s/n, C = G/n - mu mu^T, parallel-order two-sided Jacobi in float64,
-//                one workgroup per basis; sort, keep k columns, fix signs.
+//   3. covariance and its eigendecomposition: gvq_eigen.hip.
 #include "gvq_internal.h"
 
 __device__ __forceinline__ float load_elem(const void* g, bool bf16, int64_t idx)
@@ -395,382 +394,8 @@ __global__ void unpack_moments_kernel(const double* packed, double* mom, int D)
     if (T1 != T2) o[e2 * D + e1] = v;
 }
 
-// --------------------------------------------------------------------------------------
-// Eigensolver: two-sided Jacobi with the round-robin ("chess tournament") ordering.  In one
-// step the n/2 disjoint index pairs (p_i, q_i) are rotated at once: A <- J^T A J with J the
-// product of the n/2 plane rotations, which maps every 2x2 block A[{p_i,q_i}][{p_j,q_j}] to
-// R_i^T (block) R_j independently of all other blocks -- one thread per block, no ordering
-// needed inside the step.  A rotation R = [[c, s], [-s, c]] annihilates a_pq with
-// theta = (a_qq - a_pp) / (2 a_pq), t = sign(theta) / (|theta| + sqrt(theta^2 + 1)),
-// c = 1/sqrt(1 + t^2), s = t c.  The matrix lives in LDS, the eigenvectors V (V <- V J) in
-// global memory.  n = d rounded up to even; a padding index has a zero row/column and is
-// never rotated.
-// --------------------------------------------------------------------------------------
-struct EigArgs {
-    const double* mom;     // [B][d*d+d]
-    const unsigned long long* nsamp;   // [B] samples behind the moments
-    int d, k;
-    double* cov;           // [B][d][d]
-    double* V;             // [B][n][n]
-    double* eig;           // [B][d]
-    float* U;              // [B][d][k]
-    float* mu;             // [B][d]
-    int* sweeps;           // [B]
-    int max_sweeps;
-    double tol;
-};
-
-__device__ double block_sum(double v, double* red)
-{
-    // red: LDS array of at least blockDim.x / 64 doubles
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-    __syncthreads();
-    if (lane == 0) red[wave] = v;
-    __syncthreads();
-    double tot = 0.0;
-    for (int i = 0; i < nw; ++i) tot += red[i];
-    return tot;
-}
-
-// The sweeps of the parallel-order Jacobi on the n x n matrix A in LDS (n even), V <- V J in
-// global memory (n x n, row-major), all threads of the work-group.  fro2 = squared Frobenius
-// norm of A.  Returns the number of sweeps used, -1 if the off-diagonal mass did not fall below
-// tol^2 fro2 within max_sweeps (or turned NaN).
-__device__ __forceinline__ int jacobi_lds_sweeps(double* A, double* V, int n, double* cs, double* sn, double* red, int* pp, int* qq,
-                                 double fro2, int max_sweeps, double tol)
-{
-    const int half = n >> 1, tid = threadIdx.x, nth = blockDim.x;
-    int sweeps_used = -1;
-    for (int sweep = 0; sweep <= max_sweeps; ++sweep) {
-        double off2 = 0.0;
-        for (int i = tid; i < n * n; i += nth) {
-            int r = i / n, c = i - r * n;
-            if (r != c) off2 += A[i] * A[i];
-        }
-        off2 = block_sum(off2, red);
-        if (off2 != off2 || fro2 != fro2) break;  // NaN: no convergence (sweeps_used stays -1)
-        if (!(off2 > tol * tol * fro2)) { sweeps_used = sweep; break; }
-        if (sweep == max_sweeps) break;
-
-        for (int round = 0; round < n - 1; ++round) {
-            if (tid < half) {
-                int p, q;
-                if (tid == 0) { p = round; q = n - 1; }
-                else { p = (round + tid) % (n - 1); q = (round - tid + (n - 1)) % (n - 1); }
-                if (p > q) { int t = p; p = q; q = t; }
-                double apq = A[p * n + q], c = 1.0, s = 0.0;
-                if (apq != 0.0) {
-                    double theta = (A[q * n + q] - A[p * n + p]) / (2.0 * apq);
-                    double t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-                    c = 1.0 / sqrt(1.0 + t * t);
-                    s = t * c;
-                }
-                pp[tid] = p; qq[tid] = q; cs[tid] = c; sn[tid] = s;
-            }
-            __syncthreads();
-            // eigenvector pairs of this round: start their (global memory) loads first, so the
-            // latency runs under the LDS work on the matrix; at most 8 pairs per thread for
-            // every launch shape used (n*half <= 8 * blockDim)
-            double vr[8], vt[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int idx = tid + u * nth;
-                if (idx < n * half) {
-                    const int row = idx / half, j = idx - row * half;
-                    vr[u] = V[row * n + pp[j]];
-                    vt[u] = V[row * n + qq[j]];
-                }
-            }
-            for (int idx = tid; idx < half * half; idx += nth) {
-                const int i = idx / half, j = idx - i * half;
-                const int p = pp[i], q = qq[i], r = pp[j], t = qq[j];
-                const double ci = cs[i], si = sn[i], cj = cs[j], sj = sn[j];
-                double apr = A[p * n + r], apt = A[p * n + t], aqr = A[q * n + r], aqt = A[q * n + t];
-                // rows: R_i^T * block
-                double xpr = ci * apr - si * aqr, xpt = ci * apt - si * aqt;
-                double xqr = si * apr + ci * aqr, xqt = si * apt + ci * aqt;
-                // columns: * R_j
-                double ypr = cj * xpr - sj * xpt, ypt = sj * xpr + cj * xpt;
-                double yqr = cj * xqr - sj * xqt, yqt = sj * xqr + cj * xqt;
-                if (i == j) { ypt = 0.0; yqr = 0.0; }
-                A[p * n + r] = ypr; A[p * n + t] = ypt; A[q * n + r] = yqr; A[q * n + t] = yqt;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int idx = tid + u * nth;
-                if (idx < n * half) {
-                    const int row = idx / half, j = idx - row * half;
-                    const double cj = cs[j], sj = sn[j];
-                    V[row * n + pp[j]] = cj * vr[u] - sj * vt[u];
-                    V[row * n + qq[j]] = sj * vr[u] + cj * vt[u];
-                }
-            }
-            __syncthreads();
-        }
-    }
-    return sweeps_used;
-}
-
-__global__ void eigen_kernel(EigArgs a)
-{
-    extern __shared__ double smem[];
-    const int d = a.d, n = d + (d & 1), half = n >> 1;
-    double* A = smem;                       // [n][n]
-    double* cs = A + n * n;                 // [half]
-    double* sn = cs + half;                 // [half]
-    double* red = sn + half;                // [32]
-    double* lam = red + 32;                 // [n]
-    int* pp = (int*)(lam + n);              // [half]
-    int* qq = pp + half;                    // [half]
-    int* order = qq + half;                 // [n]
-    const int b = blockIdx.x, tid = threadIdx.x, nth = blockDim.x;
-
-    const int W = d * d + d;
-    const double* mom = a.mom + (size_t)b * W;
-    const double ns = (double)a.nsamp[b];
-
-    double* V = a.V + (size_t)b * n * n;
-    double* cov = a.cov + (size_t)b * d * d;
-    double fro2 = 0.0;
-    for (int i = tid; i < n * n; i += nth) {
-        int r = i / n, c = i - r * n;
-        double v = 0.0;
-        if (r < d && c < d) {
-            // upper and lower halves of the Gram sum are bit-identical (same products, same order)
-            // true divisions: a constant gradient then gives exactly C = 0
-            v = ns > 0.0 ? mom[r * d + c] / ns - (mom[d * d + r] / ns) * (mom[d * d + c] / ns) : 0.0;
-            cov[r * d + c] = v;
-        }
-        A[i] = v;
-        V[i] = r == c ? 1.0 : 0.0;
-        fro2 += v * v;
-    }
-    for (int i = tid; i < d; i += nth) a.mu[(size_t)b * d + i] = ns > 0.0 ? (float)(mom[d * d + i] / ns) : 0.0f;
-    fro2 = block_sum(fro2, red);
-
-    const int sweeps_used = jacobi_lds_sweeps(A, V, n, cs, sn, red, pp, qq, fro2, a.max_sweeps, a.tol);
-
-    // eigenvalues in decreasing order (ties: lower index first)
-    for (int i = tid; i < d; i += nth) lam[i] = A[i * n + i];
-    __syncthreads();
-    for (int i = tid; i < d; i += nth) {
-        // NaN sorts last: compare with NaN replaced by -inf
-        const double li = lam[i] == lam[i] ? lam[i] : -INFINITY;
-        int rank = 0;
-        for (int j = 0; j < d; ++j) {
-            const double lj = lam[j] == lam[j] ? lam[j] : -INFINITY;
-            if (lj > li || (lj == li && j < i)) ++rank;
-        }
-        order[rank] = i;
-    }
-    __syncthreads();
-    for (int i = tid; i < d; i += nth) a.eig[(size_t)b * d + i] = lam[order[i]];
-    // kept eigenvectors, sign: largest-magnitude entry (lowest index on ties) positive
-    for (int i = tid; i < a.k; i += nth) {
-        const int col = order[i];
-        int arg = 0;
-        double big = -1.0;
-        for (int e = 0; e < d; ++e) {
-            double m = fabs(V[e * n + col]);
-            if (m > big) { big = m; arg = e; }
-        }
-        const double sign = V[arg * n + col] < 0.0 ? -1.0 : 1.0;
-        for (int e = 0; e < d; ++e) a.U[((size_t)b * d + e) * a.k + i] = (float)(sign * V[e * n + col]);
-    }
-    if (tid == 0) a.sweeps[b] = sweeps_used;
-}
-
-// --------------------------------------------------------------------------------------
-// First-slice sampling with fewer samples than dimensions (Section 3: L time samples of one slice,
-// slice sizes in the hundreds).  The covariance C = Xc^T Xc / L (Xc: the L centred samples as
-// rows) has rank < L, and its non-zero eigenpairs are those of the small L x L matrix
-// K = Xc Xc^T / L: K v = lambda v  =>  C (Xc^T v) = lambda (Xc^T v).  So the Jacobi runs on K in
-// LDS whatever d is, and the kept directions are u_i = Xc^T v_i, normalised and cleaned with one
-// round of Gram-Schmidt against the columns before them.  Directions beyond the rank of the data
-// (eigenvalue <= 1e-12 of the largest) are not determined by it; they are completed with unit
-// vectors made orthogonal to the columns so far, so that U always has orthonormal columns.
-// One work-group per basis.  work[b]: [m*m] eigenvectors of K, then [k][d] the columns of U in
-// float64.
-// --------------------------------------------------------------------------------------
-#define GVQ_GRAM_MAX_L 128
-#define GVQ_GRAM_MAX_K 256
-struct GramArgs {
-    gvq_ptrs grads[GVQ_GRAM_MAX_L / GVQ_MAX_PTRS];
-    int L;
-    const double* mom;     // [B][d*d+d] from first_slice_moments_kernel
-    const unsigned long long* nsamp;   // [B] samples behind the moments (L, or 0 without a full first slice)
-    const int64_t* offs;
-    int64_t M;
-    int d, k, bf16;
-    double* cov;           // [B][d][d]
-    double* work;          // [B][work_stride]
-    size_t work_stride;
-    double* eig;           // [B][d]
-    float* U;              // [B][d][k]
-    float* mu;             // [B][d]
-    int* sweeps;           // [B]
-    int max_sweeps;
-    double tol;
-};
-
-size_t gvq_gram_lds_bytes(int L, int k)
-{
-    const int m = L + (L & 1), half = m / 2;
-    return sizeof(double) * ((size_t)m * m + 2 * half + 32 + m + k) + sizeof(int) * (2 * half + m);
-}
-
-__global__ __launch_bounds__(1024) void gram_eigen_kernel(GramArgs a)
-{
-    extern __shared__ double smem[];
-    const int d = a.d, k = a.k, L = a.L, m = L + (L & 1), half = m >> 1;
-    double* A = smem;                       // [m][m]
-    double* cs = A + m * m;                 // [half]
-    double* sn = cs + half;                 // [half]
-    double* red = sn + half;                // [32]
-    double* lam = red + 32;                 // [m]
-    double* dots = lam + m;                 // [k]
-    int* pp = (int*)(dots + k);             // [half]
-    int* qq = pp + half;                    // [half]
-    int* order = qq + half;                 // [m]
-    const int b = blockIdx.x, tid = threadIdx.x, nth = blockDim.x, lane = tid & 63, wave = tid >> 6, nw = nth >> 6;
-
-    const double* mom = a.mom + (size_t)b * ((size_t)d * d + d);
-    double* cov = a.cov + (size_t)b * d * d;
-    double* V = a.work + (size_t)b * a.work_stride;   // [m][m]
-    double* Uw = V + (size_t)m * m;                   // [k][d]
-    const int64_t j = a.offs[b];
-    if (a.nsamp[b] == 0) {
-        // no full first slice: the trivial basis, as in the general solver
-        for (int i = tid; i < d * d; i += nth) cov[i] = 0.0;
-        for (int i = tid; i < d; i += nth) { a.mu[(size_t)b * d + i] = 0.f; a.eig[(size_t)b * d + i] = 0.0; }
-        for (int i = tid; i < d * k; i += nth) a.U[(size_t)b * d * k + i] = (i / k == i % k) ? 1.f : 0.f;
-        if (tid == 0) a.sweeps[b] = 0;
-        return;
-    }
-    const double ns = (double)a.nsamp[b];   // = L
-    for (int i = tid; i < d * d; i += nth) {
-        const int r = i / d, c = i - r * d;
-        cov[i] = mom[i] / ns - (mom[(size_t)d * d + r] / ns) * (mom[(size_t)d * d + c] / ns);
-    }
-    for (int i = tid; i < d; i += nth) a.mu[(size_t)b * d + i] = (float)(mom[(size_t)d * d + i] / ns);
-    auto xc = [&](int l, int e) {   // centred sample l, element e
-        return (double)load_elem(a.grads[l / GVQ_MAX_PTRS].p[l % GVQ_MAX_PTRS], a.bf16 != 0, j * d + e) -
-               mom[(size_t)d * d + e] / ns;
-    };
-    // K (upper triangle computed, mirrored), zero row/column for the padding index
-    for (int i = tid; i < m * m; i += nth) {
-        const int r = i / m, c = i - r * m;
-        if (r > c) continue;
-        double v = 0.0;
-        if (c < L) {
-            for (int e = 0; e < d; ++e) v = fma(xc(r, e), xc(c, e), v);
-            v /= ns;
-        }
-        A[r * m + c] = v;
-        A[c * m + r] = v;
-    }
-    for (int i = tid; i < m * m; i += nth) V[i] = (i / m == i % m) ? 1.0 : 0.0;
-    __syncthreads();
-    double fro2 = 0.0;
-    for (int i = tid; i < m * m; i += nth) fro2 += A[i] * A[i];
-    fro2 = block_sum(fro2, red);
-    const int sweeps_used = jacobi_lds_sweeps(A, V, m, cs, sn, red, pp, qq, fro2, a.max_sweeps, a.tol);
-    __syncthreads();
-
-    // eigenvalues of K in decreasing order (ties: lower index first, NaN last)
-    // K is positive semi-definite: a negative eigenvalue is rounding noise around zero
-    for (int i = tid; i < L; i += nth) lam[i] = A[i * m + i] < 0.0 ? 0.0 : A[i * m + i];
-    __syncthreads();
-    for (int i = tid; i < L; i += nth) {
-        const double li = lam[i] == lam[i] ? lam[i] : -INFINITY;
-        int rank = 0;
-        for (int q = 0; q < L; ++q) {
-            const double lq = lam[q] == lam[q] ? lam[q] : -INFINITY;
-            if (lq > li || (lq == li && q < i)) ++rank;
-        }
-        order[rank] = i;
-    }
-    __syncthreads();
-    for (int i = tid; i < d; i += nth) a.eig[(size_t)b * d + i] = i < L ? lam[order[i]] : 0.0;
-    const double top = lam[order[0]];
-
-    // raw directions Xc^T v_i for the columns the data determines, zero for the others
-    for (int i = tid; i < k * d; i += nth) {
-        const int col = i / d, e = i - col * d;
-        double v = 0.0;
-        if (col < L && lam[order[col]] > 1e-12 * top) {
-            const int vc = order[col];
-            for (int l = 0; l < L; ++l) v = fma(V[l * m + vc], xc(l, e), v);
-        }
-        Uw[i] = v;
-    }
-    __syncthreads();
-
-    // columns one after the other: orthogonalise against the earlier ones (twice), normalise
-    int next_unit = 0;
-    for (int col = 0; col < k; ++col) {
-        double* w = Uw + (size_t)col * d;
-        const bool determined = col < L && lam[order[col]] > 1e-12 * top;   // uniform
-        for (;;) {   // ends: every retry takes a new unit vector, and there are d of them
-            if (!determined) {
-                for (int e = tid; e < d; e += nth) w[e] = e == next_unit ? 1.0 : 0.0;
-                ++next_unit;
-                __syncthreads();
-            }
-            for (int pass = 0; pass < 2; ++pass) {
-                for (int q = wave; q < col; q += nw) {
-                    const double* u = Uw + (size_t)q * d;
-                    double acc = 0.0;
-                    for (int e = lane; e < d; e += 64) acc = fma(u[e], w[e], acc);
-                    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-                    if (lane == 0) dots[q] = acc;
-                }
-                __syncthreads();
-                for (int e = tid; e < d; e += nth) {
-                    double v = w[e];
-                    for (int q = 0; q < col; ++q) v = fma(-dots[q], Uw[(size_t)q * d + e], v);
-                    w[e] = v;
-                }
-                __syncthreads();
-            }
-            double n2 = 0.0;
-            for (int e = tid; e < d; e += nth) n2 += w[e] * w[e];
-            n2 = block_sum(n2, red);
-            // a unit vector that lies almost inside the span so far is a poor start: take the next one
-            if (!determined && n2 < 0.25 && next_unit < d) continue;
-            const double inv = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
-            for (int e = tid; e < d; e += nth) w[e] *= inv;
-            __syncthreads();
-            break;
-        }
-    }
-    // sign: largest-magnitude entry (lowest index on ties) positive
-    for (int col = tid; col < k; col += nth) {
-        const double* w = Uw + (size_t)col * d;
-        int arg = 0;
-        double big = -1.0;
-        for (int e = 0; e < d; ++e) {
-            const double mag = fabs(w[e]);
-            if (mag > big) { big = mag; arg = e; }
-        }
-        const double sign = w[arg] < 0.0 ? -1.0 : 1.0;
-        for (int e = 0; e < d; ++e) a.U[((size_t)b * d + e) * k + col] = (float)(sign * w[e]);
-    }
-    if (tid == 0) a.sweeps[b] = sweeps_used;
-}
-
-// The small-matrix route is taken when it applies and its scratch fits the eigenvector work space.
-bool gvq_gram_shape(int d, int k, int L)
-{
-    // scratch: (L rounded up to even)^2 + k d doubles inside the d x d eigenvector work space
-    const int64_t m = L + (L & 1);
-    return L >= 2 && L <= GVQ_GRAM_MAX_L && 2 * L <= d && k <= GVQ_GRAM_MAX_K &&
-           m * m + (int64_t)k * d <= (int64_t)d * d;
-}
-
 // Section 3, "compressor reuse": moments of the first slice of every basis only -- L samples of d
-// numbers per basis, a few KB; one work-group per basis, one thread per matrix entry.
+// numbers per basis, a few KB; one thread per matrix entry.  For more samples than gvq_sample.hip takes.
 __global__ void first_slice_moments_kernel(gvq_ptrs grads, int L, const int64_t* offs, int64_t M, int d, int bf16,
                                            int accumulate, double* mom, unsigned long long* nsamp)
 {
@@ -822,12 +447,6 @@ int gvq_launch_select_k(const gvq_basis* h, double lambda, hipStream_t st)
 }
 
 // ======================================================================================
-size_t gvq_eigen_lds_bytes(int d)
-{
-    const int n = d + (d & 1), half = n / 2;
-    return sizeof(double) * ((size_t)n * n + 2 * half + 32 + n) + sizeof(int) * (2 * half + n);
-}
-
 template <int D>
 static void launch_moments_mfma(const gvq_basis* h, const MomMfmaArgs& a, hipStream_t st)
 {
@@ -859,8 +478,12 @@ __global__ void zero_counts_kernel(unsigned long long* p, int n)
 int gvq_launch_fit(gvq_basis* h, const void* const* grads, int L, bool first_slice_only, hipStream_t st)
 {
     const int d = h->d, W = d * d + d;
-    hipLaunchKernelGGL(zero_counts_kernel, dim3((h->B + 255) / 256), dim3(256), 0, st, h->d_nsamp, h->B);
+    hipLaunchKernelGGL(zero_counts_kernel, dim3((2 * h->B + 255) / 256), dim3(256), 0, st, h->d_nsamp, 2 * h->B);
     GVQ_HIP(hipGetLastError());
+    if (first_slice_only && gvq_sample_shape(d, L)) {
+        const int rc = gvq_launch_fit_samples(h, grads, L, st);
+        return rc != GVQ_OK ? rc : gvq_launch_pack(h, st);
+    }
     if (first_slice_only) {
         for (int l0 = 0; l0 < L; l0 += GVQ_MAX_PTRS) {
             gvq_ptrs p;
@@ -903,36 +526,6 @@ int gvq_launch_fit(gvq_basis* h, const void* const* grads, int L, bool first_sli
         GVQ_HIP(hipGetLastError());
     }
 
-    if (first_slice_only && gvq_gram_shape(d, h->k, L)) {
-        GramArgs g;
-        for (int l = 0; l < L; ++l) g.grads[l / GVQ_MAX_PTRS].p[l % GVQ_MAX_PTRS] = grads[l];
-        g.L = L; g.mom = h->d_mom; g.nsamp = h->d_nsamp; g.offs = h->d_offs; g.M = h->M; g.d = d; g.k = h->k;
-        g.bf16 = h->dtype == GVQ_BF16 ? 1 : 0;
-        g.cov = h->d_cov; g.work = h->d_V; g.work_stride = (size_t)(d + (d & 1)) * (d + (d & 1));
-        g.eig = h->d_eig; g.U = h->d_U; g.mu = h->d_mu; g.sweeps = h->d_sweeps; g.max_sweeps = 60; g.tol = 1e-15;
-        static gvq_once_per_device gram_once;
-        if (gram_once.first(h->device))
-            GVQ_HIP(hipFuncSetAttribute((const void*)gram_eigen_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        (int)gvq_gram_lds_bytes(GVQ_GRAM_MAX_L, GVQ_GRAM_MAX_K)));
-        hipLaunchKernelGGL(gram_eigen_kernel, dim3(h->B), dim3(1024), gvq_gram_lds_bytes(L, h->k), st, g);
-        GVQ_HIP(hipGetLastError());
-        return gvq_launch_pack(h, st);
-    }
-    if (d > GVQ_LDS_EIGEN_MAX_D) {
-        const int rc = gvq_launch_eigen_block(h, st);
-        return rc != GVQ_OK ? rc : gvq_launch_pack(h, st);
-    }
-    EigArgs e;
-    e.mom = h->d_mom; e.nsamp = h->d_nsamp; e.d = d; e.k = h->k;
-    e.cov = h->d_cov; e.V = h->d_V; e.eig = h->d_eig; e.U = h->d_U; e.mu = h->d_mu;
-    e.sweeps = h->d_sweeps; e.max_sweeps = 60; e.tol = 1e-15;
-    const size_t lds = gvq_eigen_lds_bytes(d);
-    static gvq_once_per_device once;
-    if (once.first(h->device))
-        GVQ_HIP(hipFuncSetAttribute((const void*)eigen_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)gvq_eigen_lds_bytes(GVQ_LDS_EIGEN_MAX_D)));
-    const int threads = d > 16 ? 256 : 64;
-    hipLaunchKernelGGL(eigen_kernel, dim3(h->B), dim3(threads), lds, st, e);
-    GVQ_HIP(hipGetLastError());
-    return gvq_launch_pack(h, st);
+    const int rc = gvq_launch_eigen(h, true, st);
+    return rc != GVQ_OK ? rc : gvq_launch_pack(h, st);
 }

@@ -6,8 +6,8 @@
 #include "gvq.h"
 
 #define GVQ_MAX_PTRS 32  // device pointers passed by value in one kernel launch
-#define GVQ_LDS_EIGEN_MAX_D 64   // longest slice that goes to the one-work-group eigensolver with the matrix in LDS;
-                                 // longer ones take the block Jacobi method (gvq_eigen_block.hip)
+#define GVQ_EIGEN_SMALL 128      // largest matrix one work-group tridiagonalises in its registers
+#define GVQ_SAMPLE_MAX_L 128     // most samples of a first-slice refresh that keeps them centred in memory
 
 // Many bases: the split of the gradient's 16-slice tiles into super-tiles (G consecutive tiles of
 // whole slices of one basis, for the branch-free fast phase of the register-resident codec kernels)
@@ -43,19 +43,18 @@ struct gvq_basis {
     float* d_Umu = nullptr;     // [B][KP] U^T mu (bf16 gradients)
     double* d_eig = nullptr;    // [B][d]
     double* d_cov = nullptr;    // [B][d][d]
-    double* d_V = nullptr;      // [B][dp][dp] eigenvector work space, dp = d rounded up to even (block Jacobi: to
-                                // a whole number of block pairs)
     double* d_part = nullptr;   // moment partials: [B][P][packed width] for d in {16,32,64,128}, else
                                 // [B][block pairs][P][64*64+64] (64 x 64 blocks, P sample chunks)
     double* d_part2 = nullptr;  // [B][ceil(P/32)][width] second level of the partial sum (MFMA path)
     int mom_wgs = 0;            // work-groups per basis of the MFMA moments kernel (P = streams * mom_wgs there)
     double* d_mom = nullptr;    // [B][d*d+d] reduced moments (sum x x^T, then sum x)
-    unsigned long long* d_nsamp = nullptr;  // [B] sample slices the moment kernels of the last fit took in, counted by them
-    double* d_bjA = nullptr;    // block Jacobi (d > 64): [B][n][n] the matrix, n = d padded to whole block pairs
-    double* d_bjQ = nullptr;    // [B][pairs per round][2nb][2nb] rotations of the current round
-    double* d_bjfro = nullptr;  // [B] squared Frobenius norm of the matrix, then [B][32][2] partial sums of its check
-    int* d_jstate = nullptr;    // [B][4] its per-basis state
-    int* d_sweeps = nullptr;    // [B] Jacobi sweeps used, -1 = not converged
+    unsigned long long* d_nsamp = nullptr;  // [B] sample slices the moment kernels of the last fit took in, counted by
+                                // them; then [B] largest |entry| of the decomposed matrix, as bits
+    double* d_eA = nullptr;     // eigensolver: [B][(d+1) d] matrix, then its reflectors (first-slice refresh: samples too)
+    double* d_eT = nullptr;     // [B][5 d] tridiagonal matrix and work vectors
+    double* d_eZ = nullptr;     // [B][k][d] eigenvectors
+    double* d_eLU = nullptr;    // d > GVQ_EIGEN_SMALL: factors of the inverse iteration
+    int* d_sweeps = nullptr;    // [B] solves per eigenvector (0 = zero matrix), -1 = not converged
     int* d_ksel = nullptr;      // [B] result of the last gvq_select_k
     float* d_loss_slice = nullptr;  // [S] per-slice squared residual of the last gvq_local_loss
     double* d_loss_part = nullptr;  // [B][loss_groups] partial sums of those
@@ -157,6 +156,8 @@ int gvq_launch_compress_ws(const gvq_basis* h, const void* grad, int n_workers, 
 int gvq_large_groups(int d);
 size_t gvq_large_partial_doubles(int d, int chunks);   // per basis
 int gvq_launch_moments_large(gvq_basis* h, const void* const* grads, int L, hipStream_t st);
-int gvq_bj_padded(int d);                  // block Jacobi: matrix size
-size_t gvq_bj_q_doubles(int d);            // doubles per basis of its rotation buffer
-int gvq_launch_eigen_block(gvq_basis* h, hipStream_t st);
+size_t gvq_eigen_lu_doubles(int d, int k);   // doubles per basis of d_eLU
+// d_cov (made from d_mom first if from_moments) -> d_eig, d_U.
+int gvq_launch_eigen(const gvq_basis* h, bool from_moments, hipStream_t st);
+bool gvq_sample_shape(int d, int L);         // first-slice refresh: gvq_launch_fit_samples takes it
+int gvq_launch_fit_samples(const gvq_basis* h, const void* const* grads, int L, hipStream_t st);

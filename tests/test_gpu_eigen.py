@@ -1,0 +1,99 @@
+"""The eigensolver of the basis refresh at the edges of its kernels: matrix sizes around the register tiles of the
+one-work-group tridiagonalisation (32, 64, 128), around the pieces of 64 that the long kernels hold per lane, odd sizes,
+few and all eigenvectors; repeated eigenvalues and null spaces; sample counts around the 16 x 16 products of the
+first-slice refresh.  Reference: numpy's symmetric eigensolver on the covariance that the library exports."""
+import numpy as np
+import pytest
+
+from paper_1811_03617_amd import gvq
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _fit(slices, d, k, first_slice_only=False, dtype="f32"):
+    """slices: list of [S][d] arrays, one per gradient."""
+    b = gvq.Basis(slices[0].size, d, k, None, dtype)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    b.fit([torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32).reshape(-1)).to(DEV).to(tdt) for x in slices],
+          first_slice_only=first_slice_only)
+    status = b.fit_status()
+    U, mu, eig = b.export()
+    C, n = b.export_cov()
+    b.close()
+    return status, U[0].astype(np.float64), mu[0], eig[0], C[0], n[0]
+
+
+def _check(U, eig, C, k, columns=None):
+    d = C.shape[0]
+    w = np.linalg.eigvalsh(C)[::-1]
+    lam = w[0]
+    # both solvers are backward stable: a few d roundings of the largest eigenvalue
+    assert np.max(np.abs(eig - w)) <= 1e-15 * (d + 10) * lam
+    assert np.all(np.diff(eig) <= 0)
+    # U is rounded to fp32, each entry by at most 2^-24 of itself: products of two unit columns move by 2 * 2^-24,
+    # C u - lambda u by at most (|C| + lambda) * 2^-24 |u| in 2-norm; 1e-8 for everything in float64
+    assert np.max(np.abs(U.T @ U - np.eye(k))) <= 2 * 2.0 ** -24 + 1e-8
+    cols = U[:, :columns]
+    resid = np.linalg.norm(C @ cols - cols * eig[:cols.shape[1]], axis=0)
+    assert np.max(resid) <= (2 * 2.0 ** -24 + 1e-8) * lam
+    for i in range(k):
+        assert U[np.argmax(np.abs(U[:, i])), i] > 0
+
+
+@pytest.mark.parametrize("d,k", [(2, 1), (2, 2), (3, 2), (4, 4), (5, 1), (15, 15), (17, 4), (31, 31), (33, 9), (63, 63), (64, 64),
+                                 (65, 17), (127, 127), (128, 128), (129, 129), (130, 1), (191, 33), (192, 64), (255, 65),
+                                 (257, 31), (300, 300), (511, 32), (513, 100), (767, 96), (769, 128), (1023, 7), (1024, 130)])
+def test_sizes(d, k):
+    rng = np.random.default_rng(d * 1000 + k)
+    A = rng.standard_normal((d, max(1, d // 8)))
+    x = rng.standard_normal((2 * d + 70, A.shape[1])) @ A.T + 0.1 * rng.standard_normal((2 * d + 70, d))
+    status, U, mu, eig, C, n = _fit([x], d, k)
+    assert status > 0 and n == len(x)
+    _check(U, eig, C, k)
+
+
+@pytest.mark.parametrize("d,k", [(16, 16), (48, 20), (96, 96), (128, 40), (200, 80)])
+@pytest.mark.parametrize("levels", [1, 3])
+def test_repeated_eigenvalues(d, k, levels):
+    """Slices +a_i e_i and -a_i e_i: C is diagonal with `levels` different entries, each many times over."""
+    a = 1.0 + np.arange(d) % levels
+    x = np.zeros((2 * d, d))
+    x[np.arange(d), np.arange(d)] = a
+    x[d + np.arange(d), np.arange(d)] = -a
+    _, U, _, eig, C, _ = _fit([x], d, k)
+    assert np.count_nonzero(C - np.diag(np.diag(C))) == 0
+    _check(U, eig, C, k)
+
+
+@pytest.mark.parametrize("d,k,rank", [(24, 24, 3), (64, 40, 5), (128, 60, 12), (160, 100, 9), (768, 96, 24)])
+def test_more_columns_than_the_rank(d, k, rank):
+    """Exactly rank-deficient data (small whole numbers): the trailing columns come from the null space."""
+    rng = np.random.default_rng(d + rank)
+    x = rng.integers(-3, 4, (3 * d, rank)).astype(np.float64) @ rng.integers(-2, 3, (rank, d))
+    _, U, _, eig, C, _ = _fit([x], d, k)
+    _check(U, eig, C, k)
+    assert np.all(np.abs(eig[rank:]) <= 1e-12 * eig[0])
+
+
+@pytest.mark.parametrize("d,k,L,dtype", [(64, 7, 2, "f32"), (65, 9, 3, "f32"), (96, 14, 15, "bf16"), (97, 15, 16, "f32"), (130, 16, 17, "f32"),
+                                         (128, 31, 33, "f32"), (256, 60, 64, "bf16"), (257, 64, 65, "f32"), (768, 96, 100, "f32"),
+                                         (1023, 127, 128, "f32"), (300, 50, 127, "f32"),     # the sample matrix
+                                         (100, 30, 100, "f32"), (129, 20, 128, "f32"), (64, 64, 40, "bf16"),   # the covariance itself
+                                         (768, 200, 20, "f32")])                             # most columns undetermined
+def test_first_slice_sizes(d, k, L, dtype):
+    rng = np.random.default_rng(d * 131 + L)
+    x = [rng.standard_normal((3, d)) + 0.5 for _ in range(L)]
+    if dtype == "bf16":
+        x = [torch.from_numpy(v).to(torch.bfloat16).double().numpy() for v in x]
+    else:
+        x = [v.astype(np.float32).astype(np.float64) for v in x]
+    _, U, mu, eig, C, n = _fit(x, d, k, first_slice_only=True, dtype=dtype)
+    X = np.stack([v[0] for v in x])
+    assert n == L
+    np.testing.assert_allclose(mu, X.mean(0), rtol=2.0 ** -23, atol=1e-9)
+    Xc = X - X.mean(0)
+    assert np.max(np.abs(C - Xc.T @ Xc / L)) <= 1e-15 * (L + 10) * np.max(np.abs(C))
+    assert np.array_equal(C, C.T)
+    _check(U, eig, C, k, columns=min(k, L - 1))
