@@ -6,230 +6,264 @@
 // That is the order in which neighbouring numbers are linearly correlated, which is what the
 // slice-wise PCA lives on.  Pure permutation; bound by HBM.
 //
-// One work-group moves a tile of TF filters x TD depths x all H*W positions through LDS: it
-// reads, for each filter, the contiguous run grad[f][d0 .. d0+TD) (TD*H*W numbers) and writes,
-// for each (h, w, d), the TF adjacent numbers of the flat layout.  LDS rows get an odd stride,
-// so both directions are free of bank conflicts.
+// One work-group moves a tile of TF filters x a run of consecutive numbers of each filter (TD depths x all H*W
+// positions, or one depth x a piece of H*W when that alone is longer than a tile) through LDS, tile[row][filter] with
+// row = hw * nd + dd the order of the flat side.
+//   [F][D][H][W] side: a thread takes GV consecutive numbers of VT = 16 / sizeof(T) neighbouring filters (VT accesses),
+//     transposes them in registers and exchanges GV whole 16-byte words with LDS.  GV = VT where runs are 16-byte
+//     aligned (D*H*W and the pieces multiples of VT), else 1.
+//   flat side: a thread moves FV neighbouring filters of one row; FV = VT where F is a multiple of VT, else 1.
+// A thread's accesses of a side are all requested before the first of them is waited for (up to eight 16-byte words):
+// with one at a time, as before, a tile took a memory latency per word.  The 16-byte words of a row are permuted by
+// x -> x ^ (row ^ row >> 2): words of one filter group in rows 4 c + i, c = 0, 1, 2 .., then sit in different banks, and so
+// does a whole row; no padding.
+// Every access is 256 bytes or more in one piece; what is left is how the pieces in flight lie in memory.  A layer too
+// large for the last-level cache takes its tiles with the filter groups fastest (whole rows of the flat side at a time):
+// fully connected 4096 x 25088, fp32 4.7 -> 5.1 TB/s read + written; smaller ones along the runs (1000 x 4096 4.1
+// against 3.7).  Tiles of 128 filters are no faster (4096 x 4096: 5.6 against 6.3), nor are non-temporal accesses.
+// fp32 / bf16, flatten, TB/s: 4096 x 25088 5.1 / 4.8 (one access at a time and LDS rows of odd length: 4.3 / 3.5), 4096 x 4096
+// 6.3 / 6.0, 512 x 4096 x 3 x 3 5.0 / 5.9, 512 x 512 x 3 x 3 3.1 / 2.1 (6 and 4.5 us: a tile's latency).
 #include "gvq_internal.h"
-
-typedef float f4 __attribute__((ext_vector_type(4)));
 
 #define LAYOUT_THREADS 256
 #define LAYOUT_TF 64
-#define LAYOUT_LDS_ELEMS 8192   // 32-bit words of LDS per work-group
+#define LAYOUT_TILE 32768   // bytes of LDS per work-group
 
 struct LayoutArgs {
     const void* src;
     void* dst;
-    int F, D, HW, TD, RS;   // RS: LDS row stride (odd, >= TD*HW)
-    int n_dtiles;
-};
-
-template <typename T, bool FLATTEN>
-__global__ __launch_bounds__(LAYOUT_THREADS) void conv_layout_kernel(LayoutArgs a)
-{
-    extern __shared__ unsigned int tile_raw[];
-    T* tile = (T*)tile_raw;   // [TF][RS]
-    const int ft = blockIdx.x / a.n_dtiles, dt = blockIdx.x % a.n_dtiles;
-    const int f0 = ft * LAYOUT_TF, d0 = dt * a.TD;
-    const int nf = a.F - f0 < LAYOUT_TF ? a.F - f0 : LAYOUT_TF;
-    const int nd = a.D - d0 < a.TD ? a.D - d0 : a.TD;
-    const int run = nd * a.HW;                 // contiguous numbers per filter in the [F][D][H][W] layout
-    const T* grad = (const T*)(FLATTEN ? a.src : a.dst);   // the [F][D][H][W] side
-    const T* flat = (const T*)(FLATTEN ? a.dst : a.src);   // the flat side
-    if (FLATTEN) {
-        for (int i = threadIdx.x; i < nf * run; i += LAYOUT_THREADS) {
-            const int f = i / run, r = i - f * run;
-            tile[f * a.RS + r] = grad[((size_t)(f0 + f) * a.D + d0) * a.HW + r];
-        }
-        __syncthreads();
-        for (int i = threadIdx.x; i < run * nf; i += LAYOUT_THREADS) {
-            const int g = i / nf, f = i - g * nf;            // g = (hw, d) group, f innermost
-            const int hw = g / nd, dd = g - hw * nd;
-            ((T*)a.dst)[((size_t)hw * a.D + d0 + dd) * a.F + f0 + f] = tile[f * a.RS + dd * a.HW + hw];
-        }
-    } else {
-        for (int i = threadIdx.x; i < run * nf; i += LAYOUT_THREADS) {
-            const int g = i / nf, f = i - g * nf;
-            const int hw = g / nd, dd = g - hw * nd;
-            tile[f * a.RS + dd * a.HW + hw] = flat[((size_t)hw * a.D + d0 + dd) * a.F + f0 + f];
-        }
-        __syncthreads();
-        for (int i = threadIdx.x; i < nf * run; i += LAYOUT_THREADS) {
-            const int f = i / run, r = i - f * run;
-            ((T*)a.dst)[((size_t)(f0 + f) * a.D + d0) * a.HW + r] = tile[f * a.RS + r];
-        }
-    }
-}
-
-// 16-byte aligned sides, F and D*H*W multiples of V = 16 / sizeof(T) (4 for fp32, 8 for bf16): the same tile scheme
-// with 128-bit global accesses and no division per element.  LDS holds the tile in the flat order, tile[g][f],
-// g = hw * nd + dd the position inside the tile and f fastest (row stride TF + V elements: 128-bit rows, and 8 lanes x
-// 128 bits cover all banks).  On the [F][D][H][W] side a thread moves V consecutive numbers of one filter's run (and
-// scatters them to, or gathers them from, V rows of the tile); on the flat side a thread moves V adjacent filters of
-// one row.  A tile is TD depths x all H*W positions, or, when H*W alone is longer than a tile (and a multiple of V),
-// one depth x a piece of H*W; either way a filter's part of it is one contiguous run.
-#define LF_BYTES 32768          // LDS per work-group
-
-struct LayoutFastArgs {
-    const void* src;
-    void* dst;
-    int F, D, HW, TD;           // TD * HWT is a multiple of V and at most LF_BYTES / sizeof(T) / (TF + V)
-    int n_dtiles;
-    int HWT, n_hwtiles;         // positions per tile: H*W (one tile over them), or a multiple of V when H*W is too long
-                                // for one tile (then TD = 1)
+    int F, D, HW;
+    int TD, HWT;               // depths and positions per tile (TD = 1 or HWT = H*W)
+    int n_ftiles, n_dtiles, n_hwtiles;
+    unsigned int magic;        // n / H*W = n * magic >> 16 for the positions of a tile (TD > 1)
+    int filters_fast;          // order of the tiles: the filter groups, or the runs, fastest
 };
 
 typedef unsigned int lu4 __attribute__((ext_vector_type(4)));
 
-// TF: filters per tile (a row of the flat side is TF elements contiguous)
-template <typename T, bool FLATTEN, int TF>
-__global__ __launch_bounds__(LAYOUT_THREADS) void conv_layout_fast_kernel(LayoutFastArgs a)
+template <typename T, int N> union LayoutVec {
+    lu4 v;
+    T e[N];
+};
+
+template <typename T, bool FLATTEN, int GV, int FV>
+__global__ __launch_bounds__(LAYOUT_THREADS) void conv_layout_kernel(LayoutArgs a)
 {
-    extern __shared__ lu4 ftile_raw[];
-    T* ftile = (T*)ftile_raw;   // [run][RS]
-    constexpr int V = 16 / sizeof(T), RS = TF + V, QF = TF / V, ROWS = LAYOUT_THREADS / QF;
-    union Vec { lu4 v; T e[V]; };
+    extern __shared__ lu4 tile[];                         // [rows][TF / VT] 16-byte words, permuted within a row
+    constexpr int TF = LAYOUT_TF, VT = 16 / sizeof(T), QF = TF / VT;
+    constexpr int GI = GV > 1 ? LAYOUT_TILE / 16 / VT / LAYOUT_THREADS : 2;   // items in flight on the [F][D][H][W] side
+    constexpr int FI = 8;                                                     // accesses in flight on the flat side
+    typedef LayoutVec<T, VT> Vec;
     const int tid = threadIdx.x;
     const int ht = blockIdx.x % a.n_hwtiles, fd = blockIdx.x / a.n_hwtiles;
-    const int ft = fd / a.n_dtiles, dt = fd % a.n_dtiles;
+    const int ft = a.filters_fast ? fd % a.n_ftiles : fd / a.n_dtiles;
+    const int dt = a.filters_fast ? fd / a.n_ftiles : fd - ft * a.n_dtiles;
     const int f0 = ft * TF, d0 = dt * a.TD, hw0 = ht * a.HWT;
-    const int nf = a.F - f0 < TF ? a.F - f0 : TF;             // a multiple of V
+    const int nf = a.F - f0 < TF ? a.F - f0 : TF;
     const int nd = a.D - d0 < a.TD ? a.D - d0 : a.TD;
     const int nhw = a.HW - hw0 < a.HWT ? a.HW - hw0 : a.HWT;
-    const int run = nd * nhw, rq = run / V;                  // run: a multiple of V, contiguous in a filter (nd = 1 or nhw = H*W)
-    const T* grad = (const T*)(FLATTEN ? a.src : a.dst);
-    const T* flat = (const T*)(FLATTEN ? a.dst : a.src);
-    // the [F][D][H][W] side: this thread's chunk c of a run, for filters fsub, fsub + fpp, ...
-    const int fpp = LAYOUT_THREADS / rq, fsub = tid / rq, c = tid - fsub * rq;
-    int g[V];
+    const int run = nd * nhw;                             // consecutive numbers of a filter
+    const size_t fstride = (size_t)a.D * a.HW;
+    T* const gside = (T*)(FLATTEN ? a.src : a.dst) + (size_t)f0 * fstride + (size_t)d0 * a.HW + hw0;
+    T* const fside = (T*)(FLATTEN ? a.dst : a.src) + ((size_t)hw0 * a.D + d0) * a.F + f0;
+    const auto word = [](int row, int q) { return row * QF + (q ^ ((row ^ (row >> 2)) & (QF - 1))); };
+
+    // [F][D][H][W] side: item = (group of VT filters, GV consecutive numbers)
+    const auto g_side = [&]() {
+        const int rq = run / GV, nq = (nf + VT - 1) / VT, items = rq * nq;
+        for (int it0 = tid; it0 < items; it0 += GI * LAYOUT_THREADS) {
+            int q[GI], r0[GI];
+            T x[GI][VT][GV];       // [item][filter][number]
 #pragma unroll
-    for (int i = 0; i < V; ++i) {
-        const int r = V * c + i, dd = r / nhw, hw = r - dd * nhw;
-        g[i] = (hw * nd + dd) * RS;
-    }
-    // the flat side: V adjacent filters q of rows gr, gr + ROWS, ...
-    const int q = tid % QF, gr = tid / QF;
-    auto grad_ptr = [&](int f) { return (T*)grad + ((size_t)(f0 + f) * a.D + d0) * a.HW + hw0 + V * c; };
-    auto flat_rows = [&](auto&& body) {
-        int hw = gr / nd, dd = gr - hw * nd;
-        for (int gg = gr; gg < run; gg += ROWS) {
-            if (V * q < nf) body(gg, (T*)flat + ((size_t)(hw0 + hw) * a.D + d0 + dd) * a.F + f0 + V * q);
-            dd += ROWS;
-            while (dd >= nd) { dd -= nd; ++hw; }
+            for (int n = 0; n < GI; ++n) {
+                const int it = it0 + n * LAYOUT_THREADS;
+                q[n] = it < items ? it / rq : -1;
+                r0[n] = GV * (it - q[n] * rq);
+            }
+            if (FLATTEN) {
+#pragma unroll
+                for (int n = 0; n < GI; ++n) {
+                    if (q[n] < 0) continue;
+                    const T* p = gside + (size_t)(VT * q[n]) * fstride + r0[n];
+#pragma unroll
+                    for (int u = 0; u < VT; ++u, p += fstride) {
+                        if (FV == 1 && VT * q[n] + u >= nf) continue;     // F a multiple of VT otherwise
+                        if constexpr (GV > 1) {
+                            const lu4 w = *(const lu4*)p;
+                            __builtin_memcpy(x[n][u], &w, 16);
+                        } else {
+                            x[n][u][0] = *p;
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int n = 0; n < GI; ++n) {
+                if (q[n] < 0) continue;
+#pragma unroll
+                for (int i = 0; i < GV; ++i) {
+                    int row = r0[n] + i;
+                    if (nd > 1) {
+                        const int dd = (int)((unsigned int)row * a.magic >> 16);
+                        row = (row - dd * nhw) * nd + dd;
+                    }
+                    Vec w;
+                    if (FLATTEN) {
+#pragma unroll
+                        for (int u = 0; u < VT; ++u) w.e[u] = x[n][u][i];
+                        tile[word(row, q[n])] = w.v;
+                    } else {
+                        w.v = tile[word(row, q[n])];
+#pragma unroll
+                        for (int u = 0; u < VT; ++u) x[n][u][i] = w.e[u];
+                    }
+                }
+            }
+            if (!FLATTEN) {
+#pragma unroll
+                for (int n = 0; n < GI; ++n) {
+                    if (q[n] < 0) continue;
+                    T* p = gside + (size_t)(VT * q[n]) * fstride + r0[n];
+#pragma unroll
+                    for (int u = 0; u < VT; ++u, p += fstride) {
+                        if (FV == 1 && VT * q[n] + u >= nf) continue;
+                        if constexpr (GV > 1) {
+                            lu4 w;
+                            __builtin_memcpy(&w, x[n][u], 16);
+                            *(lu4*)p = w;
+                        } else {
+                            *p = x[n][u][0];
+                        }
+                    }
+                }
+            }
+        }
+    };
+    // flat side: rows of the tile, FV filters per access; a row of the tile is TF / FV accesses wide
+    const auto f_side = [&]() {
+        constexpr int W = TF / FV, ROWS = LAYOUT_THREADS / W;
+        const int c = tid % W;                            // this thread's access within every row
+        if (c * FV >= nf) return;
+        for (int row0 = tid / W; row0 < run; row0 += FI * ROWS) {
+            lu4 xv[FI];
+            T xs[FI];
+            T* p[FI];
+#pragma unroll
+            for (int n = 0; n < FI; ++n) {
+                const int row = row0 + n * ROWS;
+                const int hw = nhw == 1 ? 0 : nd == 1 ? row : row / nd, dd = row - hw * nd;   // row = hw * nd + dd
+                p[n] = fside + ((size_t)hw * a.D + dd) * a.F + FV * c;
+                if (!FLATTEN && row < run) {
+                    if constexpr (FV > 1) xv[n] = *(const lu4*)p[n];
+                    else xs[n] = *p[n];
+                }
+            }
+#pragma unroll
+            for (int n = 0; n < FI; ++n) {
+                const int row = row0 + n * ROWS;
+                if (row >= run) break;
+                if constexpr (FV > 1) {
+                    lu4& w = tile[word(row, c)];
+                    if (FLATTEN) xv[n] = w;
+                    else w = xv[n];
+                } else {
+                    T& w = ((T*)&tile[word(row, c / VT)])[c % VT];
+                    if (FLATTEN) xs[n] = w;
+                    else w = xs[n];
+                }
+            }
+            if (FLATTEN) {
+#pragma unroll
+                for (int n = 0; n < FI; ++n) {
+                    if (row0 + n * ROWS >= run) break;
+                    if constexpr (FV > 1) *(lu4*)p[n] = xv[n];
+                    else *p[n] = xs[n];
+                }
+            }
         }
     };
     if (FLATTEN) {
-        if (fsub < fpp)
-            for (int f = fsub; f < nf; f += fpp) {
-                Vec x;
-                x.v = __builtin_nontemporal_load((const lu4*)grad_ptr(f));
-#pragma unroll
-                for (int i = 0; i < V; ++i) ftile[g[i] + f] = x.e[i];
-            }
+        g_side();
         __syncthreads();
-        flat_rows([&](int gg, T* p) { __builtin_nontemporal_store(*(const lu4*)(ftile + gg * RS + V * q), (lu4*)p); });
+        f_side();
     } else {
-        flat_rows([&](int gg, T* p) { *(lu4*)(ftile + gg * RS + V * q) = __builtin_nontemporal_load((const lu4*)p); });
+        f_side();
         __syncthreads();
-        if (fsub < fpp)
-            for (int f = fsub; f < nf; f += fpp) {
-                Vec x;
-#pragma unroll
-                for (int i = 0; i < V; ++i) x.e[i] = ftile[g[i] + f];
-                __builtin_nontemporal_store(x.v, (lu4*)grad_ptr(f));
-            }
+        g_side();
     }
 }
 
-// Depths per tile for the kernel above with at most max_run rows (a multiple of V), or 0 when the shape does not fit
-// it; *hwt: the positions per tile.
-static int layout_fast_td(const void* src, const void* dst, int F, int D, int HW, int V, int max_run, int* hwt)
+// Layers whose two orders are the same (a bias: D = H*W = 1, or one filter with D or H*W = 1): a copy, 16 bytes per
+// thread where both sides are aligned.  Through the tiles a bias took 3.6 us on average instead of 2.6, all of it latency.
+template <typename T>
+__global__ __launch_bounds__(LAYOUT_THREADS) void layout_copy_kernel(const T* src, T* dst, size_t n, int words)
 {
-    *hwt = HW;
-    if ((((uintptr_t)src | (uintptr_t)dst) & 15) || F % V || ((int64_t)D * HW) % V) return 0;
-    if (HW > max_run) {   // one depth per tile, H*W in pieces
-        if (HW % V) return 0;
-        *hwt = max_run;
-        return 1;
-    }
-    int step = V;                                  // TD * HW must be a multiple of V: TD of V / gcd(HW, V)
-    while (step > 1 && (HW * (step / 2)) % V == 0) step /= 2;
-    int td = max_run / HW / step * step;
-    if (td < step) return 0;
-    if (td >= D) return D;                         // one depth tile: D * HW is a multiple of V
-    return td;
+    constexpr int VT = 16 / sizeof(T);
+    const size_t i0 = (size_t)blockIdx.x * LAYOUT_THREADS + threadIdx.x, step = (size_t)gridDim.x * LAYOUT_THREADS;
+    const size_t w = words ? n / VT : 0;
+    for (size_t i = i0; i < w; i += step) ((lu4*)dst)[i] = ((const lu4*)src)[i];
+    for (size_t i = w * VT + i0; i < n; i += step) dst[i] = src[i];
 }
 
-template <typename T, bool FLATTEN, int TF>
-static int launch_layout_fast(const void* src, void* dst, int F, int D, int HW, int td, int hwt, hipStream_t st)
+template <typename T, bool FLATTEN, int GV, int FV>
+static int launch_tiles(const LayoutArgs& a, int64_t grid, size_t lds, hipStream_t st)
 {
-    LayoutFastArgs a;
-    a.src = src; a.dst = dst; a.F = F; a.D = D; a.HW = HW; a.TD = td;
-    a.n_dtiles = (D + td - 1) / td;
-    a.HWT = hwt; a.n_hwtiles = (HW + hwt - 1) / hwt;
-    const int n_ftiles = (F + TF - 1) / TF;
-    const size_t lds = sizeof(T) * (size_t)td * hwt * (TF + 16 / sizeof(T));
-    const int64_t grid = (int64_t)n_ftiles * a.n_dtiles * a.n_hwtiles;
-    if (grid > 0x7fffffff) return GVQ_EINVAL;
-    hipLaunchKernelGGL((conv_layout_fast_kernel<T, FLATTEN, TF>), dim3((unsigned)grid), dim3(LAYOUT_THREADS), lds,
-                       st, a);
+    hipLaunchKernelGGL((conv_layout_kernel<T, FLATTEN, GV, FV>), dim3((unsigned)grid), dim3(LAYOUT_THREADS), lds, st, a);
     GVQ_HIP(hipGetLastError());
     return GVQ_OK;
-}
-
-// H*W too large for an LDS tile and not a multiple of the vector width: one thread per number (correct, not fast).
-template <typename T, bool FLATTEN>
-__global__ void conv_layout_direct_kernel(const T* src, T* dst, int F, int D, int HW)
-{
-    const size_t n = (size_t)F * D * HW;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const int f = (int)(i % F);          // i indexes the flat side
-        const size_t g = i / F;
-        const int dd = (int)(g % D), hw = (int)(g / D);
-        const size_t j = ((size_t)f * D + dd) * HW + hw;
-        if (FLATTEN) dst[i] = src[j]; else dst[j] = src[i];
-    }
 }
 
 template <typename T, bool FLATTEN>
 static int launch_layout(const void* src, void* dst, int F, int D, int HW, hipStream_t st)
 {
-    {
-        // 64 filters per tile; 128 for a fully connected layer when it is flattened or holds bf16 (measured on 67 - 411 MB
-        // layers: fp32 flatten 4.2 - 4.6 against 3.9 TB/s, bf16 3.5 / 3.2 against 2.7 / 2.6; with H*W > 1, and for the
-        // fp32 unflatten, 128 is 15 - 30 % slower)
-        constexpr int V = 16 / sizeof(T);
-        const int tf = HW == 1 && F >= 128 && (FLATTEN || sizeof(T) == 2) ? 128 : 64;
-        int hwt = HW;
-        const int td = layout_fast_td(src, dst, F, D, HW, V, LF_BYTES / (int)sizeof(T) / (tf + V) / V * V, &hwt);
-        if (td > 0) {
-            if (tf == 128) return launch_layout_fast<T, FLATTEN, 128>(src, dst, F, D, HW, td, hwt, st);
-            return launch_layout_fast<T, FLATTEN, 64>(src, dst, F, D, HW, td, hwt, st);
-        }
-    }
-    if ((int64_t)LAYOUT_TF * HW > LAYOUT_LDS_ELEMS) {
-        const size_t n = (size_t)F * D * HW;
-        int grid = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-        hipLaunchKernelGGL((conv_layout_direct_kernel<T, FLATTEN>), dim3(grid), dim3(256), 0, st, (const T*)src,
-                           (T*)dst, F, D, HW);
+    constexpr int VT = 16 / sizeof(T);
+    const bool aligned = (((uintptr_t)src | (uintptr_t)dst) & 15) == 0;
+    if (D * (int64_t)HW == 1 || (F == 1 && (D == 1 || HW == 1))) {
+        const size_t n = (size_t)F * D * HW, per = (size_t)LAYOUT_THREADS * (aligned ? VT : 1);
+        const size_t grid = (n + per - 1) / per;
+        hipLaunchKernelGGL((layout_copy_kernel<T>), dim3((unsigned)(grid < 2048 ? grid : 2048)), dim3(LAYOUT_THREADS), 0, st,
+                           (const T*)src, (T*)dst, n, aligned ? 1 : 0);
         GVQ_HIP(hipGetLastError());
         return GVQ_OK;
     }
+    const bool fv = aligned && F % VT == 0;
+    bool gv = aligned && ((int64_t)D * HW) % VT == 0;
+    const int max_run = LAYOUT_TILE / LAYOUT_TF / (int)sizeof(T);   // numbers of one filter, a multiple of VT
+    const int n_ftiles = (F + LAYOUT_TF - 1) / LAYOUT_TF;
     LayoutArgs a;
     a.src = src; a.dst = dst; a.F = F; a.D = D; a.HW = HW;
-    int td = LAYOUT_LDS_ELEMS / (LAYOUT_TF * HW);
-    if (td > 16) td = 16;
-    if (td > D) td = D;
-    while (td > 1 && (int64_t)LAYOUT_TF * ((td * HW) | 1) > LAYOUT_LDS_ELEMS) --td;
-    a.TD = td;
-    a.RS = (td * HW) | 1;
-    a.n_dtiles = (D + td - 1) / td;
-    const int n_ftiles = (F + LAYOUT_TF - 1) / LAYOUT_TF;
-    const size_t lds = sizeof(unsigned int) * (size_t)LAYOUT_TF * a.RS;
-    hipLaunchKernelGGL((conv_layout_kernel<T, FLATTEN>), dim3(n_ftiles * a.n_dtiles), dim3(LAYOUT_THREADS), lds, st, a);
-    GVQ_HIP(hipGetLastError());
-    return GVQ_OK;
+    // a small layer is cut into shorter runs, down to 32 numbers, so that its tiles reach more of the chip
+    int most = max_run;
+    while (most > 32 && (int64_t)n_ftiles * (((int64_t)D * HW + most - 1) / most) < 512) most /= 2;
+    a.HWT = HW;
+    a.TD = 1;
+    if (HW > most && HW > max_run) {
+        if (HW % VT) gv = false;
+        a.HWT = most;
+    } else {
+        const int fit = HW > most ? HW : most;
+        int step = 1;                                         // depths whose run is a multiple of VT
+        if (gv) while ((HW * step) % VT) step *= 2;
+        int td = fit / HW / step * step;
+        if (td < step) {                                      // not one such group of depths in a tile
+            td = max_run / HW / step * step;
+            if (td < step) { td = max_run / HW; gv = false; }
+            else td = step;
+        }
+        a.TD = td < D ? td : D;
+    }
+    a.n_dtiles = (D + a.TD - 1) / a.TD;
+    a.n_hwtiles = (HW + a.HWT - 1) / a.HWT;
+    a.magic = (65536u + (unsigned int)a.HWT - 1) / (unsigned int)a.HWT;
+    a.n_ftiles = n_ftiles;
+    a.filters_fast = (size_t)F * D * HW * sizeof(T) >= (32u << 20);
+    const size_t lds = sizeof(T) * (size_t)a.TD * a.HWT * LAYOUT_TF;
+    const int64_t grid = (int64_t)n_ftiles * a.n_dtiles * a.n_hwtiles;
+    if (grid > 0x7fffffff) return GVQ_EINVAL;
+    if (gv && fv) return launch_tiles<T, FLATTEN, VT, VT>(a, grid, lds, st);
+    if (gv) return launch_tiles<T, FLATTEN, VT, 1>(a, grid, lds, st);
+    if (fv) return launch_tiles<T, FLATTEN, 1, VT>(a, grid, lds, st);
+    return launch_tiles<T, FLATTEN, 1, 1>(a, grid, lds, st);
 }
 
 int gvq_launch_layout(const void* src, void* dst, int F, int D, int HW, gvq_dtype_t dtype, bool flatten,
