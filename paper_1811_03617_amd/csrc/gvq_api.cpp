@@ -69,7 +69,7 @@ int gvq_basis_destroy(gvq_basis_t* h)
 {
     if (!h) return GVQ_OK;
     (void)hipDeviceSynchronize();
-    void* dev[] = {h->d_offs, h->d_tile_block, h->d_U, h->d_Upc, h->d_Upd, h->d_Upb, h->d_Uws, h->d_Umu, h->d_mu, h->d_eig, h->d_cov, h->d_eA, h->d_eT, h->d_eZ, h->d_eLU, h->d_part, h->d_part2, h->d_mom, h->d_nsamp, h->d_ltile, h->d_sweeps, h->d_ksel, h->d_loss_slice, h->d_loss_part};
+    void* dev[] = {h->d_offs, h->d_tile_block, h->d_U, h->d_Upc, h->d_Upd, h->d_Upb, h->d_Uws, h->d_Umu, h->d_mu, h->d_eig, h->d_cov, h->d_eA, h->d_eT, h->d_eZ, h->d_eLU, h->d_part, h->d_mom, h->d_nsamp, h->d_ltile, h->d_sweeps, h->d_ksel, h->d_loss_slice, h->d_loss_part};
     for (void* p : dev)
         if (p) (void)hipFree(p);
     for (gvq_plan& pl : h->plan) {
@@ -107,8 +107,6 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
     if (offs) memcpy(h->h_offs, offs, sizeof(int64_t) * (n_blocks + 1));
     else { h->h_offs[0] = 0; h->h_offs[1] = S; }
 
-    // moment partials per basis: enough workgroups to fill the chip, never more than one
-    // per 64 sample slices of the largest basis
     int64_t longest = 0;
     for (int b = 0; b < n_blocks; ++b)
         if (h->h_offs[b + 1] - h->h_offs[b] > longest) longest = h->h_offs[b + 1] - h->h_offs[b];
@@ -121,30 +119,7 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
         TRY(hipGetDevice(&h->device));
         TRY(hipGetDeviceProperties(&prop, h->device));
         h->num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-        size_t width = (size_t)d * d + d;
-        size_t part_doubles = 0;   // per basis, when not P * width
-        if (!gvq_moments_mfma_shape(d)) {
-            // one wave per (64 x 64 block, sample chunk): as many chunks as fill, but do not exceed, the
-            // two waves per SIMD the kernel runs at (one wave more would cost a whole second round),
-            // never less than 64 sample slices per chunk
-            const int64_t ng = gvq_large_groups(d), npairs = ng * (ng + 1) / 2;
-            int64_t chunks = (8LL * h->num_cu) / (npairs * n_blocks);
-            if (chunks > (longest + 63) / 64) chunks = (longest + 63) / 64;
-            if (chunks < 1) chunks = 1;
-            h->P = (int)chunks;
-            part_doubles = gvq_large_partial_doubles(d, h->P);
-        } else {
-            // two work-groups of 4 waves per compute unit, spread over the bases (rounded down: every
-            // work-group runs for the whole launch, so a few more than fit would cost a second
-            // round as long as the first); never less than 64 sample slices per stream
-            const int streams = gvq_moments_streams(d);
-            int64_t wgs = (2LL * h->num_cu) / n_blocks;
-            if (wgs > (longest + 64LL * streams - 1) / (64LL * streams)) wgs = (longest + 64LL * streams - 1) / (64LL * streams);
-            if (wgs < 1) wgs = 1;
-            h->mom_wgs = (int)wgs;
-            h->P = (int)wgs * streams;
-            width = (size_t)gvq_moments_packed_width(d);
-        }
+        h->mom_part = gvq_moments_plan(h, longest);
         const size_t B = (size_t)n_blocks, W = (size_t)d * d + d;
         TRY(hipMalloc((void**)&h->d_offs, sizeof(int64_t) * (B + 1)));
         TRY(hipMalloc((void**)&h->d_U, sizeof(float) * B * d * k));
@@ -179,12 +154,7 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
         TRY(hipMalloc((void**)&h->d_eT, sizeof(double) * B * 5 * d));
         TRY(hipMalloc((void**)&h->d_eZ, sizeof(double) * B * k * d));
         if (gvq_eigen_lu_doubles(d, k)) TRY(hipMalloc((void**)&h->d_eLU, sizeof(double) * B * gvq_eigen_lu_doubles(d, k)));
-        if (part_doubles) {
-            TRY(hipMalloc((void**)&h->d_part, sizeof(double) * B * part_doubles));
-        } else {
-            TRY(hipMalloc((void**)&h->d_part, sizeof(double) * B * (size_t)h->P * width));
-            TRY(hipMalloc((void**)&h->d_part2, sizeof(double) * B * (size_t)((h->P + 31) / 32) * width));
-        }
+        TRY(hipMalloc((void**)&h->d_part, sizeof(double) * B * h->mom_part));
         TRY(hipMalloc((void**)&h->d_mom, sizeof(double) * B * W));
         TRY(hipMalloc((void**)&h->d_nsamp, sizeof(unsigned long long) * 2 * B));
         TRY(hipMalloc((void**)&h->d_sweeps, sizeof(int) * B));

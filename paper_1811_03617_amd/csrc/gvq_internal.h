@@ -43,10 +43,9 @@ struct gvq_basis {
     float* d_Umu = nullptr;     // [B][KP] U^T mu (bf16 gradients)
     double* d_eig = nullptr;    // [B][d]
     double* d_cov = nullptr;    // [B][d][d]
-    double* d_part = nullptr;   // moment partials: [B][P][packed width] for d in {16,32,64,128}, else
-                                // [B][block pairs][P][64*64+64] (64 x 64 blocks, P sample chunks)
-    double* d_part2 = nullptr;  // [B][ceil(P/32)][width] second level of the partial sum (MFMA path)
-    int mom_wgs = 0;            // work-groups per basis of the MFMA moments kernel (P = streams * mom_wgs there)
+    double* d_part = nullptr;   // moment partials: [B][mom_part]
+    size_t mom_part = 0;        // doubles per basis
+    int mom_diag = 1, mom_off = 0;   // sample chunks per panel, and per pair of different panels, of the moments kernel
     double* d_mom = nullptr;    // [B][d*d+d] reduced moments (sum x x^T, then sum x)
     unsigned long long* d_nsamp = nullptr;  // [B] sample slices the moment kernels of the last fit took in, counted by
                                 // them; then [B] largest |entry| of the decomposed matrix, as bits
@@ -59,7 +58,6 @@ struct gvq_basis {
     float* d_loss_slice = nullptr;  // [S] per-slice squared residual of the last gvq_local_loss
     double* d_loss_part = nullptr;  // [B][loss_groups] partial sums of those
     int loss_groups = 1;
-    int P = 0;                  // moment partials per basis
     int fit_L = 0;              // gradients of the last fit
     bool fit_first_slice = false;  // the last fit sampled only the first slice of every basis
     bool fitted = false;        // basis usable (fit or import)
@@ -127,10 +125,9 @@ int gvq_launch_pack(const gvq_basis* h, hipStream_t st);
 bool gvq_mfma_shape(int d, int k);
 int gvq_build_plans(gvq_basis* h);   // fills h->plan (needs h_offs; no-op for one basis or other shapes)
 bool gvq_bf16_pipe_shape(const gvq_basis* h);
-bool gvq_moments_mfma_shape(int d);
-int gvq_moments_packed_width(int d);
-int gvq_moments_streams(int d);   // sample streams (partial slots) per work-group
-// Moments in 64 x 64 blocks (every d other than 16, 32, 64, 128).
+// Moments: chooses the sample chunks (`longest`: slices of the longest basis), returns the partials' doubles per basis.
+size_t gvq_moments_plan(gvq_basis* h, int64_t longest);
+int gvq_launch_moments(gvq_basis* h, const void* const* grads, int L, hipStream_t st);   // -> d_mom, d_nsamp
 bool gvq_long_shape(int d, int k);            // codec: the LDS-tiled MFMA kernels take this shape (d > 128, or any
                                               // shape with k <= 128 that the register-resident kernels do not)
 size_t gvq_long_pack_floats(int d, int k);    // floats per basis in either operand-order copy of U
@@ -153,9 +150,6 @@ int gvq_launch_decompress_ws(const gvq_basis* h, const float* comp, int64_t firs
 int gvq_launch_pack_ws(const gvq_basis* h, hipStream_t st);
 int gvq_launch_compress_ws(const gvq_basis* h, const void* grad, int n_workers, int64_t first_slice, int64_t n_slices,
                            const float* comp_in, float* out, bool exact, hipStream_t st, int64_t* done);
-int gvq_large_groups(int d);
-size_t gvq_large_partial_doubles(int d, int chunks);   // per basis
-int gvq_launch_moments_large(gvq_basis* h, const void* const* grads, int L, hipStream_t st);
 size_t gvq_eigen_lu_doubles(int d, int k);   // doubles per basis of d_eLU
 // d_cov (made from d_mom first if from_moments) -> d_eig, d_U.
 int gvq_launch_eigen(const gvq_basis* h, bool from_moments, hipStream_t st);
