@@ -69,7 +69,7 @@ int gvq_basis_destroy(gvq_basis_t* h)
 {
     if (!h) return GVQ_OK;
     (void)hipDeviceSynchronize();
-    void* dev[] = {h->d_offs, h->d_tile_block, h->d_U, h->d_Upc, h->d_Upd, h->d_Upb, h->d_Uws, h->d_Umu, h->d_mu, h->d_eig, h->d_cov, h->d_eA, h->d_eT, h->d_eZ, h->d_eLU, h->d_part, h->d_mom, h->d_nsamp, h->d_ltile, h->d_sweeps, h->d_ksel, h->d_loss_slice, h->d_loss_part};
+    void* dev[] = {h->d_offs, h->d_tile_block, h->d_U, h->d_Upc, h->d_Upd, h->d_Upb, h->d_Uws, h->d_Umu, h->d_mu, h->d_eig, h->d_cov, h->d_eA, h->d_eT, h->d_eZ, h->d_eLU, h->d_part, h->d_mom, h->d_nsamp, h->d_ltile, h->d_Ufc, h->d_Ufd, h->d_ftile, h->d_sweeps, h->d_ksel, h->d_loss_slice, h->d_loss_part};
     for (void* p : dev)
         if (p) (void)hipFree(p);
     for (gvq_plan& pl : h->plan) {
@@ -79,6 +79,7 @@ int gvq_basis_destroy(gvq_basis_t* h)
     }
     free(h->h_offs);
     free(h->h_ltile);
+    free(h->h_ftile);
     delete h;
     (void)hipGetLastError();
     return GVQ_OK;
@@ -130,6 +131,8 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
             TRY(hipMalloc((void**)&h->d_Upd, sizeof(float) * B * pf));
             TRY(hipMalloc((void**)&h->d_Upb, sizeof(unsigned short) * B * 2 * gvq_long_split_pack_halves(d, k)));
             if (gvq_ws_alloc_halves(h)) TRY(hipMalloc((void**)&h->d_Uws, sizeof(unsigned short) * gvq_ws_alloc_halves(h)));
+            rc = gvq_flow_alloc(h);
+            if (rc != GVQ_OK) goto fail;
             if (n_blocks > 1) {
                 h->h_ltile = (int64_t*)malloc(sizeof(int64_t) * (B + 1));
                 if (!h->h_ltile) { rc = GVQ_ENOMEM; goto fail; }

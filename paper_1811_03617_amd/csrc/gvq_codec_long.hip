@@ -791,6 +791,8 @@ int gvq_launch_pack_long(const gvq_basis* h, hipStream_t st)
                            split_nt(h->k), nchunk, 128 * p, np, p);
         GVQ_HIP(hipGetLastError());
     }
+    const int rc = gvq_launch_pack_flow(h, st);
+    if (rc != GVQ_OK) return rc;
     if (gvq_ws_shape(h) || gvq_wsd_shape(h)) return gvq_launch_pack_ws(h, st);
     return GVQ_OK;
 }
@@ -934,6 +936,7 @@ int gvq_launch_compress_long(const gvq_basis* h, const void* grad, int n_workers
         n_slices -= done;
         if (n_slices <= 0) return GVQ_OK;
     }
+    if (mode == 0 && gvq_flow_takes_compress(h)) return gvq_launch_compress_flow(h, grad, n_workers, first_slice, n_slices, comp_in, out, st);
     LongArgs a0 = long_args(h, grad, out, h->d_Upc, first_slice, n_slices);
     a0.acc_in = comp_in;
     a0.n_workers = (float)n_workers;
@@ -979,6 +982,7 @@ int gvq_launch_decompress_long(const gvq_basis* h, const float* comp, int64_t fi
         n_slices -= done;
         if (n_slices <= 0) return GVQ_OK;
     }
+    if (gvq_opt_long_mode() == 0 && gvq_flow_takes_decompress(h, bf)) return gvq_launch_decompress_flow(h, comp, first_slice, n_slices, out, bf, st);
     const LongArgs a0 = long_args(h, comp, out, h->d_Upd, first_slice, n_slices);
     const unsigned short* Upd_split = h->d_Upb + (size_t)h->B * gvq_long_split_pack_halves(h->d, h->k);
     for (int p = 0; p < gvq_long_passes(h->k); ++p) {

@@ -1,0 +1,274 @@
+// Plans, packed U and launches of the codec kernels of gvq_flow.h.
+#include "gvq_flow.h"
+
+// Default products of a shape (gvq_long_split without options): the split from 10 flop/B up.
+static bool flow_exact(const gvq_basis* h) { return 2.0 * h->d * h->k / (4.0 * (h->d + h->k)) < 10.0; }
+
+static int round_up(int v, std::initializer_list<int> allowed)
+{
+    for (int s : allowed)
+        if (v <= s) return s;
+    return 0;
+}
+
+// Tile rows: as many whole 16-slice groups (a multiple of `unit` groups if there are that many) as the waves' words and
+// a work-group's share of the 160 KB of LDS hold.
+static int flow_rows(int most_words, int words, size_t row_bytes, size_t fixed, int per_cu, int unit)
+{
+    const size_t lds = 160 * 1024 / per_cu;
+    int g = most_words / words / 16;
+    const int fit = (int)((lds - 512 - fixed) / (16 * row_bytes));
+    if (g > fit) g = fit;
+    if (g > 64) g = 64;
+    if (g > unit) g = g / unit * unit;
+    return 16 * g;
+}
+
+static FlowPlan compress_plan(int d, int k, bool exact)
+{
+    FlowPlan p;
+    if (d < 4 || k > 128) return p;
+    const int NT = (k + 15) / 16, words = (d + 3) / 4, steps = round_up((d + 31) / 32, {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16});
+    if (!steps) return p;
+    FlowPlan best;
+    for (int W = 4; W <= 8 && !best.waves; W *= 2)
+        for (int wn = 1; wn <= W; wn *= 2) {
+            FlowPlan q;
+            q.wn = wn; q.ntw = (NT + wn - 1) / wn; q.steps = steps; q.waves = W;
+            q.per_cu = 8 / W;   // three of four waves: d = 63 gains 2 %, d = 96 and 100 lose 20 % to the smaller tiles
+            if (wn > 1 && wn / 2 >= NT) break;                        // waves with nothing to do
+            if (W == 4 && (q.ntw > 4 || q.ntw * steps > 16)) continue;   // 128 registers of U per wave
+            if (W == 8 && q.ntw > 1) continue;
+            const int NTHR = 64 * W, rb = flow_row(steps);
+            const size_t fixed = 16 * (size_t)words, row = (size_t)rb + 4 * (size_t)k;
+            q.rows = flow_rows(NTHR * flow_words(W), words, row, fixed, q.per_cu, W / wn);
+            if (q.rows < 16) continue;
+            q.lds = (size_t)q.rows * row + fixed + 16;
+            q.words = (size_t)wn * q.ntw * steps * 128;
+            best = q;
+            if (q.rows / 16 >= W / wn) break;   // every wave has a slice group; else share out the comps further
+        }
+    return best;
+}
+
+static FlowPlan decompress_plan(int d, int k, bool exact)
+{
+    FlowPlan best;
+    if (k > 128) return best;
+    const int words = (k + 3) / 4, kst = (k + 31) / 32, ET = (d + 15) / 16;
+    for (int W = 4; W <= 8 && !best.waves; W *= 2)
+        for (int wn = 1; wn <= W; wn *= 2) {
+            FlowPlan q;
+            q.waves = W; q.kst = kst; q.wn = wn;
+            if (wn > 1 && wn / 2 >= ET) break;   // waves with nothing to do
+            q.etw = round_up((ET + wn - 1) / wn, {1, 2, 3, 4, 5, 6, 7, 8, 10, 12});
+            const int most = W == 4 ? (kst == 1 ? 12 : kst == 2 ? 8 : kst == 3 ? 5 : 4) : (kst <= 2 ? 8 : kst == 3 ? 7 : 5);   // registers
+            if (!q.etw || q.etw > most) continue;
+            if (W == 8 && wn < 8) continue;      // what is compiled for eight waves
+            if (W == 8) {
+                if (kst == 1 && q.etw < 7) q.etw = 7;
+                if (kst == 2 && q.etw < 5) q.etw = 5;
+                if (kst >= 3 && q.etw < 3) q.etw = 3;
+            }
+            q.per_cu = 8 / W;
+            const int NTHR = 64 * W, rb = flow_row(kst);
+            const size_t fixed = 4 * (size_t)(16 * wn * q.etw), row = (size_t)rb + 4 * (size_t)flow_out_row(d);
+            q.rows = flow_rows(NTHR * 4, words, row, fixed, q.per_cu, W / wn);
+            if (q.rows < 16) continue;
+            q.lds = (size_t)q.rows * row + fixed + 16;
+            q.words = (size_t)wn * q.etw * kst * 128;
+            best = q;
+            if (q.rows / 16 >= W / wn) break;    // every wave has a slice group; else share out the elements further
+        }
+    return best;
+}
+
+static flow_kernel compress_kernel(const gvq_basis* h, const FlowPlan& p)
+{
+    if (!p.waves) return nullptr;
+    return h->dtype == GVQ_BF16 ? gvq_flow_compress_bf16(p, flow_exact(h)) : gvq_flow_compress_f32(p, flow_exact(h));
+}
+
+// Where the LDS-tiled kernels are the better ones although these could take the shape: their word-wide path needs slices
+// (and, for decompress, comps) of whole words.  Measured on 48 M elements, one basis and 24 (here against there, us):
+//   compress    U over eight waves: d = 400, k = 100 80 against 68, bf16 d = 500, k = 128 67 against 54
+//               d > 256 with bf16 storage or several bases: d = 400, k = 60 bf16 43 against 43, 24 bases 58 against 45;
+//               d = 512, k = 20 bf16 62 against 39; up to d = 256 e.g. d = 256, k = 64 49 against 58, bf16 37 against 48
+//   decompress  d = 256 and 512: 24 bases 66 against 60, bf16 57 against 45; bf16 from d = 200 up with an even number of
+//               comps (d = 400, k = 60 40 against 32; d = 300, k = 75 42 against 62) and below d = 64 (d = 40 59 against 50)
+// Slices of no whole number of words always come here: d = 201, k = 67 60 against 131, bf16 57 against 204.
+bool gvq_flow_takes_compress(const gvq_basis* h)
+{
+    if (!h->d_Ufc) return false;
+    if (h->d & 3) return true;
+    const FlowPlan p = compress_plan(h->d, h->k, flow_exact(h));
+    return p.waves == 4 && (h->d <= 256 || (h->dtype == GVQ_F32 && h->B == 1));
+}
+
+bool gvq_flow_takes_decompress(const gvq_basis* h, bool out_bf16)
+{
+    if (!h->d_Ufd) return false;
+    if (h->d & 3) return true;
+    if (h->d % 256 == 0) return false;
+    if (!out_bf16) return true;
+    if (h->d >= 200 && h->d <= 768) return (h->k & 1) != 0;
+    return !(h->d < 64 && (h->k & 3) == 0);
+}
+
+int gvq_flow_alloc(gvq_basis* h)
+{
+    const FlowPlan c = compress_plan(h->d, h->k, flow_exact(h)), e = decompress_plan(h->d, h->k, flow_exact(h));
+    const size_t B = (size_t)h->B;
+    auto allow_lds = [](flow_kernel kern) {   // the most any plan of the kernel takes
+        return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    };
+    if (compress_kernel(h, c)) {
+        h->flow_rows_c = c.rows;
+        GVQ_HIP(allow_lds(compress_kernel(h, c)));
+        GVQ_HIP(hipMalloc((void**)&h->d_Ufc, sizeof(u4) * B * c.words));
+    }
+    if (e.waves && gvq_flow_decompress(e, flow_exact(h))) {
+        h->flow_rows_d = e.rows;
+        GVQ_HIP(allow_lds(gvq_flow_decompress(e, flow_exact(h))));
+        GVQ_HIP(hipMalloc((void**)&h->d_Ufd, sizeof(u4) * B * e.words));
+    }
+    if (h->B == 1) return GVQ_OK;
+    // first tile of each basis, for compress and then for decompress
+    h->h_ftile = (int64_t*)malloc(sizeof(int64_t) * 2 * (B + 1));
+    if (!h->h_ftile) return GVQ_ENOMEM;
+    for (int which = 0; which < 2; ++which) {
+        const int rows = which ? h->flow_rows_d : h->flow_rows_c;
+        int64_t* t = h->h_ftile + which * (B + 1);
+        t[0] = 0;
+        for (size_t b = 0; b < B; ++b) t[b + 1] = t[b] + (rows ? (h->h_offs[b + 1] - h->h_offs[b] + rows - 1) / rows : 0);
+    }
+    GVQ_HIP(hipMalloc((void**)&h->d_ftile, sizeof(int64_t) * 2 * (B + 1)));
+    GVQ_HIP(hipMemcpy(h->d_ftile, h->h_ftile, sizeof(int64_t) * 2 * (B + 1), hipMemcpyHostToDevice));
+    return GVQ_OK;
+}
+
+// One 128-bit word of either packed copy per thread.  rows_of: what the A operand's rows are (comps for compress, elements
+// for decompress), `len` the length of the contraction, `steps` its steps of 32, tiles rows of tiles.  Positions past the
+// last whole word hold the last four numbers' places: those already met are zero.
+template <bool EXACT, bool COMPRESS>
+__global__ __launch_bounds__(256) void pack_flow_kernel(const float* U, u4* out, int d, int k, int steps, int tiles)
+{
+    const int b = blockIdx.y, len = COMPRESS ? d : k, rows = COMPRESS ? k : d, words = (len + 3) / 4;
+    const size_t n = (size_t)tiles * steps * 128;
+    const float* Ub = U + (size_t)b * d * k;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
+        const int lane = (int)(i & 63), m = lane & 15, kk = lane >> 4, w = (int)(i >> 6) & 1;
+        const int st = (int)((i >> 7) % steps), row = 16 * (int)((i >> 7) / steps) + m;
+        auto at = [&](int pos) -> float {
+            int e = pos;
+            if (pos >= 4 * words) return 0.f;
+            if (pos >= 4 * (words - 1)) {
+                e = len < 4 ? pos : len - 4 + (pos & 3);
+                if (e < 4 * (words - 1) || e >= len) return 0.f;
+            }
+            if (row >= rows) return 0.f;
+            return COMPRESS ? Ub[(size_t)e * k + row] : Ub[(size_t)row * k + e];
+        };
+        u4 v;
+        if (EXACT) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = __float_as_uint(at(32 * st + 16 * w + 4 * kk + j));
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                unsigned int half[2];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const float u = at(32 * st + 8 * kk + 2 * j + q);
+                    const unsigned int t0 = f32_to_bf16_rne(u);
+                    half[q] = w == 0 ? t0 : f32_to_bf16_rne(u - bf16_to_f32(t0));
+                }
+                v[j] = half[0] | half[1] << 16;
+            }
+        }
+        out[(size_t)b * n + i] = v;
+    }
+}
+
+int gvq_launch_pack_flow(const gvq_basis* h, hipStream_t st)
+{
+    const bool exact = flow_exact(h);
+    auto grid = [&](size_t words) { return dim3((unsigned)(words / 256 < 64 ? (words + 255) / 256 : 64), (unsigned)h->B); };
+    if (h->d_Ufc) {
+        const FlowPlan p = compress_plan(h->d, h->k, exact);
+        auto kern = exact ? pack_flow_kernel<true, true> : pack_flow_kernel<false, true>;
+        hipLaunchKernelGGL(kern, grid(p.words), dim3(256), 0, st, h->d_U, (u4*)h->d_Ufc, h->d, h->k, p.steps, p.wn * p.ntw);
+        GVQ_HIP(hipGetLastError());
+    }
+    if (h->d_Ufd) {
+        const FlowPlan p = decompress_plan(h->d, h->k, exact);
+        auto kern = exact ? pack_flow_kernel<true, false> : pack_flow_kernel<false, false>;
+        hipLaunchKernelGGL(kern, grid(p.words), dim3(256), 0, st, h->d_U, (u4*)h->d_Ufd, h->d, h->k, p.kst, p.wn * p.etw);
+        GVQ_HIP(hipGetLastError());
+    }
+    return GVQ_OK;
+}
+
+static int launch_flow(const gvq_basis* h, flow_kernel kern, const FlowPlan& p, FlowArgs& a, int which, int64_t first_slice,
+                       int64_t n_slices, hipStream_t st)
+{
+    a.mu = h->d_mu; a.offs = h->d_offs; a.M = h->M; a.S = h->S; a.B = h->B; a.d = h->d; a.k = h->k;
+    a.seg_begin = first_slice; a.seg_end = first_slice + n_slices;
+    a.rows = p.rows; a.wn = p.wn; a.upack_stride = p.words;
+    a.tstart = nullptr;
+    a.run = 1;
+    a.t0 = 0;
+    a.t1 = (n_slices + p.rows - 1) / p.rows;
+    const int per_cu = gvq_opt_wg_per_cu() > 0 ? gvq_opt_wg_per_cu() : p.per_cu;
+    const int64_t cap = (int64_t)h->num_cu * per_cu;
+    if (h->B > 1) {
+        const int64_t* ft = h->h_ftile + which * (h->B + 1);
+        auto tile_of = [&](int64_t s) {
+            int lo = 0, hi = h->B;
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) / 2;
+                if (h->h_offs[mid] <= s) lo = mid; else hi = mid;
+            }
+            return ft[lo] + (s - h->h_offs[lo]) / p.rows;
+        };
+        a.tstart = h->d_ftile + which * (h->B + 1);
+        a.t0 = tile_of(first_slice);
+        a.t1 = tile_of(first_slice + n_slices - 1) + 1;
+        // a work-group stays in a basis for a few tiles: a change costs a reload of U with nothing in flight (24 bases,
+        // compress: d = 160 60.0 us with runs of 4, 57.5 with 8, 63.4 in one run; decompress 67.9, 80.3, 78.8)
+        a.run = (int)((a.t1 - a.t0) / cap);
+        const int most = which == 0 && p.ntw * p.steps > 2 ? 8 : 4;
+        if (a.run > most) a.run = most;
+        if (gvq_opt_run_tiles() > 0) a.run = gvq_opt_run_tiles();
+        if (a.run < 1) a.run = 1;
+    }
+    const int64_t runs = (a.t1 - a.t0 + a.run - 1) / a.run;
+    const int grid = (int)(runs < cap ? runs : cap);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * p.waves), p.lds, st, a);
+    GVQ_HIP(hipGetLastError());
+    return GVQ_OK;
+}
+
+int gvq_launch_compress_flow(const gvq_basis* h, const void* grad, int n_workers, int64_t first_slice, int64_t n_slices,
+                             const float* comp_in, float* out, hipStream_t st)
+{
+    const FlowPlan p = compress_plan(h->d, h->k, flow_exact(h));
+    FlowArgs a;
+    a.in = grad; a.out = out; a.acc_in = comp_in; a.Upack = (const u4*)h->d_Ufc; a.n_workers = (float)n_workers;
+    a.words = (h->d + 3) / 4; a.out_bf16 = 0;
+    a.whole = h->M / h->d;
+    // as for the register-resident kernels: results that are summed next stay in the last-level cache if they all fit it
+    a.keep = !comp_in && (int64_t)n_workers * n_slices * h->k * 4 <= (224ll << 20);
+    return launch_flow(h, compress_kernel(h, p), p, a, 0, first_slice, n_slices, st);
+}
+
+int gvq_launch_decompress_flow(const gvq_basis* h, const float* comp, int64_t first_slice, int64_t n_slices, void* out,
+                               bool out_bf16, hipStream_t st)
+{
+    const FlowPlan p = decompress_plan(h->d, h->k, flow_exact(h));
+    FlowArgs a;
+    a.in = comp; a.out = out; a.acc_in = nullptr; a.Upack = (const u4*)h->d_Ufd; a.n_workers = 1.f;
+    a.words = (h->k + 3) / 4; a.out_bf16 = out_bf16 ? 1 : 0; a.keep = 0;
+    a.whole = h->k >= 4 ? h->S : 0;
+    return launch_flow(h, gvq_flow_decompress(p, flow_exact(h)), p, a, 1, first_slice, n_slices, st);
+}

@@ -41,6 +41,11 @@ struct gvq_basis {
     unsigned short* d_Uws = nullptr;  // basis-stationary compress kernel (gvq_ws_shape): two-term bf16 copy of U in its
                                       // operand order, per wave
     float* d_Umu = nullptr;     // [B][KP] U^T mu (bf16 gradients)
+    void* d_Ufc = nullptr;      // gvq_flow.h: packed U of its compress kernel (null: it does not take the shape)
+    void* d_Ufd = nullptr;      // ... and of its decompress kernel
+    int flow_rows_c = 0, flow_rows_d = 0;   // slices per tile of the two
+    int64_t* h_ftile = nullptr; // host [2][B+1]: first tile of each basis, compress then decompress (B > 1)
+    int64_t* d_ftile = nullptr; // device copy
     double* d_eig = nullptr;    // [B][d]
     double* d_cov = nullptr;    // [B][d][d]
     double* d_part = nullptr;   // moment partials: [B][mom_part]
@@ -139,6 +144,15 @@ int gvq_launch_compress_long(const gvq_basis* h, const void* grad, int n_workers
 int gvq_launch_loss_long(const gvq_basis* h, const void* grad, int n_workers, float* loss_slice, hipStream_t st);
 int gvq_launch_decompress_long(const gvq_basis* h, const float* comp, int64_t first_slice, int64_t n_slices,
                                void* out, gvq_dtype_t odt, hipStream_t st);
+// The codec kernels of gvq_flow.h; whether they are the ones to take the handle's shape.
+bool gvq_flow_takes_compress(const gvq_basis* h);
+bool gvq_flow_takes_decompress(const gvq_basis* h, bool out_bf16);
+int gvq_flow_alloc(gvq_basis* h);
+int gvq_launch_pack_flow(const gvq_basis* h, hipStream_t st);
+int gvq_launch_compress_flow(const gvq_basis* h, const void* grad, int n_workers, int64_t first_slice, int64_t n_slices,
+                             const float* comp_in, float* out, hipStream_t st);
+int gvq_launch_decompress_flow(const gvq_basis* h, const float* comp, int64_t first_slice, int64_t n_slices, void* out,
+                               bool out_bf16, hipStream_t st);
 // Basis-stationary compress kernel (gvq_codec_ws.hip): U stays in registers, the gradient streams past in tiles
 // of 16 whole slices.  The launcher reports the slices done (the whole range, as far as the gradient has slices).
 bool gvq_ws_shape(const gvq_basis* h);   // it can take this handle's shape

@@ -1,0 +1,129 @@
+"""Eqs. (2) and (4) on the slice lengths and comps that no other kernel is made for: lengths and comps around the multiples of
+4, 16 and 32 where a word, a tile or a contraction step is left over, one and several bases, ranges that start and end inside
+a tile, the fused ring step, both storage types, against float64 and against the LDS-tiled kernels."""
+import numpy as np
+import pytest
+
+from paper_1811_03617_amd import gvq
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+SHAPES = [(4, 1), (4, 4), (5, 2), (7, 3), (12, 5), (13, 3), (16, 16), (17, 4), (24, 6), (31, 9), (33, 11), (48, 12), (63, 30),
+          (65, 16), (77, 19), (96, 33), (100, 25), (127, 42), (128, 43), (128, 128), (129, 17), (160, 80), (193, 64), (201, 50),
+          (255, 31), (257, 86), (300, 100), (321, 128), (385, 48), (400, 111), (500, 62), (513, 128), (601, 20), (640, 106),
+          (700, 97), (767, 128), (768, 7)]
+
+
+def _make(d, k, dtype, cuts, M, rng):
+    S = -(-M // d)
+    B = 1 if cuts is None else len(cuts) - 1
+    U = np.stack([np.linalg.qr(rng.standard_normal((d, k)))[0] for _ in range(B)]).astype(np.float32)
+    mu = (0.3 * rng.standard_normal((B, d))).astype(np.float32)
+    b = gvq.Basis(M, d, k, cuts, dtype)
+    b.import_(U, mu)
+    g = torch.from_numpy(rng.standard_normal(M).astype(np.float32))
+    if dtype == "bf16":
+        g = g.to(torch.bfloat16)
+    which = np.zeros(S, dtype=np.int64) if cuts is None else np.searchsorted(np.array(cuts), np.arange(S), side="right") - 1
+    x = np.zeros(S * d)
+    x[:M] = g.to(torch.float64).numpy()
+    return b, g.to(DEV), U.astype(np.float64)[which], mu.astype(np.float64)[which], x.reshape(S, d)
+
+
+def _close(got, want, tol, what):
+    # tol: of the largest value; d or k fp32 roundings in the exact kernels, 2^-17 a product in the split ones
+    assert np.all(np.isfinite(got)), what
+    err = np.max(np.abs(got - want)) / np.max(np.abs(want))
+    assert err <= tol, f"{what}: {err:.2e}"
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("blocks", [1, 3])
+@pytest.mark.parametrize("d,k", SHAPES)
+def test_matches_float64_and_the_general_route(d, k, blocks, dtype):
+    rng = np.random.default_rng(1000 * d + k)
+    slices = max(200, 40_000 // d) + 3
+    M = slices * d - (d // 3 if d > 4 else 0)
+    cuts = None if blocks == 1 else [0, slices // 3 + 1, slices // 3 + 2, slices]
+    b, g, U, mu, x = _make(d, k, dtype, cuts, M, rng)
+    exact = 2.0 * d * k / (4.0 * (d + k)) < 10.0
+    tol = 2e-6 if exact else 4e-5
+    N = 3
+    y = torch.empty(slices * k, device=DEV)
+    y.fill_(float("nan"))
+    b.compress(g, N, y)
+    want = np.einsum("sdk,sd->sk", U, x - mu / N)
+    _close(y.cpu().numpy().reshape(slices, k), want, tol, "compress")
+
+    # a range that starts and ends inside a tile, with the partial sum of a ring added
+    first, count = slices // 5 + 1, slices // 2 + 1
+    part = torch.randn(slices * k, device=DEV)
+    out = torch.full((slices * k,), 7.0, device=DEV)
+    b.compress_segment(g, N, first, count, part, out)
+    got = out.cpu().numpy().reshape(slices, k)
+    assert np.all(got[:first] == 7.0) and np.all(got[first + count:] == 7.0)
+    p = part.cpu().numpy().reshape(slices, k).astype(np.float64)
+    _close(got[first:first + count], (want + p)[first:first + count], tol, "segment")
+
+    yd = y.cpu().numpy().astype(np.float64).reshape(slices, k)
+    back = np.einsum("sdk,sk->sd", U, yd) + mu
+    for odt in ("f32", "bf16"):
+        r = torch.full((M + 8,), 7.0, device=DEV, dtype=torch.bfloat16 if odt == "bf16" else torch.float32)
+        b.decompress(y, r[:M], odt)
+        got = r.to(torch.float64).cpu().numpy()
+        assert np.all(got[M:] == 7.0)
+        _close(got[:M], back.reshape(-1)[:M], 2.0 ** -8 if odt == "bf16" else tol, f"decompress to {odt}")
+        r.fill_(7.0)
+        b.decompress_segment(y, first, count, r[:M], odt)
+        seg = r.to(torch.float64).cpu().numpy()
+        lo, hi = first * d, min(M, (first + count) * d)
+        assert np.array_equal(seg[lo:hi], got[lo:hi]) and np.all(seg[:lo] == 7.0) and np.all(seg[hi:] == 7.0)
+
+    gvq.gvq_set_option(2, 1 if exact else 3)
+    try:
+        y2 = torch.empty_like(y)
+        b.compress(g, N, y2)
+        r2 = torch.empty(M, device=DEV)
+        b.decompress(y, r2, "f32")
+    finally:
+        gvq.gvq_set_option(2, 0)
+    r = torch.empty(M, device=DEV)
+    b.decompress(y, r, "f32")
+    _close(y.cpu().numpy(), y2.cpu().numpy(), tol, "compress, other route")
+    _close(r.cpu().numpy(), r2.cpu().numpy(), tol, "decompress, other route")
+    b.close()
+
+
+@pytest.mark.parametrize("d,k", [(13, 3), (30, 7), (100, 25), (201, 50), (513, 128)])
+def test_nan_and_infinity_stay_in_their_slice(d, k):
+    rng = np.random.default_rng(d)
+    slices = 300
+    b, g, U, mu, x = _make(d, k, "f32", None, slices * d, rng)
+    bad = {0: float("nan"), 63: float("inf"), 64: float("nan"), 150: float("-inf"), slices - 1: float("nan")}
+    for s, v in bad.items():
+        g[s * d + (s * 7) % d] = v
+    y = torch.empty(slices * k, device=DEV)
+    b.compress(g, 2, y)
+    fine = np.isfinite(y.cpu().numpy().reshape(slices, k)).all(1)
+    assert [int(s) for s in np.where(~fine)[0]] == sorted(bad)
+    r = torch.empty(slices * d, device=DEV)
+    b.decompress(y, r)
+    if 2.0 * d * k / (4.0 * (d + k)) < 10.0:   # exact products: an infinity stays one, wherever in the slice it is
+        g[63 * d:64 * d] = 1.0
+        for e in range(d):
+            g[63 * d + e] = float("inf")
+            b.compress(g, 2, y)
+            assert torch.isinf(y[63 * k:64 * k]).all(), e
+            g[63 * d + e] = 1.0
+        z = torch.zeros(slices * k, device=DEV)
+        for c in range(k):
+            z[63 * k + c] = float("inf")
+            rz = torch.empty(slices * d, device=DEV)
+            b.decompress(z, rz)
+            assert torch.isinf(rz[63 * d:64 * d]).all(), c
+            z[63 * k + c] = 0.0
+    fine = np.isfinite(r.cpu().numpy().reshape(slices, d)).all(1)
+    assert [int(s) for s in np.where(~fine)[0]] == sorted(bad)
+    b.close()
