@@ -260,7 +260,9 @@ const char* gvq_strerror(int status);
  *             about 1e-5 of its magnitude, results within 1e-5 of the exact ones relative to the
  *             largest value, up to 2 times faster); 1 = always exact products; 2 = always the split;
  *             3 = always the split, and never the kernels that keep U in registers (the default
- *             for fp32 gradients with one basis and d a multiple of 256; for A/B timing);
+ *             for fp32 gradients with one basis and d a multiple of 256; for A/B timing); any
+ *             value but 0 also leaves out the kernels that move whole slices (gvq_flow.h, the default
+ *             for most other shapes) in favour of the LDS-tiled ones;
  *   option 3: bit mask that sends every tile of a kernel family through its bounds-checked general loop
  *             instead of the branch-free loop over whole tiles (1: fp32-pipe compress, 2: bf16-pipe
  *             compress, 4: decompress); results are identical, for A/B timing;
