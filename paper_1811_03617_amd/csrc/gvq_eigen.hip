@@ -12,7 +12,7 @@
 //   out            order, sign and conversion to the fp32 basis.
 //
 // It replaces Jacobi methods, which compute all d eigenvectors and need 12 - 14 sweeps over the matrix whatever k is:
-// d = 128 4.0 -> 0.5 ms, d = 768 (k = 96) 22 -> 5.6 ms.  What bounds it is the chain of dependent steps (d reflections,
+// d = 128 4.0 -> 0.42 ms, d = 768 (k = 96) 22 -> 5.3 ms.  What bounds it is the chain of dependent steps (d reflections,
 // each needing the whole of the one before), not arithmetic or memory.
 //
 // Every kernel returns at once for a basis whose matrix is zero (unit vectors, eigenvalues 0) or not finite
@@ -57,6 +57,32 @@ __device__ __forceinline__ double fast_rcp(double x)
     y = fma(fma(-x, y, 1.0), y, y);
     y = fma(fma(-x, y, 1.0), y, y);
     return y;
+}
+
+// sqrt(x) and 1/sqrt(x) likewise, x > 0 and far from the ends of the range (squares of what fp32 numbers' products leave).
+__device__ __forceinline__ double fast_sqrt(double x, double& inverse)
+{
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    const double r = x * y;
+    inverse = y;
+    return fma(0.5 * y, fma(-r, r, x), r);
+}
+
+// The reflector that takes (x0, rest) to (beta, 0), n2 = |rest|^2: v = (1, rest * sc), H = I - t v v^T.  Every wave of a
+// work-group forms it, four to a SIMD, so what counts is the number of instructions: with the library's square root and
+// divisions a step of tri_small_kernel took 2.4 us, 2.2 with these.
+__device__ __forceinline__ void reflector(double x0, double n2, double& beta, double& t, double& sc)
+{
+    beta = x0; t = 0.0; sc = 0.0;
+    if (n2 > 0.0) {
+        double inv;
+        beta = fast_sqrt(fma(x0, x0, n2), inv);
+        if (x0 > 0.0) { beta = -beta; inv = -inv; }
+        t = (beta - x0) * inv;
+        sc = fast_rcp(x0 - beta);
+    }
 }
 
 #define EIG_E_FLOOR 1e-20     // smallest off-diagonal entry of T relative to the matrix: decoupled blocks stay coupled
@@ -164,13 +190,8 @@ __global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
     __syncthreads();
     n2 = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
     const double x0 = first;
-    double beta = x0, t = 0.0, sc = 0.0;
-    if (n2 > 0.0) {
-        beta = sqrt(fma(x0, x0, n2));
-        if (x0 > 0.0) beta = -beta;
-        t = (beta - x0) / beta;
-        sc = 1.0 / (x0 - beta);
-    }
+    double beta, t, sc;
+    reflector(x0, n2, beta, t, sc);
     double* R = A + (size_t)i * n;   // row i-1 of the matrix
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
@@ -283,13 +304,8 @@ __global__ __launch_bounds__(TJ * TJ) void tri_small_kernel(EigenArgs a, int i0)
             }
             n2 = wave_sum(n2);
             const double x0 = col[i + 1];
-            double beta = x0, t = 0.0, sc = 0.0;
-            if (n2 > 0.0) {
-                beta = sqrt(fma(x0, x0, n2));
-                if (x0 > 0.0) beta = -beta;
-                t = (beta - x0) / beta;
-                sc = 1.0 / (x0 - beta);
-            }
+            double beta, t, sc;
+            reflector(x0, n2, beta, t, sc);
             if (tid < 64) {
 #pragma unroll
                 for (int u = 0; u < PL; ++u) {
@@ -350,7 +366,7 @@ __global__ __launch_bounds__(TJ * TJ) void tri_small_kernel(EigenArgs a, int i0)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) x[r][c] -= fma(vr[r], wc[c], wr[r] * vc[c]);
+                for (int c = 0; c < 4; ++c) x[r][c] = fma(-vr[r], wc[c], fma(-wr[r], vc[c], x[r][c]));
         }
     }
 }
@@ -652,39 +668,48 @@ __global__ __launch_bounds__(512) void orthonormalise_kernel(double* Z, size_t Z
 
 // ---- back ---------------------------------------------------------------------------------------------------------------
 //
-// z <- H_0 H_1 ... H_{n-3} z, one wave per vector held in registers, the next reflector requested ahead.
+// z <- H_0 H_1 ... H_{n-3} z, one wave per vector held in registers.  A step is a dot product and an update of a few numbers
+// per lane, far less than the time its reflector takes to arrive, so PF of them are in flight (d = 768, k = 96: 526 us with
+// one in flight, 376 with four; d = 128 55 and 29).
 template <int NE>
 __global__ __launch_bounds__(256) void back_kernel(EigenArgs a)
 {
+    constexpr int PF = 4;
     const int b = blockIdx.y, n = a.n, lane = threadIdx.x & 63;
     const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (eig_skip(a.norm[b]) || j >= a.k) return;
     const double* R = a.A + (size_t)b * a.A_stride;   // reflector i is row i (row i-1 of the matrix)
     const double* tau = a.T + (size_t)b * 5 * a.t_ld + 2 * a.t_ld;
     double* Z = a.Z + (size_t)b * a.Z_stride + (size_t)j * n;
-    double z[NE], v[NE];
+    double z[NE], v[PF][NE], t[PF];
 #pragma unroll
     for (int e = 0; e < NE; ++e) z[e] = 64 * e + lane < n ? Z[64 * e + lane] : 0.0;
-    auto fetch = [&](int i) {
+    auto fetch = [&](int i, double (&w)[NE], double& tw) {
+        const int at = i > 0 ? i : 0;   // past the last: its words again, unused
+        tw = tau[at];
 #pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            const int c = 64 * e + lane;
-            v[e] = i >= 0 && c > i && c < n ? R[(size_t)i * n + c] : 0.0;
-        }
+        for (int e = 0; e < NE; ++e) w[e] = R[(size_t)at * n + (64 * e + lane < n ? 64 * e + lane : n - 1)];
     };
-    fetch(n - 3);
-    for (int i = n - 3; i >= 0; --i) {
-        double cur[NE], dot = 0.0;
-        const double t = tau[i];
 #pragma unroll
-        for (int e = 0; e < NE; ++e) cur[e] = v[e];
-        fetch(i - 1);
-        if (t == 0.0) continue;   // its vector was not written
+    for (int u = 0; u < PF; ++u) fetch(n - 3 - u, v[u], t[u]);
+    for (int i = n - 3; i >= 0; i -= PF) {
 #pragma unroll
-        for (int e = 0; e < NE; ++e) dot = fma(cur[e], z[e], dot);
-        dot = t * wave_sum(dot);
+        for (int u = 0; u < PF; ++u) {
+            double cur[NE], dot = 0.0;
+            const double tc = t[u];
 #pragma unroll
-        for (int e = 0; e < NE; ++e) z[e] = fma(-dot, cur[e], z[e]);
+            for (int e = 0; e < NE; ++e) {
+                const int c = 64 * e + lane;
+                cur[e] = c > i - u && c < n ? v[u][e] : 0.0;
+            }
+            fetch(i - u - PF, v[u], t[u]);
+            if (i - u < 0 || tc == 0.0) continue;   // none, or its vector was not written
+#pragma unroll
+            for (int e = 0; e < NE; ++e) dot = fma(cur[e], z[e], dot);
+            dot = tc * wave_sum(dot);
+#pragma unroll
+            for (int e = 0; e < NE; ++e) z[e] = fma(-dot, cur[e], z[e]);
+        }
     }
 #pragma unroll
     for (int e = 0; e < NE; ++e)
