@@ -28,14 +28,19 @@ typedef float fw4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned short hw4 __attribute__((ext_vector_type(4), aligned(2)));
 typedef unsigned int hu4 __attribute__((ext_vector_type(4), aligned(2)));
 
+// A tile of a handle with several bases: `rows` slices of basis b from `first` on.
+struct FlowTile {
+    int64_t first;
+    int rows, b;
+};
+
 struct FlowArgs {
     const void* in;
     void* out;
     const float* acc_in;     // compress only, may be null: added to the result
     const u4* Upack;
     const float* mu;         // [B][d]
-    const int64_t* offs;     // [B+1]
-    const int64_t* tstart;   // [B+1] first tile of each basis (B > 1 only)
+    const FlowTile* tiles;   // the handle's tiles (B > 1 only)
     int64_t M, S, seg_begin, seg_end, t0, t1;
     int64_t whole;           // rows of the input that can be read word by word: whole ones, of at least four numbers
     int B, d, k;
@@ -48,64 +53,60 @@ struct FlowArgs {
     float n_workers;
 };
 
-struct FlowTile {
-    int b, rows;
-    int64_t first;
-};
-
-// The tiles of one work-group: runs of a.run consecutive ones, runs interleaved across the grid.  What a tile needs to know
-// about its basis is kept from one to the next: looked up anew for every tile (a binary search is a chain of scalar
-// loads) it cost 10 - 30 % with 24 bases.
+// The tiles of one work-group: runs of a.run consecutive ones, runs interleaved across the grid.  With several bases a tile
+// comes out of a table that the host made: one scalar load, asked for a tile ahead.  (Found by searching the bases' offsets
+// for every tile it cost 10 - 30 % with 24 bases; walking from one basis to the next, which a work-group with few tiles of
+// thousands of short bases does hundreds of times between two of its tiles, a millisecond: 24 M elements in 16216 bases,
+// d = 40, k = 10 968 us, now 88.)
 struct FlowIter {
-    int64_t tile, tiles_begin, tiles_end;     // tiles_begin .. tiles_end - 1: those of basis b
-    int64_t slice_begin, slice_end;           // slice_begin: first slice of tile tiles_begin; slice_end: end of b and of the range
-    int pos, b;
-    __device__ __forceinline__ void enter(const FlowArgs& a)
+    int64_t tile, ahead;   // this tile, the one after it (past the last one: this one again)
+    int pos;               // of `ahead` in its run
+    FlowTile rec, next;    // B > 1: their entries of the table
+    static __device__ __forceinline__ FlowTile entry(const FlowArgs& a, int64_t i)
     {
-        tiles_begin = uniform_load(a.tstart + b);
-        tiles_end = uniform_load(a.tstart + b + 1);
-        slice_begin = uniform_load(a.offs + b);
-        slice_end = uniform_load(a.offs + b + 1);
-        if (slice_end > a.seg_end) slice_end = a.seg_end;
+        return __builtin_bit_cast(FlowTile, uniform_load((const u4*)(a.tiles + i)));
+    }
+    __device__ __forceinline__ void step(const FlowArgs& a)
+    {
+        ++ahead;
+        if (++pos == a.run) {
+            pos = 0;
+            ahead += (int64_t)(gridDim.x - 1) * a.run;
+        }
+        if (ahead >= a.t1) ahead = tile;
+        if (a.B > 1) next = entry(a, ahead);
     }
     __device__ __forceinline__ FlowIter(const FlowArgs& a)
     {
-        tile = a.t0 + (int64_t)blockIdx.x * a.run;
+        tile = ahead = a.t0 + (int64_t)blockIdx.x * a.run;
         pos = 0;
-        b = 0;
-        tiles_begin = 0; tiles_end = a.t1; slice_begin = a.seg_begin; slice_end = a.seg_end;
-        if (a.B > 1 && tile < a.t1) {
-            int hi = a.B;
-            while (hi - b > 1) {
-                const int mid = (b + hi) >> 1;
-                if (uniform_load(a.tstart + mid) <= tile) b = mid; else hi = mid;
-            }
-            enter(a);
-        }
+        if (tile >= a.t1) return;
+        if (a.B > 1) rec = entry(a, tile);
+        step(a);
     }
     // To the next tile; false: none is left.
     __device__ __forceinline__ bool advance(const FlowArgs& a)
     {
-        ++tile;
-        if (++pos == a.run) {
-            pos = 0;
-            tile += (int64_t)(gridDim.x - 1) * a.run;
-        }
-        if (tile >= a.t1) return false;
-        while (tile >= tiles_end) {
-            ++b;
-            enter(a);
-        }
+        if (ahead == tile) return false;
+        tile = ahead;
+        rec = next;
+        step(a);
         return true;
     }
+    // What of it lies in the requested range.
     __device__ __forceinline__ FlowTile get(const FlowArgs& a) const
     {
         FlowTile t;
-        t.b = b;
-        t.first = slice_begin + (tile - tiles_begin) * a.rows;
+        t.b = 0;
+        t.first = a.seg_begin + tile * a.rows;
         int64_t end = t.first + a.rows;
-        if (end > slice_end) end = slice_end;
+        if (a.B > 1) {
+            t.b = rec.b;
+            t.first = rec.first;
+            end = rec.first + rec.rows;
+        }
         if (t.first < a.seg_begin) t.first = a.seg_begin;
+        if (end > a.seg_end) end = a.seg_end;
         t.rows = (int)(end - t.first);
         return t;
     }
@@ -329,7 +330,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void compress_flow_kernel(FlowArgs a
         if (!plain) in.load_rest(a, tn, d, a.M);
         if (!first) store_y(before);
         __syncthreads();
-        for (int g = ws; g < a.rows / 16; g += WS) {
+        for (int g = ws; 16 * g < t.rows; g += WS) {
             f4 acc[NTW];
 #pragma unroll
             for (int nt = 0; nt < NTW; ++nt) acc[nt] = f4{0.f, 0.f, 0.f, 0.f};
@@ -487,7 +488,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void decompress_flow_kernel(FlowArgs
         if (!plain) in.load_rest(a, tn, k, a.S * k);
         if (!first) store_x(before);
         __syncthreads();
-        for (int g = ws; g < a.rows / 16; g += WS) {
+        for (int g = ws; 16 * g < t.rows; g += WS) {
             const char* yr = yh + (16 * g + n_) * RB + 16 * kk;
             f4 acc[ETW];
 #pragma unroll

@@ -133,18 +133,37 @@ int gvq_flow_alloc(gvq_basis* h)
         GVQ_HIP(hipMalloc((void**)&h->d_Ufd, sizeof(u4) * B * e.words));
     }
     if (h->B == 1) return GVQ_OK;
-    // first tile of each basis, for compress and then for decompress
+    // No tile holds slices of two bases: where all bases are short, tiles are, too.
+    int64_t longest = 0;
+    for (size_t b = 0; b < B; ++b)
+        if (h->h_offs[b + 1] - h->h_offs[b] > longest) longest = h->h_offs[b + 1] - h->h_offs[b];
+    const int most = longest < 1024 ? (int)(longest + 15) / 16 * 16 : 1024;
+    if (h->flow_rows_c > most) h->flow_rows_c = most;
+    if (h->flow_rows_d > most) h->flow_rows_d = most;
+    // first tile of each basis, and the tiles themselves, for compress and then for decompress
     h->h_ftile = (int64_t*)malloc(sizeof(int64_t) * 2 * (B + 1));
     if (!h->h_ftile) return GVQ_ENOMEM;
     for (int which = 0; which < 2; ++which) {
         const int rows = which ? h->flow_rows_d : h->flow_rows_c;
         int64_t* t = h->h_ftile + which * (B + 1);
-        t[0] = 0;
+        t[0] = which ? h->h_ftile[B] : 0;
         for (size_t b = 0; b < B; ++b) t[b + 1] = t[b] + (rows ? (h->h_offs[b + 1] - h->h_offs[b] + rows - 1) / rows : 0);
     }
-    GVQ_HIP(hipMalloc((void**)&h->d_ftile, sizeof(int64_t) * 2 * (B + 1)));
-    GVQ_HIP(hipMemcpy(h->d_ftile, h->h_ftile, sizeof(int64_t) * 2 * (B + 1), hipMemcpyHostToDevice));
-    return GVQ_OK;
+    const int64_t n = h->h_ftile[2 * B + 1];
+    if (n == 0) return GVQ_OK;
+    FlowTile* tiles = (FlowTile*)malloc(sizeof(FlowTile) * (size_t)n);
+    if (!tiles) return GVQ_ENOMEM;
+    FlowTile* t = tiles;
+    for (int which = 0; which < 2; ++which) {
+        const int rows = which ? h->flow_rows_d : h->flow_rows_c;
+        for (size_t b = 0; rows && b < B; ++b)
+            for (int64_t s = h->h_offs[b], end = h->h_offs[b + 1]; s < end; s += rows)
+                *t++ = FlowTile{s, (int)(end - s < rows ? end - s : rows), (int)b};
+    }
+    hipError_t err = hipMalloc(&h->d_ftile, sizeof(FlowTile) * (size_t)n);
+    if (err == hipSuccess) err = hipMemcpy(h->d_ftile, tiles, sizeof(FlowTile) * (size_t)n, hipMemcpyHostToDevice);
+    free(tiles);
+    return err == hipSuccess ? GVQ_OK : gvq_hip_fail(err, "table of tiles");
 }
 
 // One 128-bit word of either packed copy per thread.  rows_of: what the A operand's rows are (comps for compress, elements
@@ -212,13 +231,13 @@ int gvq_launch_pack_flow(const gvq_basis* h, hipStream_t st)
 static int launch_flow(const gvq_basis* h, flow_kernel kern, const FlowPlan& p, FlowArgs& a, int which, int64_t first_slice,
                        int64_t n_slices, hipStream_t st)
 {
-    a.mu = h->d_mu; a.offs = h->d_offs; a.M = h->M; a.S = h->S; a.B = h->B; a.d = h->d; a.k = h->k;
+    a.mu = h->d_mu; a.M = h->M; a.S = h->S; a.B = h->B; a.d = h->d; a.k = h->k;
     a.seg_begin = first_slice; a.seg_end = first_slice + n_slices;
-    a.rows = p.rows; a.wn = p.wn; a.upack_stride = p.words;
-    a.tstart = nullptr;
+    a.rows = which ? h->flow_rows_d : h->flow_rows_c; a.wn = p.wn; a.upack_stride = p.words;
+    a.tiles = (const FlowTile*)h->d_ftile;
     a.run = 1;
     a.t0 = 0;
-    a.t1 = (n_slices + p.rows - 1) / p.rows;
+    a.t1 = (n_slices + a.rows - 1) / a.rows;
     const int per_cu = gvq_opt_wg_per_cu() > 0 ? gvq_opt_wg_per_cu() : p.per_cu;
     const int64_t cap = (int64_t)h->num_cu * per_cu;
     if (h->B > 1) {
@@ -229,9 +248,8 @@ static int launch_flow(const gvq_basis* h, flow_kernel kern, const FlowPlan& p, 
                 const int mid = (lo + hi) / 2;
                 if (h->h_offs[mid] <= s) lo = mid; else hi = mid;
             }
-            return ft[lo] + (s - h->h_offs[lo]) / p.rows;
+            return ft[lo] + (s - h->h_offs[lo]) / a.rows;
         };
-        a.tstart = h->d_ftile + which * (h->B + 1);
         a.t0 = tile_of(first_slice);
         a.t1 = tile_of(first_slice + n_slices - 1) + 1;
         // a work-group stays in a basis for a few tiles: a change costs a reload of U with nothing in flight (24 bases,

@@ -45,7 +45,7 @@ struct gvq_basis {
     void* d_Ufd = nullptr;      // ... and of its decompress kernel
     int flow_rows_c = 0, flow_rows_d = 0;   // slices per tile of the two
     int64_t* h_ftile = nullptr; // host [2][B+1]: first tile of each basis, compress then decompress (B > 1)
-    int64_t* d_ftile = nullptr; // device copy
+    void* d_ftile = nullptr;    // those tiles (FlowTile), compress then decompress
     double* d_eig = nullptr;    // [B][d]
     double* d_cov = nullptr;    // [B][d][d]
     double* d_part = nullptr;   // moment partials: [B][mom_part]

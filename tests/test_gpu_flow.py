@@ -127,3 +127,103 @@ def test_nan_and_infinity_stay_in_their_slice(d, k):
     fine = np.isfinite(r.cpu().numpy().reshape(slices, d)).all(1)
     assert [int(s) for s in np.where(~fine)[0]] == sorted(bad)
     b.close()
+
+
+def _einsum_close(got, want, tol, what):
+    err = float((got.double() - want).abs().max() / want.abs().max())
+    assert err <= tol, f"{what}: {err:.2e}"   # a NaN fails, too
+
+
+def _uneven_cuts(S, B, rng):
+    """B bases: most of them a few slices short or long, some of a single slice, some longer than any tile."""
+    w = rng.choice([0.01, 1.0, 3.0, 40.0], B, p=[0.2, 0.5, 0.2, 0.1]) * rng.uniform(0.5, 1.5, B)
+    cuts = np.concatenate([[0], 1 + np.arange(B) + np.floor(np.cumsum(w) / w.sum() * (S - B)).astype(np.int64)])
+    cuts[-1] = S
+    assert (np.diff(cuts) >= 1).all()
+    return cuts
+
+
+def _check_on_device(b, d, k, B, cuts, M, dtype, rng, N=3):
+    """Eqs. (2) and (4), and a ring step over a range, against float64 on the device."""
+    S = -(-M // d)
+    U = torch.from_numpy(np.linalg.qr(rng.standard_normal((B, d, k)))[0].astype(np.float32))
+    mu = torch.from_numpy((0.3 * rng.standard_normal((B, d))).astype(np.float32))
+    b.import_(U.numpy(), mu.numpy())
+    gen = torch.Generator(device=DEV).manual_seed(int(rng.integers(1 << 30)))
+    g = torch.randn(M, device=DEV, generator=gen).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    x = torch.zeros(S * d, device=DEV, dtype=torch.float64)
+    x[:M] = g.double()
+    x = x.view(S, d)
+    U, mu = U.to(DEV).double(), mu.to(DEV).double()
+    want = torch.empty(S, k, device=DEV, dtype=torch.float64)
+    for i in range(B):
+        lo, hi = int(cuts[i]), int(cuts[i + 1])
+        want[lo:hi] = (x[lo:hi] - mu[i] / N) @ U[i]
+    tol = 2e-6 if 2.0 * d * k / (4.0 * (d + k)) < 10.0 else 4e-5
+    y = torch.full((S * k,), float("nan"), device=DEV)
+    b.compress(g, N, y)
+    _einsum_close(y.view(S, k), want, tol, "compress")
+
+    first, count = S // 7 + 5, S // 2 + 3
+    part = torch.randn(S * k, device=DEV, generator=gen)
+    out = torch.full((S * k,), 7.0, device=DEV)
+    b.compress_segment(g, N, first, count, part, out)
+    o = out.view(S, k)
+    assert (o[:first] == 7.0).all() and (o[first + count:] == 7.0).all()
+    _einsum_close(o[first:first + count], (want + part.view(S, k).double())[first:first + count], tol, "ring step")
+
+    back = torch.empty(S, d, device=DEV, dtype=torch.float64)
+    yd = y.view(S, k).double()
+    for i in range(B):
+        lo, hi = int(cuts[i]), int(cuts[i + 1])
+        back[lo:hi] = yd[lo:hi] @ U[i].T + mu[i]
+    for odt in ("f32", "bf16"):
+        r = torch.full((M + 8,), 7.0, device=DEV, dtype=torch.bfloat16 if odt == "bf16" else torch.float32)
+        b.decompress(y, r[:M], odt)
+        assert (r[M:] == 7.0).all()
+        _einsum_close(r[:M], back.view(-1)[:M], 2.0 ** -8 if odt == "bf16" else tol, f"decompress to {odt}")
+        seg = torch.full_like(r, 7.0)
+        b.decompress_segment(y, first, count, seg[:M], odt)
+        lo, hi = first * d, min(M, (first + count) * d)
+        assert torch.equal(seg[lo:hi], r[lo:hi]) and (seg[:lo] == 7.0).all() and (seg[hi:] == 7.0).all()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,k", [(24, 6), (40, 10), (100, 25), (201, 50)])
+def test_many_short_bases(d, k, dtype):
+    """Thousands of bases of a few dozen slices: right, and not slower than the kernels that search for a tile's basis (whose
+    time per tile does not depend on the number of bases; measured at about their time or below, the bound leaves 2x)."""
+    rng = np.random.default_rng(d)
+    B = 3000 if d < 200 else 1500
+    S = 37 * B
+    cuts = np.arange(B + 1) * 37
+    M = S * d - d // 3
+    b = gvq.Basis(M, d, k, cuts, dtype)
+    _check_on_device(b, d, k, B, cuts, M, dtype, rng)
+
+    g = torch.randn(M, device=DEV).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    y, r = torch.randn(S * k, device=DEV), torch.empty_like(g)
+
+    def best_of(f):
+        f()
+        times = []
+        for _ in range(5):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            for _ in range(5):
+                f()
+            t1.record()
+            torch.cuda.synchronize()
+            times.append(t0.elapsed_time(t1))
+        return min(times)
+
+    exact = 2.0 * d * k / (4.0 * (d + k)) < 10.0
+    for what, f in (("compress", lambda: b.compress(g, 3, y)), ("decompress", lambda: b.decompress(y, r))):
+        here = best_of(f)
+        gvq.gvq_set_option(2, 1 if exact else 3)
+        try:
+            there = best_of(f)
+        finally:
+            gvq.gvq_set_option(2, 0)
+        assert here <= 2.0 * there, f"{what}: {here / 5:.3f} ms, LDS-tiled kernels {there / 5:.3f} ms"
+    b.close()
