@@ -1,5 +1,6 @@
 // Plans, packed U and launches of the codec kernels of gvq_flow.h.
 #include "gvq_flow.h"
+#include "gvq_flow_plan.h"
 
 // Default products of a shape (gvq_long_split without options): the split from 10 flop/B up.
 static bool flow_exact(const gvq_basis* h) { return 2.0 * h->d * h->k / (4.0 * (h->d + h->k)) < 10.0; }
@@ -133,13 +134,8 @@ int gvq_flow_alloc(gvq_basis* h)
         GVQ_HIP(hipMalloc((void**)&h->d_Ufd, sizeof(u4) * B * e.words));
     }
     if (h->B == 1) return GVQ_OK;
-    // No tile holds slices of two bases: where all bases are short, tiles are, too.
-    int64_t longest = 0;
-    for (size_t b = 0; b < B; ++b)
-        if (h->h_offs[b + 1] - h->h_offs[b] > longest) longest = h->h_offs[b + 1] - h->h_offs[b];
-    const int most = longest < 1024 ? (int)(longest + 15) / 16 * 16 : 1024;
-    if (h->flow_rows_c > most) h->flow_rows_c = most;
-    if (h->flow_rows_d > most) h->flow_rows_d = most;
+    if (h->flow_rows_c) h->flow_rows_c = flow_tile_rows(h->h_offs, (int64_t)B, c.rows, 16 * (c.waves / c.wn), (int64_t)h->num_cu * c.per_cu);
+    if (h->flow_rows_d) h->flow_rows_d = flow_tile_rows(h->h_offs, (int64_t)B, e.rows, 16 * (e.waves / e.wn), (int64_t)h->num_cu * e.per_cu);
     // first tile of each basis, and the tiles themselves, for compress and then for decompress
     h->h_ftile = (int64_t*)malloc(sizeof(int64_t) * 2 * (B + 1));
     if (!h->h_ftile) return GVQ_ENOMEM;
@@ -233,13 +229,15 @@ static int launch_flow(const gvq_basis* h, flow_kernel kern, const FlowPlan& p, 
 {
     a.mu = h->d_mu; a.M = h->M; a.S = h->S; a.B = h->B; a.d = h->d; a.k = h->k;
     a.seg_begin = first_slice; a.seg_end = first_slice + n_slices;
-    a.rows = which ? h->flow_rows_d : h->flow_rows_c; a.wn = p.wn; a.upack_stride = p.words;
+    a.wn = p.wn; a.upack_stride = p.words;
+    const int per_cu = gvq_opt_wg_per_cu() > 0 ? gvq_opt_wg_per_cu() : p.per_cu;
+    const int64_t cap = (int64_t)h->num_cu * per_cu;
+    const int64_t range[2] = {0, n_slices};
+    a.rows = h->B > 1 ? (which ? h->flow_rows_d : h->flow_rows_c) : flow_tile_rows(range, 1, p.rows, 16 * (p.waves / p.wn), cap);
     a.tiles = (const FlowTile*)h->d_ftile;
     a.run = 1;
     a.t0 = 0;
     a.t1 = (n_slices + a.rows - 1) / a.rows;
-    const int per_cu = gvq_opt_wg_per_cu() > 0 ? gvq_opt_wg_per_cu() : p.per_cu;
-    const int64_t cap = (int64_t)h->num_cu * per_cu;
     if (h->B > 1) {
         const int64_t* ft = h->h_ftile + which * (h->B + 1);
         auto tile_of = [&](int64_t s) {
@@ -252,13 +250,9 @@ static int launch_flow(const gvq_basis* h, flow_kernel kern, const FlowPlan& p, 
         };
         a.t0 = tile_of(first_slice);
         a.t1 = tile_of(first_slice + n_slices - 1) + 1;
-        // a work-group stays in a basis for a few tiles: a change costs a reload of U with nothing in flight (24 bases,
-        // compress: d = 160 60.0 us with runs of 4, 57.5 with 8, 63.4 in one run; decompress 67.9, 80.3, 78.8)
-        a.run = (int)((a.t1 - a.t0) / cap);
-        const int most = which == 0 && p.ntw * p.steps > 2 ? 8 : 4;
-        if (a.run > most) a.run = most;
+        // (24 bases, compress: d = 160 60.0 us with runs of 4, 57.5 with 8, 63.4 in one run; decompress 67.9, 80.3, 78.8)
+        a.run = flow_run(a.t1 - a.t0, cap, which == 0 && p.ntw * p.steps > 2 ? 8 : 4);
         if (gvq_opt_run_tiles() > 0) a.run = gvq_opt_run_tiles();
-        if (a.run < 1) a.run = 1;
     }
     const int64_t runs = (a.t1 - a.t0 + a.run - 1) / a.run;
     const int grid = (int)(runs < cap ? runs : cap);
