@@ -1,6 +1,5 @@
 // Plans, packed U and launches of the codec kernels of gvq_flow.h.
 #include "gvq_flow.h"
-#include "gvq_flow_plan.h"
 
 // Default products of a shape (gvq_long_split without options): the split from 10 flop/B up.
 static bool flow_exact(const gvq_basis* h) { return 2.0 * h->d * h->k / (4.0 * (h->d + h->k)) < 10.0; }
@@ -267,7 +266,7 @@ int gvq_launch_compress_flow(const gvq_basis* h, const void* grad, int n_workers
     const FlowPlan p = compress_plan(h->d, h->k, flow_exact(h));
     FlowArgs a;
     a.in = grad; a.out = out; a.acc_in = comp_in; a.Upack = (const u4*)h->d_Ufc; a.n_workers = (float)n_workers;
-    a.words = (h->d + 3) / 4; a.out_bf16 = 0;
+    a.words = (h->d + 3) / 4; a.by_words = flow_divisor(a.words); a.by_out = 0; a.out_bf16 = 0;
     a.whole = h->M / h->d;
     // as for the register-resident kernels: results that are summed next stay in the last-level cache if they all fit it
     a.keep = !comp_in && (int64_t)n_workers * n_slices * h->k * 4 <= (224ll << 20);
@@ -280,7 +279,8 @@ int gvq_launch_decompress_flow(const gvq_basis* h, const float* comp, int64_t fi
     const FlowPlan p = decompress_plan(h->d, h->k, flow_exact(h));
     FlowArgs a;
     a.in = comp; a.out = out; a.acc_in = nullptr; a.Upack = (const u4*)h->d_Ufd; a.n_workers = 1.f;
-    a.words = (h->k + 3) / 4; a.out_bf16 = out_bf16 ? 1 : 0; a.keep = 0;
+    a.words = (h->k + 3) / 4; a.by_words = flow_divisor(a.words); a.out_bf16 = out_bf16 ? 1 : 0; a.keep = 0;
+    a.by_out = flow_divisor(flow_out_row(h->d) == h->d ? 1 : out_bf16 ? h->d / 8 : h->d / 4);
     a.whole = h->k >= 4 ? h->S : 0;
     return launch_flow(h, gvq_flow_decompress(p, flow_exact(h)), p, a, 1, first_slice, n_slices, st);
 }

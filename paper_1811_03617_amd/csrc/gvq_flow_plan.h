@@ -46,3 +46,6 @@ inline int flow_run(int64_t tiles, int64_t slots, int most)
     }
     return 1;
 }
+
+// What flow_divide multiplies by in place of a division by n: i / n = (2 i * flow_divisor(n)) >> 32 for i < 4096, n < 4096.
+inline unsigned int flow_divisor(int n) { return (0x80000000u + (unsigned int)n - 1) / (unsigned int)n; }

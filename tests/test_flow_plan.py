@@ -61,3 +61,15 @@ int main()
     return rows == 128 ? 0 : (printf("%d\n", rows), 1);
 }
 """)
+
+
+def test_division_by_multiplication(tmp_path):
+    _run(tmp_path, r"""
+int main()
+{
+    for (unsigned n = 1; n < 4096; ++n)
+        for (unsigned i = 0; i < 4096; ++i)
+            if ((unsigned)(((unsigned long long)(2u * i) * flow_divisor((int)n)) >> 32) != i / n) { printf("%u / %u\n", i, n); return 1; }
+    return 0;
+}
+""")
