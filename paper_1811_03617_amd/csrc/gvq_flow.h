@@ -1,6 +1,6 @@
 // Eqs. (2) and (4) for the slice lengths and numbers of comps that the register-resident and the basis-stationary kernels
-// do not take: lengths from 4 to 512 (decompress: 1024), any number of bases, up to 128 comps, within the registers that
-// U leaves (compress_plan, decompress_plan in gvq_flow.hip).
+// do not take: lengths from 4 to 512, any number of bases, up to 128 comps; decompress up to 640, up to 896 with 96 comps
+// and up to 1024 with 64, as the registers have room for U (gvq_flow_plan.h, which also says where others are faster).
 //
 // Bound: memory.  What kept the LDS-tiled kernels (gvq_codec_long.hip) at 1.4 - 3.6 TB/s on these shapes was how they
 // touched it: lanes walked down 16 slices 64 bytes at a time, and a slice length that is no multiple of 4 (three lengths out
@@ -130,10 +130,6 @@ __device__ __forceinline__ void split4(const f4& v, u2& hi, u2& lo)
     }
 }
 
-// The rows of x in LDS, `len` numbers each: 16 lanes write 16 rows at a time, so rows of an even number of 16-byte words get
-// one more (48 M elements, decompress: d = 96 65.7 -> 59.0 us, d = 160 59.6 -> 50.5, d = 160 to bf16 47.4 -> 41.2).
-__host__ __device__ constexpr int flow_out_row(int len) { return len % 8 == 0 ? len + 4 : len; }
-
 // A tile's results as one run of words of V numbers (V divides a padded row's length): f(word, its numbers in LDS).
 template <int V, int NTHR>
 struct FlowRun {
@@ -237,11 +233,6 @@ struct FlowInput {
         return v;
     }
 };
-
-__host__ __device__ constexpr int flow_words(int waves) { return waves == 4 ? 8 : 6; }   // most words per thread and tile
-// bytes of a row of `steps` 32-number steps in LDS: fp32, or the first bf16 terms and then the second ones; an odd number of
-// 16-byte words, so that the 16 rows an operand is read from start in different banks
-__host__ __device__ constexpr int flow_row(int steps) { return 128 * steps + 16; }
 
 // --------------------------------------------------------------------------------------
 // compress.  Wave (wn, ws): comp tiles wn NTW .. + NTW - 1 of slice groups ws, ws + W/wn, ...  Step st of 32 numbers:
@@ -549,25 +540,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void decompress_flow_kernel(FlowArgs
 }
 
 // ---- host side --------------------------------------------------------------------------------------------------------
-// How the kernels take a shape (0 waves: not at all).
-struct FlowPlan {
-    int waves = 0, rows = 0, per_cu = 1;
-    int wn = 1, ntw = 0, steps = 0;   // compress: waves over the comps, comp tiles per wave, steps of 32 elements
-    int etw = 0, kst = 0;             // decompress: element tiles per wave, steps of 32 comps
-    size_t lds = 0;
-    size_t words = 0;                 // 128-bit words of the packed U per basis
-};
 typedef void (*flow_kernel)(FlowArgs);
-flow_kernel gvq_flow_compress_f32(const FlowPlan& p, bool exact);
-flow_kernel gvq_flow_compress_bf16(const FlowPlan& p, bool exact);
-flow_kernel gvq_flow_decompress(const FlowPlan& p, bool exact);
-
-
-// Steps and element tiles a wave's registers are compiled for; a shape takes the next one up (the rest is zeros).
-template <int... S> struct FlowSteps {};
-template <int T, typename F, int... S> static flow_kernel flow_pick(int s, FlowSteps<S...>, F f)
-{
-    flow_kernel kern = nullptr;
-    ((s == S ? (void)(kern = f(std::integral_constant<int, T>{}, std::integral_constant<int, S>{})) : (void)0), ...);
-    return kern;
-}
+flow_kernel gvq_flow_compress_f32(const FlowPlan& p);    // null: there is no instance for the plan
+flow_kernel gvq_flow_compress_bf16(const FlowPlan& p);
+flow_kernel gvq_flow_decompress(const FlowPlan& p);

@@ -1,92 +1,12 @@
 // Plans, packed U and launches of the codec kernels of gvq_flow.h.
 #include "gvq_flow.h"
 
-// Default products of a shape (gvq_long_split without options): the split from 10 flop/B up.
-static bool flow_exact(const gvq_basis* h) { return 2.0 * h->d * h->k / (4.0 * (h->d + h->k)) < 10.0; }
-
-static int round_up(int v, std::initializer_list<int> allowed)
-{
-    for (int s : allowed)
-        if (v <= s) return s;
-    return 0;
-}
-
-// Tile rows: as many whole 16-slice groups (a multiple of `unit` groups if there are that many) as the waves' words and
-// a work-group's share of the 160 KB of LDS hold.
-static int flow_rows(int most_words, int words, size_t row_bytes, size_t fixed, int per_cu, int unit)
-{
-    const size_t lds = 160 * 1024 / per_cu;
-    int g = most_words / words / 16;
-    const int fit = (int)((lds - 512 - fixed) / (16 * row_bytes));
-    if (g > fit) g = fit;
-    if (g > 64) g = 64;
-    if (g > unit) g = g / unit * unit;
-    return 16 * g;
-}
-
-static FlowPlan compress_plan(int d, int k, bool exact)
-{
-    FlowPlan p;
-    if (d < 4 || k > 128) return p;
-    const int NT = (k + 15) / 16, words = (d + 3) / 4, steps = round_up((d + 31) / 32, {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16});
-    if (!steps) return p;
-    FlowPlan best;
-    for (int W = 4; W <= 8 && !best.waves; W *= 2)
-        for (int wn = 1; wn <= W; wn *= 2) {
-            FlowPlan q;
-            q.wn = wn; q.ntw = (NT + wn - 1) / wn; q.steps = steps; q.waves = W;
-            q.per_cu = 8 / W;   // three of four waves: d = 63 gains 2 %, d = 96 and 100 lose 20 % to the smaller tiles
-            if (wn > 1 && wn / 2 >= NT) break;                        // waves with nothing to do
-            if (W == 4 && (q.ntw > 4 || q.ntw * steps > 16)) continue;   // 128 registers of U per wave
-            if (W == 8 && q.ntw > 1) continue;
-            const int NTHR = 64 * W, rb = flow_row(steps);
-            const size_t fixed = 16 * (size_t)words, row = (size_t)rb + 4 * (size_t)k;
-            q.rows = flow_rows(NTHR * flow_words(W), words, row, fixed, q.per_cu, W / wn);
-            if (q.rows < 16) continue;
-            q.lds = (size_t)q.rows * row + fixed + 16;
-            q.words = (size_t)wn * q.ntw * steps * 128;
-            best = q;
-            if (q.rows / 16 >= W / wn) break;   // every wave has a slice group; else share out the comps further
-        }
-    return best;
-}
-
-static FlowPlan decompress_plan(int d, int k, bool exact)
-{
-    FlowPlan best;
-    if (k > 128) return best;
-    const int words = (k + 3) / 4, kst = (k + 31) / 32, ET = (d + 15) / 16;
-    for (int W = 4; W <= 8 && !best.waves; W *= 2)
-        for (int wn = 1; wn <= W; wn *= 2) {
-            FlowPlan q;
-            q.waves = W; q.kst = kst; q.wn = wn;
-            if (wn > 1 && wn / 2 >= ET) break;   // waves with nothing to do
-            q.etw = round_up((ET + wn - 1) / wn, {1, 2, 3, 4, 5, 6, 7, 8, 10, 12});
-            const int most = W == 4 ? (kst == 1 ? 12 : kst == 2 ? 8 : kst == 3 ? 5 : 4) : (kst <= 2 ? 8 : kst == 3 ? 7 : 5);   // registers
-            if (!q.etw || q.etw > most) continue;
-            if (W == 8 && wn < 8) continue;      // what is compiled for eight waves
-            if (W == 8) {
-                if (kst == 1 && q.etw < 7) q.etw = 7;
-                if (kst == 2 && q.etw < 5) q.etw = 5;
-                if (kst >= 3 && q.etw < 3) q.etw = 3;
-            }
-            q.per_cu = 8 / W;
-            const int NTHR = 64 * W, rb = flow_row(kst);
-            const size_t fixed = 4 * (size_t)(16 * wn * q.etw), row = (size_t)rb + 4 * (size_t)flow_out_row(d);
-            q.rows = flow_rows(NTHR * 4, words, row, fixed, q.per_cu, W / wn);
-            if (q.rows < 16) continue;
-            q.lds = (size_t)q.rows * row + fixed + 16;
-            q.words = (size_t)wn * q.etw * kst * 128;
-            best = q;
-            if (q.rows / 16 >= W / wn) break;    // every wave has a slice group; else share out the elements further
-        }
-    return best;
-}
+static FlowPlan compress_plan(const gvq_basis* h) { return flow_compress_plan(h->d, h->k); }
+static FlowPlan decompress_plan(const gvq_basis* h) { return flow_decompress_plan(h->d, h->k); }
 
 static flow_kernel compress_kernel(const gvq_basis* h, const FlowPlan& p)
 {
-    if (!p.waves) return nullptr;
-    return h->dtype == GVQ_BF16 ? gvq_flow_compress_bf16(p, flow_exact(h)) : gvq_flow_compress_f32(p, flow_exact(h));
+    return h->dtype == GVQ_BF16 ? gvq_flow_compress_bf16(p) : gvq_flow_compress_f32(p);
 }
 
 // Where the LDS-tiled kernels are the better ones although these could take the shape: their word-wide path needs slices
@@ -101,7 +21,7 @@ bool gvq_flow_takes_compress(const gvq_basis* h)
 {
     if (!h->d_Ufc) return false;
     if (h->d & 3) return true;
-    const FlowPlan p = compress_plan(h->d, h->k, flow_exact(h));
+    const FlowPlan p = compress_plan(h);
     return p.waves == 4 && (h->d <= 256 || (h->dtype == GVQ_F32 && h->B == 1));
 }
 
@@ -117,7 +37,7 @@ bool gvq_flow_takes_decompress(const gvq_basis* h, bool out_bf16)
 
 int gvq_flow_alloc(gvq_basis* h)
 {
-    const FlowPlan c = compress_plan(h->d, h->k, flow_exact(h)), e = decompress_plan(h->d, h->k, flow_exact(h));
+    const FlowPlan c = compress_plan(h), e = decompress_plan(h);
     const size_t B = (size_t)h->B;
     auto allow_lds = [](flow_kernel kern) {   // the most any plan of the kernel takes
         return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -127,9 +47,9 @@ int gvq_flow_alloc(gvq_basis* h)
         GVQ_HIP(allow_lds(compress_kernel(h, c)));
         GVQ_HIP(hipMalloc((void**)&h->d_Ufc, sizeof(u4) * B * c.words));
     }
-    if (e.waves && gvq_flow_decompress(e, flow_exact(h))) {
+    if (gvq_flow_decompress(e)) {
         h->flow_rows_d = e.rows;
-        GVQ_HIP(allow_lds(gvq_flow_decompress(e, flow_exact(h))));
+        GVQ_HIP(allow_lds(gvq_flow_decompress(e)));
         GVQ_HIP(hipMalloc((void**)&h->d_Ufd, sizeof(u4) * B * e.words));
     }
     if (h->B == 1) return GVQ_OK;
@@ -206,16 +126,16 @@ __global__ __launch_bounds__(256) void pack_flow_kernel(const float* U, u4* out,
 
 int gvq_launch_pack_flow(const gvq_basis* h, hipStream_t st)
 {
-    const bool exact = flow_exact(h);
+    const bool exact = flow_exact(h->d, h->k);
     auto grid = [&](size_t words) { return dim3((unsigned)(words / 256 < 64 ? (words + 255) / 256 : 64), (unsigned)h->B); };
     if (h->d_Ufc) {
-        const FlowPlan p = compress_plan(h->d, h->k, exact);
+        const FlowPlan p = compress_plan(h);
         auto kern = exact ? pack_flow_kernel<true, true> : pack_flow_kernel<false, true>;
         hipLaunchKernelGGL(kern, grid(p.words), dim3(256), 0, st, h->d_U, (u4*)h->d_Ufc, h->d, h->k, p.steps, p.wn * p.ntw);
         GVQ_HIP(hipGetLastError());
     }
     if (h->d_Ufd) {
-        const FlowPlan p = decompress_plan(h->d, h->k, exact);
+        const FlowPlan p = decompress_plan(h);
         auto kern = exact ? pack_flow_kernel<true, false> : pack_flow_kernel<false, false>;
         hipLaunchKernelGGL(kern, grid(p.words), dim3(256), 0, st, h->d_U, (u4*)h->d_Ufd, h->d, h->k, p.kst, p.wn * p.etw);
         GVQ_HIP(hipGetLastError());
@@ -255,7 +175,7 @@ static int launch_flow(const gvq_basis* h, flow_kernel kern, const FlowPlan& p, 
     }
     const int64_t runs = (a.t1 - a.t0 + a.run - 1) / a.run;
     const int grid = (int)(runs < cap ? runs : cap);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * p.waves), p.lds, st, a);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * p.waves), p.lds(a.rows), st, a);
     GVQ_HIP(hipGetLastError());
     return GVQ_OK;
 }
@@ -263,7 +183,7 @@ static int launch_flow(const gvq_basis* h, flow_kernel kern, const FlowPlan& p, 
 int gvq_launch_compress_flow(const gvq_basis* h, const void* grad, int n_workers, int64_t first_slice, int64_t n_slices,
                              const float* comp_in, float* out, hipStream_t st)
 {
-    const FlowPlan p = compress_plan(h->d, h->k, flow_exact(h));
+    const FlowPlan p = compress_plan(h);
     FlowArgs a;
     a.in = grad; a.out = out; a.acc_in = comp_in; a.Upack = (const u4*)h->d_Ufc; a.n_workers = (float)n_workers;
     a.words = (h->d + 3) / 4; a.by_words = flow_divisor(a.words); a.by_out = 0; a.out_bf16 = 0;
@@ -276,11 +196,11 @@ int gvq_launch_compress_flow(const gvq_basis* h, const void* grad, int n_workers
 int gvq_launch_decompress_flow(const gvq_basis* h, const float* comp, int64_t first_slice, int64_t n_slices, void* out,
                                bool out_bf16, hipStream_t st)
 {
-    const FlowPlan p = decompress_plan(h->d, h->k, flow_exact(h));
+    const FlowPlan p = decompress_plan(h);
     FlowArgs a;
     a.in = comp; a.out = out; a.acc_in = nullptr; a.Upack = (const u4*)h->d_Ufd; a.n_workers = 1.f;
     a.words = (h->k + 3) / 4; a.by_words = flow_divisor(a.words); a.out_bf16 = out_bf16 ? 1 : 0; a.keep = 0;
     a.by_out = flow_divisor(flow_out_row(h->d) == h->d ? 1 : out_bf16 ? h->d / 8 : h->d / 4);
     a.whole = h->k >= 4 ? h->S : 0;
-    return launch_flow(h, gvq_flow_decompress(p, flow_exact(h)), p, a, 1, first_slice, n_slices, st);
+    return launch_flow(h, gvq_flow_decompress(p), p, a, 1, first_slice, n_slices, st);
 }

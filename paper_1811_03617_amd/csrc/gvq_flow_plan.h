@@ -1,6 +1,154 @@
-// How the kernels of gvq_flow.h cut a range of slices into tiles and deal them out.  Plain C++: nothing here needs HIP.
+// How the kernels of gvq_flow.h take a shape, and how they cut a range of slices into tiles and deal them out.  Plain C++:
+// nothing here needs HIP.
 #pragma once
+#include <cstddef>
 #include <cstdint>
+#include <initializer_list>
+#include <type_traits>
+
+constexpr int flow_words(int waves) { return waves == 4 ? 8 : 6; }   // most words per thread and tile
+// bytes of a row of `steps` 32-number steps in LDS: fp32, or the first bf16 terms and then the second ones; an odd number of
+// 16-byte words, so that the 16 rows an operand is read from start in different banks
+constexpr int flow_row(int steps) { return 128 * steps + 16; }
+// The rows of x in LDS, `len` numbers each: 16 lanes write 16 rows at a time, so rows of an even number of 16-byte words get
+// one more (48 M elements, decompress: d = 96 65.7 -> 59.0 us, d = 160 59.6 -> 50.5, d = 160 to bf16 47.4 -> 41.2).
+constexpr int flow_out_row(int len) { return len % 8 == 0 ? len + 4 : len; }
+
+// How a kernel takes a shape (0 waves: not at all).
+struct FlowPlan {
+    bool exact = false;               // fp32 products, else the bf16 split
+    int waves = 0, rows = 0, per_cu = 1;
+    int wn = 1, ntw = 0, steps = 0;   // compress: waves over the comps, comp tiles per wave, steps of 32 elements
+    int etw = 0, kst = 0;             // decompress: element tiles per wave, steps of 32 comps
+    size_t words = 0;                 // 128-bit words of the packed U per basis
+    size_t row_bytes = 0, fixed_bytes = 0;   // LDS per row of a tile, and besides
+    size_t lds(int tile_rows) const { return tile_rows * row_bytes + fixed_bytes + 16; }
+};
+
+// Default products of a shape (gvq_long_split without options): the split from 10 flop/B up.
+inline bool flow_exact(int d, int k) { return 2.0 * d * k / (4.0 * (d + k)) < 10.0; }
+
+inline int flow_round_up(int v, std::initializer_list<int> allowed)
+{
+    for (int s : allowed)
+        if (v <= s) return s;
+    return 0;
+}
+
+// Most rows of a tile: as many whole 16-slice groups (a multiple of `unit` groups if there are that many) as the waves'
+// words and a work-group's share of the 160 KB of LDS hold.
+inline int flow_most_rows(int most_words, int words, const FlowPlan& q, int unit)
+{
+    const size_t lds = 160 * 1024 / q.per_cu;
+    int g = most_words / words / 16;
+    const int fit = (int)((lds - 512 - q.fixed_bytes) / (16 * q.row_bytes));
+    if (g > fit) g = fit;
+    if (g > 64) g = 64;
+    if (g > unit) g = g / unit * unit;
+    return 16 * g;
+}
+
+inline FlowPlan flow_compress_plan(int d, int k)
+{
+    FlowPlan best;
+    if (d < 4 || k > 128) return best;
+    const int NT = (k + 15) / 16, words = (d + 3) / 4, steps = flow_round_up((d + 31) / 32, {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16});
+    if (!steps) return best;
+    for (int W = 4; W <= 8 && !best.waves; W *= 2)
+        for (int wn = 1; wn <= W; wn *= 2) {
+            FlowPlan q;
+            q.exact = flow_exact(d, k);
+            q.wn = wn; q.ntw = (NT + wn - 1) / wn; q.steps = steps; q.waves = W;
+            q.per_cu = 8 / W;   // three of four waves: d = 63 gains 2 %, d = 96 and 100 lose 20 % to the smaller tiles
+            if (wn > 1 && wn / 2 >= NT) break;                        // waves with nothing to do
+            if (W == 4 && (q.ntw > 4 || q.ntw * steps > 16)) continue;   // 128 registers of U per wave
+            if (W == 8 && q.ntw > 1) continue;
+            q.fixed_bytes = 16 * (size_t)words;
+            q.row_bytes = flow_row(steps) + 4 * (size_t)k;
+            q.rows = flow_most_rows(64 * W * flow_words(W), words, q, W / wn);
+            if (q.rows < 16) continue;
+            q.words = (size_t)wn * q.ntw * steps * 128;
+            best = q;
+            if (q.rows / 16 >= W / wn) break;   // every wave has a slice group; else share out the comps further
+        }
+    return best;
+}
+
+inline FlowPlan flow_decompress_plan(int d, int k)
+{
+    FlowPlan best;
+    if (k > 128) return best;
+    const int words = (k + 3) / 4, kst = (k + 31) / 32, ET = (d + 15) / 16;
+    for (int W = 4; W <= 8 && !best.waves; W *= 2)
+        for (int wn = 1; wn <= W; wn *= 2) {
+            FlowPlan q;
+            q.exact = flow_exact(d, k);
+            q.waves = W; q.kst = kst; q.wn = wn;
+            if (wn > 1 && wn / 2 >= ET) break;   // waves with nothing to do
+            q.etw = flow_round_up((ET + wn - 1) / wn, {1, 2, 3, 4, 5, 6, 7, 8, 10, 12});
+            const int most = W == 4 ? (kst == 1 ? 12 : kst == 2 ? 8 : kst == 3 ? 5 : 4) : (kst <= 2 ? 8 : kst == 3 ? 7 : 5);   // registers
+            if (!q.etw || q.etw > most) continue;
+            if (W == 8 && wn < 8) continue;      // what is compiled for eight waves
+            q.per_cu = 8 / W;
+            q.fixed_bytes = 4 * (size_t)(16 * wn * q.etw);
+            q.row_bytes = flow_row(kst) + 4 * (size_t)flow_out_row(d);
+            q.rows = flow_most_rows(64 * W * 4, words, q, W / wn);
+            if (q.rows < 16) continue;
+            q.words = (size_t)wn * q.etw * kst * 128;
+            best = q;
+            if (q.rows / 16 >= W / wn) break;    // every wave has a slice group; else share out the elements further
+        }
+    return best;
+}
+
+// The instances of the kernels, all that a plan can ask for and no more: f(tiles per wave, steps, exact, waves) as constants
+// (compress: comp tiles, steps of elements; decompress: steps of comps, element tiles).  False: there is none.
+template <int... S> struct FlowSteps {};
+template <int T, bool EXACT, int W, typename F, int... S> bool flow_instance(int s, FlowSteps<S...>, F f)
+{
+    bool found = false;
+    ((s == S ? (f(std::integral_constant<int, T>{}, std::integral_constant<int, S>{}, std::integral_constant<bool, EXACT>{},
+                  std::integral_constant<int, W>{}),
+                (void)(found = true))
+             : (void)0),
+     ...);
+    return found;
+}
+template <typename F> bool flow_compress_instance(const FlowPlan& p, F f)
+{
+    if (p.waves == 8) return !p.exact && p.ntw == 1 && flow_instance<1, false, 8>(p.steps, FlowSteps<10, 12, 16>{}, f);
+    if (p.waves != 4) return false;
+    if (p.exact) {
+        // fewer than 10 flop/B: more than 16 comps only with short slices
+        if (p.ntw == 1) return flow_instance<1, true, 4>(p.steps, FlowSteps<1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16>{}, f);
+        if (p.ntw == 2) return flow_instance<2, true, 4>(p.steps, FlowSteps<1, 2, 3, 4>{}, f);
+        return p.ntw == 3 && flow_instance<3, true, 4>(p.steps, FlowSteps<2>{}, f);
+    }
+    if (p.ntw == 1) return flow_instance<1, false, 4>(p.steps, FlowSteps<5, 6, 7, 8, 10, 12, 16>{}, f);
+    if (p.ntw == 2) return flow_instance<2, false, 4>(p.steps, FlowSteps<2, 3, 4, 5, 6, 7, 8>{}, f);
+    if (p.ntw == 3) return flow_instance<3, false, 4>(p.steps, FlowSteps<2, 3, 4, 5>{}, f);
+    return p.ntw == 4 && flow_instance<4, false, 4>(p.steps, FlowSteps<2, 3, 4>{}, f);
+}
+template <typename F> bool flow_decompress_instance(const FlowPlan& p, F f)
+{
+    if (p.waves == 8) {
+        if (p.kst == 1) return p.exact ? flow_instance<1, true, 8>(p.etw, FlowSteps<7, 8>{}, f) : flow_instance<1, false, 8>(p.etw, FlowSteps<7, 8>{}, f);
+        if (p.exact) return false;
+        if (p.kst == 2) return flow_instance<2, false, 8>(p.etw, FlowSteps<5, 6, 7, 8>{}, f);
+        if (p.kst == 3) return flow_instance<3, false, 8>(p.etw, FlowSteps<3, 4, 5, 6, 7>{}, f);
+        return p.kst == 4 && flow_instance<4, false, 8>(p.etw, FlowSteps<3, 4, 5>{}, f);
+    }
+    if (p.waves != 4) return false;
+    if (p.exact) {
+        // fewer than 10 flop/B: more than 32 comps only with slices of 33 to 50
+        if (p.kst == 1) return flow_instance<1, true, 4>(p.etw, FlowSteps<1, 2, 3, 4, 5, 6, 7, 8, 10, 12>{}, f);
+        return p.kst == 2 && flow_instance<2, true, 4>(p.etw, FlowSteps<3, 4>{}, f);
+    }
+    if (p.kst == 1) return flow_instance<1, false, 4>(p.etw, FlowSteps<4, 5, 6, 7, 8, 10, 12>{}, f);
+    if (p.kst == 2) return flow_instance<2, false, 4>(p.etw, FlowSteps<3, 4, 5, 6, 7, 8>{}, f);
+    if (p.kst == 3) return flow_instance<3, false, 4>(p.etw, FlowSteps<3, 4, 5>{}, f);
+    return p.kst == 4 && flow_instance<4, false, 4>(p.etw, FlowSteps<3, 4>{}, f);
+}
 
 // Tiles of `rows` slices that cover the slices of `bases` bases, none of them holding slices of two
 // (offs: [bases + 1] first slice of each).

@@ -14,7 +14,7 @@ def _run(tmp_path, body):
     cxx = shutil.which("g++") or shutil.which("c++")
     if cxx is None:
         pytest.skip("no C++ compiler")
-    subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, "-o", str(exe), str(src)], check=True)
+    subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-Wno-parentheses", "-Werror", "-I", CSRC, "-o", str(exe), str(src)], check=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout[-4000:]
     return out.stdout
@@ -70,6 +70,54 @@ int main()
     for (unsigned n = 1; n < 4096; ++n)
         for (unsigned i = 0; i < 4096; ++i)
             if ((unsigned)(((unsigned long long)(2u * i) * flow_divisor((int)n)) >> 32) != i / n) { printf("%u / %u\n", i, n); return 1; }
+    return 0;
+}
+""")
+
+
+def test_every_plan_has_an_instance_and_every_instance_a_plan(tmp_path):
+    """A plan without an instance would send its shapes to the LDS-tiled kernels without a word (an odd slice length then
+    goes number by number); an instance without a plan would be compiled for nothing."""
+    _run(tmp_path, r"""
+#include <set>
+#include <tuple>
+int main()
+{
+    typedef std::tuple<int, int, int, int> key;   // waves, exact, tiles per wave or steps of comps, steps or element tiles
+    std::set<key> compress, decompress;
+    for (int d = 2; d <= 1024; ++d)
+        for (int k = 1; k <= d && k <= 128; ++k) {
+            const FlowPlan c = flow_compress_plan(d, k), e = flow_decompress_plan(d, k);
+            auto none = [](auto, auto, auto, auto) {};
+            // what the kernels are stated to take
+            if (!c.waves != (d < 4 || d > 512) || !e.waves != (d > 640 && k > 96 || d > 896 && k > 64)) { printf("no plan: %d %d\n", d, k); return 1; }
+            if (c.waves) {
+                if (!flow_compress_instance(c, none)) { printf("no compress instance: %d %d\n", d, k); return 1; }
+                if (16 * c.ntw * c.wn < k || 32 * c.steps < d || c.rows < 16 || c.rows % 16 || c.lds(c.rows) * c.per_cu > 160 * 1024
+                    || c.rows * ((d + 3) / 4) > 64 * c.waves * flow_words(c.waves)) { printf("compress plan: %d %d\n", d, k); return 1; }
+                compress.insert(key(c.waves, c.exact, c.ntw, c.steps));
+            }
+            if (!e.waves) continue;
+            if (!flow_decompress_instance(e, none)) { printf("no decompress instance: %d %d\n", d, k); return 1; }
+            if (32 * e.kst < k || 16 * e.etw * e.wn < d || e.rows < 16 || e.rows % 16 || e.lds(e.rows) * e.per_cu > 160 * 1024
+                || e.rows * ((k + 3) / 4) > 64 * e.waves * 4) { printf("decompress plan: %d %d\n", d, k); return 1; }
+            decompress.insert(key(e.waves, e.exact, e.kst, e.etw));
+        }
+    for (int waves = 4; waves <= 8; waves *= 2)
+        for (int exact = 0; exact < 2; ++exact)
+            for (int t = 1; t <= 8; ++t)
+                for (int s = 1; s <= 16; ++s) {
+                    FlowPlan p;
+                    p.waves = waves; p.exact = exact; p.ntw = p.kst = t; p.steps = p.etw = s;
+                    auto same = [&](auto a, auto b, auto c, auto d) {
+                        if (a != t || b != s || c != exact || d != waves) { printf("wrong instance\n"); exit(1); }
+                    };
+                    if (flow_compress_instance(p, same) != (compress.count(key(waves, exact, t, s)) == 1)
+                        || flow_decompress_instance(p, same) != (decompress.count(key(waves, exact, t, s)) == 1)) {
+                        printf("instance without a plan: %d waves, exact %d, %d, %d\n", waves, exact, t, s);
+                        return 1;
+                    }
+                }
     return 0;
 }
 """)
