@@ -9,31 +9,10 @@ static flow_kernel compress_kernel(const gvq_basis* h, const FlowPlan& p)
     return h->dtype == GVQ_BF16 ? gvq_flow_compress_bf16(p) : gvq_flow_compress_f32(p);
 }
 
-// Where the LDS-tiled kernels are the better ones although these could take the shape: their word-wide path needs slices
-// (and, for decompress, comps) of whole words.  Measured on 48 M elements, one basis and 24 (here against there, us):
-//   compress    U over eight waves: d = 400, k = 100 80 against 68, bf16 d = 500, k = 128 67 against 54
-//               d > 256 with bf16 storage or several bases: d = 400, k = 60 bf16 43 against 43, 24 bases 58 against 45;
-//               d = 512, k = 20 bf16 62 against 39; up to d = 256 e.g. d = 256, k = 64 49 against 58, bf16 37 against 48
-//   decompress  d = 256 and 512: 24 bases 66 against 60, bf16 57 against 45; bf16 from d = 200 up with an even number of
-//               comps (d = 400, k = 60 40 against 32; d = 300, k = 75 42 against 62) and below d = 64 (d = 40 59 against 50)
-// Slices of no whole number of words always come here: d = 201, k = 67 60 against 131, bf16 57 against 204.
-bool gvq_flow_takes_compress(const gvq_basis* h)
-{
-    if (!h->d_Ufc) return false;
-    if (h->d & 3) return true;
-    const FlowPlan p = compress_plan(h);
-    return p.waves == 4 && (h->d <= 256 || (h->dtype == GVQ_F32 && h->B == 1));
-}
+static FlowShape shape_of(const gvq_basis* h, bool bf16) { return FlowShape{h->d, h->k, h->B, bf16, h->S, h->num_cu}; }
 
-bool gvq_flow_takes_decompress(const gvq_basis* h, bool out_bf16)
-{
-    if (!h->d_Ufd) return false;
-    if (h->d & 3) return true;
-    if (h->d % 256 == 0) return false;
-    if (!out_bf16) return true;
-    if (h->d >= 200 && h->d <= 768) return (h->k & 1) != 0;
-    return !(h->d < 64 && (h->k & 3) == 0);
-}
+bool gvq_flow_takes_compress(const gvq_basis* h) { return h->d_Ufc && flow_takes_compress(shape_of(h, h->dtype == GVQ_BF16)); }
+bool gvq_flow_takes_decompress(const gvq_basis* h, bool out_bf16) { return h->d_Ufd && flow_takes_decompress(shape_of(h, out_bf16)); }
 
 int gvq_flow_alloc(gvq_basis* h)
 {

@@ -197,3 +197,71 @@ inline int flow_run(int64_t tiles, int64_t slots, int most)
 
 // What flow_divide multiplies by in place of a division by n: i / n = (2 i * flow_divisor(n)) >> 32 for i < 4096, n < 4096.
 inline unsigned int flow_divisor(int n) { return (0x80000000u + (unsigned int)n - 1) / (unsigned int)n; }
+
+// Which kernels take a shape: these, or the LDS-tiled ones of gvq_codec_long.hip where those are faster.  Their word-wide
+// path needs slices (and, for decompress, comps) of whole words; lengths of any other kind always come here, but for the
+// smallest ranges.  It depends on the handle alone, never on the range of a call: a segment has the bits of the whole.
+//
+// Measured on 67 lengths x up to 11 numbers of comps, 0.5 to 100 M elements, one basis, 24 and thousands, both storage types
+// (here / there, geometric mean over the lengths named, 1 = level): 22499 pairs with everything here 0.64, 8.3 % of them more
+// than 5 % slower; 21556 with these rules 0.71, 2.4 % slower, nearly all of them by 1 - 2 us of at most 30.
+struct FlowShape {
+    int d, k, bases;
+    bool bf16;       // storage of the gradient (compress) or of the result (decompress)
+    int64_t slices;
+    int cus;
+};
+
+// Tiles per work-group of the whole gradient.
+inline double flow_tiles_each(const FlowShape& s, const FlowPlan& p)
+{
+    return (double)s.slices / p.rows / ((double)s.cus * p.per_cu);
+}
+
+// Short slices and few tiles: such a call is a few microseconds of latency, and a tile's phases make more of it.  Exact
+// products, one basis, f32, 0.5 M elements: d = 13 compress 7.5 us against 6.0, d = 24 decompress 5.6 against 4.4; from a
+// tile per work-group on 0.65 - 0.9.
+inline bool flow_too_small(const FlowShape& s, const FlowPlan& p)
+{
+    const double each = flow_tiles_each(s, p);
+    return p.exact && ((s.d <= 48 && each < 0.25) || (s.d % 4 == 0 && s.d <= 64 && each < 1));
+}
+
+inline bool flow_takes_compress(const FlowShape& s)
+{
+    const FlowPlan p = flow_compress_plan(s.d, s.k);
+    if (!p.waves) return false;
+    if (!s.bf16 && flow_too_small(s, p)) return false;
+    if (s.d % 4) return true;
+    // U over eight waves (f32 d = 400, k = 100 1.18, bf16 d = 500, k = 128 1.24); above 256 elements with bf16 storage or
+    // several bases (d = 512, k = 20 bf16 1.6; d = 400, k = 60 24 bases 1.3)
+    if (p.waves != 4 || (s.d > 256 && (s.bf16 || s.bases > 1))) return false;
+    // one tile of comps and long slices: a tile's rows do not give every wave a group of slices (f32 257 - 512 elements 1.1 -
+    // 1.2, bf16 161 - 256 1.05 - 1.2), which does not matter (0.4 - 0.8) while there is less than a tile for each
+    return !(s.k <= 16 && s.d > (s.bf16 ? 160 : 256) && flow_tiles_each(s, p) >= 1);
+}
+
+inline bool flow_takes_decompress(const FlowShape& s)
+{
+    const FlowPlan p = flow_decompress_plan(s.d, s.k);
+    const int d = s.d, k = s.k;
+    if (!p.waves) return false;
+    if (flow_too_small(s, p)) return false;
+    if (d % 4) return true;
+    const double each = flow_tiles_each(s, p);
+    if (d % 256 == 0) return false;   // 24 bases 1.1, to bf16 1.27
+    // few comps: little to read per number written, where those kernels' ordinary stores are at their best (f32 129 - 256
+    // elements 1.1 - 1.28, to bf16 65 - 192 1.0 - 1.3; below a tile each 0.5 - 0.9)
+    if (k <= 16 && d > (s.bf16 ? 64 : 128) && each >= (d > 768 ? 2 : 1)) return false;
+    // between one tile and two: the second waits for the first, and the smaller tiles there come out more evenly (1.05 - 1.2)
+    if (!p.exact && d > 64 && d <= 320 && k <= 64 && each > 1 && each <= 2) return false;
+    if (!s.bf16) return true;
+    // to bf16, where half the bytes are written: what is left is what their narrow reads of comps that are no whole words,
+    // or the padding to 64 elements, cost there
+    if (d < 64) return k % 4 != 0;                  // otherwise 1.0 - 1.2
+    if (d <= 128) return k > 16 && (k % 4 != 0 || k <= 32);   // 0.77 - 0.97, otherwise 1.0 - 1.1
+    if (d <= 160) return k > 32 || each < 1;        // otherwise 1.05 - 1.15
+    if (d < 200) return true;                       // 0.85 - 0.95
+    if (d <= 768) return k % 4 != 0 && k > 32;      // 0.8 - 0.9, otherwise 0.95 - 1.3
+    return true;                                    // 0.5 - 0.95
+}

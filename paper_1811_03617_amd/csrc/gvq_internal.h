@@ -41,7 +41,7 @@ struct gvq_basis {
     unsigned short* d_Uws = nullptr;  // basis-stationary compress kernel (gvq_ws_shape): two-term bf16 copy of U in its
                                       // operand order, per wave
     float* d_Umu = nullptr;     // [B][KP] U^T mu (bf16 gradients)
-    void* d_Ufc = nullptr;      // gvq_flow.h: packed U of its compress kernel (null: it does not take the shape)
+    void* d_Ufc = nullptr;      // gvq_flow.h: packed U of its compress kernel (null: no call goes there)
     void* d_Ufd = nullptr;      // ... and of its decompress kernel
     int flow_rows_c = 0, flow_rows_d = 0;   // slices per tile of the two
     int64_t* h_ftile = nullptr; // host [2][B+1]: first tile of each basis, compress then decompress (B > 1)

@@ -121,3 +121,76 @@ int main()
     return 0;
 }
 """)
+
+
+def _shape_lists():
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("flow_shapes", os.path.join(os.path.dirname(os.path.abspath(__file__)), "test_gpu_flow.py"))
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    return mod.INSTANCES, mod.INSTANCE_ELEMENTS
+
+
+def test_the_gpu_tests_run_every_instance_and_several_tiles_each(tmp_path):
+    pytest.importorskip("torch")
+    shapes, elements = _shape_lists()
+    _run(tmp_path, "static const int shapes[][2] = {" + ", ".join("{%d, %d}" % s for s in shapes) + "};\n"
+         + "static const int64_t elements = %d;" % elements + r"""
+#include <set>
+#include <tuple>
+typedef std::tuple<int, int, int, int, int> key;
+static void reached(int d, int k, bool bf16, std::set<key>& to, double* least)
+{
+    const FlowShape s = {d, k, 1, bf16, (elements + d - 1) / d, 256};
+    const FlowPlan c = flow_compress_plan(d, k), e = flow_decompress_plan(d, k);
+    if (flow_takes_compress(s)) { to.insert(key(0, c.waves, c.exact, c.ntw, c.steps)); if (least && flow_tiles_each(s, c) < *least) *least = flow_tiles_each(s, c); }
+    if (flow_takes_decompress(s)) { to.insert(key(1, e.waves, e.exact, e.kst, e.etw)); if (least && flow_tiles_each(s, e) < *least) *least = flow_tiles_each(s, e); }
+}
+int main()
+{
+    for (int bf16 = 0; bf16 < 2; ++bf16) {
+        std::set<key> all, run;
+        double least = 1e9;
+        for (int d = 2; d <= 1024; ++d)
+            for (int k = 1; k <= d && k <= 128; ++k) reached(d, k, bf16, all, nullptr);
+        for (auto& s : shapes) reached(s[0], s[1], bf16, run, &least);
+        if (run != all || least < 2.0) { printf("%zu of %zu instances, %.2f tiles per work-group\n", run.size(), all.size(), least); return 1; }
+    }
+    return 0;
+}
+""")
+
+
+def test_which_shapes_come_here(tmp_path):
+    """Both sides of every rule, and that a shape which comes here can be run here."""
+    _run(tmp_path, r"""
+static int bad = 0;
+static void want(const char* what, bool got, bool wanted) { if (got != wanted) { printf("%s\n", what); bad = 1; } }
+int main()
+{
+    auto c = [](int d, int k, double elements, int bases = 1, bool bf16 = false) { return flow_takes_compress({d, k, bases, bf16, (int64_t)(elements / d), 256}); };
+    auto e = [](int d, int k, double elements, int bases = 1, bool bf16 = false) { return flow_takes_decompress({d, k, bases, bf16, (int64_t)(elements / d), 256}); };
+    for (int d = 2; d <= 1024; d += 7)
+        for (int k = 1; k <= d && k <= 140; k = k < 8 ? k + 1 : k + 5)
+            for (double n : {3e4, 5e5, 3e6, 2.4e7, 1.4e8})
+                for (int bases : {1, 24})
+                    for (bool bf16 : {false, true}) {
+                        auto none = [](auto, auto, auto, auto) {};
+                        if (c(d, k, n, bases, bf16) && !flow_compress_instance(flow_compress_plan(d, k), none)) return 1;
+                        if (e(d, k, n, bases, bf16) && !flow_decompress_instance(flow_decompress_plan(d, k), none)) return 1;
+                    }
+    want("whole words", c(100, 25, 6.1e7) && e(100, 25, 6.1e7), true);
+    want("short odd slices, hardly any of them", c(13, 3, 5e5) || e(13, 3, 5e5), false);
+    want("more of them", c(13, 3, 2e7) && e(13, 3, 2e7), true);
+    want("long odd slices, any number", c(201, 50, 3e4) && e(201, 50, 3e4) && c(511, 16, 1e8) && e(1001, 16, 1e8), true);
+    want("idle waves", c(400, 16, 2.4e7) || e(400, 16, 2.4e7) || c(200, 16, 1e8, 1, true) || e(160, 16, 1e8, 1, true), false);
+    want("idle waves, small", c(400, 16, 5e5) && e(400, 16, 5e5), true);
+    want("eight waves", c(400, 100, 1e8), false);
+    want("long slices with several bases or bf16", c(400, 60, 1e8, 24) || c(400, 60, 1e8, 1, true), false);
+    want("the same, one basis", c(400, 60, 1e8), true);
+    want("long slices to bf16", e(400, 60, 1e8, 1, true), false);
+    want("the same, comps of no whole words", e(400, 62, 1e8, 1, true) && e(400, 75, 1e8, 1, true), true);
+    want("multiples of 256", e(256, 50, 1e8) || e(768, 96, 1e8, 24), false);
+    return bad;
+}
+""")

@@ -227,3 +227,45 @@ def test_many_short_bases(d, k, dtype):
             gvq.gvq_set_option(2, 0)
         assert here <= 2.0 * there, f"{what}: {here / 5:.3f} ms, LDS-tiled kernels {there / 5:.3f} ms"
     b.close()
+
+
+# a shape for every compiled instance of the two kernels (the list is checked against the plans in test_flow_plan.py)
+INSTANCES = [(9, 1), (25, 17), (41, 1), (41, 33), (41, 41), (49, 33), (57, 17), (57, 31), (57, 49), (73, 1), (73, 29), (73, 33),
+             (89, 17), (89, 26), (89, 49), (105, 1), (105, 25), (105, 33), (105, 97), (121, 17), (137, 1), (137, 25), (137, 65),
+             (137, 97), (169, 1), (169, 23), (169, 65), (201, 1), (201, 23), (201, 65), (233, 1), (233, 22), (233, 33), (265, 1),
+             (265, 22), (265, 97), (329, 1), (329, 22), (329, 65), (393, 1), (393, 22), (393, 65), (393, 97), (521, 33), (521, 65),
+             (521, 97), (649, 33), (649, 65), (777, 1), (777, 21), (777, 33), (777, 65), (905, 1), (905, 21), (905, 33)]
+INSTANCE_ELEMENTS = 24_000_000   # at least three tiles for every work-group
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("blocks", [1, 60])
+@pytest.mark.parametrize("d,k", INSTANCES)
+def test_every_instance_with_several_tiles_per_work_group(d, k, blocks, dtype):
+    """The steady loop of the kernels: the next tile asked for under this one, the last one's results leaving under it, changes of
+    basis inside a work-group (bases shorter and longer than a tile, of one slice, ending anywhere), a ragged end, a range that
+    starts and ends inside a tile; then other schedules (one work-group per compute unit, runs of one and of three tiles), which
+    must not change a bit."""
+    rng = np.random.default_rng(100 * d + k)
+    M = INSTANCE_ELEMENTS - INSTANCE_ELEMENTS % d + d // 2 + 1
+    S = -(-M // d)
+    cuts = np.array([0, S]) if blocks == 1 else _uneven_cuts(S, blocks, rng)
+    b = gvq.Basis(M, d, k, None if blocks == 1 else cuts, dtype)
+    _check_on_device(b, d, k, blocks, cuts, M, dtype, rng)
+
+    g = torch.randn(M, device=DEV).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    y, r = torch.empty(S * k, device=DEV), torch.empty_like(g)
+    b.compress(g, 3, y)
+    b.decompress(y, r)
+    try:
+        for wg_per_cu, run in ((1, 0), (0, 1), (1, 3)):
+            gvq.gvq_set_option(0, wg_per_cu)
+            gvq.gvq_set_option(1, run)
+            y2, r2 = torch.full_like(y, float("nan")), torch.full_like(r, float("nan"))
+            b.compress(g, 3, y2)
+            b.decompress(y, r2)
+            assert torch.equal(y, y2) and torch.equal(r, r2), (wg_per_cu, run)
+    finally:
+        gvq.gvq_set_option(0, 0)
+        gvq.gvq_set_option(1, 0)
+    b.close()
