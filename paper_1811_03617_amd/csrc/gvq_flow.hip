@@ -21,12 +21,13 @@ int gvq_flow_alloc(gvq_basis* h)
     auto allow_lds = [](flow_kernel kern) {   // the most any plan of the kernel takes
         return hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     };
-    if (compress_kernel(h, c)) {
+    // nothing for a direction that no call takes here
+    if (flow_takes_compress(shape_of(h, h->dtype == GVQ_BF16))) {
         h->flow_rows_c = c.rows;
         GVQ_HIP(allow_lds(compress_kernel(h, c)));
         GVQ_HIP(hipMalloc((void**)&h->d_Ufc, sizeof(u4) * B * c.words));
     }
-    if (gvq_flow_decompress(e)) {
+    if (flow_takes_decompress(shape_of(h, false)) || flow_takes_decompress(shape_of(h, true))) {
         h->flow_rows_d = e.rows;
         GVQ_HIP(allow_lds(gvq_flow_decompress(e)));
         GVQ_HIP(hipMalloc((void**)&h->d_Ufd, sizeof(u4) * B * e.words));
