@@ -17,12 +17,16 @@
 // with one at a time, as before, a tile took a memory latency per word.  The 16-byte words of a row are permuted by
 // x -> x ^ (row ^ row >> 2): words of one filter group in rows 4 c + i, c = 0, 1, 2 .., then sit in different banks, and so
 // does a whole row; no padding.
-// Every access is 256 bytes or more in one piece; what is left is how the pieces in flight lie in memory.  A layer too
-// large for the last-level cache takes its tiles with the filter groups fastest (whole rows of the flat side at a time):
-// fully connected 4096 x 25088, fp32 4.7 -> 5.1 TB/s read + written; smaller ones along the runs (1000 x 4096 4.1
-// against 3.7).  Tiles of 128 filters are no faster (4096 x 4096: 5.6 against 6.3), nor are non-temporal accesses.
-// fp32 / bf16, flatten, TB/s: 4096 x 25088 5.1 / 4.8 (one access at a time and LDS rows of odd length: 4.3 / 3.5), 4096 x 4096
-// 6.3 / 6.0, 512 x 4096 x 3 x 3 5.0 / 5.9, 512 x 512 x 3 x 3 3.1 / 2.1 (6 and 4.5 us: a tile's latency).
+// Every access is 256 bytes or more in one piece; what is left is how the pieces in flight lie in memory.  A layer of 32 MB
+// and more takes its tiles with the filter groups fastest (whole rows of the flat side at a time; fully connected 4096 x 25088
+// fp32 5.1 TB/s read + written against 4.65 along the runs), a smaller one along the runs (1000 x 4096 4.1 against 3.7).  With
+// the filter groups fastest, work-groups side by side read the same columns of rows D*H*W numbers apart; where that is close to
+// a multiple of 8 KB they meet in the same channels, and each filter group starts one run further on instead (the diagonals of
+// the grid of tiles: 4096 x 16384 flatten 3.7 -> 5.0, 4096 x 4112 3.6 -> 4.7, 4096 x 16448 4.1 -> 4.8; 4096 x 25088 would lose
+// 1 - 2 %).  Tiles of 128 filters are no faster (4096 x 4096: 5.6 against 6.3), nor are non-temporal accesses.
+// fp32 / bf16, flatten, TB/s: 4096 x 25088 5.1 / 4.8 (one access at a time and LDS rows of odd length: 4.4 / 3.7), 4096 x 16384
+// 5.0 / 5.0 (4.4 / 3.5), 4096 x 4096 4.9 / 4.4 (6.3 / 6.0 out of the last-level cache), 512 x 4096 x 3 x 3 4.4 / 4.2, 512 x 512
+// x 3 x 3 3.1 / 2.1 (6 and 4.5 us: a tile's latency).
 #include "gvq_internal.h"
 
 #define LAYOUT_THREADS 256
@@ -37,6 +41,7 @@ struct LayoutArgs {
     int n_ftiles, n_dtiles, n_hwtiles;
     unsigned int magic;        // n / H*W = n * magic >> 16 for the positions of a tile (TD > 1)
     int filters_fast;          // order of the tiles: the filter groups, or the runs, fastest
+    int skew;                  // filter groups fastest: runs that each group starts after the one before it
 };
 
 typedef unsigned int lu4 __attribute__((ext_vector_type(4)));
@@ -55,9 +60,11 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void conv_layout_kernel(LayoutArgs 
     constexpr int FI = 8;                                                     // accesses in flight on the flat side
     typedef LayoutVec<T, VT> Vec;
     const int tid = threadIdx.x;
-    const int ht = blockIdx.x % a.n_hwtiles, fd = blockIdx.x / a.n_hwtiles;
-    const int ft = a.filters_fast ? fd % a.n_ftiles : fd / a.n_dtiles;
-    const int dt = a.filters_fast ? fd / a.n_ftiles : fd - ft * a.n_dtiles;
+    const int nr = a.n_dtiles * a.n_hwtiles;              // runs of a filter
+    const int ft = a.filters_fast ? (int)blockIdx.x % a.n_ftiles : (int)blockIdx.x / nr;
+    int rt = a.filters_fast ? (int)blockIdx.x / a.n_ftiles : (int)blockIdx.x - ft * nr;
+    if (a.skew) rt = (rt + a.skew * ft) % nr;
+    const int dt = rt / a.n_hwtiles, ht = rt - dt * a.n_hwtiles;
     const int f0 = ft * TF, d0 = dt * a.TD, hw0 = ht * a.HWT;
     const int nf = a.F - f0 < TF ? a.F - f0 : TF;
     const int nd = a.D - d0 < a.TD ? a.D - d0 : a.TD;
@@ -257,6 +264,7 @@ static int launch_layout(const void* src, void* dst, int F, int D, int HW, hipSt
     a.magic = (65536u + (unsigned int)a.HWT - 1) / (unsigned int)a.HWT;
     a.n_ftiles = n_ftiles;
     a.filters_fast = (size_t)F * D * HW * sizeof(T) >= (32u << 20);
+    a.skew = a.filters_fast && (size_t)D * HW * sizeof(T) % 8192 < 1024;
     const size_t lds = sizeof(T) * (size_t)a.TD * a.HWT * LAYOUT_TF;
     const int64_t grid = (int64_t)n_ftiles * a.n_dtiles * a.n_hwtiles;
     if (grid > 0x7fffffff) return GVQ_EINVAL;

@@ -72,3 +72,48 @@ def test_layout_argument_checks():
     assert L.gvq_unflatten_conv(x.data_ptr(), y.data_ptr(), 2, 2, 2, 2, 9, st) == gvq.EINVAL
     assert L.gvq_flatten_conv(x.data_ptr() + 2, y.data_ptr(), 2, 2, 2, 2, gvq.BF16, st) == gvq.OK
     torch.cuda.synchronize()
+
+
+# 32 MB and more: filter groups fastest, straight and along the diagonals of the grid of tiles (row lengths near a multiple of
+# 8 KB or not), ragged last tiles, several depths per tile, H*W in pieces, filters that are no multiple of a word
+LARGE = [(1024, 8192, 1, 1), (1000, 8448, 1, 1), (1030, 16448, 1, 1), (513, 25088, 1, 1), (512, 2048, 3, 3), (130, 8192, 4, 4),
+         (256, 3, 128, 128), (2051, 8192, 1, 1)]
+
+
+@pytest.mark.parametrize("F,D,H,W", LARGE)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_large_layers_and_unaligned_arrays(F, D, H, W, dtype, shift):
+    n = F * D * H * W
+    t = torch.int32 if dtype == "f32" else torch.int16
+    code = gvq.F32 if dtype == "f32" else gvq.BF16
+    gen = torch.Generator(device=DEV).manual_seed(F + D)
+    bits = torch.randint(-2 ** 15, 2 ** 15 - 1, (n + 16,), device=DEV, generator=gen).to(t)
+    src = bits[shift:shift + n]
+    flat, back = torch.zeros(n + 16, device=DEV, dtype=t), torch.zeros(n + 16, device=DEV, dtype=t)
+    gvq.gvq_flatten_conv(src, flat[shift:], F, D, H, W, code)
+    gvq.gvq_unflatten_conv(flat[shift:], back[shift:], F, D, H, W, code)
+    assert torch.equal(flat[shift:shift + n], src.view(F, D, H, W).permute(2, 3, 1, 0).reshape(-1))
+    assert torch.equal(back[shift:shift + n], src)
+    for x in (flat, back):
+        assert not x[:shift].any() and not x[shift + n:].any()
+
+
+def test_the_length_of_a_row_does_not_decide_the_speed():
+    """Two fully connected layers whose rows are 64 KB and 98 KB long: bytes per second within a quarter (1.02 measured; 0.73
+    with the filter groups fastest and every group at the same run)."""
+    times = []
+    for F, D in ((4096, 16384), (4096, 25088)):
+        x, y = torch.randn(F * D, device=DEV), torch.empty(F * D, device=DEV)
+        gvq.gvq_flatten_conv(x, y, F, D, 1, 1, gvq.F32)
+        best = 1e9
+        for _ in range(5):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            for _ in range(4):
+                gvq.gvq_flatten_conv(x, y, F, D, 1, 1, gvq.F32)
+            t1.record()
+            torch.cuda.synchronize()
+            best = min(best, t0.elapsed_time(t1) / (F * D))
+        times.append(best)
+    assert times[0] <= 1.25 * times[1], times
