@@ -12,7 +12,9 @@
 //   [F][D][H][W] side: a thread takes GV consecutive numbers of VT = 16 / sizeof(T) neighbouring filters (VT accesses),
 //     transposes them in registers and exchanges GV whole 16-byte words with LDS.  GV = VT where runs are 16-byte
 //     aligned (D*H*W and the pieces multiples of VT), else 1.
-//   flat side: a thread moves FV neighbouring filters of one row; FV = VT where F is a multiple of VT, else 1.
+//   flat side: a thread moves FV neighbouring filters of one row; FV = VT where F is a multiple of VT (and both arrays are
+//     16-byte aligned), else one 32-bit word at whatever address: one fp32 number or two bf16 (a bf16 number at a time, two
+//     lanes shared a bank: 4097 x 4096 unflatten 68 us, 19 now, 51 before the words of LDS were permuted).
 // A thread's accesses of a side are all requested before the first of them is waited for (up to eight 16-byte words):
 // with one at a time, as before, a tile took a memory latency per word.  The 16-byte words of a row are permuted by
 // x -> x ^ (row ^ row >> 2): words of one filter group in rows 4 c + i, c = 0, 1, 2 .., then sit in different banks, and so
@@ -27,6 +29,8 @@
 // fp32 / bf16, flatten, TB/s: 4096 x 25088 5.1 / 4.8 (one access at a time and LDS rows of odd length: 4.4 / 3.7), 4096 x 16384
 // 5.0 / 5.0 (4.4 / 3.5), 4096 x 4096 4.9 / 4.4 (6.3 / 6.0 out of the last-level cache), 512 x 4096 x 3 x 3 4.4 / 4.2, 512 x 512
 // x 3 x 3 3.1 / 2.1 (6 and 4.5 us: a tile's latency).
+#include <type_traits>
+
 #include "gvq_internal.h"
 
 #define LAYOUT_THREADS 256
@@ -46,6 +50,9 @@ struct LayoutArgs {
 
 typedef unsigned int lu4 __attribute__((ext_vector_type(4)));
 
+__device__ __forceinline__ unsigned int first_of(unsigned int x) { return x; }
+__device__ __forceinline__ unsigned int first_of(lu4 x) { return x[0]; }
+
 template <typename T, int N> union LayoutVec {
     lu4 v;
     T e[N];
@@ -58,6 +65,8 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void conv_layout_kernel(LayoutArgs 
     constexpr int TF = LAYOUT_TF, VT = 16 / sizeof(T), QF = TF / VT;
     constexpr int GI = GV > 1 ? LAYOUT_TILE / 16 / VT / LAYOUT_THREADS : 2;   // items in flight on the [F][D][H][W] side
     constexpr int FI = 8;                                                     // accesses in flight on the flat side
+    typedef typename std::conditional<FV == VT, lu4, unsigned int>::type FVec;
+    static_assert(FV * sizeof(T) == sizeof(FVec), "an access of the flat side");
     typedef LayoutVec<T, VT> Vec;
     const int tid = threadIdx.x;
     const int nr = a.n_dtiles * a.n_hwtiles;              // runs of a filter
@@ -94,7 +103,7 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void conv_layout_kernel(LayoutArgs 
                     const T* p = gside + (size_t)(VT * q[n]) * fstride + r0[n];
 #pragma unroll
                     for (int u = 0; u < VT; ++u, p += fstride) {
-                        if (FV == 1 && VT * q[n] + u >= nf) continue;     // F a multiple of VT otherwise
+                        if (FV < VT && VT * q[n] + u >= nf) continue;     // F a multiple of VT otherwise
                         if constexpr (GV > 1) {
                             const lu4 w = *(const lu4*)p;
                             __builtin_memcpy(x[n][u], &w, 16);
@@ -133,7 +142,7 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void conv_layout_kernel(LayoutArgs 
                     T* p = gside + (size_t)(VT * q[n]) * fstride + r0[n];
 #pragma unroll
                     for (int u = 0; u < VT; ++u, p += fstride) {
-                        if (FV == 1 && VT * q[n] + u >= nf) continue;
+                        if (FV < VT && VT * q[n] + u >= nf) continue;
                         if constexpr (GV > 1) {
                             lu4 w;
                             __builtin_memcpy(&w, x[n][u], 16);
@@ -151,9 +160,9 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void conv_layout_kernel(LayoutArgs 
         constexpr int W = TF / FV, ROWS = LAYOUT_THREADS / W;
         const int c = tid % W;                            // this thread's access within every row
         if (c * FV >= nf) return;
+        const bool single = FV == 2 && c * FV + 1 >= nf;  // the last of an odd number of filters
         for (int row0 = tid / W; row0 < run; row0 += FI * ROWS) {
-            lu4 xv[FI];
-            T xs[FI];
+            FVec x[FI];
             T* p[FI];
 #pragma unroll
             for (int n = 0; n < FI; ++n) {
@@ -161,30 +170,27 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void conv_layout_kernel(LayoutArgs 
                 const int hw = nhw == 1 ? 0 : nd == 1 ? row : row / nd, dd = row - hw * nd;   // row = hw * nd + dd
                 p[n] = fside + ((size_t)hw * a.D + dd) * a.F + FV * c;
                 if (!FLATTEN && row < run) {
-                    if constexpr (FV > 1) xv[n] = *(const lu4*)p[n];
-                    else xs[n] = *p[n];
+                    if (single) x[n] = FVec{} + *p[n];
+                    else if constexpr (FV == VT) x[n] = *(const FVec*)p[n];
+                    else __builtin_memcpy(&x[n], p[n], sizeof(FVec));   // of any alignment
                 }
             }
 #pragma unroll
             for (int n = 0; n < FI; ++n) {
                 const int row = row0 + n * ROWS;
                 if (row >= run) break;
-                if constexpr (FV > 1) {
-                    lu4& w = tile[word(row, c)];
-                    if (FLATTEN) xv[n] = w;
-                    else w = xv[n];
-                } else {
-                    T& w = ((T*)&tile[word(row, c / VT)])[c % VT];
-                    if (FLATTEN) xs[n] = w;
-                    else w = xs[n];
-                }
+                // FVec is the type of the 16-byte words' parts here, whose address is a multiple of its size
+                FVec& w = ((FVec*)&tile[word(row, c * FV / VT)])[c % (VT / FV)];
+                if (FLATTEN) x[n] = w;
+                else w = x[n];
             }
             if (FLATTEN) {
 #pragma unroll
                 for (int n = 0; n < FI; ++n) {
                     if (row0 + n * ROWS >= run) break;
-                    if constexpr (FV > 1) *(lu4*)p[n] = xv[n];
-                    else *p[n] = xs[n];
+                    if (single) *p[n] = (T)first_of(x[n]);
+                    else if constexpr (FV == VT) *(FVec*)p[n] = x[n];
+                    else __builtin_memcpy(p[n], &x[n], sizeof(FVec));
                 }
             }
         }
@@ -223,7 +229,7 @@ static int launch_tiles(const LayoutArgs& a, int64_t grid, size_t lds, hipStream
 template <typename T, bool FLATTEN>
 static int launch_layout(const void* src, void* dst, int F, int D, int HW, hipStream_t st)
 {
-    constexpr int VT = 16 / sizeof(T);
+    constexpr int VT = 16 / sizeof(T), F1 = 4 / sizeof(T);
     const bool aligned = (((uintptr_t)src | (uintptr_t)dst) & 15) == 0;
     if (D * (int64_t)HW == 1 || (F == 1 && (D == 1 || HW == 1))) {
         const size_t n = (size_t)F * D * HW, per = (size_t)LAYOUT_THREADS * (aligned ? VT : 1);
@@ -269,9 +275,9 @@ static int launch_layout(const void* src, void* dst, int F, int D, int HW, hipSt
     const int64_t grid = (int64_t)n_ftiles * a.n_dtiles * a.n_hwtiles;
     if (grid > 0x7fffffff) return GVQ_EINVAL;
     if (gv && fv) return launch_tiles<T, FLATTEN, VT, VT>(a, grid, lds, st);
-    if (gv) return launch_tiles<T, FLATTEN, VT, 1>(a, grid, lds, st);
+    if (gv) return launch_tiles<T, FLATTEN, VT, F1>(a, grid, lds, st);
     if (fv) return launch_tiles<T, FLATTEN, 1, VT>(a, grid, lds, st);
-    return launch_tiles<T, FLATTEN, 1, 1>(a, grid, lds, st);
+    return launch_tiles<T, FLATTEN, 1, F1>(a, grid, lds, st);
 }
 
 int gvq_launch_layout(const void* src, void* dst, int F, int D, int HW, gvq_dtype_t dtype, bool flatten,
