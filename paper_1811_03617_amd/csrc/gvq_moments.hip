@@ -305,7 +305,7 @@ template <int NT, bool BF16, bool OFF>
 __device__ __forceinline__ void moments_waves(const MomArgs& a, double* lds, int pa, int pb, int chunk, int chunks, double* out)
 {
     if constexpr (MomShape<NT, OFF>::SPLIT) {
-        switch (threadIdx.x >> 6) {
+        switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {   // uniform: the cases hold barriers
         case 0: moments_task<NT, BF16, OFF, 0>(a, lds, pa, pb, chunk, chunks, out); break;
         case 1: moments_task<NT, BF16, OFF, 1>(a, lds, pa, pb, chunk, chunks, out); break;
         case 2: moments_task<NT, BF16, OFF, 2>(a, lds, pa, pb, chunk, chunks, out); break;
