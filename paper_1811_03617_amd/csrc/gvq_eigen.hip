@@ -593,15 +593,22 @@ __global__ __launch_bounds__(64) void inverse_kernel(EigenArgs a)
 // Modified Gram-Schmidt over k columns of length n, one work-group per basis, panels of 32 columns in registers (four
 // per wave, NE numbers per lane each).  A panel first sheds its components along the finished columns, then along its
 // own, column by column through LDS.
-template <int NE>
-__global__ __launch_bounds__(512) void orthonormalise_kernel(double* Z, size_t Z_stride, int k, int n,
+//
+// One work-group per basis is a 256th of the chip, and what many columns take is the first part: more than 256 columns are
+// finished panel by panel, each in a launch of its own (FINISH), and after each the later panels shed their components along
+// it, a work-group each (SHED): the same operations in the same order (d = k = 1024 20.6 -> 2.8 ms; the whole refresh 29.4 -> 11.6, d = k = 512 6.4 -> 3.9).
+enum OrthoPart { ORTHO_ALL, ORTHO_FINISH, ORTHO_SHED };
+template <int NE, OrthoPart PART>
+__global__ __launch_bounds__(512) void orthonormalise_kernel(double* Z, size_t Z_stride, int k, int n, int panel,
                                                              const unsigned long long* norm)
 {
     __shared__ double q[2][NE * 64];
-    const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int b = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (eig_skip(norm[b])) return;
     Z += (size_t)b * Z_stride;
-    for (int c0 = 0; c0 < k; c0 += 32) {
+    const int first = PART == ORTHO_ALL ? 0 : 32 * (PART == ORTHO_FINISH ? panel : panel + 1 + (int)blockIdx.x);
+    const int end = PART == ORTHO_ALL ? k : first + 32;
+    for (int c0 = first; c0 < end; c0 += 32) {
         double x[4][NE];
 #pragma unroll
         for (int s = 0; s < 4; ++s)
@@ -610,7 +617,8 @@ __global__ __launch_bounds__(512) void orthonormalise_kernel(double* Z, size_t Z
                 const int c = c0 + 8 * s + wave, i = 64 * e + lane;
                 x[s][e] = c < k && i < n ? Z[(size_t)c * n + i] : 0.0;
             }
-        for (int done = 0; done < c0; ++done) {
+        const int done0 = PART == ORTHO_SHED ? 32 * panel : 0, done1 = PART == ORTHO_ALL ? c0 : PART == ORTHO_SHED ? done0 + 32 : 0;
+        for (int done = done0; done < done1; ++done) {
             double y[NE], dot[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
             for (int e = 0; e < NE; ++e) y[e] = 64 * e + lane < n ? Z[(size_t)done * n + 64 * e + lane] : 0.0;
@@ -624,6 +632,16 @@ __global__ __launch_bounds__(512) void orthonormalise_kernel(double* Z, size_t Z
 #pragma unroll
                 for (int e = 0; e < NE; ++e) x[s][e] = fma(-dot[s], y[e], x[s][e]);
             }
+        }
+        if (PART == ORTHO_SHED) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int e = 0; e < NE; ++e) {
+                    const int c = c0 + 8 * s + wave, i = 64 * e + lane;
+                    if (c < k && i < n) Z[(size_t)c * n + i] = x[s][e];
+                }
+            return;
         }
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -770,7 +788,16 @@ template <int NE> struct go_step {
 template <int NE> struct go_ortho {
     static void go(double* Z, size_t stride, int k, int n, int B, const unsigned long long* norm, hipStream_t st)
     {
-        hipLaunchKernelGGL((orthonormalise_kernel<NE>), dim3(B), dim3(512), 0, st, Z, stride, k, n, norm);
+        const dim3 threads(512);
+        if (k <= 256) {
+            hipLaunchKernelGGL((orthonormalise_kernel<NE, ORTHO_ALL>), dim3(1, B), threads, 0, st, Z, stride, k, n, 0, norm);
+            return;
+        }
+        for (int p = 0; 32 * p < k; ++p) {
+            const int later = (k - 1) / 32 - p;
+            hipLaunchKernelGGL((orthonormalise_kernel<NE, ORTHO_FINISH>), dim3(1, B), threads, 0, st, Z, stride, k, n, p, norm);
+            if (later) hipLaunchKernelGGL((orthonormalise_kernel<NE, ORTHO_SHED>), dim3(later, B), threads, 0, st, Z, stride, k, n, p, norm);
+        }
     }
 };
 template <int NE> struct go_back {
