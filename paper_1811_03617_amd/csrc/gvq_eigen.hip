@@ -50,6 +50,16 @@ __device__ __forceinline__ double wave_sum(double v)
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
+// Largest of the 64 lanes' values, in every lane.
+__device__ __forceinline__ double wave_max(double v)
+{
+    v = fmax(v, dpp_move<DPP_XOR1>(v));
+    v = fmax(v, dpp_move<DPP_XOR2>(v));
+    v = fmax(v, dpp_move<DPP_HALF_MIRROR>(v));
+    v = fmax(v, dpp_move<DPP_MIRROR>(v));
+    return fmax(fmax(lane_value(v, 0), lane_value(v, 16)), fmax(lane_value(v, 32), lane_value(v, 48)));
+}
+
 // 1/x to the last bit or two for normal x and 1/x: the hardware's approximation and two Newton steps.
 __device__ __forceinline__ double fast_rcp(double x)
 {
@@ -380,15 +390,15 @@ __global__ __launch_bounds__(TJ * TJ) void tri_small_kernel(EigenArgs a, int i0)
 // they come out ordered.
 __global__ __launch_bounds__(256) void bisect_kernel(EigenArgs a)
 {
-    __shared__ double2 t[GVQ_MAX_D];   // d_i, e_{i-1}^2
+    extern __shared__ double2 t[];   // [n] d_i, e_{i-1}^2
     __shared__ double bound[2];
-    const int b = blockIdx.y, n = a.n, tid = threadIdx.x;
+    const int b = blockIdx.y, n = a.n, tid = threadIdx.x, nthr = blockDim.x;
     const unsigned long long norm = a.norm[b];
     double* eig = a.eig + (size_t)b * a.eig_ld;
-    const int g = blockIdx.x * (256 / a.lanes) + tid / a.lanes;   // this group's eigenvalue, in increasing order
+    const int g = blockIdx.x * (nthr / a.lanes) + tid / a.lanes;   // this group's eigenvalue, in increasing order
     const int l = tid % a.lanes;
     if (blockIdx.x == 0)
-        for (int i = n + tid; i < a.eig_ld; i += 256) eig[i] = norm >= EIG_INF_BITS ? __longlong_as_double(-1ll) : 0.0;
+        for (int i = n + tid; i < a.eig_ld; i += nthr) eig[i] = norm >= EIG_INF_BITS ? __longlong_as_double(-1ll) : 0.0;
     if (eig_skip(norm)) {
         if (l == 0 && g < n) eig[g] = norm ? __longlong_as_double(-1ll) : 0.0;   // NaN where the input was not finite
         return;
@@ -396,7 +406,7 @@ __global__ __launch_bounds__(256) void bisect_kernel(EigenArgs a)
     const double* T = a.T + (size_t)b * 5 * a.t_ld;
     const int ex = eig_scale_exp(norm);
     double lo = 0.0, hi = 0.0;
-    for (int i = tid; i < n; i += 256) {
+    for (int i = tid; i < n; i += nthr) {
         const double d = ldexp(T[i], ex);
         const double e0 = i ? fmax(fabs(ldexp(T[a.t_ld + i - 1], ex)), EIG_E_FLOOR) : 0.0;
         const double e1 = i + 1 < n ? fmax(fabs(ldexp(T[a.t_ld + i], ex)), EIG_E_FLOOR) : 0.0;
@@ -406,16 +416,21 @@ __global__ __launch_bounds__(256) void bisect_kernel(EigenArgs a)
     }
     if (tid == 0) { bound[0] = 0.0; bound[1] = 0.0; }
     __syncthreads();
-    // |bounds| as integers: positive doubles order like their bits
-    atomicMax((unsigned long long*)&bound[0], (unsigned long long)__double_as_longlong(fmax(-lo, 0.0)));
-    atomicMax((unsigned long long*)&bound[1], (unsigned long long)__double_as_longlong(fmax(hi, 0.0)));
+    // One LDS atomic per wave and bound; from every thread they queued up at one address (n = 4, one matrix: 10.4 us a launch,
+    // 4.4 now).  |bounds| as integers: positive doubles order like their bits.
+    lo = wave_max(fabs(lo));
+    hi = wave_max(fabs(hi));
+    if ((tid & 63) == 0) {
+        atomicMax((unsigned long long*)&bound[0], (unsigned long long)__double_as_longlong(lo));
+        atomicMax((unsigned long long*)&bound[1], (unsigned long long)__double_as_longlong(hi));
+    }
     __syncthreads();
     const double slack = 1e-15 * (bound[0] + bound[1]) + 1e-18;
     lo = -bound[0] - slack;
     hi = bound[1] + slack;
 
     const double step = 1.0 / (a.lanes + 1);
-    const int passes = a.lanes == 64 ? 9 : a.lanes == 16 ? 14 : 18;   // (lanes + 1)^passes > 2^54
+    const int passes = a.lanes == 64 ? 9 : a.lanes == 16 ? 14 : a.lanes == 8 ? 18 : 24;   // (lanes + 1)^passes > 2^54
     for (int pass = 0; pass < passes; ++pass) {
         const double w = (hi - lo) * step, s = fma(w, (double)(l + 1), lo);
         double p0 = 1.0, p1 = t[0].x - s;
@@ -776,7 +791,8 @@ size_t gvq_eigen_lu_doubles(int d, int k)   // per basis
 template <template <int> class F, typename... Args>
 static void by_pieces(int n, Args... args)
 {
-    if (n <= 128) F<2>::go(args...);
+    if (n <= 64) F<1>::go(args...);
+    else if (n <= 128) F<2>::go(args...);
     else if (n <= 256) F<4>::go(args...);
     else if (n <= 512) F<8>::go(args...);
     else if (n <= 768) F<12>::go(args...);
@@ -788,7 +804,7 @@ template <int NE> struct go_step {
 template <int NE> struct go_ortho {
     static void go(double* Z, size_t stride, int k, int n, int B, const unsigned long long* norm, hipStream_t st)
     {
-        const dim3 threads(512);
+        const dim3 threads(64 * (k < 8 ? k : 8));   // a wave per column of eight
         if (k <= 256) {
             hipLaunchKernelGGL((orthonormalise_kernel<NE, ORTHO_ALL>), dim3(1, B), threads, 0, st, Z, stride, k, n, 0, norm);
             return;
@@ -822,9 +838,12 @@ int gvq_launch_sym_eigen(const gvq_basis* h, EigenArgs a, bool ortho, hipStream_
     else if (n - i0 <= 64) hipLaunchKernelGGL((tri_small_kernel<16>), dim3(B), dim3(256), 0, st, a, i0);
     else hipLaunchKernelGGL((tri_small_kernel<32>), dim3(B), dim3(1024), 0, st, a, i0);
     GVQ_HIP(hipGetLastError());
-    // a wave per eigenvalue while that leaves the chip's 1024 SIMDs a handful each, fewer lanes for many small matrices
-    a.lanes = (int64_t)n * B <= 4096 ? 64 : (int64_t)n * B <= 65536 ? 16 : 8;
-    hipLaunchKernelGGL(bisect_kernel, dim3((unsigned)((n * a.lanes + 255) / 256), B), dim3(256), 0, st, a);
+    // a wave per eigenvalue while that leaves the chip's 1024 SIMDs a handful each, fewer lanes for many small matrices (the
+    // passes that more lanes spare are fewer than the lanes: 16 x 16, 4000 of them 69 us with 16 lanes, 36 with 4 and a wave each)
+    a.lanes = (int64_t)n * B <= 4096 ? 64 : (int64_t)n * B <= 16384 ? 16 : (int64_t)n * B <= 32768 ? 8 : 4;
+    const int bisect_threads = n * a.lanes >= 256 ? 256 : (n * a.lanes + 63) / 64 * 64;
+    hipLaunchKernelGGL(bisect_kernel, dim3((unsigned)((n * a.lanes + bisect_threads - 1) / bisect_threads), B), dim3(bisect_threads),
+                       sizeof(double2) * n, st, a);
     GVQ_HIP(hipGetLastError());
     if (n <= GVQ_EIGEN_SMALL) {
         const size_t lds = sizeof(double) * 5 * n * 16;

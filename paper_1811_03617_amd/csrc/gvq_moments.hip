@@ -344,7 +344,8 @@ __global__ __launch_bounds__(256, 2) void moments_kernel(MomArgs a)
 
 // mom [B][d*d + d] (sum x x^T, both triangles, then sum x) from the partials: 64 entries per work-group, 16 threads per
 // entry that each add a sixteenth of the chunks in order, then those sums in order.  (One thread per entry walking
-// through all chunks took 0.5 ms for a 24 x 24 matrix in 512 chunks.)
+// through all chunks took 0.5 ms for a 24 x 24 matrix in 512 chunks.)  Up to 16 chunks, with many bases, one thread per entry
+// and a wave per work-group: the same sums (4000 bases of 16 x 16 48 -> 12 us).
 template <int NT>
 __global__ __launch_bounds__(1024) void moments_reduce_kernel(const double* part_all, size_t part_basis, double* mom, int d,
                                                               int np, int pw, int chunks_diag, int chunks_off)
@@ -353,7 +354,7 @@ __global__ __launch_bounds__(1024) void moments_reduce_kernel(const double* part
     using Off = MomShape<NT, true>;
     __shared__ double sub[16][64];
     const int b = blockIdx.z, lane = threadIdx.x & 63, s = threadIdx.x >> 6;
-    const int at = blockIdx.x * 64 + lane;
+    const int at = blockIdx.x * 64 + lane, parts = blockDim.x / 64;
     int q = blockIdx.y;
     const bool off = q >= np;
     const int width = off ? Off::PART : Diag::PART, chunks = off ? chunks_off : chunks_diag;
@@ -371,16 +372,18 @@ __global__ __launch_bounds__(1024) void moments_reduce_kernel(const double* part
     }
     double v = 0.0;
     if (at < width) {
-        const int c1 = (int)((int64_t)chunks * (s + 1) / 16);
+        const int c1 = (int)((int64_t)chunks * (s + 1) / parts);
 #pragma unroll 8
-        for (int c = (int)((int64_t)chunks * s / 16); c < c1; ++c) v += src[(size_t)c * width + at];
+        for (int c = (int)((int64_t)chunks * s / parts); c < c1; ++c) v += src[(size_t)c * width + at];
     }
-    sub[s][lane] = v;
-    __syncthreads();
-    if (s != 0 || at >= width) return;
-    v = 0.0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v += sub[i][lane];
+    if (parts > 1) {
+        sub[s][lane] = v;
+        __syncthreads();
+        if (s != 0) return;
+        v = 0.0;
+        for (int i = 0; i < parts; ++i) v += sub[i][lane];
+    }
+    if (at >= width) return;
     double* o = mom + (size_t)b * ((size_t)d * d + d);
     const int npair = off ? Off::NPAIR : Diag::NPAIR;
     if (at >= npair * 256) {
@@ -487,7 +490,7 @@ int gvq_launch_moments(gvq_basis* h, const void* const* grads, int L, hipStream_
         if (rc != GVQ_OK) return rc;
         const int width = a.np > 1 ? Off::PART : Diag::PART;
         hipLaunchKernelGGL((moments_reduce_kernel<NT>), dim3((unsigned)((width + 63) / 64), (unsigned)(a.np + poff), (unsigned)h->B),
-                           dim3(1024), 0, st, h->d_part, h->mom_part, h->d_mom, h->d, a.np, a.pw, a.chunks_diag, a.chunks_off);
+                           dim3(a.chunks_diag > 16 || a.chunks_off > 16 ? 1024 : 64), 0, st, h->d_part, h->mom_part, h->d_mom, h->d, a.np, a.pw, a.chunks_diag, a.chunks_off);
         GVQ_HIP(hipGetLastError());
         return GVQ_OK;
     });

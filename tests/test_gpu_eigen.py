@@ -97,3 +97,36 @@ def test_first_slice_sizes(d, k, L, dtype):
     assert np.max(np.abs(C - Xc.T @ Xc / L)) <= 1e-15 * (L + 10) * np.max(np.abs(C))
     assert np.array_equal(C, C.T)
     _check(U, eig, C, k, columns=min(k, L - 1))
+
+
+@pytest.mark.parametrize("d,k", [(257, 257), (512, 288), (513, 289), (700, 320), (1000, 1000), (1024, 300)])
+def test_many_columns(d, k):
+    """More than 256 columns: panels finished in launches of their own, full and short last panels."""
+    test_sizes(d, k)
+
+
+@pytest.mark.parametrize("d,k,B", [(2, 2, 3000), (3, 1, 9000), (16, 5, 900), (16, 16, 5000), (33, 9, 600), (48, 20, 400), (64, 64, 300),
+                                   (65, 30, 300), (128, 16, 600), (40, 12, 120)])
+def test_many_small_matrices(d, k, B):
+    """Bases side by side, for every number of lanes that shares an eigenvalue (16, 8 and 4 from 4096, 16384 and 32768 rows of
+    matrices on), matrices with few rows in a part of a work-group, a zero matrix and unequal scales among them."""
+    rng = np.random.default_rng(d * B)
+    per = d + 9 + rng.integers(0, 5, B)
+    cuts = np.concatenate([[0], np.cumsum(per)])
+    x = rng.standard_normal((cuts[-1], d)) * np.exp(rng.uniform(-6, 6, B)).repeat(per)[:, None]
+    x[cuts[7]:cuts[8]] = 0.25
+    b = gvq.Basis(x.size, d, k, cuts, "f32")
+    b.fit([torch.from_numpy(x.astype(np.float32).reshape(-1)).to(DEV)])
+    assert b.fit_status() > 0
+    U, mu, eig = b.export()
+    C, n = b.export_cov()
+    b.close()
+    assert np.array_equal(n, per)
+    w = np.linalg.eigvalsh(C)[:, ::-1]
+    lam = w[:, :1]
+    assert not C[7].any() and not eig[7].any() and np.array_equal(U[7], np.eye(d, k))
+    assert np.all(np.abs(eig - w) <= 1e-15 * (d + 10) * lam)
+    U = U.astype(np.float64)
+    assert np.max(np.abs(np.swapaxes(U, 1, 2) @ U - np.eye(k))) <= 2 * 2.0 ** -24 + 1e-8
+    resid = np.linalg.norm(C @ U - U * eig[:, None, :k], axis=1)
+    assert np.all(resid <= (2 * 2.0 ** -24 + 1e-8) * lam)
