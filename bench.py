@@ -100,10 +100,10 @@ def run_workload(name, args):
         rng = np.random.default_rng(w.seed)
         U0 = np.stack([np.linalg.qr(rng.standard_normal((w.d, w.k)))[0] for _ in range(w.n_blocks)])
         basis.import_(U0.astype(np.float32), np.zeros((w.n_blocks, w.d), np.float32))
-        sweeps, fit_ms = None, float("nan")
+        solves, fit_ms = None, float("nan")
     else:
         basis.fit(fit_grads)
-        sweeps = basis.fit_status()
+        solves = basis.fit_status()
         e0, e1 = ev(), ev()
         e0.record()
         basis.fit(fit_grads)
@@ -271,7 +271,7 @@ def run_workload(name, args):
         "kernels_GBs": {"compress": round(comp_bytes / comp_ms / 1e6, 1),
                         "aggregate": round(agg_bytes / agg_ms / 1e6, 1),
                         "decompress": round(dec_bytes / dec_ms / 1e6, 1)},
-        "fit": None if args.skip_fit else {"ms": round(fit_ms, 3), "L": L, "jacobi_sweeps": sweeps,
+        "fit": None if args.skip_fit else {"ms": round(fit_ms, 3), "L": L, "eigenvector_solves": solves,
                                             "input_GBs": round(L * w.M * es / fit_ms / 1e6, 1)},
         "reconstruction_loss": loss,
         "next_rows": next_rows,

@@ -55,7 +55,7 @@ typedef enum {
     GVQ_EHIP = -4,       /* a HIP call failed; gvq_strerror gives the HIP text */
     GVQ_ENOMEM = -5,     /* host or device allocation failed */
     GVQ_ENONFINITE = -6, /* gvq_fit_status: a fitted eigenvalue is NaN or Inf */
-    GVQ_ENOCONV = -7,    /* gvq_fit_status: the eigensolver hit its sweep limit */
+    GVQ_ENOCONV = -7,    /* gvq_fit_status: an eigenvector did not converge */
     GVQ_ETOOBIG = -8     /* gvq_local_loss_static: more slices or bases than its fixed scratch buffer holds */
 } gvq_status_t;
 
@@ -114,13 +114,13 @@ int gvq_fit_basis(gvq_basis_t* h, const void* const* grads, int L, void* stream)
 int gvq_fit_basis_first_slice(gvq_basis_t* h, const void* const* grads, int L, void* stream);
 
 /*
- * Waits for `stream`'s work, then reports on the last fit: *max_sweeps (may be NULL)
- * receives the largest iteration count of the eigensolver over the bases (0: every covariance is
- * zero).  Returns GVQ_ENOCONV if an
- * eigenvector of a basis did not converge, GVQ_ENONFINITE if an eigenvalue is not finite (e.g. NaN/Inf in a
- * fit gradient), GVQ_ENOTFIT if no fit was run.
+ * Waits for `stream`'s work, then reports on the last fit: *max_solves (may be NULL) receives the most solves that
+ * inverse iteration took for any kept eigenvector of any basis (two but for an unlucky start, at most five; 0: every
+ * covariance is zero, nothing was solved).  Returns GVQ_ENOCONV if an eigenvector did not converge in five (its growth
+ * in the last solve says so), GVQ_ENONFINITE if an eigenvalue is not finite (e.g. NaN/Inf in a fit gradient),
+ * GVQ_ENOTFIT if no fit was run.
  */
-int gvq_fit_status(const gvq_basis_t* h, int* max_sweeps, void* stream);
+int gvq_fit_status(const gvq_basis_t* h, int* max_solves, void* stream);
 
 /*
  * Eq. (2): comp_out[j][:] = U_b^T (x_j - mu_b / n_workers) for every slice j of `grad`

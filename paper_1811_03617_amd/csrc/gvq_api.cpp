@@ -69,7 +69,7 @@ int gvq_basis_destroy(gvq_basis_t* h)
 {
     if (!h) return GVQ_OK;
     (void)hipDeviceSynchronize();
-    void* dev[] = {h->d_offs, h->d_tile_block, h->d_U, h->d_Upc, h->d_Upd, h->d_Upb, h->d_Uws, h->d_Umu, h->d_mu, h->d_eig, h->d_cov, h->d_eA, h->d_eT, h->d_eZ, h->d_eLU, h->d_part, h->d_mom, h->d_nsamp, h->d_ltile, h->d_Ufc, h->d_Ufd, h->d_ftile, h->d_sweeps, h->d_ksel, h->d_loss_slice, h->d_loss_part};
+    void* dev[] = {h->d_offs, h->d_tile_block, h->d_U, h->d_Upc, h->d_Upd, h->d_Upb, h->d_Uws, h->d_Umu, h->d_mu, h->d_eig, h->d_cov, h->d_eA, h->d_eT, h->d_eZ, h->d_eLU, h->d_part, h->d_mom, h->d_nsamp, h->d_ltile, h->d_Ufc, h->d_Ufd, h->d_ftile, h->d_solves, h->d_ksel, h->d_loss_slice, h->d_loss_part};
     for (void* p : dev)
         if (p) (void)hipFree(p);
     for (gvq_plan& pl : h->plan) {
@@ -160,7 +160,7 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
         TRY(hipMalloc((void**)&h->d_part, sizeof(double) * B * h->mom_part));
         TRY(hipMalloc((void**)&h->d_mom, sizeof(double) * B * W));
         TRY(hipMalloc((void**)&h->d_nsamp, sizeof(unsigned long long) * 2 * B));
-        TRY(hipMalloc((void**)&h->d_sweeps, sizeof(int) * B));
+        TRY(hipMalloc((void**)&h->d_solves, sizeof(int) * B));
         TRY(hipMalloc((void**)&h->d_ksel, sizeof(int) * B));
         TRY(hipMalloc((void**)&h->d_loss_slice, sizeof(float) * (size_t)S));
         h->loss_groups = (int)((longest + 4095) / 4096);
@@ -222,7 +222,7 @@ int gvq_fit_basis_first_slice(gvq_basis_t* h, const void* const* grads, int L, v
     return fit_call(h, grads, L, true, stream);
 }
 
-int gvq_fit_status(const gvq_basis_t* h, int* max_sweeps, void* stream)
+int gvq_fit_status(const gvq_basis_t* h, int* max_solves, void* stream)
 {
     if (!h) return GVQ_EINVAL;
     if (!h->has_cov) return GVQ_ENOTFIT;
@@ -231,21 +231,21 @@ int gvq_fit_status(const gvq_basis_t* h, int* max_sweeps, void* stream)
     int* sw = (int*)malloc(sizeof(int) * B);
     double* eig = (double*)malloc(sizeof(double) * B * h->d);
     if (!sw || !eig) { free(sw); free(eig); return GVQ_ENOMEM; }
-    hipError_t e1 = hipMemcpy(sw, h->d_sweeps, sizeof(int) * B, hipMemcpyDeviceToHost);
+    hipError_t e1 = hipMemcpy(sw, h->d_solves, sizeof(int) * B, hipMemcpyDeviceToHost);
     hipError_t e2 = hipMemcpy(eig, h->d_eig, sizeof(double) * B * h->d, hipMemcpyDeviceToHost);
     int rc = GVQ_OK;
-    if (e1 != hipSuccess) rc = gvq_hip_fail(e1, "hipMemcpy(sweeps)");
+    if (e1 != hipSuccess) rc = gvq_hip_fail(e1, "hipMemcpy(solves)");
     else if (e2 != hipSuccess) rc = gvq_hip_fail(e2, "hipMemcpy(eig)");
     else {
         int mx = 0;
         bool noconv = false, nonfinite = false;
         for (size_t b = 0; b < B; ++b) {
-            if (sw[b] < 0) noconv = true;
+            if (sw[b] >= GVQ_NO_CONVERGENCE) noconv = true;
             else if (sw[b] > mx) mx = sw[b];
         }
         for (size_t i = 0; i < B * h->d; ++i)
             if (!isfinite(eig[i])) nonfinite = true;
-        if (max_sweeps) *max_sweeps = mx;
+        if (max_solves) *max_solves = mx;
         if (nonfinite) rc = GVQ_ENONFINITE;
         else if (noconv) rc = GVQ_ENOCONV;
     }

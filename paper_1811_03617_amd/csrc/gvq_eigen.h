@@ -3,7 +3,7 @@
 #include "gvq_internal.h"
 
 #define EIG_INF_BITS 0x7FF0000000000000ull
-#define EIG_SOLVES 2   // solves per eigenvector, what gvq_fit_status reports
+#define EIG_MOST_SOLVES 5   // most solves for an eigenvector; two do but for a start that hardly has it
 
 struct EigenArgs {
     int n;                      // matrix size
@@ -22,7 +22,7 @@ struct EigenArgs {
     double* lu;                 // n > 128: factors, 5 n 64 doubles per 64 vectors
     int lanes;                  // bisect: lanes per eigenvalue
     int clamp;                  // 1: negative eigenvalues become 0
-    int* sweeps;                // [B]
+    int* solves;                // [B] most solves any vector took, GVQ_NO_CONVERGENCE if one did not converge
 };
 
 // A zero or a not finite matrix: nothing to decompose.

@@ -109,7 +109,7 @@ __device__ __forceinline__ int eig_scale_exp(unsigned long long norm)
 
 // cov = G/n - mu mu^T, mu, and the largest |entry| (as the bits of a positive double: NaN and Inf sort above all).
 __global__ __launch_bounds__(256) void cov_kernel(const double* mom_all, const unsigned long long* nsamp, int d,
-                                                  double* cov_all, float* mu, unsigned long long* norm, int* sweeps)
+                                                  double* cov_all, float* mu, unsigned long long* norm, int* solves)
 {
     const int b = blockIdx.y;
     const size_t W = (size_t)d * d + d;
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(256) void cov_kernel(const double* mom_all, const u
     for (int i = blockIdx.x * 256 + threadIdx.x; i < d; i += gridDim.x * 256)
         mu[(size_t)b * d + i] = ns > 0.0 ? (float)(mom[(size_t)d * d + i] / ns) : 0.0f;
     eig_norm_max(bad != bad ? bad : big, norm + b);
-    if (blockIdx.x == 0 && threadIdx.x == 0) sweeps[b] = EIG_SOLVES;
+    if (blockIdx.x == 0 && threadIdx.x == 0) solves[b] = 0;   // the solver raises it
 }
 
 // ---- tridiagonal ----------------------------------------------------------------------------------------------------
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(256) void bisect_kernel(EigenArgs a)
 // ---- eigenvectors of T ------------------------------------------------------------------------------------------------
 //
 // One lane per vector: LU with partial pivoting of T - s I (s the eigenvalue), then two solves, the first with a random
-// right-hand side of U alone.  A solve multiplies what other eigenvectors contribute by (rounding / gap), so two leave
+// right-hand side of U alone (more, up to EIG_MOST_SOLVES, while a solve does not make the vector grow).  A solve multiplies what other eigenvectors contribute by (rounding / gap), so two leave
 // nothing of any whose eigenvalue can be told apart.  Vectors of eigenvalues that cannot are independent random
 // members of their common space, which the orthonormalisation sorts out.  NV vectors per work-group (one wave); the
 // factors sit in LDS up to n = 128, else in global memory, entry-major so that a step's access is one contiguous run.
@@ -497,6 +497,7 @@ __global__ __launch_bounds__(64) void inverse_kernel(EigenArgs a)
     double* base = IN_LDS ? lu_lds : a.lu + ((size_t)b * gridDim.x + blockIdx.x) * 5 * n * NV;
     const size_t plane = (size_t)n * NV;
     const int j = blockIdx.x * NV + lane;
+    int used = 0;
     if (lane < NV && j < a.k) {
         double* ip = base + lane;        // 1 / pivot
         double* u1 = ip + plane;         // U's first and second superdiagonal
@@ -527,7 +528,7 @@ __global__ __launch_bounds__(64) void inverse_kernel(EigenArgs a)
         // worked through, so that the chain waits for arithmetic only.
         constexpr int K = 8;
         double big = 1.0;
-        for (int solve = 0; solve < EIG_SOLVES; ++solve) {
+        for (int solve = 0; solve < EIG_MOST_SOLVES; ++solve) {
             double y = hash_unit((unsigned int)(n - 1), (unsigned int)j);
             if (solve > 0) {
                 // forward, on the first solution scaled to its largest entry
@@ -588,12 +589,16 @@ __global__ __launch_bounds__(64) void inverse_kernel(EigenArgs a)
 #pragma unroll
                 for (int u = 0; u < K; ++u) { rc[u] = rn[u]; ac[u] = an[u]; bc[u] = bn[u]; zc[u] = zn[u]; }
             }
+            used = solve + 1;
+            // a vector that has converged grows by about 1 / (rounding) in a solve
+            if (solve > 0 && big > 1e9) break;
         }
-        // a converged vector grows by about 1 / (rounding) in the last solve
-        if (!(big > 1e9)) a.sweeps[b] = -1;
+        if (!(big > 1e9)) used = GVQ_NO_CONVERGENCE;
         lm[0] = 1.0 / big;   // this vector's scale, for the copy below
     }
     __syncthreads();
+    for (int o = 32; o > 0; o >>= 1) used = max(used, __shfl_xor(used, o, 64));
+    if (lane == 0) atomicMax(a.solves + b, used);
     for (int v = 0; v < NV; ++v) {
         const int jv = blockIdx.x * NV + v;
         if (jv >= a.k) break;
@@ -754,7 +759,7 @@ __global__ __launch_bounds__(256) void back_kernel(EigenArgs a)
 // U = the k columns of Z as float, each negated if needed so that its largest-magnitude entry (lowest index on ties) is
 // positive; unit vectors for a zero matrix, NaN for one that is not finite.  One wave per column.
 __global__ __launch_bounds__(256) void basis_out_kernel(const double* Z, size_t Z_stride, int k, int d,
-                                                        const unsigned long long* norm, float* U, int* sweeps)
+                                                        const unsigned long long* norm, float* U, int* solves)
 {
     const int b = blockIdx.y, lane = threadIdx.x & 63, c = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (c >= k) return;
@@ -762,7 +767,7 @@ __global__ __launch_bounds__(256) void basis_out_kernel(const double* Z, size_t 
     const unsigned long long nb = norm[b];
     if (eig_skip(nb)) {
         for (int i = lane; i < d; i += 64) U[(size_t)i * k + c] = nb ? __int_as_float(0x7FC00000) : i == c ? 1.f : 0.f;
-        if (c == 0 && lane == 0) sweeps[b] = nb ? -1 : 0;
+        if (c == 0 && lane == 0) solves[b] = nb ? GVQ_NO_CONVERGENCE : 0;
         return;
     }
     const double* z = Z + (size_t)b * Z_stride + (size_t)c * d;
@@ -878,14 +883,14 @@ EigenArgs gvq_eigen_args(const gvq_basis* h)
     a.norm = h->d_nsamp + h->B;
     a.eig = h->d_eig; a.eig_ld = h->d;
     a.Z = h->d_eZ; a.Z_stride = (size_t)h->k * d;
-    a.lu = h->d_eLU; a.lanes = 64; a.clamp = 0; a.sweeps = h->d_sweeps;
+    a.lu = h->d_eLU; a.lanes = 64; a.clamp = 0; a.solves = h->d_solves;
     return a;
 }
 
 int gvq_launch_basis_out(const gvq_basis* h, hipStream_t st)
 {
     hipLaunchKernelGGL(basis_out_kernel, dim3((unsigned)((h->k + 3) / 4), h->B), dim3(256), 0, st, h->d_eZ,
-                       (size_t)h->k * h->d, h->k, h->d, h->d_nsamp + h->B, h->d_U, h->d_sweeps);
+                       (size_t)h->k * h->d, h->k, h->d, h->d_nsamp + h->B, h->d_U, h->d_solves);
     GVQ_HIP(hipGetLastError());
     return GVQ_OK;
 }
@@ -896,7 +901,7 @@ int gvq_launch_eigen(const gvq_basis* h, bool from_moments, hipStream_t st)
         int g = (int)(((int64_t)h->d * h->d + 1023) / 1024);
         if (g > 256) g = 256;
         hipLaunchKernelGGL(cov_kernel, dim3(g, h->B), dim3(256), 0, st, h->d_mom, h->d_nsamp, h->d, h->d_cov, h->d_mu,
-                           h->d_nsamp + h->B, h->d_sweeps);
+                           h->d_nsamp + h->B, h->d_solves);
         GVQ_HIP(hipGetLastError());
     }
     const int rc = gvq_launch_sym_eigen(h, gvq_eigen_args(h), true, st);

@@ -7,6 +7,7 @@
 
 #define GVQ_MAX_PTRS 32  // device pointers passed by value in one kernel launch
 #define GVQ_EIGEN_SMALL 128      // largest matrix one work-group tridiagonalises in its registers
+#define GVQ_NO_CONVERGENCE (1 << 20)   // in place of a number of solves
 #define GVQ_SAMPLE_MAX_L 128     // most samples of a first-slice refresh that keeps them centred in memory
 
 // Many bases: the split of the gradient's 16-slice tiles into super-tiles (G consecutive tiles of
@@ -58,7 +59,7 @@ struct gvq_basis {
     double* d_eT = nullptr;     // [B][5 d] tridiagonal matrix and work vectors
     double* d_eZ = nullptr;     // [B][k][d] eigenvectors
     double* d_eLU = nullptr;    // d > GVQ_EIGEN_SMALL: factors of the inverse iteration
-    int* d_sweeps = nullptr;    // [B] solves per eigenvector (0 = zero matrix), -1 = not converged
+    int* d_solves = nullptr;    // [B] most solves any eigenvector took (0 = zero matrix), or GVQ_NO_CONVERGENCE
     int* d_ksel = nullptr;      // [B] result of the last gvq_select_k
     float* d_loss_slice = nullptr;  // [S] per-slice squared residual of the last gvq_local_loss
     double* d_loss_part = nullptr;  // [B][loss_groups] partial sums of those

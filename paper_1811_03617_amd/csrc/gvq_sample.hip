@@ -30,7 +30,7 @@ struct SampleArgs {
     const double* eig;     // [B][d]
     unsigned long long* nsamp;   // [B] samples, then [B] norms
     int B;
-    int* sweeps;           // [B]
+    int* solves;           // [B]
 };
 
 __device__ __forceinline__ float load_elem(const void* g, bool bf16, int64_t idx)
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256) void centre_kernel(SampleArgs a)
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         a.nsamp[b] = full ? (unsigned long long)a.L : 0ull;
-        a.sweeps[b] = EIG_SOLVES;
+        a.solves[b] = 0;   // the solver raises it
     }
 }
 
@@ -249,7 +249,7 @@ int gvq_launch_fit_samples(const gvq_basis* h, const void* const* grads, int L, 
     a.K = work + L;
     a.V = work + (size_t)(L + 1) * L;
     a.cov = h->d_cov; a.mu = h->d_mu; a.Z = h->d_eZ; a.eig = h->d_eig; a.nsamp = h->d_nsamp; a.B = B;
-    a.sweeps = h->d_sweeps;
+    a.solves = h->d_solves;
     const bool gram = gram_shape(d, L);
     hipLaunchKernelGGL(centre_kernel, dim3((unsigned)((d + 63) / 64), B), dim3(256), 0, st, a);
     GVQ_HIP(hipGetLastError());

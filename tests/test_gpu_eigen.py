@@ -130,3 +130,27 @@ def test_many_small_matrices(d, k, B):
     assert np.max(np.abs(np.swapaxes(U, 1, 2) @ U - np.eye(k))) <= 2 * 2.0 ** -24 + 1e-8
     resid = np.linalg.norm(C @ U - U * eig[:, None, :k], axis=1)
     assert np.all(resid <= (2 * 2.0 ** -24 + 1e-8) * lam)
+
+
+def test_status_reports_what_the_solver_did():
+    """The most solves for any vector: at least two where there was something to solve, none for a zero covariance, whatever
+    the handle's last fit left behind."""
+    d, k = 24, 5
+    rng = np.random.default_rng(5)
+    x = torch.from_numpy(rng.standard_normal(50 * d).astype(np.float32)).to(DEV)
+    bad = x.clone()
+    bad[7] = float("nan")
+    b = gvq.Basis(x.numel(), d, k)
+    for first_slice_only in (False, True):
+        grads = [x, x.roll(11), x.roll(30)]
+        b.fit(grads, first_slice_only=first_slice_only)
+        assert 2 <= b.fit_status() <= 5
+        b.fit([torch.ones_like(x)] * 3, first_slice_only=first_slice_only)
+        assert b.fit_status() == 0
+        b.fit([x, bad, x], first_slice_only=first_slice_only)
+        with pytest.raises(gvq.GvqError) as e:
+            b.fit_status()
+        assert e.value.status == gvq.ENONFINITE
+    b.fit(grads)
+    assert 2 <= b.fit_status() <= 5
+    b.close()

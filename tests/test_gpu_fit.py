@@ -23,16 +23,16 @@ def _fit_both(w, mean_offset=None):
     b = gvq.Basis(w.M, w.d, w.k, offs, w.dtype)
     dev = [g.to(DEV) for g in fit]
     b.fit(dev)
-    sweeps = b.fit_status()
+    solves = b.fit_status()
     U, mu, eig = b.export()
     C, n = b.export_cov()
     b.close()
-    return (Uo, muo, eigo, Co), (U, mu, eig, C, n, sweeps)
+    return (Uo, muo, eigo, Co), (U, mu, eig, C, n, solves)
 
 
 def _check_fit(w, mean_offset=None, angle_rank=None):
-    (Uo, muo, eigo, Co), (U, mu, eig, C, n, sweeps) = _fit_both(w, mean_offset)
-    assert 0 <= sweeps < 40
+    (Uo, muo, eigo, Co), (U, mu, eig, C, n, solves) = _fit_both(w, mean_offset)
+    assert 2 <= solves <= 5
     full = w.M // w.d
     offs = w.block_offsets() or [0, w.S]
     for b in range(len(offs) - 1):
@@ -167,7 +167,7 @@ def test_fit_first_slice_sampling_mode(M, d, k, L, block_elems, dtype):
                                    first_slice_only=True, return_cov=True)
     b = gvq.Basis(M, d, k, offs, dtype)
     b.fit([g.to(DEV) for g in fit], first_slice_only=True)
-    assert 0 <= b.fit_status() < 40
+    assert 2 <= b.fit_status() <= 5
     U, mu, eig = b.export()
     C, n = b.export_cov()
     b.close()
@@ -228,7 +228,7 @@ def test_thousands_of_small_bases():
     Uo, muo, eigo = oracle.fit([synth.to_numpy(g) for g in fit], d, k, offsets=offs)
     b = gvq.Basis(M, d, k, offs)
     b.fit([g.to(DEV) for g in fit])
-    assert 0 <= b.fit_status() < 40
+    assert 2 <= b.fit_status() <= 5
     U, mu, eig = b.export()
     np.testing.assert_allclose(eig, eigo, rtol=0, atol=1e-10 * eigo.max())
     np.testing.assert_allclose(mu, muo, rtol=2e-7, atol=1e-7 * np.abs(muo).max())

@@ -273,8 +273,8 @@ def test_fullsize_fit(name):
     assert len(fit) == L
     b = gvq.Basis(w.M, w.d, w.k, w.block_offsets(), w.dtype)
     b.fit(fit)
-    sweeps = b.fit_status()
-    assert 0 < sweeps < 40
+    solves = b.fit_status()
+    assert 2 <= solves <= 5
     U, mu, eig = b.export()
     C, n = b.export_cov()
     b.close()
@@ -402,7 +402,7 @@ def test_fit_on_more_than_2_to_31_elements(d, k):
     C_ref = (G / full).cpu().numpy() - np.outer(mu_ref, mu_ref)
     b = gvq.Basis(M, d, k)
     b.fit([g])
-    assert b.fit_status() >= 0
+    assert 2 <= b.fit_status() <= 5
     _, mu, eig = b.export()
     C, n = b.export_cov()
     b.close()
