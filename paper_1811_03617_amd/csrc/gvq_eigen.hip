@@ -19,6 +19,8 @@
 // (eigenvalues NaN, reported by gvq_fit_status), which the largest |entry| says (EigenArgs::norm).
 #include "gvq_eigen.h"
 
+#include <type_traits>
+
 // ---- helpers ----------------------------------------------------------------------------------------------------
 
 template <int CTRL> __device__ __forceinline__ double dpp_move(double v)
@@ -528,9 +530,10 @@ __global__ __launch_bounds__(64) void inverse_kernel(EigenArgs a)
         // worked through, so that the chain waits for arithmetic only.
         constexpr int K = 8;
         double big = 1.0;
-        for (int solve = 0; solve < EIG_MOST_SOLVES; ++solve) {
+        auto solve = [&](auto first) {   // a constant: as a number that is looked at in the loops it cost 420 -> 730 us at d = 768
+            constexpr bool FIRST = decltype(first)::value;
             double y = hash_unit((unsigned int)(n - 1), (unsigned int)j);
-            if (solve > 0) {
+            if constexpr (!FIRST) {
                 // forward, on the first solution scaled to its largest entry
                 const double sc = 1.0 / big;
                 double zc[K], lc[K], uc[K], zn[K], ln[K], un[K];
@@ -571,7 +574,7 @@ __global__ __launch_bounds__(64) void inverse_kernel(EigenArgs a)
                     rr[u] = ip[(size_t)at * NV];
                     aa[u] = u1[(size_t)at * NV];
                     bb[u] = at == n - 2 ? 0.0 : u2[(size_t)at * NV];
-                    zz[u] = solve == 0 ? hash_unit((unsigned int)at, (unsigned int)j) : z[(size_t)at * NV];
+                    zz[u] = FIRST ? hash_unit((unsigned int)at, (unsigned int)j) : z[(size_t)at * NV];
                 }
             };
             fetch(n - 2, rc, ac, bc, zc);
@@ -589,10 +592,14 @@ __global__ __launch_bounds__(64) void inverse_kernel(EigenArgs a)
 #pragma unroll
                 for (int u = 0; u < K; ++u) { rc[u] = rn[u]; ac[u] = an[u]; bc[u] = bn[u]; zc[u] = zn[u]; }
             }
-            used = solve + 1;
+        };
+        solve(std::true_type{});
+        used = 1;
+        do {
+            solve(std::false_type{});
+            ++used;
             // a vector that has converged grows by about 1 / (rounding) in a solve
-            if (solve > 0 && big > 1e9) break;
-        }
+        } while (!(big > 1e9) && used < EIG_MOST_SOLVES);
         if (!(big > 1e9)) used = GVQ_NO_CONVERGENCE;
         lm[0] = 1.0 / big;   // this vector's scale, for the copy below
     }

@@ -354,7 +354,7 @@ __global__ __launch_bounds__(1024) void moments_reduce_kernel(const double* part
     using Off = MomShape<NT, true>;
     __shared__ double sub[16][64];
     const int b = blockIdx.z, lane = threadIdx.x & 63, s = threadIdx.x >> 6;
-    const int at = blockIdx.x * 64 + lane, parts = blockDim.x / 64;
+    const int at = blockIdx.x * 64 + lane, parts = blockDim.x > 64 ? 16 : 1;
     int q = blockIdx.y;
     const bool off = q >= np;
     const int width = off ? Off::PART : Diag::PART, chunks = off ? chunks_off : chunks_diag;
@@ -381,7 +381,8 @@ __global__ __launch_bounds__(1024) void moments_reduce_kernel(const double* part
         __syncthreads();
         if (s != 0) return;
         v = 0.0;
-        for (int i = 0; i < parts; ++i) v += sub[i][lane];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v += sub[i][lane];
     }
     if (at >= width) return;
     double* o = mom + (size_t)b * ((size_t)d * d + d);
