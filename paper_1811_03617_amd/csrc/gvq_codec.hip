@@ -307,7 +307,7 @@ __device__ __forceinline__ void compress_fast_phase(const CodecArgs& a, f4* lds,
 // --------------------------------------------------------------------------------------
 // LOSS with one basis (SHARED): both copies of U in registers (128 at D = 128, k = 32) left room for one wave per SIMD,
 // whose matrix pipe stood still while the wave loaded, parked and added up; with the second copy in LDS, read between the
-// products, two fit (138 M elements: 183 -> 166 us, bf16 199 -> 184; the pipe alone needs 113).
+// products, two fit (138 M elements: 183 -> 164 - 169 us, bf16 199 -> 184; the pipe alone needs 113).
 template <int D, int NT, bool BF16, int VAR, bool LOSS, int YS, bool SHARED = false>
 __global__ __launch_bounds__(WG_THREADS, LOSS && !SHARED ? 1 : 2) void compress_mfma_kernel(CodecArgs a)
 {

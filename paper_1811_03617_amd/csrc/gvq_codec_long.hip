@@ -1,8 +1,7 @@
-// Codec kernels for long slices, 128 < d <= GVQ_MAX_D and k <= 128 (GradiVeQ Eqs. 2 and 4 with
-// the slice sizes of Section 3, e.g. d = 768), and for every shorter shape that the
-// register-resident kernels do not take (d not in {16,32,64,128}, or k > 32), as far as neither the basis-stationary
-// kernels (gvq_codec_ws.hip) nor those that move whole slices (gvq_flow.h; gvq_flow_takes_compress, _decompress) do:
-// compress above d = 512 or with U over eight waves, the local loss, more than 128 comps, lengths below 4.  U (d x k floats, up
+// Codec kernels (GradiVeQ Eqs. 2 and 4) for the shapes that neither the register-resident kernels (d in {16,32,64,128},
+// k <= 32), nor the basis-stationary ones (gvq_codec_ws.hip), nor those that move whole slices (gvq_flow.h) take: compress
+// above d = 512, more than 128 comps, lengths below 4, the local loss, and what flow_takes_compress and flow_takes_decompress
+// (gvq_flow_plan.h) leave here because it is faster here.  U (d x k floats, up
 // to 512 KB) does not fit a wave's registers, so these are LDS-tiled contractions on the matrix
 // pipes (first the exact fp32 products on v_mfma_f32_16x16x4_f32, further down the bf16 split):
 //   a work-group of 4 waves owns LW_SLICES = 128 consecutive slices of one basis, 32 per wave

@@ -24,7 +24,7 @@ SHAPES = [
     (72, 40, 5, 5), (200, 24, 3, 3), (8, 16, 2, 2),   # ... and multiples of 8 for bf16
     (16, 8, 16, 16), (72, 3, 16, 24), (64, 5, 12, 12),   # H*W longer than a tile: one depth per tile, H*W in pieces
     # one side in 16-byte words, the other number by number: filters that are no multiple of the word, runs that are none,
-    # both, in tiles of 64 and of 128 filters, with ragged last tiles; H*W in pieces of odd length
+    # both, with ragged last tiles of 64 filters; H*W in pieces of odd length
     (1233, 64, 1, 1), (130, 12, 1, 1), (129, 136, 1, 1), (131, 7, 1, 1), (128, 131, 1, 1), (66, 16, 3, 3), (63, 5, 3, 3),
     (64, 3, 3, 3), (20, 7, 19, 19), (3, 5, 17, 31), (4096, 1, 1, 1), (1001, 1, 1, 1), (1, 2050, 1, 1), (1, 1, 5, 67), (1, 6, 5, 7), (65, 24, 16, 18), (2056, 520, 1, 1),
 ]
