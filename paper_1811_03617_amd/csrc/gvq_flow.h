@@ -4,9 +4,9 @@
 //
 // Bound: memory.  What kept the LDS-tiled kernels (gvq_codec_long.hip) at 1.4 - 3.6 TB/s on these shapes was how they
 // touched it: lanes walked down 16 slices 64 bytes at a time, and a slice length that is no multiple of 4 (three lengths out
-// of four) went number by number.  48 M elements, compress / decompress in us, there -> here: d = 13, k = 3 169 / 188 ->
-// 68 / 82; d = 63, k = 16 124 / 111 -> 46 / 62; d = 100, k = 25 73 / 69 -> 46 / 48 (5.2 TB/s); d = 201, k = 67 131 / 140 ->
-// 59 / 65; bf16 d = 401, k = 60 183 / 90 -> 46 / 45.  Short of memory (bf16 storage, eight waves) it is the chain of a
+// of four) went number by number.  48 M elements, compress / decompress in us, there -> here: d = 13, k = 3 167 / 190 ->
+// 70 / 87; d = 63, k = 16 124 / 112 -> 48 / 59; d = 100, k = 25 74 / 70 -> 46 / 49 (5.2 TB/s); d = 201, k = 67 129 / 140 ->
+// 65 / 67; bf16 d = 401, k = 60 182 / 91 -> 50 / 48.  Short of memory (bf16 storage, eight waves) it is the chain of a
 // tile's phases: words -> LDS, barrier, products, barrier, results.
 //
 // A tile is a run of whole slices, moved in words of four numbers in memory order: global_load_dwordx4 takes any 4-byte
@@ -59,40 +59,45 @@ struct FlowArgs {
 // comes out of a table that the host made: one scalar load, asked for a tile ahead.  (Found by searching the bases' offsets
 // for every tile it cost 10 - 30 % with 24 bases; walking from one basis to the next, which a work-group with few tiles of
 // thousands of short bases does hundreds of times between two of its tiles, a millisecond: 24 M elements in 16216 bases,
-// d = 40, k = 10 968 us, now 88.)
+// d = 40, k = 10 968 us, now 88.)  With one basis none of that is touched: the next tile's number carried along for both
+// kinds, and the products of a tile bounded by its own rows there too, cost decompress up to 4 % (48 M elements, d = 13, k = 3
+// 89.8 -> 87.0 us; d = 24, k = 6 72.7 -> 69.7; d = 127, k = 32 55.3 -> 53.9; d = 201, k = 50 52.9 -> 51.6).
 struct FlowIter {
-    int64_t tile, ahead;   // this tile, the one after it (past the last one: this one again)
-    int pos;               // of `ahead` in its run
-    FlowTile rec, next;    // B > 1: their entries of the table
+    int64_t tile;
+    int pos;               // of `tile` in its run
+    FlowTile rec, next;    // B > 1: the entries of this tile and of the one after it (past the last one: this one's again)
     static __device__ __forceinline__ FlowTile entry(const FlowArgs& a, int64_t i)
     {
         return __builtin_bit_cast(FlowTile, uniform_load((const u4*)(a.tiles + i)));
     }
-    __device__ __forceinline__ void step(const FlowArgs& a)
+    __device__ __forceinline__ void prefetch(const FlowArgs& a)
     {
-        ++ahead;
-        if (++pos == a.run) {
-            pos = 0;
-            ahead += (int64_t)(gridDim.x - 1) * a.run;
-        }
-        if (ahead >= a.t1) ahead = tile;
-        if (a.B > 1) next = entry(a, ahead);
+        int64_t i = tile + 1;
+        if (pos + 1 == a.run) i += (int64_t)(gridDim.x - 1) * a.run;
+        next = entry(a, i < a.t1 ? i : tile);
     }
     __device__ __forceinline__ FlowIter(const FlowArgs& a)
     {
-        tile = ahead = a.t0 + (int64_t)blockIdx.x * a.run;
+        tile = a.t0 + (int64_t)blockIdx.x * a.run;
         pos = 0;
-        if (tile >= a.t1) return;
-        if (a.B > 1) rec = entry(a, tile);
-        step(a);
+        if (a.B > 1 && tile < a.t1) {
+            rec = entry(a, tile);
+            prefetch(a);
+        }
     }
     // To the next tile; false: none is left.
     __device__ __forceinline__ bool advance(const FlowArgs& a)
     {
-        if (ahead == tile) return false;
-        tile = ahead;
-        rec = next;
-        step(a);
+        ++tile;
+        if (++pos == a.run) {
+            pos = 0;
+            tile += (int64_t)(gridDim.x - 1) * a.run;
+        }
+        if (tile >= a.t1) return false;
+        if (a.B > 1) {
+            rec = next;
+            prefetch(a);
+        }
         return true;
     }
     // What of it lies in the requested range.
@@ -328,7 +333,9 @@ __global__ __launch_bounds__(64 * W, 8 / W) void compress_flow_kernel(FlowArgs a
         if (!plain) in.load_rest(a, tn, d, a.M);
         if (!first) store_y(before);
         __syncthreads();
-        for (int g = ws; 16 * g < t.rows; g += WS) {
+        // (short bases leave most of a tile empty)
+        const int groups = a.B > 1 ? (t.rows + 15) / 16 : a.rows / 16;
+        for (int g = ws; g < groups; g += WS) {
             f4 acc[NTW];
 #pragma unroll
             for (int nt = 0; nt < NTW; ++nt) acc[nt] = f4{0.f, 0.f, 0.f, 0.f};
@@ -486,7 +493,8 @@ __global__ __launch_bounds__(64 * W, 8 / W) void decompress_flow_kernel(FlowArgs
         if (!plain) in.load_rest(a, tn, k, a.S * k);
         if (!first) store_x(before);
         __syncthreads();
-        for (int g = ws; 16 * g < t.rows; g += WS) {
+        const int groups = a.B > 1 ? (t.rows + 15) / 16 : a.rows / 16;
+        for (int g = ws; g < groups; g += WS) {
             const char* yr = yh + (16 * g + n_) * RB + 16 * kk;
             f4 acc[ETW];
 #pragma unroll
