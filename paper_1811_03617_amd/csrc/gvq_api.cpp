@@ -69,7 +69,7 @@ int gvq_basis_destroy(gvq_basis_t* h)
 {
     if (!h) return GVQ_OK;
     (void)hipDeviceSynchronize();
-    void* dev[] = {h->d_offs, h->d_tile_block, h->d_U, h->d_Upc, h->d_Upd, h->d_Upb, h->d_Uws, h->d_Umu, h->d_mu, h->d_eig, h->d_cov, h->d_eA, h->d_eT, h->d_eZ, h->d_eLU, h->d_part, h->d_mom, h->d_nsamp, h->d_ltile, h->d_Ufc, h->d_Ufd, h->d_ftile, h->d_solves, h->d_ksel, h->d_loss_slice, h->d_loss_part};
+    void* dev[] = {h->d_offs, h->d_tile_block, h->d_U, h->d_Upc, h->d_Upd, h->d_Upb, h->d_Uws, h->d_Umu, h->d_mu, h->d_eig, h->d_cov, h->d_eA, h->d_eT, h->d_eZ, h->d_eX, h->d_eLU, h->d_part, h->d_mom, h->d_nsamp, h->d_ltile, h->d_Ufc, h->d_Ufd, h->d_ftile, h->d_solves, h->d_ksel, h->d_loss_slice, h->d_loss_part};
     for (void* p : dev)
         if (p) (void)hipFree(p);
     for (gvq_plan& pl : h->plan) {
@@ -156,6 +156,7 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
         TRY(hipMalloc((void**)&h->d_eA, sizeof(double) * B * (d + 1) * d));
         TRY(hipMalloc((void**)&h->d_eT, sizeof(double) * B * 5 * d));
         TRY(hipMalloc((void**)&h->d_eZ, sizeof(double) * B * k * d));
+        if (d > GVQ_EIGEN_SMALL) TRY(hipMalloc((void**)&h->d_eX, sizeof(unsigned long long) * B * 6 * d));
         if (gvq_eigen_lu_doubles(d, k)) TRY(hipMalloc((void**)&h->d_eLU, sizeof(double) * B * gvq_eigen_lu_doubles(d, k)));
         TRY(hipMalloc((void**)&h->d_part, sizeof(double) * B * h->mom_part));
         TRY(hipMalloc((void**)&h->d_mom, sizeof(double) * B * W));

@@ -2012,7 +2012,6 @@ int gvq_launch_local_loss(const gvq_basis* h, const void* grad, int n_workers, d
 #define GVQ_STATIC_PART_DOUBLES 65536
 static __device__ __align__(256) unsigned char scratch[sizeof(float) * GVQ_STATIC_MAX_SLICES +
                                                         sizeof(double) * GVQ_STATIC_PART_DOUBLES];
-#define GVQ_MAX_DEVICES 64
 static void* g_scratch_ptr[GVQ_MAX_DEVICES];
 static std::mutex g_scratch_mutex;
 

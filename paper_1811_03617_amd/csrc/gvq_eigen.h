@@ -19,6 +19,8 @@ struct EigenArgs {
     int eig_ld;
     double* Z;                  // [B][k][n], Z_stride apart: eigenvectors
     size_t Z_stride;
+    unsigned long long* xchg;   // n > 128: [B][3][2 n], xchg_stride apart: what the work-groups of one matrix tell each other
+    size_t xchg_stride;
     double* lu;                 // n > 128: factors, 5 n 64 doubles per 64 vectors
     int lanes;                  // bisect: lanes per eigenvalue
     int clamp;                  // 1: negative eigenvalues become 0

@@ -19,6 +19,7 @@
 // (eigenvalues NaN, reported by gvq_fit_status), which the largest |entry| says (EigenArgs::norm).
 #include "gvq_eigen.h"
 
+#include <mutex>
 #include <type_traits>
 
 // ---- helpers ----------------------------------------------------------------------------------------------------
@@ -235,6 +236,215 @@ __global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
         dot = wave_sum(dot);
         if (lane == 0) p_new[r] = t * dot;
     }
+}
+
+// All of those steps in one launch, where the matrices' rows find a place in the registers of the chip at once (eight rows
+// per work-group and at most one work-group per compute unit, gvq_launch_sym_eigen).  What a step needs from the others are p of
+// the step before and its own column: both are published as plain 64-bit words, and a word that still holds the mark
+// (all bits set, which no arithmetic on finite numbers gives) has not arrived.  Waiting for the words themselves takes one way
+// through memory per step, where a counter takes three (the data, the count, the data again) and the end of a launch about
+// five microseconds: d = 768 6.4 -> 3.6 us a column, the refresh's eigenvalue part 5.7 -> 3.8 ms.
+//
+// Slots: p of step i and row i + 1 go to slot i % 3.  Who has seen all of p of step i - 1 knows that every work-group which
+// still takes part is done with slot (i - 2) % 3; those that will write it in step i + 1 put the mark back in step i, before
+// they publish p of step i, which every later reader of that slot has to see first.  A work-group leaves when its rows are
+// reflected away, so nobody who no longer publishes still reads.  The wait is bounded: a work-group that gives up (never, as
+// long as the grid is resident) reports a solver that did not converge.
+#define TRI_CHAIN_MARK 0xFFFFFFFFFFFFFFFFull
+#define TRI_CHAIN_SPINS (1 << 22)
+
+__global__ __launch_bounds__(256) void tri_chain_clear_kernel(unsigned long long* x, size_t stride, int n)
+{
+    x += (size_t)blockIdx.y * stride;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) x[i] = TRI_CHAIN_MARK;
+}
+
+__device__ __forceinline__ unsigned long long chain_load(const unsigned long long* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void chain_store(unsigned long long* p, unsigned long long v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void chain_publish(unsigned long long* p, double v)
+{
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(v);
+    chain_store(p, bits == TRI_CHAIN_MARK ? 0x7FF8000000000000ull : bits);
+}
+
+template <int NE>
+__global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
+{
+    constexpr int NT = (NE + 3) / 4;
+    __shared__ double cb[NE * 64], wp[NE * 64], red[2][4], pi_s, first_s;
+    __shared__ int lost;
+    const int b = blockIdx.y, n = a.n, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (eig_skip(a.norm[b])) return;
+    const double* src = a.src + (size_t)b * a.src_stride;
+    double* A = a.A + (size_t)b * a.A_stride;
+    double* T = a.T + (size_t)b * 5 * a.t_ld;
+    unsigned long long* X = a.xchg + (size_t)b * a.xchg_stride;   // [3][2 n]: p, row
+    const int r0 = (blockIdx.x * 4 + wave) * 2, r_last = blockIdx.x * 8 + 7;
+    const bool writer = blockIdx.x == gridDim.x - 1;   // takes part to the end: it keeps the reflectors
+
+    double x[2][NE], vl[NE], v[NT], vr[2] = {0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < NE; ++q) {
+        vl[q] = 0.0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int c = 64 * q + lane;
+            x[u][q] = r0 + u < n && c < n ? src[(size_t)(r0 + u) * n + c] : 0.0;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < NT; ++u) v[u] = 0.0;
+    if (tid == 0) lost = 0;
+    __syncthreads();
+
+    double tau = 0.0;   // of the step before
+    bool gone = false;
+    for (int i = 0; i < steps; ++i) {
+        if (r_last <= i) { gone = true; break; }
+        double col[NT], p[NT], s = 0.0;
+        if (i == 0) {
+#pragma unroll
+            for (int u = 0; u < NT; ++u) {
+                const int c = tid + 256 * u;
+                col[u] = c < n ? src[c] : 0.0;
+                p[u] = 0.0;
+            }
+        } else {
+            const unsigned long long* from = X + (size_t)((i - 1) % 3) * 2 * n;
+            unsigned long long pw[NT], rw[NT];
+            int spins = 0;
+            for (;;) {
+                bool missing = false;
+#pragma unroll
+                for (int u = 0; u < NT; ++u) {
+                    const int c = tid + 256 * u;
+                    const bool on = c >= i && c < n;
+                    pw[u] = on ? chain_load(from + c) : 0ull;
+                    rw[u] = on ? chain_load(from + n + c) : 0ull;
+                }
+#pragma unroll
+                for (int u = 0; u < NT; ++u) missing |= pw[u] == TRI_CHAIN_MARK || rw[u] == TRI_CHAIN_MARK;
+                if (!missing) break;
+                if (++spins > TRI_CHAIN_SPINS) { lost = 1; break; }
+            }
+#pragma unroll
+            for (int u = 0; u < NT; ++u) {
+                p[u] = __longlong_as_double((long long)pw[u]);
+                col[u] = __longlong_as_double((long long)rw[u]);
+                s = fma(p[u], v[u], s);
+                if (tid + 256 * u == i) pi_s = p[u];
+            }
+        }
+        s = wave_sum(s);
+        if (lane == 0) red[0][wave] = s;
+        __syncthreads();
+        if (lost) break;   // uniform
+        // slot (i + 1) % 3 takes the mark back: by whoever writes it in step i + 1
+        {
+            unsigned long long* next = X + (size_t)((i + 1) % 3) * 2 * n;
+            if (lane < 2 && r0 + lane >= i + 2 && r0 + lane < n) chain_store(next + r0 + lane, TRI_CHAIN_MARK);
+            if (r0 == i + 2 || r0 + 1 == i + 2) {
+#pragma unroll
+                for (int q = 0; q < NE; ++q)
+                    if (64 * q + lane < n) chain_store(next + n + 64 * q + lane, TRI_CHAIN_MARK);
+            }
+        }
+        s = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
+        const double half = 0.5 * tau * s, wi = i > 0 ? pi_s - half : 0.0;   // v[i] of the previous step is 1
+        double n2 = 0.0;
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+            const int c = tid + 256 * u;
+            const double w = fma(-half, v[u], p[u]);
+            if (i > 0) col[u] -= fma(v[u], wi, w);
+            if (c < NE * 64) {
+                cb[c] = c > i ? col[u] : 0.0;
+                wp[c] = w;
+            }
+            if (c > i + 1) n2 = fma(col[u], col[u], n2);
+            if (c == i + 1) first_s = col[u];
+        }
+        n2 = wave_sum(n2);
+        if (lane == 0) red[1][wave] = n2;
+        __syncthreads();
+        n2 = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+        double beta, t, sc;
+        reflector(first_s, n2, beta, t, sc);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+            const int c = tid + 256 * u;
+            const double h = c == i + 1 ? 1.0 : c > i ? col[u] * sc : 0.0;
+            v[u] = c < n ? h : 0.0;
+        }
+        tau = t;
+
+        // the previous step's update of this wave's rows, and their entries of p
+        double hl[NE], wl[NE];
+#pragma unroll
+        for (int q = 0; q < NE; ++q) {
+            const int c = 64 * q + lane;
+            hl[q] = c == i + 1 ? 1.0 : cb[c] * sc;   // zero up to column i
+            wl[q] = wp[c];
+        }
+        unsigned long long* to = X + (size_t)(i % 3) * 2 * n;
+        double dot[2] = {0.0, 0.0};
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the marks are back before this wave's p says so
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int r = r0 + u;
+            if (r <= i || r >= n) continue;   // uniform over the wave
+            const double wr = wp[r], vo = vr[u];
+            vr[u] = r == i + 1 ? 1.0 : cb[r] * sc;
+#pragma unroll
+            for (int q = 0; q < NE; ++q) {
+                x[u][q] -= fma(vo, wl[q], wr * vl[q]);
+                dot[u] = fma(x[u][q], hl[q], dot[u]);
+            }
+            if (r == i + 1) {
+#pragma unroll
+                for (int q = 0; q < NE; ++q) {
+                    const int c = 64 * q + lane;
+                    if (c > i && c < n) chain_publish(to + n + c, x[u][q]);
+                }
+            }
+        }
+        const double d0 = wave_sum(dot[0]), d1 = wave_sum(dot[1]);
+#pragma unroll
+        for (int q = 0; q < NE; ++q) vl[q] = hl[q];
+        const int r = r0 + (lane & 1);
+        const double pr = t * (lane & 1 ? d1 : d0);
+        if (lane < 2 && r > i && r < n) {
+            chain_publish(to + r, pr);
+            if (i == steps - 1) T[(size_t)(3 + (i & 1)) * a.t_ld + r] = pr;
+        }
+        if (writer) {
+#pragma unroll
+            for (int u = 0; u < NT; ++u) {
+                const int c = tid + 256 * u;
+                if (c > i && c < n) A[(size_t)i * n + c] = v[u];
+                if (c == i) { T[i] = col[u]; T[a.t_ld + i] = beta; T[2 * a.t_ld + i] = t; }
+            }
+        }
+    }
+    if (lost) {
+        if (tid == 0) atomicMax(a.solves + b, GVQ_NO_CONVERGENCE);
+        return;
+    }
+    if (gone) return;
+    // what is left, as tri_step_kernel leaves it: the last step's update pending
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int q = 0; q < NE; ++q) {
+            const int r = r0 + u, c = 64 * q + lane;
+            if (r >= steps && r < n && c >= steps && c < n) A[(size_t)(r + 1) * n + c] = x[u][q];
+        }
 }
 
 // The whole matrix (n <= 128), or what is left of a larger one from row i0 on, in the registers of one work-group:
@@ -813,6 +1023,9 @@ static void by_pieces(int n, Args... args)
 template <int NE> struct go_step {
     static void go(dim3 grid, EigenArgs a, int i, hipStream_t st) { hipLaunchKernelGGL((tri_step_kernel<NE>), grid, dim3(256), 0, st, a, i); }
 };
+template <int NE> struct go_chain {
+    static void go(dim3 grid, EigenArgs a, int steps, hipStream_t st) { hipLaunchKernelGGL((tri_chain_kernel<NE>), grid, dim3(256), 0, st, a, steps); }
+};
 template <int NE> struct go_ortho {
     static void go(double* Z, size_t stride, int k, int n, int B, const unsigned long long* norm, hipStream_t st)
     {
@@ -839,10 +1052,44 @@ int gvq_launch_orthonormalise(const gvq_basis* h, double* Z, size_t Z_stride, in
     return GVQ_OK;
 }
 
+// All columns up to the trailing block in one launch (*done), where every work-group (8 rows) has a compute unit to itself;
+// more matrices than that take turns, and a launch per column serves them all at once.  Work-groups that wait for each other
+// have to be on the chip together, so such launches of one process wait for one another, whatever their streams: two of
+// them, each half resident, would wait for ever.  A stream that is being captured keeps the launches per column: the graph may be
+// replayed beside anything.
+static int launch_chain(const gvq_basis* h, const EigenArgs& a, int steps, hipStream_t st, bool* done)
+{
+    static std::mutex lock;
+    static hipEvent_t last[GVQ_MAX_DEVICES];
+    const int wgs = (a.n + 7) / 8;
+    if ((int64_t)wgs * h->B > h->num_cu || h->device < 0 || h->device >= GVQ_MAX_DEVICES) return GVQ_OK;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return GVQ_OK;
+    }
+    hipLaunchKernelGGL(tri_chain_clear_kernel, dim3((unsigned)((6 * a.n + 255) / 256), h->B), dim3(256), 0, st, a.xchg, a.xchg_stride, 6 * a.n);
+    GVQ_HIP(hipGetLastError());
+    std::lock_guard<std::mutex> guard(lock);
+    hipEvent_t& ev = last[h->device];
+    if (!ev) GVQ_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    else GVQ_HIP(hipStreamWaitEvent(st, ev, 0));
+    by_pieces<go_chain>(a.n, dim3((unsigned)wgs, h->B), a, steps, st);
+    GVQ_HIP(hipGetLastError());
+    GVQ_HIP(hipEventRecord(ev, st));
+    *done = true;
+    return GVQ_OK;
+}
+
 int gvq_launch_sym_eigen(const gvq_basis* h, EigenArgs a, bool ortho, hipStream_t st)
 {
     const int n = a.n, B = h->B, i0 = n > GVQ_EIGEN_SMALL ? n - GVQ_EIGEN_SMALL : 0;
-    for (int i = 0; i < i0; ++i) {
+    bool chain = false;
+    if (i0 > 0) {
+        const int rc = launch_chain(h, a, i0, st, &chain);
+        if (rc != GVQ_OK) return rc;
+    }
+    for (int i = 0; i < i0 && !chain; ++i) {
         by_pieces<go_step>(n, dim3((unsigned)((n - 1 - i + 7) / 8), B), a, i, st);
         GVQ_HIP(hipGetLastError());
     }
@@ -890,6 +1137,7 @@ EigenArgs gvq_eigen_args(const gvq_basis* h)
     a.norm = h->d_nsamp + h->B;
     a.eig = h->d_eig; a.eig_ld = h->d;
     a.Z = h->d_eZ; a.Z_stride = (size_t)h->k * d;
+    a.xchg = h->d_eX; a.xchg_stride = 6 * d;
     a.lu = h->d_eLU; a.lanes = 64; a.clamp = 0; a.solves = h->d_solves;
     return a;
 }

@@ -9,6 +9,7 @@
 #define GVQ_EIGEN_SMALL 128      // largest matrix one work-group tridiagonalises in its registers
 #define GVQ_NO_CONVERGENCE (1 << 20)   // in place of a number of solves
 #define GVQ_SAMPLE_MAX_L 128     // most samples of a first-slice refresh that keeps them centred in memory
+#define GVQ_MAX_DEVICES 64       // devices a per-device table of this process has room for
 
 // Many bases: the split of the gradient's 16-slice tiles into super-tiles (G consecutive tiles of
 // whole slices of one basis, for the branch-free fast phase of the register-resident codec kernels)
@@ -58,6 +59,7 @@ struct gvq_basis {
     double* d_eA = nullptr;     // eigensolver: [B][(d+1) d] matrix, then its reflectors (first-slice refresh: samples too)
     double* d_eT = nullptr;     // [B][5 d] tridiagonal matrix and work vectors
     double* d_eZ = nullptr;     // [B][k][d] eigenvectors
+    unsigned long long* d_eX = nullptr;   // d > GVQ_EIGEN_SMALL: [B][6 d] exchange between the work-groups of one matrix
     double* d_eLU = nullptr;    // d > GVQ_EIGEN_SMALL: factors of the inverse iteration
     int* d_solves = nullptr;    // [B] most solves any eigenvector took (0 = zero matrix), or GVQ_NO_CONVERGENCE
     int* d_ksel = nullptr;      // [B] result of the last gvq_select_k

@@ -154,3 +154,67 @@ def test_status_reports_what_the_solver_did():
     b.fit(grads)
     assert 2 <= b.fit_status() <= 5
     b.close()
+
+
+@pytest.mark.parametrize("d,k,B", [(136, 9, 2), (137, 9, 14), (137, 9, 15), (300, 40, 6), (300, 40, 7), (1024, 5, 2), (1024, 5, 3)])
+def test_matrices_that_share_the_chip(d, k, B):
+    """Bases side by side on both sides of where their rows no longer fit the compute units together (256 groups of 8 rows)."""
+    rng = np.random.default_rng(d * B)
+    per = 2 * d + 11
+    x = (rng.standard_normal((B * per, d // 8)) @ rng.standard_normal((d // 8, d))
+         + 0.1 * rng.standard_normal((B * per, d))) * np.exp(rng.uniform(-6, 6, B)).repeat(per)[:, None]
+    if B > 2:
+        x[per:2 * per] = 0.25
+    b = gvq.Basis(x.size, d, k, np.arange(B + 1) * per, "f32")
+    g = torch.from_numpy(x.astype(np.float32).reshape(-1)).to(DEV)
+    for _ in range(2):   # also what the fit before left behind
+        b.fit([g])
+        assert b.fit_status() > 0
+    U, _, eig = b.export()
+    C, _ = b.export_cov()
+    b.close()
+    for i in range(B):
+        if B > 2 and i == 1:
+            assert not eig[i].any() and np.array_equal(U[i], np.eye(d, k))
+        else:
+            _check(U[i].astype(np.float64), eig[i], C[i], k)
+
+
+def test_refreshes_on_several_streams_and_captured():
+    """Handles refreshed on streams of their own at the same time give the bits of one after the other; a captured refresh
+    gives them up to rounding, at every replay."""
+    n, d, k = 4, 520, 24
+    rng = np.random.default_rng(3)
+    xs = [torch.from_numpy((rng.standard_normal((900, 40)) @ rng.standard_normal((40, d))
+                            + 0.1 * rng.standard_normal((900, d))).astype(np.float32).reshape(-1)).to(DEV) for _ in range(n)]
+    bases = [gvq.Basis(900 * d, d, k) for _ in range(n)]
+    alone = []
+    for b, x in zip(bases, xs):
+        b.fit([x])
+        b.fit_status()
+        alone.append(b.export())
+    streams = [torch.cuda.Stream() for _ in range(n)]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for b, x, s in zip(bases, xs, streams):
+            b.fit([x], stream=s.cuda_stream)
+    torch.cuda.synchronize()
+    for b, want in zip(bases, alone):
+        for got, w in zip(b.export(), want):
+            assert np.array_equal(got, w)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=streams[0]):
+        bases[0].fit([xs[0]], stream=streams[0].cuda_stream)
+    for _ in range(3):
+        bases[0].fit([xs[1]])
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert bases[0].fit_status() > 0
+        U, _, eig = bases[0].export()
+        C, _ = bases[0].export_cov()
+        _check(U[0].astype(np.float64), eig[0], C[0], k)
+        # two backward stable solvers: a few d roundings of the largest eigenvalue apart
+        assert np.max(np.abs(eig - alone[0][2])) <= 2e-15 * (d + 10) * eig[0, 0]
+    for b in bases:
+        b.close()
