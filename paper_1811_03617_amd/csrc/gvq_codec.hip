@@ -1430,6 +1430,10 @@ int gvq_launch_pack(const gvq_basis* h, hipStream_t st)
     hipLaunchKernelGGL(pack_basis_kernel, dim3(h->B), dim3(256), 0, st, h->d_U, h->d_Upc, h->d_Upd,
                        h->d, h->k, h->k <= 16 ? 1 : 2);
     GVQ_HIP(hipGetLastError());
+    if (gvq_loss_split_shape(h)) {
+        const int rc = gvq_launch_pack_loss(h, st);
+        if (rc != GVQ_OK) return rc;
+    }
     if (gvq_bf16_pipe_shape(h)) {
         hipLaunchKernelGGL(pack_basis_bf16_kernel, dim3(h->B), dim3(256), 0, st, h->d_U, h->d_mu, h->d_Upb,
                            h->d_Umu, h->d, h->k, h->k <= 16 ? 1 : 2);
@@ -1969,6 +1973,15 @@ static int launch_local_loss(const gvq_basis* h, const void* grad, int n_workers
     a.Upack2 = (const f4*)h->d_Upd;
     const bool bf = h->dtype == GVQ_BF16;
     int rc = GVQ_OK;
+    if (gvq_loss_split_shape(h)) {
+        int parts = 0;
+        double* part = (double*)loss_slice;
+        rc = gvq_launch_loss_split(h, grad, n_workers, part, &parts, st);
+        if (rc != GVQ_OK) return rc;
+        hipLaunchKernelGGL(loss_reduce2_kernel, dim3(1), dim3(256), 0, st, part, parts, loss_out);
+        GVQ_HIP(hipGetLastError());
+        return GVQ_OK;
+    }
     if (gvq_long_shape(h->d, h->k) && h->k <= 128) {
         rc = gvq_launch_loss_long(h, grad, n_workers, loss_slice, st);
     } else if (gvq_mfma_shape(h->d, h->k)) {

@@ -21,6 +21,8 @@ struct EigenArgs {
     size_t Z_stride;
     unsigned long long* xchg;   // n > 128: [B][3][2 n], xchg_stride apart: what the work-groups of one matrix tell each other
     size_t xchg_stride;
+    double* wy;                 // n > 128: [B][(n - 2) / 32 rounded up][32][32], wy_stride apart: T of each block of reflectors
+    size_t wy_stride;
     double* lu;                 // n > 128: factors, 5 n 64 doubles per 64 vectors
     int lanes;                  // bisect: lanes per eigenvalue
     int clamp;                  // 1: negative eigenvalues become 0

@@ -98,6 +98,8 @@ __device__ __forceinline__ void reflector(double x0, double n2, double& beta, do
     }
 }
 
+typedef double d4 __attribute__((ext_vector_type(4)));
+
 #define EIG_E_FLOOR 1e-20     // smallest off-diagonal entry of T relative to the matrix: decoupled blocks stay coupled
                               // by far less than rounding, which spares every recurrence its special cases
 #define EIG_PIVOT 2.3e-16     // smallest pivot relative to the matrix
@@ -924,8 +926,8 @@ __global__ __launch_bounds__(512) void orthonormalise_kernel(double* Z, size_t Z
 // ---- back ---------------------------------------------------------------------------------------------------------------
 //
 // z <- H_0 H_1 ... H_{n-3} z, one wave per vector held in registers.  A step is a dot product and an update of a few numbers
-// per lane, far less than the time its reflector takes to arrive, so PF of them are in flight (d = 768, k = 96: 526 us with
-// one in flight, 376 with four; d = 128 55 and 29).
+// per lane, far less than the time its reflector takes to arrive, so PF of them are in flight (d = 128 55 us with one in
+// flight, 29 with four).  Up to 128 rows.
 template <int NE>
 __global__ __launch_bounds__(256) void back_kernel(EigenArgs a)
 {
@@ -971,6 +973,160 @@ __global__ __launch_bounds__(256) void back_kernel(EigenArgs a)
         if (64 * e + lane < n) Z[64 * e + lane] = z[e];
 }
 
+// More than 128 rows: the same reflectors 32 at a time, H_i .. H_{i+31} = I - V^T T V (rows of V: the reflectors, T upper triangular).
+// One at a time a vector goes through n dependent steps, each a sum over a wave, and every wave reads every reflector
+// (d = 768, k = 96: 374 us, 490 ns a step; a compute unit's four waves fetched 24 KB each step).  Here the chain is n / 32 steps, and
+// the four waves of a vector fetch eight reflectors of a block each, once, into registers that serve both products.
+// d = 768, k = 96: 374 -> 91 us and 22 for T; at 128 rows and below 28 + 13 against 30 us, and thousands of small matrices lose a tenth.
+#define WY_ROWS 32
+
+// T of every block, and zeros where V has none (a reflector's row holds old entries up to its column; all of it if tau is 0).
+// T(0..j-1, j) = -tau_j T(0..j-1, 0..j-1) G(0..j-1, j), G = V V^T: products on the fp64 matrix pipe, a quarter of the columns per wave.
+__global__ __launch_bounds__(256) void wy_kernel(EigenArgs a)
+{
+    __shared__ double part[4][3][256], G[WY_ROWS][WY_ROWS + 1];
+    const int b = blockIdx.y, n = a.n, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = lane & 15, kk = lane >> 4;
+    if (eig_skip(a.norm[b])) return;
+    double* A = a.A + (size_t)b * a.A_stride;
+    const double* tau = a.T + (size_t)b * 5 * a.t_ld + 2 * a.t_ld;
+    double* out = a.wy + (size_t)b * a.wy_stride + (size_t)blockIdx.x * WY_ROWS * WY_ROWS;
+    const int nref = n - 2, i0 = WY_ROWS * blockIdx.x;
+    for (int r = wave; r < WY_ROWS && i0 + r < nref; r += 4) {
+        const int i = i0 + r, end = tau[i] == 0.0 ? n : i + 1;
+        for (int c = lane; c < end; c += 64) A[(size_t)i * n + c] = 0.0;
+    }
+    __syncthreads();   // also orders the stores above before the loads below: one work-group, one compute unit
+    d4 g[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) g[t] = d4{0.0, 0.0, 0.0, 0.0};
+    // columns 16 at a time from the block's first; the order of a contraction is free, so a lane takes four that are neighbours
+    const double* row0 = A + (size_t)(i0 + m < nref ? i0 + m : nref - 1) * n;
+    const double* row1 = A + (size_t)(i0 + 16 + m < nref ? i0 + 16 + m : nref - 1) * n;
+    for (int c0 = i0 / 16 * 16 + 16 * wave; c0 < n; c0 += 64) {
+        double x0[4], x1[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int c = c0 + 4 * kk + u, at = c < n ? c : n - 1;
+            x0[u] = row0[at];
+            x1[u] = row1[at];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool in = c0 + 4 * kk + u < n;
+            x0[u] = in && i0 + m < nref ? x0[u] : 0.0;
+            x1[u] = in && i0 + 16 + m < nref ? x1[u] : 0.0;
+            g[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0[u], x0[u], g[0], 0, 0, 0);
+            g[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(x0[u], x1[u], g[1], 0, 0, 0);
+            g[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(x1[u], x1[u], g[2], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[wave][t][(4 * r + kk) * 16 + m] = g[t][r];
+    __syncthreads();
+    for (int e = tid; e < 3 * 256; e += 256) {
+        const int t = e >> 8, r = (e >> 4) & 15, c = e & 15;
+        G[r + (t == 2 ? 16 : 0)][c + (t == 0 ? 0 : 16)] =
+            (part[0][t][e & 255] + part[1][t][e & 255]) + (part[2][t][e & 255] + part[3][t][e & 255]);
+    }
+    __syncthreads();
+    if (tid >= WY_ROWS) return;
+    double row[WY_ROWS];   // row tid of T: each depends on itself and G alone
+#pragma unroll
+    for (int j = 0; j < WY_ROWS; ++j) {
+        const double t = i0 + j < nref ? tau[i0 + j] : 0.0;
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < j; ++q) s = fma(row[q], G[q][j], s);
+        row[j] = tid == j ? t : tid < j ? -t * s : 0.0;
+        out[tid * WY_ROWS + j] = row[j];
+    }
+}
+
+template <int NE>
+__global__ __launch_bounds__(256) void back_wy_kernel(EigenArgs a)
+{
+    constexpr int RW = WY_ROWS / 4;   // reflectors of a block per wave
+    __shared__ double part[4][NE * 64], ws[WY_ROWS];
+    const int b = blockIdx.y, n = a.n, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (eig_skip(a.norm[b])) return;
+    const double* R = a.A + (size_t)b * a.A_stride;   // reflector i is row i
+    const double* TW = a.wy + (size_t)b * a.wy_stride;
+    double* Z = a.Z + (size_t)b * a.Z_stride + (size_t)blockIdx.x * n;
+    const int nref = n - 2, blocks = (nref + WY_ROWS - 1) / WY_ROWS;
+    double z[NE], v[RW][NE], t[4];
+    int at[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+        const int c = 64 * e + lane;
+        at[e] = c < n ? c : n - 1;   // past the row: its last entry, which meets zeros of z
+        z[e] = c < n ? Z[c] : 0.0;
+    }
+    auto fetch = [&](int blk) {
+        const int i0 = WY_ROWS * blk;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) t[u] = TW[(size_t)blk * WY_ROWS * WY_ROWS + (RW * wave + (lane >> 3)) * WY_ROWS + 4 * (lane & 7) + u];
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            const int i = i0 + RW * wave + r;
+            const double* row = R + (size_t)(i < nref ? i : nref - 1) * n;   // past the last: meets zeros of T
+#pragma unroll
+            for (int e = 0; e < NE; ++e) v[r][e] = 64 * e + 63 > i0 ? row[at[e]] : 0.0;   // uniform: nothing up to column i0
+        }
+    };
+    fetch(blocks - 1);
+    for (int blk = blocks - 1; blk >= 0; --blk) {
+        double d8[RW];
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            d8[r] = 0.0;
+#pragma unroll
+            for (int e = 0; e < NE; ++e) d8[r] = fma(v[r][e], z[e], d8[r]);
+        }
+        // eight sums over the 64 lanes: each exchange halves the sums a lane holds
+        double s4[4], s2[2], d1;
+        const bool o1 = lane & 1, o2 = lane & 2, o4 = lane & 4;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s4[r] = (o1 ? d8[r + 4] : d8[r]) + dpp_move<DPP_XOR1>(o1 ? d8[r] : d8[r + 4]);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) s2[r] = (o2 ? s4[r + 2] : s4[r]) + dpp_move<DPP_XOR2>(o2 ? s4[r] : s4[r + 2]);
+        d1 = (o4 ? s2[1] : s2[0]) + __shfl_xor(o4 ? s2[0] : s2[1], 4, 64);
+        d1 += dpp_move<DPP_ROR8>(d1);
+        d1 += __shfl_xor(d1, 16, 64);
+        d1 += __shfl_xor(d1, 32, 64);
+        if (lane < RW) ws[RW * wave + 4 * (lane & 1) + 2 * ((lane >> 1) & 1) + (lane >> 2)] = d1;
+        __syncthreads();
+        double y = 0.0;   // T w, eight lanes a row
+#pragma unroll
+        for (int u = 0; u < 4; ++u) y = fma(t[u], ws[4 * (lane & 7) + u], y);
+        y += dpp_move<DPP_XOR1>(y);
+        y += dpp_move<DPP_XOR2>(y);
+        y += dpp_move<DPP_HALF_MIRROR>(y);
+        double f[RW];
+#pragma unroll
+        for (int r = 0; r < RW; ++r) f[r] = lane_value(y, 8 * r);
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            double s = 0.0;
+#pragma unroll
+            for (int r = 0; r < RW; ++r) s = fma(v[r][e], f[r], s);
+            part[wave][64 * e + lane] = s;
+        }
+        fetch(blk > 0 ? blk - 1 : 0);
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const int c = 64 * e + lane;
+            const double s = (part[0][c] + part[1][c]) + (part[2][c] + part[3][c]);
+            z[e] = c < n ? z[e] - s : 0.0;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+        if (e % 4 == wave && 64 * e + lane < n) Z[64 * e + lane] = z[e];
+}
+
 // ---- out ----------------------------------------------------------------------------------------------------------------
 //
 // U = the k columns of Z as float, each negated if needed so that its largest-magnitude entry (lowest index on ties) is
@@ -1011,14 +1167,19 @@ size_t gvq_eigen_lu_doubles(int d, int k)   // per basis
 }
 
 template <template <int> class F, typename... Args>
+static void by_long_pieces(int n, Args... args)   // n > 128
+{
+    if (n <= 256) F<4>::go(args...);
+    else if (n <= 512) F<8>::go(args...);
+    else if (n <= 768) F<12>::go(args...);
+    else F<16>::go(args...);
+}
+template <template <int> class F, typename... Args>
 static void by_pieces(int n, Args... args)
 {
     if (n <= 64) F<1>::go(args...);
     else if (n <= 128) F<2>::go(args...);
-    else if (n <= 256) F<4>::go(args...);
-    else if (n <= 512) F<8>::go(args...);
-    else if (n <= 768) F<12>::go(args...);
-    else F<16>::go(args...);
+    else by_long_pieces<F>(n, args...);
 }
 template <int NE> struct go_step {
     static void go(dim3 grid, EigenArgs a, int i, hipStream_t st) { hipLaunchKernelGGL((tri_step_kernel<NE>), grid, dim3(256), 0, st, a, i); }
@@ -1041,8 +1202,8 @@ template <int NE> struct go_ortho {
         }
     }
 };
-template <int NE> struct go_back {
-    static void go(dim3 grid, EigenArgs a, hipStream_t st) { hipLaunchKernelGGL((back_kernel<NE>), grid, dim3(256), 0, st, a); }
+template <int NE> struct go_back_wy {
+    static void go(dim3 grid, EigenArgs a, hipStream_t st) { hipLaunchKernelGGL((back_wy_kernel<NE>), grid, dim3(256), 0, st, a); }
 };
 
 int gvq_launch_orthonormalise(const gvq_basis* h, double* Z, size_t Z_stride, int k, int n, hipStream_t st)
@@ -1074,7 +1235,7 @@ static int launch_chain(const gvq_basis* h, const EigenArgs& a, int steps, hipSt
     hipEvent_t& ev = last[h->device];
     if (!ev) GVQ_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
     else GVQ_HIP(hipStreamWaitEvent(st, ev, 0));
-    by_pieces<go_chain>(a.n, dim3((unsigned)wgs, h->B), a, steps, st);
+    by_long_pieces<go_chain>(a.n, dim3((unsigned)wgs, h->B), a, steps, st);
     GVQ_HIP(hipGetLastError());
     GVQ_HIP(hipEventRecord(ev, st));
     *done = true;
@@ -1090,7 +1251,7 @@ int gvq_launch_sym_eigen(const gvq_basis* h, EigenArgs a, bool ortho, hipStream_
         if (rc != GVQ_OK) return rc;
     }
     for (int i = 0; i < i0 && !chain; ++i) {
-        by_pieces<go_step>(n, dim3((unsigned)((n - 1 - i + 7) / 8), B), a, i, st);
+        by_long_pieces<go_step>(n, dim3((unsigned)((n - 1 - i + 7) / 8), B), a, i, st);
         GVQ_HIP(hipGetLastError());
     }
     if (n - i0 <= 32) hipLaunchKernelGGL((tri_small_kernel<8>), dim3(B), dim3(64), 0, st, a, i0);
@@ -1119,8 +1280,15 @@ int gvq_launch_sym_eigen(const gvq_basis* h, EigenArgs a, bool ortho, hipStream_
         const int rc = gvq_launch_orthonormalise(h, a.Z, a.Z_stride, a.k, n, st);
         if (rc != GVQ_OK) return rc;
     }
-    if (n > 2) {
-        by_pieces<go_back>(n, dim3((unsigned)((a.k + 3) / 4), B), a, st);
+    if (n > GVQ_EIGEN_SMALL) {
+        hipLaunchKernelGGL(wy_kernel, dim3((unsigned)((n - 2 + WY_ROWS - 1) / WY_ROWS), B), dim3(256), 0, st, a);
+        GVQ_HIP(hipGetLastError());
+        by_long_pieces<go_back_wy>(n, dim3((unsigned)a.k, B), a, st);
+        GVQ_HIP(hipGetLastError());
+    } else if (n > 2) {
+        const dim3 grid((unsigned)((a.k + 3) / 4), B);
+        if (n <= 64) hipLaunchKernelGGL((back_kernel<1>), grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((back_kernel<2>), grid, dim3(256), 0, st, a);
         GVQ_HIP(hipGetLastError());
     }
     return GVQ_OK;
@@ -1137,6 +1305,7 @@ EigenArgs gvq_eigen_args(const gvq_basis* h)
     a.norm = h->d_nsamp + h->B;
     a.eig = h->d_eig; a.eig_ld = h->d;
     a.Z = h->d_eZ; a.Z_stride = (size_t)h->k * d;
+    a.wy = h->d_mom; a.wy_stride = d * d + d;   // the covariance is made: the moments are not needed any more
     a.xchg = h->d_eX; a.xchg_stride = 6 * d;
     a.lu = h->d_eLU; a.lanes = 64; a.clamp = 0; a.solves = h->d_solves;
     return a;

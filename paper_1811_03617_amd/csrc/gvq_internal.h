@@ -43,6 +43,7 @@ struct gvq_basis {
     unsigned short* d_Uws = nullptr;  // basis-stationary compress kernel (gvq_ws_shape): two-term bf16 copy of U in its
                                       // operand order, per wave
     float* d_Umu = nullptr;     // [B][KP] U^T mu (bf16 gradients)
+    unsigned short* d_Uls = nullptr;  // gvq_monitor.hip: three-term bf16 copies of U for the two products of Eq. 6
     void* d_Ufc = nullptr;      // gvq_flow.h: packed U of its compress kernel (null: no call goes there)
     void* d_Ufd = nullptr;      // ... and of its decompress kernel
     int flow_rows_c = 0, flow_rows_d = 0;   // slices per tile of the two
@@ -63,7 +64,7 @@ struct gvq_basis {
     double* d_eLU = nullptr;    // d > GVQ_EIGEN_SMALL: factors of the inverse iteration
     int* d_solves = nullptr;    // [B] most solves any eigenvector took (0 = zero matrix), or GVQ_NO_CONVERGENCE
     int* d_ksel = nullptr;      // [B] result of the last gvq_select_k
-    float* d_loss_slice = nullptr;  // [S] per-slice squared residual of the last gvq_local_loss
+    float* d_loss_slice = nullptr;  // [S] per-slice squared residual of the last gvq_local_loss (gvq_monitor.hip: its sums)
     double* d_loss_part = nullptr;  // [B][loss_groups] partial sums of those
     int loss_groups = 1;
     int fit_L = 0;              // gradients of the last fit
@@ -125,6 +126,12 @@ int gvq_launch_local_loss(const gvq_basis* h, const void* grad, int n_workers, d
                           hipStream_t st);
 int gvq_launch_local_loss_static(const gvq_basis* h, const void* grad, int n_workers, double* loss_out,
                                  hipStream_t st);
+// Eq. 6 on the bf16 matrix pipe (gvq_monitor.hip): one sum per work-group into part [GVQ_LOSS_MAX_PARTS], *parts of them.
+#define GVQ_LOSS_MAX_PARTS 1024
+bool gvq_loss_split_shape(const gvq_basis* h);
+size_t gvq_loss_split_pack_halves(int d);
+int gvq_launch_pack_loss(const gvq_basis* h, hipStream_t st);
+int gvq_launch_loss_split(const gvq_basis* h, const void* grad, int n_workers, double* part, int* parts, hipStream_t st);
 int gvq_launch_layout(const void* src, void* dst, int F, int D, int HW, gvq_dtype_t dtype, bool flatten,
                       hipStream_t st);
 int gvq_launch_select_k(const gvq_basis* h, double lambda, hipStream_t st);
