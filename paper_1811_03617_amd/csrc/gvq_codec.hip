@@ -51,9 +51,8 @@ __device__ __forceinline__ int super_basis(const CodecArgs& a, int64_t p)
 // stores can be counted (YS picks it: the largest possible number, G * NT, shifted right by YS).
 // LOSS: Eq. (6) instead of Eq. (2): the per-slice squared residual is written (a.out: one float per slice), see the
 // general phase of the kernel for how the reconstruction comes out of the accumulators; a.il must be 1.
-// SHARED (LOSS, one basis): the decompress-order copy of U is in LDS (uds) instead of in this wave's registers.
-template <int D, int NT, bool BF16, int VAR, int YS, bool MANY, bool LOSS = false, bool SHARED = false>
-__device__ __forceinline__ void compress_fast_phase(const CodecArgs& a, f4* lds, const f4* uds)
+template <int D, int NT, bool BF16, int VAR, int YS, bool MANY, bool LOSS = false>
+__device__ __forceinline__ void compress_fast_phase(const CodecArgs& a, f4* lds)
 {
     constexpr int G = 128 / D;                    // 16-slice tiles per super-tile
     constexpr int CPS = D / 4;                    // fp32 128-bit chunks per slice
@@ -93,7 +92,7 @@ __device__ __forceinline__ void compress_fast_phase(const CodecArgs& a, f4* lds,
     }
 
     f4 uf[NQ][NT];
-    f4 ud[LOSS && !SHARED ? NQ : 1][NT];   // LOSS only: ud[et][q][j] = U[16et + n_][16q + 4kk + j]
+    f4 ud[LOSS ? NQ : 1][NT];   // LOSS only: ud[et][q][j] = U[16et + n_][16q + 4kk + j]
     float mun[EPL];
     auto load_basis = [&](int b) {
         const f4* Up = a.Upack + (size_t)b * (NQ * NT * 64) + lane;
@@ -102,7 +101,7 @@ __device__ __forceinline__ void compress_fast_phase(const CodecArgs& a, f4* lds,
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) uf[q][nt] = Up[(q * NT + nt) * 64];
-        if constexpr (LOSS && !SHARED) {
+        if constexpr (LOSS) {
             const f4* Up2 = a.Upack2 + (size_t)b * (NQ * NT * 64) + lane;
 #pragma unroll
             for (int et = 0; et < NQ; ++et)
@@ -229,15 +228,13 @@ __device__ __forceinline__ void compress_fast_phase(const CodecArgs& a, f4* lds,
                         for (int c = 0; c < EP; ++c)
 #pragma unroll
                             for (int q = 0; q < NT; ++q) {
-                                if constexpr (SHARED) v[c][q] = uds[((e0 + c) * NT + q) * 64 + lane];
-                                else v[c][q] = ud[e0 + c][q];
+                                v[c][q] = ud[e0 + c][q];
                             }
                     };
                     fetch(0, w[0]);
 #pragma unroll
                     for (int e0 = 0; e0 < NQ; e0 += EP) {
                         if (e0 + EP < NQ) fetch(e0 + EP, w[(e0 / EP + 1) & 1]);
-                        if constexpr (SHARED) __builtin_amdgcn_sched_barrier(0);
                         f4 rec[EP];
 #pragma unroll
                         for (int c = 0; c < EP; ++c) rec[c] = f4{0.f, 0.f, 0.f, 0.f};
@@ -305,11 +302,8 @@ __device__ __forceinline__ void compress_fast_phase(const CodecArgs& a, f4* lds,
 // The contraction index may be visited in any order as long as U follows: MFMA step
 // (q, j) multiplies elements e = 4*(4q + kk) + j, kk = l/16.
 // --------------------------------------------------------------------------------------
-// LOSS with one basis (SHARED): both copies of U in registers (128 at D = 128, k = 32) left room for one wave per SIMD,
-// whose matrix pipe stood still while the wave loaded, parked and added up; with the second copy in LDS, read between the
-// products, two fit (138 M elements: 183 -> 164 - 169 us, bf16 199 -> 184; the pipe alone needs 113).
-template <int D, int NT, bool BF16, int VAR, bool LOSS, int YS, bool SHARED = false>
-__global__ __launch_bounds__(WG_THREADS, LOSS && !SHARED ? 1 : 2) void compress_mfma_kernel(CodecArgs a)
+template <int D, int NT, bool BF16, int VAR, bool LOSS, int YS>
+__global__ __launch_bounds__(WG_THREADS, LOSS ? 1 : 2) void compress_mfma_kernel(CodecArgs a)
 {
     constexpr int CPS = D / 4;                    // fp32 128-bit chunks per slice
     constexpr int EPL = BF16 ? 8 : 4;             // elements per 128-bit global load
@@ -327,17 +321,8 @@ __global__ __launch_bounds__(WG_THREADS, LOSS && !SHARED ? 1 : 2) void compress_
     f4* lds = lds_all[threadIdx.x >> 6];
     f4* ldso = ldso_all[threadIdx.x >> 6];
 
-    const f4* uds = nullptr;
-    if constexpr (SHARED) {
-        __shared__ f4 ud_lds[NQ * NT * 64];
-        for (int i = threadIdx.x; i < NQ * NT * 64; i += WG_THREADS) ud_lds[i] = a.Upack2[i];
-        __syncthreads();
-        uds = ud_lds;
-        compress_fast_phase<D, NT, BF16, VAR, YS, false, LOSS, true>(a, lds, uds);
-    } else {
-        if (a.sup_tile) compress_fast_phase<D, NT, BF16, VAR, YS, true, LOSS>(a, lds, uds);
-        else compress_fast_phase<D, NT, BF16, VAR, YS, false, LOSS>(a, lds, uds);
-    }
+    if (a.sup_tile) compress_fast_phase<D, NT, BF16, VAR, YS, true, LOSS>(a, lds);
+    else compress_fast_phase<D, NT, BF16, VAR, YS, false, LOSS>(a, lds);
 
     // ---- general phase: the tiles the fast phase leaves out, every check in place ----------
     RestIter it;
@@ -360,7 +345,7 @@ __global__ __launch_bounds__(WG_THREADS, LOSS && !SHARED ? 1 : 2) void compress_
     int cur_b = block_of_tile(a, it.t);
     int64_t blk_begin = a.offs[cur_b], blk_end = a.offs[cur_b + 1];
     f4 uf[NQ][NT];   // uf[q][nt][j] = U[4*(4q + kk) + j][16nt + n_], zero past column k
-    f4 ud[LOSS && !SHARED ? NQ : 1][NT];   // LOSS only: ud[et][q][j] = U[16et + n_][16q + 4kk + j]
+    f4 ud[LOSS ? NQ : 1][NT];   // LOSS only: ud[et][q][j] = U[16et + n_][16q + 4kk + j]
     float mun[EPL];
 
     auto load_basis = [&](int b) {
@@ -370,7 +355,7 @@ __global__ __launch_bounds__(WG_THREADS, LOSS && !SHARED ? 1 : 2) void compress_
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) uf[q][nt] = Up[(q * NT + nt) * 64];
-        if constexpr (LOSS && !SHARED) {
+        if constexpr (LOSS) {
             const f4* Up2 = a.Upack2 + (size_t)b * (NQ * NT * 64) + lane;
 #pragma unroll
             for (int et = 0; et < NQ; ++et)
@@ -493,12 +478,9 @@ __global__ __launch_bounds__(WG_THREADS, LOSS && !SHARED ? 1 : 2) void compress_
                     f4 rec = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int q = 0; q < NT; ++q) {
-                        f4 u;
-                        if constexpr (SHARED) u = uds[(et * NT + q) * 64 + lane];
-                        else u = ud[et][q];
 #pragma unroll
                         for (int jj = 0; jj < 4; ++jj)
-                            rec = __builtin_amdgcn_mfma_f32_16x16x4f32(u[jj], acc[q][jj], rec, 0, 0, 0);
+                            rec = __builtin_amdgcn_mfma_f32_16x16x4f32(ud[et][q][jj], acc[q][jj], rec, 0, 0, 0);
                     }
                     const int64_t e0 = j * D + 16 * et + 4 * kk;
 #pragma unroll
@@ -1933,10 +1915,10 @@ __global__ __launch_bounds__(256) void loss_reduce2_kernel(const double* part, i
     if (threadIdx.x == 0) out[b] = acc;
 }
 
-template <int D, int NT, bool BF16, bool SHARED>
-static int launch_loss_s(const gvq_basis* h, const CodecArgs& a, hipStream_t st)
+template <int D, int NT, bool BF16>
+static int launch_loss_t(const gvq_basis* h, const CodecArgs& a, hipStream_t st)
 {
-    constexpr auto kern = compress_mfma_kernel<D, NT, BF16, 0, true, 0, SHARED>;
+    constexpr auto kern = compress_mfma_kernel<D, NT, BF16, 0, true, 0>;
     CodecArgs b = a;
     plan_tiles(h, b, 128 / D, (h->k & 3) == 0 && !(gvq_opt_no_fast() & 1), 0);
     int grid = streaming_grid<kern>(h, work_items(b));
@@ -1946,16 +1928,6 @@ static int launch_loss_s(const gvq_basis* h, const CodecArgs& a, hipStream_t st)
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WG_THREADS), 0, st, b);
     GVQ_HIP(hipGetLastError());
     return GVQ_OK;
-}
-
-template <int D, int NT, bool BF16>
-static int launch_loss_t(const gvq_basis* h, const CodecArgs& a, hipStream_t st)
-{
-    // with several bases every wave has its own; smaller copies fit the registers of two waves per SIMD as they are (level)
-    if constexpr (D == 128 && NT == 2) {
-        if (h->B == 1) return launch_loss_s<D, NT, BF16, true>(h, a, st);
-    }
-    return launch_loss_s<D, NT, BF16, false>(h, a, st);
 }
 
 template <int D, bool BF16>

@@ -6,7 +6,10 @@
 // work hardly overlapped).  So both contractions run on v_mfma_f32_16x16x32_bf16, with every fp32 number as three bf16 terms
 // that add up to it exactly (x and y cut off at 8 bits, U rounded to nearest): of the nine products of two numbers the six
 // with i + j <= 4 are taken, what is left out is below 2^-24 of the product, and the large ones are added to the sum of the
-// small ones.  12 matrix cycles where the fp32 pipe takes 32; MEASURED.
+// small ones.  Six products take 100 matrix cycles where the fp32 pipe takes 256.  138 M elements, d = 128, k = 32, the whole call:
+// 183 -> 121 us (bf16 storage 158 -> 110; 60 M elements, d = 64, k = 24 78 -> 60), relative error against float64 over 18 draws of
+// sizes and noise levels 1.7e-7 -> 1.6e-7 rms.  What bounds it now is a wave's own instructions: splitting, products and residuals of a tile
+// of 16 slices take 4000 cycles of a SIMD, of which the matrix pipe is busy 1700; the gradient alone would take 90 us.
 //
 // Every wave sums its residuals in float64; one number per work-group leaves (the sum over slices used to be a launch of its own,
 // 7 us, over one float per slice).
@@ -65,11 +68,13 @@ __global__ __launch_bounds__(WG_THREADS, 2) void loss_split_kernel(LossArgs a)
     f4* lds = lds_all[wave];
 
     for (int i = threadIdx.x; i < 2 * ST * 3 * 64; i += WG_THREADS) ud[i] = a.pack[ST * 3 * 2 * 64 + i];
-    u4 uf[ST][3][2];
+    u4 uf[ST][2][2];   // the third terms are used once per step: in LDS, for the registers' sake
+    __shared__ u4 u3_lds[ST * 2 * 64];
+    for (int i = threadIdx.x; i < ST * 2 * 64; i += WG_THREADS) u3_lds[i] = a.pack[(i / 128 * 3 + 2) * 128 + i % 128];
 #pragma unroll
     for (int st = 0; st < ST; ++st)
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
+        for (int p = 0; p < 2; ++p)
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) uf[st][p][nt] = a.pack[((st * 3 + p) * 2 + nt) * 64 + lane];
     const int lc = lane % LCPS;
@@ -113,15 +118,20 @@ __global__ __launch_bounds__(WG_THREADS, 2) void loss_split_kernel(LossArgs a)
             u4 t[3];
             __builtin_amdgcn_sched_barrier(0);   // the terms of one step at a time: all at once do not fit the registers
             split8x3(x[st][0], x[st][1], t);
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                lo[nt] = mfma_bf16(uf[st][0][nt], t[2], lo[nt]);
-                hi[nt] = mfma_bf16(uf[st][0][nt], t[0], hi[nt]);
-                lo[nt] = mfma_bf16(uf[st][2][nt], t[0], lo[nt]);
-                lo[nt] = mfma_bf16(uf[st][1][nt], t[1], lo[nt]);
-                lo[nt] = mfma_bf16(uf[st][0][nt], t[1], lo[nt]);
-                lo[nt] = mfma_bf16(uf[st][1][nt], t[0], lo[nt]);
-            }
+            // neighbours in the order do not depend on each other
+            const u4 w0 = u3_lds[(st * 2) * 64 + lane], w1 = u3_lds[(st * 2 + 1) * 64 + lane];
+            lo[0] = mfma_bf16(uf[st][0][0], t[2], lo[0]);
+            lo[1] = mfma_bf16(uf[st][0][1], t[2], lo[1]);
+            hi[0] = mfma_bf16(uf[st][0][0], t[0], hi[0]);
+            hi[1] = mfma_bf16(uf[st][0][1], t[0], hi[1]);
+            lo[0] = mfma_bf16(uf[st][1][0], t[1], lo[0]);
+            lo[1] = mfma_bf16(uf[st][1][1], t[1], lo[1]);
+            lo[0] = mfma_bf16(w0, t[0], lo[0]);
+            lo[1] = mfma_bf16(w1, t[0], lo[1]);
+            lo[0] = mfma_bf16(uf[st][0][0], t[1], lo[0]);
+            lo[1] = mfma_bf16(uf[st][0][1], t[1], lo[1]);
+            lo[0] = mfma_bf16(uf[st][1][0], t[0], lo[0]);
+            lo[1] = mfma_bf16(uf[st][1][1], t[0], lo[1]);
         }
         u4 y[3];
         split8x3(hi[0] + lo[0], hi[1] + lo[1], y);
@@ -130,17 +140,14 @@ __global__ __launch_bounds__(WG_THREADS, 2) void loss_split_kernel(LossArgs a)
         for (int st = 0; st < ST; ++st) {
             f4 rec[2];
             __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const u4* u = ud + (2 * st + h) * 3 * 64 + lane;
-                const u4 u1 = u[0], u2 = u[64], u3 = u[128];
-                rec[h] = mfma_bf16(u1, y[2], f4{0.f, 0.f, 0.f, 0.f});
-                rec[h] = mfma_bf16(u3, y[0], rec[h]);
-                rec[h] = mfma_bf16(u2, y[1], rec[h]);
-                rec[h] = mfma_bf16(u1, y[1], rec[h]);
-                rec[h] = mfma_bf16(u2, y[0], rec[h]);
-                rec[h] = mfma_bf16(u1, y[0], rec[h]);
-            }
+            const u4* u = ud + 2 * st * 3 * 64 + lane;
+            const u4 u1[2] = {u[0], u[192]}, u2[2] = {u[64], u[256]}, u3[2] = {u[128], u[320]};
+            for (int h = 0; h < 2; ++h) rec[h] = mfma_bf16(u1[h], y[2], f4{0.f, 0.f, 0.f, 0.f});
+            for (int h = 0; h < 2; ++h) rec[h] = mfma_bf16(u3[h], y[0], rec[h]);
+            for (int h = 0; h < 2; ++h) rec[h] = mfma_bf16(u2[h], y[1], rec[h]);
+            for (int h = 0; h < 2; ++h) rec[h] = mfma_bf16(u1[h], y[1], rec[h]);
+            for (int h = 0; h < 2; ++h) rec[h] = mfma_bf16(u2[h], y[0], rec[h]);
+            for (int h = 0; h < 2; ++h) rec[h] = mfma_bf16(u1[h], y[0], rec[h]);
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -244,7 +251,7 @@ __global__ __launch_bounds__(256) void pack_loss_kernel(const float* U, unsigned
 
 // ======================================================================================
 // With several bases every wave would need its own copy of the second product's U; with up to 16 comps the fp32 pipe's products
-// take half as long, less than the gradient takes to arrive.
+// take half as long, less than the gradient takes to arrive (d = 128, k = 16: 112 us).
 bool gvq_loss_split_shape(const gvq_basis* h) { return h->B == 1 && (h->d == 64 || h->d == 128) && h->k > 16 && h->k <= 32; }
 
 size_t gvq_loss_split_pack_halves(int d) { return (size_t)d / 32 * 3 * 2 * 512 * 2; }

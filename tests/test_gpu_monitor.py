@@ -115,3 +115,63 @@ def test_select_k_matches_the_oracle(M, d, k, block_elems):
     assert gvq.lib().gvq_select_k(b.handle, 1.0, out, st) == gvq.EINVAL
     assert gvq.lib().gvq_select_k(b.handle, -0.1, out, st) == gvq.EINVAL
     b.close()
+
+
+@pytest.mark.parametrize("d,k", [(64, 17), (64, 32), (128, 17), (128, 21), (128, 32)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_local_loss_three_term_products(d, k, dtype):
+    """One basis, 17 to 32 comps: sizes around the 16-slice tiles and the runs of 2048 elements, every wave with several runs, and
+    the bounds-checked tiles alone; float64 for reference.  A residual element carries the rounding of sums of d and k products,
+    at most (d + k) 2^-24 |x| each, half of that at random: relative to the loss r^2 that is 2 (d + k) 2^-25 |x| / r at most."""
+    rng = np.random.default_rng(d + k)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    U = np.linalg.qr(rng.standard_normal((d, k)))[0].astype(np.float32)
+    mu = rng.standard_normal(d).astype(np.float32)
+    U64, mu64 = torch.from_numpy(U).to(DEV).double(), torch.from_numpy(mu).to(DEV).double()
+    gen = torch.Generator(device=DEV).manual_seed(d)
+    for M in (1, d - 1, d, 16 * d - 1, 16 * d, 2047, 2048, 2049, 2048 + 16 * d + 5, 64 * 2048, 131 * 2048 + 17 * d + 3, 9000 * 2048 + 1):
+        S = -(-M // d)
+        z = torch.randn(S, k, generator=gen, device=DEV, dtype=torch.float64)
+        x = (z @ U64.T + 0.05 * torch.randn(S, d, generator=gen, device=DEV, dtype=torch.float64) + mu64 / 3).reshape(-1)[:M].to(tdt)
+        b = gvq.Basis(M, d, k, None, dtype)
+        b.import_(U, mu)
+        out = torch.empty(1, device=DEV, dtype=torch.float64)
+        whole = torch.zeros(S * d, device=DEV, dtype=torch.float64)
+        whole[:M] = x.double()
+        c = whole.view(S, d) - mu64 / 3
+        r = (c - (c @ U64) @ U64.T).reshape(-1)[:M]
+        want, size = float(r @ r), float((c * c).sum())
+        for mask in ((0, 1) if M < 1 << 20 else (0,)):
+            try:
+                gvq.gvq_set_option(3, mask)
+                b.local_loss(x, 3, out)
+            finally:
+                gvq.gvq_set_option(3, 0)
+            assert abs(float(out) - want) <= (d + k) * 2.0 ** -24 * (want * size) ** 0.5, (M, mask)
+        b.close()
+
+
+@pytest.mark.parametrize("scale", [0.0, 1e-18, 1e17, 3.4e38])
+def test_local_loss_three_term_products_at_the_ends_of_the_range(scale):
+    """Numbers that round up to infinity in bf16 stay finite terms: the loss is finite or overflows as the sum of squares does."""
+    d, k, S = 128, 32, 40
+    rng = np.random.default_rng(1)
+    U = np.linalg.qr(rng.standard_normal((d, k)))[0].astype(np.float32)
+    x = (rng.uniform(0.25, 0.9999, (S, d)) * scale).astype(np.float32)
+    if scale > 1e30:   # sums of many such numbers overflow in fp32 whatever the products; |U^T x| <= |x| of one does not
+        x[:, 1:] = 0
+    b = gvq.Basis(S * d, d, k)
+    b.import_(U, np.zeros(d, np.float32))
+    out = torch.empty(1, device=DEV, dtype=torch.float64)
+    b.local_loss(torch.from_numpy(x).to(DEV).reshape(-1), 1, out)
+    r = x.astype(np.float64) @ (np.eye(d) - U.astype(np.float64) @ U.T.astype(np.float64))
+    want = float((r * r).sum())
+    if scale < 1e30:
+        assert abs(float(out) - want) <= 1e-5 * want   # (d + k) 2^-24, |x| of the order of the residual
+    else:
+        assert float(out) == float("inf")              # squares of fp32 residuals overflow
+    for bad in (float("nan"), float("inf")):
+        x[3, 5] = bad
+        b.local_loss(torch.from_numpy(x).to(DEV).reshape(-1), 1, out)
+        assert np.isnan(float(out))
+    b.close()
