@@ -156,7 +156,7 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
         TRY(hipMalloc((void**)&h->d_eA, sizeof(double) * B * (d + 1) * d));
         TRY(hipMalloc((void**)&h->d_eT, sizeof(double) * B * 5 * d));
         TRY(hipMalloc((void**)&h->d_eZ, sizeof(double) * B * k * d));
-        if (d > GVQ_EIGEN_SMALL) TRY(hipMalloc((void**)&h->d_eX, sizeof(unsigned long long) * B * 6 * d));
+        if (d > GVQ_EIGEN_SMALL) TRY(hipMalloc((void**)&h->d_eX, sizeof(unsigned long long) * B * 8 * d));
         if (gvq_eigen_lu_doubles(d, k)) TRY(hipMalloc((void**)&h->d_eLU, sizeof(double) * B * gvq_eigen_lu_doubles(d, k)));
         TRY(hipMalloc((void**)&h->d_part, sizeof(double) * B * h->mom_part));
         TRY(hipMalloc((void**)&h->d_mom, sizeof(double) * B * W));

@@ -245,11 +245,12 @@ __global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
 // the step before and its own column: both are published as plain 64-bit words, and a word that still holds the mark
 // (all bits set, which no arithmetic on finite numbers gives) has not arrived.  Waiting for the words themselves takes one way
 // through memory per step, where a counter takes three (the data, the count, the data again) and the end of a launch about
-// five microseconds: d = 768 6.4 -> 3.6 us a column, the refresh's eigenvalue part 5.7 -> 3.8 ms.
+// five microseconds: d = 768 6.4 -> 3.0 us a column, 4.2 -> 1.94 ms for all of them.
 //
-// Slots: p of step i and row i + 1 go to slot i % 3.  Who has seen all of p of step i - 1 knows that every work-group which
-// still takes part is done with slot (i - 2) % 3; those that will write it in step i + 1 put the mark back in step i, before
-// they publish p of step i, which every later reader of that slot has to see first.  A work-group leaves when its rows are
+// Slots: p of step i and row i + 1 go to slot i % 4.  Who has seen all of p of step i - 1 knows that every work-group which
+// still takes part is done with slot (i - 2) % 4; those that will write it in step i + 2 put the mark back at the end of step i,
+// and wait for that before they publish p of step i + 1, which every later reader of that slot has to see first.  (With three slots
+// the mark goes back within the step, and a step waited for it: 3.6 against 3.0 us.)  A work-group leaves when its rows are
 // reflected away, so nobody who no longer publishes still reads.  The wait is bounded: a work-group that gives up (never, as
 // long as the grid is resident) reports a solver that did not converge.
 #define TRI_CHAIN_MARK 0xFFFFFFFFFFFFFFFFull
@@ -286,7 +287,7 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
     const double* src = a.src + (size_t)b * a.src_stride;
     double* A = a.A + (size_t)b * a.A_stride;
     double* T = a.T + (size_t)b * 5 * a.t_ld;
-    unsigned long long* X = a.xchg + (size_t)b * a.xchg_stride;   // [3][2 n]: p, row
+    unsigned long long* X = a.xchg + (size_t)b * a.xchg_stride;   // [4][2 n]: p, row
     const int r0 = (blockIdx.x * 4 + wave) * 2, r_last = blockIdx.x * 8 + 7;
     const bool writer = blockIdx.x == gridDim.x - 1;   // takes part to the end: it keeps the reflectors
 
@@ -318,7 +319,7 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
                 p[u] = 0.0;
             }
         } else {
-            const unsigned long long* from = X + (size_t)((i - 1) % 3) * 2 * n;
+            const unsigned long long* from = X + (size_t)((i - 1) % 4) * 2 * n;
             unsigned long long pw[NT], rw[NT];
             int spins = 0;
             for (;;) {
@@ -347,16 +348,6 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
         if (lane == 0) red[0][wave] = s;
         __syncthreads();
         if (lost) break;   // uniform
-        // slot (i + 1) % 3 takes the mark back: by whoever writes it in step i + 1
-        {
-            unsigned long long* next = X + (size_t)((i + 1) % 3) * 2 * n;
-            if (lane < 2 && r0 + lane >= i + 2 && r0 + lane < n) chain_store(next + r0 + lane, TRI_CHAIN_MARK);
-            if (r0 == i + 2 || r0 + 1 == i + 2) {
-#pragma unroll
-                for (int q = 0; q < NE; ++q)
-                    if (64 * q + lane < n) chain_store(next + n + 64 * q + lane, TRI_CHAIN_MARK);
-            }
-        }
         s = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
         const double half = 0.5 * tau * s, wi = i > 0 ? pi_s - half : 0.0;   // v[i] of the previous step is 1
         double n2 = 0.0;
@@ -394,9 +385,9 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
             hl[q] = c == i + 1 ? 1.0 : cb[c] * sc;   // zero up to column i
             wl[q] = wp[c];
         }
-        unsigned long long* to = X + (size_t)(i % 3) * 2 * n;
+        unsigned long long* to = X + (size_t)(i % 4) * 2 * n;
         double dot[2] = {0.0, 0.0};
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the marks are back before this wave's p says so
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the marks of the step before are back before this wave's p says so
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int r = r0 + u;
@@ -425,6 +416,16 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
             chain_publish(to + r, pr);
             if (i == steps - 1) T[(size_t)(3 + (i & 1)) * a.t_ld + r] = pr;
         }
+        // slot (i + 2) % 4 takes the mark back: by whoever writes it in step i + 2
+        {
+            unsigned long long* next = X + (size_t)((i + 2) % 4) * 2 * n;
+            if (lane < 2 && r0 + lane >= i + 3 && r0 + lane < n) chain_store(next + r0 + lane, TRI_CHAIN_MARK);
+            if (r0 == i + 3 || r0 + 1 == i + 3) {
+#pragma unroll
+                for (int q = 0; q < NE; ++q)
+                    if (64 * q + lane < n) chain_store(next + n + 64 * q + lane, TRI_CHAIN_MARK);
+            }
+        }
         if (writer) {
 #pragma unroll
             for (int u = 0; u < NT; ++u) {
@@ -450,14 +451,16 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
 }
 
 // The whole matrix (n <= 128), or what is left of a larger one from row i0 on, in the registers of one work-group:
-// thread (ti, tj) holds the 4 x 4 entries of rows 4 ti.. and columns 4 tj...  Per step: the column goes through LDS
+// thread (ti, tj) holds the R x R entries of rows R ti.. and columns R tj...  Per step: the column goes through LDS
 // (one barrier), every wave forms the reflector for itself, multiplies its tiles with it, sums over tj inside the wave,
-// the entries of p go through LDS (second barrier), update.  About 1000 cycles a step; the matrix never leaves the
+// the entries of p go through LDS (second barrier), update.  About 4500 cycles a step, most of it the
+// instructions that every wave repeats and the two passes through LDS; hence R = 8 and one wave per SIMD above 64 rows (16 waves
+// of 4 x 4: d = 128 270 -> 245 us, 1000 bases 2450 -> 1960 for the whole refresh).  The matrix never leaves the
 // registers (in LDS, 128 x 128 doubles would take 1000 cycles to read once).
-template <int TJ>
+template <int TJ, int R>
 __global__ __launch_bounds__(TJ * TJ) void tri_small_kernel(EigenArgs a, int i0)
 {
-    constexpr int N = 4 * TJ, PL = N > 64 ? N / 64 : 1;   // entries of a vector per lane
+    constexpr int N = R * TJ, PL = N > 64 ? N / 64 : 1;   // entries of a vector per lane
     __shared__ double colb[2][N], pb[N];
     const int b = blockIdx.x, n = a.n, nl = n - i0, tid = threadIdx.x, lane = tid & 63;
     const int ti = tid / TJ, tj = tid % TJ;
@@ -466,12 +469,12 @@ __global__ __launch_bounds__(TJ * TJ) void tri_small_kernel(EigenArgs a, int i0)
     const double* cur = i0 == 0 ? a.src + (size_t)b * a.src_stride : A + n;
     double* T = a.T + (size_t)b * 5 * a.t_ld;
 
-    double x[4][4];
+    double x[R][R];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int gr = i0 + 4 * ti + r, gc = i0 + 4 * tj + c;
+        for (int c = 0; c < R; ++c) {
+            const int gr = i0 + R * ti + r, gc = i0 + R * tj + c;
             x[r][c] = gr < n && gc < n ? cur[(size_t)gr * n + gc] : 0.0;
         }
     if (i0 > 0) {
@@ -482,32 +485,32 @@ __global__ __launch_bounds__(TJ * TJ) void tri_small_kernel(EigenArgs a, int i0)
         double s = 0.0;
         for (int c = i0 + lane; c < n; c += 64) s = fma(p_old[c], v_old[c], s);
         const double half = 0.5 * tau * wave_sum(s);
-        double vr[4], wr[4], vc[4], wc[4];
+        double vr[R], wr[R], vc[R], wc[R];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int r = i0 + 4 * ti + u, c = i0 + 4 * tj + u;
+        for (int u = 0; u < R; ++u) {
+            const int r = i0 + R * ti + u, c = i0 + R * tj + u;
             vr[u] = r < n ? v_old[r] : 0.0;
             wr[u] = r < n ? fma(-half, vr[u], p_old[r]) : 0.0;
             vc[u] = c < n ? v_old[c] : 0.0;
             wc[u] = c < n ? fma(-half, vc[u], p_old[c]) : 0.0;
         }
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) x[r][c] -= fma(vr[r], wc[c], wr[r] * vc[c]);
+            for (int c = 0; c < R; ++c) x[r][c] -= fma(vr[r], wc[c], wr[r] * vc[c]);
     }
 
     __builtin_amdgcn_s_waitcnt(0);   // the reflectors overwrite rows of the matrix: every thread's loads have come back
     __syncthreads();
-    for (int ib = 0; ib < nl; ib += 4) {
+    for (int ib = 0; ib < nl; ib += R) {
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
+        for (int cb = 0; cb < R; ++cb) {
             const int i = ib + cb;
             if (i >= nl) break;
             double* col = colb[cb & 1];
-            if (tj == ib / 4) {
+            if (tj == ib / R) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) col[4 * ti + r] = x[r][cb];
+                for (int r = 0; r < R; ++r) col[R * ti + r] = x[r][cb];
             }
             __syncthreads();
             // nothing to reflect in the last two columns
@@ -543,34 +546,40 @@ __global__ __launch_bounds__(TJ * TJ) void tri_small_kernel(EigenArgs a, int i0)
                 }
             }
             if (t == 0.0) continue;   // uniform over the work-group; the next column takes the other buffer
-            double vr[4], vc[4], y[4];
+            double vr[R], vc[R], y[R];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int r = 4 * ti + u, c = 4 * tj + u;
+            for (int u = 0; u < R; ++u) {
+                const int r = R * ti + u, c = R * tj + u;
                 vr[u] = r == i + 1 ? 1.0 : r > i ? col[r] * sc : 0.0;
                 vc[u] = c == i + 1 ? 1.0 : c > i ? col[c] * sc : 0.0;
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int r = 0; r < R; ++r) {
                 y[r] = x[r][0] * vc[0];
 #pragma unroll
-                for (int c = 1; c < 4; ++c) y[r] = fma(x[r][c], vc[c], y[r]);
+                for (int c = 1; c < R; ++c) y[r] = fma(x[r][c], vc[c], y[r]);
             }
-            // sum over tj; lane bit 0 keeps rows 0,1 or 2,3, bit 1 one of the two
+            // sum over tj: every exchange with a neighbour halves the rows a lane keeps
             {
                 const bool o1 = lane & 1, o2 = lane & 2;
-                const double s0 = o1 ? y[0] : y[2], s1 = o1 ? y[1] : y[3];
-                const double k0 = (o1 ? y[2] : y[0]) + dpp_move<DPP_XOR1>(s0);
-                const double k1 = (o1 ? y[3] : y[1]) + dpp_move<DPP_XOR1>(s1);
-                double z = (o2 ? k1 : k0) + dpp_move<DPP_XOR2>(o2 ? k0 : k1);
-                if (TJ >= 16) {
-                    z += dpp_move<DPP_ROR4>(z);
-                    z += dpp_move<DPP_ROR8>(z);
-                    if (TJ == 32) z += __shfl_xor(z, 16, 64);
-                } else {
-                    z += __shfl_xor(z, 4, 64);
+                double h[R / 2], z[R / 4];
+#pragma unroll
+                for (int q = 0; q < R / 2; ++q)
+                    h[q] = (o1 ? y[q + R / 2] : y[q]) + dpp_move<DPP_XOR1>(o1 ? y[q] : y[q + R / 2]);
+#pragma unroll
+                for (int q = 0; q < R / 4; ++q) {
+                    z[q] = (o2 ? h[q + R / 4] : h[q]) + dpp_move<DPP_XOR2>(o2 ? h[q] : h[q + R / 4]);
+                    if (TJ >= 16) {
+                        z[q] += dpp_move<DPP_ROR4>(z[q]);
+                        z[q] += dpp_move<DPP_ROR8>(z[q]);
+                    } else {
+                        z[q] += __shfl_xor(z[q], 4, 64);
+                    }
                 }
-                if (tj < 4) pb[4 * ti + 2 * (lane & 1) + ((lane >> 1) & 1)] = t * z;
+                if (tj < 4) {
+#pragma unroll
+                    for (int q = 0; q < R / 4; ++q) pb[R * ti + R / 2 * (lane & 1) + R / 4 * ((lane >> 1) & 1) + q] = t * z[q];
+                }
             }
             __syncthreads();
             double s = 0.0;
@@ -581,16 +590,16 @@ __global__ __launch_bounds__(TJ * TJ) void tri_small_kernel(EigenArgs a, int i0)
                 if (c < N) s = fma(pb[c], v, s);
             }
             const double half = 0.5 * t * wave_sum(s);
-            double wr[4], wc[4];
+            double wr[R], wc[R];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                wr[u] = fma(-half, vr[u], pb[4 * ti + u]);
-                wc[u] = fma(-half, vc[u], pb[4 * tj + u]);
+            for (int u = 0; u < R; ++u) {
+                wr[u] = fma(-half, vr[u], pb[R * ti + u]);
+                wc[u] = fma(-half, vc[u], pb[R * tj + u]);
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
+            for (int r = 0; r < R; ++r)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) x[r][c] = fma(-vr[r], wc[c], fma(-wr[r], vc[c], x[r][c]));
+                for (int c = 0; c < R; ++c) x[r][c] = fma(-vr[r], wc[c], fma(-wr[r], vc[c], x[r][c]));
         }
     }
 }
@@ -1229,7 +1238,7 @@ static int launch_chain(const gvq_basis* h, const EigenArgs& a, int steps, hipSt
         (void)hipGetLastError();
         return GVQ_OK;
     }
-    hipLaunchKernelGGL(tri_chain_clear_kernel, dim3((unsigned)((6 * a.n + 255) / 256), h->B), dim3(256), 0, st, a.xchg, a.xchg_stride, 6 * a.n);
+    hipLaunchKernelGGL(tri_chain_clear_kernel, dim3((unsigned)((8 * a.n + 255) / 256), h->B), dim3(256), 0, st, a.xchg, a.xchg_stride, 8 * a.n);
     GVQ_HIP(hipGetLastError());
     std::lock_guard<std::mutex> guard(lock);
     hipEvent_t& ev = last[h->device];
@@ -1254,9 +1263,9 @@ int gvq_launch_sym_eigen(const gvq_basis* h, EigenArgs a, bool ortho, hipStream_
         by_long_pieces<go_step>(n, dim3((unsigned)((n - 1 - i + 7) / 8), B), a, i, st);
         GVQ_HIP(hipGetLastError());
     }
-    if (n - i0 <= 32) hipLaunchKernelGGL((tri_small_kernel<8>), dim3(B), dim3(64), 0, st, a, i0);
-    else if (n - i0 <= 64) hipLaunchKernelGGL((tri_small_kernel<16>), dim3(B), dim3(256), 0, st, a, i0);
-    else hipLaunchKernelGGL((tri_small_kernel<32>), dim3(B), dim3(1024), 0, st, a, i0);
+    if (n - i0 <= 32) hipLaunchKernelGGL((tri_small_kernel<8, 4>), dim3(B), dim3(64), 0, st, a, i0);
+    else if (n - i0 <= 64) hipLaunchKernelGGL((tri_small_kernel<16, 4>), dim3(B), dim3(256), 0, st, a, i0);
+    else hipLaunchKernelGGL((tri_small_kernel<16, 8>), dim3(B), dim3(256), 0, st, a, i0);
     GVQ_HIP(hipGetLastError());
     // a wave per eigenvalue while that leaves the chip's 1024 SIMDs a handful each, fewer lanes for many small matrices (the
     // passes that more lanes spare are fewer than the lanes: 16 x 16, 4000 of them 69 us with 16 lanes, 36 with 4 and a wave each)
@@ -1306,7 +1315,7 @@ EigenArgs gvq_eigen_args(const gvq_basis* h)
     a.eig = h->d_eig; a.eig_ld = h->d;
     a.Z = h->d_eZ; a.Z_stride = (size_t)h->k * d;
     a.wy = h->d_mom; a.wy_stride = d * d + d;   // the covariance is made: the moments are not needed any more
-    a.xchg = h->d_eX; a.xchg_stride = 6 * d;
+    a.xchg = h->d_eX; a.xchg_stride = 8 * d;
     a.lu = h->d_eLU; a.lanes = 64; a.clamp = 0; a.solves = h->d_solves;
     return a;
 }

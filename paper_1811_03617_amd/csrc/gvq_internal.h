@@ -60,7 +60,7 @@ struct gvq_basis {
     double* d_eA = nullptr;     // eigensolver: [B][(d+1) d] matrix, then its reflectors (first-slice refresh: samples too)
     double* d_eT = nullptr;     // [B][5 d] tridiagonal matrix and work vectors
     double* d_eZ = nullptr;     // [B][k][d] eigenvectors
-    unsigned long long* d_eX = nullptr;   // d > GVQ_EIGEN_SMALL: [B][6 d] exchange between the work-groups of one matrix
+    unsigned long long* d_eX = nullptr;   // d > GVQ_EIGEN_SMALL: [B][8 d] exchange between the work-groups of one matrix
     double* d_eLU = nullptr;    // d > GVQ_EIGEN_SMALL: factors of the inverse iteration
     int* d_solves = nullptr;    // [B] most solves any eigenvector took (0 = zero matrix), or GVQ_NO_CONVERGENCE
     int* d_ksel = nullptr;      // [B] result of the last gvq_select_k
