@@ -43,6 +43,20 @@ __device__ __forceinline__ double lane_value(double v, int lane)
                             __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
+// v of this lane plus v of lane ^ 16 (^ 32), the same bits in both.
+__device__ __forceinline__ double add_xor16(double v)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double add_xor32(double v)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
 // Sum over the 64 lanes, the same bits in every lane.
 __device__ __forceinline__ double wave_sum(double v)
 {
@@ -51,6 +65,22 @@ __device__ __forceinline__ double wave_sum(double v)
     v += dpp_move<DPP_HALF_MIRROR>(v);
     v += dpp_move<DPP_MIRROR>(v);
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
+// Four of them: each exchange with a neighbour halves the sums a lane holds.
+__device__ __forceinline__ void wave_sum4(double (&v)[4])
+{
+    const bool o1 = threadIdx.x & 1, o2 = threadIdx.x & 2;
+    const double a0 = (o1 ? v[2] : v[0]) + dpp_move<DPP_XOR1>(o1 ? v[0] : v[2]);
+    const double a1 = (o1 ? v[3] : v[1]) + dpp_move<DPP_XOR1>(o1 ? v[1] : v[3]);
+    double b = (o2 ? a1 : a0) + dpp_move<DPP_XOR2>(o2 ? a0 : a1);
+    b += dpp_move<DPP_ROR4>(b);
+    b += dpp_move<DPP_ROR8>(b);
+    b = add_xor32(add_xor16(b));
+    v[0] = lane_value(b, 0);
+    v[1] = lane_value(b, 2);
+    v[2] = lane_value(b, 1);
+    v[3] = lane_value(b, 3);
 }
 
 // Largest of the 64 lanes' values, in every lane.
@@ -699,13 +729,16 @@ __global__ __launch_bounds__(256) void bisect_kernel(EigenArgs a)
 // right-hand side of U alone (more, up to EIG_MOST_SOLVES, while a solve does not make the vector grow).  A solve multiplies what other eigenvectors contribute by (rounding / gap), so two leave
 // nothing of any whose eigenvalue can be told apart.  Vectors of eigenvalues that cannot are independent random
 // members of their common space, which the orthonormalisation sorts out.  NV vectors per work-group (one wave); the
-// factors sit in LDS up to n = 128, else in global memory, entry-major so that a step's access is one contiguous run.
+// factors sit in LDS, up to n = 128 of 16 vectors, above that of four or two while the chip has a compute unit for every
+// work-group (d = 768, k = 96 415 -> 321 us), else in global memory; entry-major, so that a step's access is one contiguous run.
 // Bound by the chain of dependent steps: n divisions and 3 n multiply-adds per vector.
+#define EIG_LDS4_ROWS 896   // four vectors' factors, 160 bytes a row, and 16 KB for T fit a compute unit's LDS
 template <int NV, bool IN_LDS>
 __global__ __launch_bounds__(64) void inverse_kernel(EigenArgs a)
 {
     extern __shared__ double lu_lds[];
-    __shared__ double td[IN_LDS ? GVQ_EIGEN_SMALL : GVQ_MAX_D], te[IN_LDS ? GVQ_EIGEN_SMALL : GVQ_MAX_D];
+    constexpr int ROWS = IN_LDS && NV == 16 ? GVQ_EIGEN_SMALL : GVQ_MAX_D;
+    __shared__ double td[ROWS], te[ROWS];
     const int b = blockIdx.y, n = a.n, lane = threadIdx.x;
     const unsigned long long norm = a.norm[b];
     if (eig_skip(norm)) return;
@@ -845,6 +878,8 @@ __global__ __launch_bounds__(64) void inverse_kernel(EigenArgs a)
 // One work-group per basis is a 256th of the chip, and what many columns take is the first part: more than 256 columns are
 // finished panel by panel, each in a launch of its own (FINISH), and after each the later panels shed their components along
 // it, a work-group each (SHED): the same operations in the same order (d = k = 1024 20.6 -> 2.8 ms; the whole refresh 29.4 -> 11.6, d = k = 512 6.4 -> 3.9).
+// A column's sums over the wave, four at a time, and its reciprocal square root are what a step waits for, and the finished
+// columns arrive while the one before them is worked through (d = 768, k = 96: 193 -> 158 us).
 enum OrthoPart { ORTHO_ALL, ORTHO_FINISH, ORTHO_SHED };
 template <int NE, OrthoPart PART>
 __global__ __launch_bounds__(512) void orthonormalise_kernel(double* Z, size_t Z_stride, int k, int n, int panel,
@@ -866,20 +901,26 @@ __global__ __launch_bounds__(512) void orthonormalise_kernel(double* Z, size_t Z
                 x[s][e] = c < k && i < n ? Z[(size_t)c * n + i] : 0.0;
             }
         const int done0 = PART == ORTHO_SHED ? 32 * panel : 0, done1 = PART == ORTHO_ALL ? c0 : PART == ORTHO_SHED ? done0 + 32 : 0;
+        double next[NE];   // the finished column after this one is on its way while this one is worked through
+        auto fetch = [&](int done) {
+#pragma unroll
+            for (int e = 0; e < NE; ++e) next[e] = Z[(size_t)done * n + (64 * e + lane < n ? 64 * e + lane : n - 1)];
+        };
+        if (done0 < done1) fetch(done0);
         for (int done = done0; done < done1; ++done) {
             double y[NE], dot[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int e = 0; e < NE; ++e) y[e] = 64 * e + lane < n ? Z[(size_t)done * n + 64 * e + lane] : 0.0;
+            for (int e = 0; e < NE; ++e) y[e] = 64 * e + lane < n ? next[e] : 0.0;
+            fetch(done + 1 < done1 ? done + 1 : done);
 #pragma unroll
             for (int e = 0; e < NE; ++e)
 #pragma unroll
                 for (int s = 0; s < 4; ++s) dot[s] = fma(y[e], x[s][e], dot[s]);
+            wave_sum4(dot);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                dot[s] = wave_sum(dot[s]);
+            for (int s = 0; s < 4; ++s)
 #pragma unroll
                 for (int e = 0; e < NE; ++e) x[s][e] = fma(-dot[s], y[e], x[s][e]);
-            }
         }
         if (PART == ORTHO_SHED) {
 #pragma unroll
@@ -902,7 +943,8 @@ __global__ __launch_bounds__(512) void orthonormalise_kernel(double* Z, size_t Z
 #pragma unroll
                     for (int e = 0; e < NE; ++e) n2 = fma(x[s][e], x[s][e], n2);
                     n2 = wave_sum(n2);
-                    const double inv = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
+                    double inv = 0.0;
+                    if (n2 > 0.0) (void)fast_sqrt(n2, inv);
 #pragma unroll
                     for (int e = 0; e < NE; ++e) {
                         x[s][e] *= inv;
@@ -919,12 +961,12 @@ __global__ __launch_bounds__(512) void orthonormalise_kernel(double* Z, size_t Z
 #pragma unroll
                     for (int s2 = 0; s2 < 4; ++s2)
                         if (s2 >= s) dot[s2] = fma(y[e], x[s2][e], dot[s2]);
+                wave_sum4(dot);
 #pragma unroll
                 for (int s2 = 0; s2 < 4; ++s2) {
                     if (s2 < s || (s2 == s && wave <= w)) continue;
-                    const double f = wave_sum(dot[s2]);
 #pragma unroll
-                    for (int e = 0; e < NE; ++e) x[s2][e] = fma(-f, y[e], x[s2][e]);
+                    for (int e = 0; e < NE; ++e) x[s2][e] = fma(-dot[s2], y[e], x[s2][e]);
                 }
             }
         }
@@ -1102,8 +1144,7 @@ __global__ __launch_bounds__(256) void back_wy_kernel(EigenArgs a)
         for (int r = 0; r < 2; ++r) s2[r] = (o2 ? s4[r + 2] : s4[r]) + dpp_move<DPP_XOR2>(o2 ? s4[r] : s4[r + 2]);
         d1 = (o4 ? s2[1] : s2[0]) + __shfl_xor(o4 ? s2[0] : s2[1], 4, 64);
         d1 += dpp_move<DPP_ROR8>(d1);
-        d1 += __shfl_xor(d1, 16, 64);
-        d1 += __shfl_xor(d1, 32, 64);
+        d1 = add_xor32(add_xor16(d1));
         if (lane < RW) ws[RW * wave + 4 * (lane & 1) + 2 * ((lane >> 1) & 1) + (lane >> 2)] = d1;
         __syncthreads();
         double y = 0.0;   // T w, eight lanes a row
@@ -1281,6 +1322,17 @@ int gvq_launch_sym_eigen(const gvq_basis* h, EigenArgs a, bool ortho, hipStream_
             GVQ_HIP(hipFuncSetAttribute((const void*)(inverse_kernel<16, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                         (int)(sizeof(double) * 5 * GVQ_EIGEN_SMALL * 16)));
         hipLaunchKernelGGL((inverse_kernel<16, true>), dim3((unsigned)((a.k + 15) / 16), B), dim3(64), lds, st, a);
+    } else if (const int nv = n <= EIG_LDS4_ROWS ? 4 : 2; (int64_t)((a.k + nv - 1) / nv) * B <= h->num_cu) {
+        static gvq_once_per_device once;
+        if (once.first(h->device)) {
+            GVQ_HIP(hipFuncSetAttribute((const void*)(inverse_kernel<4, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)(sizeof(double) * 5 * EIG_LDS4_ROWS * 4)));
+            GVQ_HIP(hipFuncSetAttribute((const void*)(inverse_kernel<2, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        (int)(sizeof(double) * 5 * GVQ_MAX_D * 2)));
+        }
+        const dim3 grid((unsigned)((a.k + nv - 1) / nv), B);
+        if (nv == 4) hipLaunchKernelGGL((inverse_kernel<4, true>), grid, dim3(64), sizeof(double) * 5 * n * 4, st, a);
+        else hipLaunchKernelGGL((inverse_kernel<2, true>), grid, dim3(64), sizeof(double) * 5 * n * 2, st, a);
     } else {
         hipLaunchKernelGGL((inverse_kernel<64, false>), dim3((unsigned)((a.k + 63) / 64), B), dim3(64), 0, st, a);
     }
