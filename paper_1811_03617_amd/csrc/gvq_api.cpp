@@ -229,30 +229,18 @@ int gvq_fit_status(const gvq_basis_t* h, int* max_solves, void* stream)
 {
     if (!h) return GVQ_EINVAL;
     if (!h->has_cov) return GVQ_ENOTFIT;
-    GVQ_HIP(hipStreamSynchronize((hipStream_t)stream));
-    const size_t B = (size_t)h->B;
-    int* sw = (int*)malloc(sizeof(int) * B);
-    double* eig = (double*)malloc(sizeof(double) * B * h->d);
-    if (!sw || !eig) { free(sw); free(eig); return GVQ_ENOMEM; }
-    hipError_t e1 = hipMemcpy(sw, h->d_solves, sizeof(int) * B, hipMemcpyDeviceToHost);
-    hipError_t e2 = hipMemcpy(eig, h->d_eig, sizeof(double) * B * h->d, hipMemcpyDeviceToHost);
-    int rc = GVQ_OK;
-    if (e1 != hipSuccess) rc = gvq_hip_fail(e1, "hipMemcpy(solves)");
-    else if (e2 != hipSuccess) rc = gvq_hip_fail(e2, "hipMemcpy(eig)");
-    else {
-        int mx = 0;
-        bool noconv = false, nonfinite = false;
-        for (size_t b = 0; b < B; ++b) {
-            if (sw[b] >= GVQ_NO_CONVERGENCE) noconv = true;
-            else if (sw[b] > mx) mx = sw[b];
-        }
-        for (size_t i = 0; i < B * h->d; ++i)
-            if (!isfinite(eig[i])) nonfinite = true;
-        if (max_solves) *max_solves = mx;
-        if (nonfinite) rc = GVQ_ENONFINITE;
-        else if (noconv) rc = GVQ_ENOCONV;
+    int* out = nullptr;   // of this call alone: callers may ask from several threads
+    GVQ_HIP(hipHostMalloc((void**)&out, 2 * sizeof(int), hipHostMallocDefault));
+    int rc = gvq_launch_fit_status(h, out, (hipStream_t)stream);
+    if (rc == GVQ_OK) {
+        const hipError_t e = hipStreamSynchronize((hipStream_t)stream);
+        if (e != hipSuccess) rc = gvq_hip_fail(e, "hipStreamSynchronize");
     }
-    free(sw); free(eig);
+    if (rc == GVQ_OK) {
+        if (max_solves) *max_solves = out[0];
+        rc = out[1] & 2 ? GVQ_ENONFINITE : out[1] & 1 ? GVQ_ENOCONV : GVQ_OK;
+    }
+    (void)hipHostFree(out);
     return rc;
 }
 

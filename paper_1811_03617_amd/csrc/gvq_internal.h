@@ -177,5 +177,6 @@ int gvq_launch_compress_ws(const gvq_basis* h, const void* grad, int n_workers, 
 size_t gvq_eigen_lu_doubles(int d, int k);   // doubles per basis of d_eLU
 // d_cov (made from d_mom first if from_moments) -> d_eig, d_U.
 int gvq_launch_eigen(const gvq_basis* h, bool from_moments, hipStream_t st);
+int gvq_launch_fit_status(const gvq_basis* h, int* out, hipStream_t st);   // out [2], memory the device can write
 bool gvq_sample_shape(int d, int L);         // first-slice refresh: gvq_launch_fit_samples takes it
 int gvq_launch_fit_samples(const gvq_basis* h, const void* const* grads, int L, hipStream_t st);
