@@ -143,6 +143,8 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
                 TRY(hipMemcpy(h->d_ltile, h->h_ltile, sizeof(int64_t) * (B + 1), hipMemcpyHostToDevice));
             }
         } else if (gvq_mfma_shape(d, k)) {
+            rc = gvq_flow_alloc(h);
+            if (rc != GVQ_OK) goto fail;
             const size_t kp = k <= 16 ? 16 : 32;
             TRY(hipMalloc((void**)&h->d_Upc, sizeof(float) * B * d * kp));
             TRY(hipMalloc((void**)&h->d_Upd, sizeof(float) * B * d * kp));

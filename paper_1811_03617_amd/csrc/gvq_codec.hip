@@ -1412,6 +1412,10 @@ int gvq_launch_pack(const gvq_basis* h, hipStream_t st)
     hipLaunchKernelGGL(pack_basis_kernel, dim3(h->B), dim3(256), 0, st, h->d_U, h->d_Upc, h->d_Upd,
                        h->d, h->k, h->k <= 16 ? 1 : 2);
     GVQ_HIP(hipGetLastError());
+    {
+        const int rc = gvq_launch_pack_flow(h, st);
+        if (rc != GVQ_OK) return rc;
+    }
     if (gvq_loss_split_shape(h)) {
         const int rc = gvq_launch_pack_loss(h, st);
         if (rc != GVQ_OK) return rc;
@@ -1602,7 +1606,9 @@ static int launch_compress_y(const gvq_basis* h, const CodecArgs& a, hipStream_t
     constexpr auto kern = compress_mfma_kernel<D, NT, BF16, VAR, false, YS>;
     const int64_t items = work_items(a);
     constexpr FastShape fs = D == 128 ? FastShape{2, 5, 4} : D == 64 ? FastShape{1, 4, 4} : FastShape{1, 0, 4};
-    int grid = streaming_grid<kern>(h, items, fs.wg_per_cu, true);
+    // Comps that are no whole words leave everything to the general phase, which wants all the waves that fit instead (60 M
+    // elements, d = 64, k = 6 74 -> 48 us; d = 128 is best with two work-groups either way).
+    int grid = streaming_grid<kern>(h, items, a.n_super || D == 128 ? fs.wg_per_cu : 0, true);
     CodecArgs b = a;
     b.pace = pace_of(fs);
     b.run_tiles = run_length(h, a.n_super, grid, fs.many_run);
@@ -1654,7 +1660,8 @@ static int launch_compress_bf16_y(const gvq_basis* h, const CodecArgs& a, hipStr
 {
     constexpr auto kern = compress_bf16_kernel<D, NT, ACC, YS>;
     constexpr FastShape fs = {1, 0, 4};
-    int grid = streaming_grid<kern>(h, work_items(a), fs.wg_per_cu, true);
+    // general phase alone: as for the fp32 pipe (60 M elements, d = 128, k = 13 56 -> 30 us, d = 64, k = 6 74 -> 33)
+    int grid = streaming_grid<kern>(h, work_items(a), a.n_super ? fs.wg_per_cu : 0, true);
     CodecArgs b = a;
     b.pace = pace_of(fs);
     b.run_tiles = run_length(h, a.n_super, grid, fs.many_run);
@@ -1698,6 +1705,8 @@ int gvq_launch_compress(const gvq_basis* h, const void* grad, int n_workers, int
 {
     if (gvq_long_shape(h->d, h->k))
         return gvq_launch_compress_long(h, grad, n_workers, first_slice, n_slices, comp_in, out, st);
+    if (gvq_opt_long_mode() == 0 && gvq_flow_takes_compress(h))   // many short slices, comps that are no whole words
+        return gvq_launch_compress_flow(h, grad, n_workers, first_slice, n_slices, comp_in, out, st);
     if (gvq_bf16_pipe_shape(h)) {
         CodecArgs a = make_args(h, grad, out, n_workers, (const float*)h->d_Upb);
         a.Umu = h->d_Umu;
@@ -1744,7 +1753,9 @@ static int launch_decompress_y(const gvq_basis* h, const CodecArgs& a, hipStream
     const int64_t items = work_items(a);
     // many bases: the basis reload of every run has to be hidden by a second work-group
     const FastShape fs = h->B > 1 ? FastShape{2, 0, 8} : FastShape{1, 0, 1};
-    int grid = streaming_grid<kern>(h, items, fs.wg_per_cu);
+    // general phase alone (comps that are no whole words): all the waves that fit (60 M elements, d = 16, k = 5 194 -> 72 us, d = 32,
+    // k = 11 125 -> 50, d = 64, k = 6 73 -> 44, d = 128, k = 21 77 -> 60; to bf16 201 -> 74, 116 -> 47, 70 -> 38, 72 -> 56)
+    int grid = streaming_grid<kern>(h, items, a.n_super ? fs.wg_per_cu : 0);
     CodecArgs b = a;
     b.pace = pace_of(fs);
     b.run_tiles = run_length(h, a.n_super, grid, fs.many_run);
@@ -1784,9 +1795,9 @@ int gvq_launch_decompress(const gvq_basis* h, const float* comp, int64_t first_s
     // (bf16 output of more than 128 comps cannot add up its column passes in place: the any-shape kernel below)
     if (gvq_long_shape(h->d, h->k) && !(h->k > 128 && odt == GVQ_BF16))
         return gvq_launch_decompress_long(h, comp, first_slice, n_slices, out, odt, st);
+    const bool bf = odt == GVQ_BF16;
     CodecArgs a = make_args(h, comp, out, 1, h->d_Upd);
     a.seg_begin = first_slice; a.seg_end = first_slice + n_slices;
-    const bool bf = odt == GVQ_BF16;
     if (gvq_mfma_shape(h->d, h->k)) {
         switch (h->d) {
         case 16: return bf ? launch_decompress_d<16, true>(h, a, st) : launch_decompress_d<16, false>(h, a, st);

@@ -227,10 +227,19 @@ inline bool flow_too_small(const FlowShape& s, const FlowPlan& p)
     return p.exact && ((s.d <= 48 && each < 0.25) || (s.d % 4 == 0 && s.d <= 64 && each < 1));
 }
 
+// The register-resident kernels of gvq_codec.hip keep a shape of theirs whose comps are whole words.  Of the others, which go
+// through their bounds-checked loop, compress of many short slices comes here (60 M elements, there / here, us, f32 and bf16:
+// d = 16, k = 5 86 / 72 and 116 / 70; d = 32, k = 11 64 / 58 and 85 / 49; d = 64, k = 21 81 / 66 and 68 / 63); fewer slices (10 M elements f32:
+// d = 16 17 / 19, d = 32 13 / 15, d = 64 17 / 17; bf16 22 / 18, 16 / 13, 14 / 16), few comps at d = 64 (k = 6 f32 48 / 50, bf16
+// 33 / 43), d = 128 (k = 13 49 / 52) and decompress (d = 16, k = 5 72 / 78) do not.
+inline bool flow_resident_shape(int d, int k) { return k <= 32 && (d == 16 || d == 32 || d == 64 || d == 128); }
+
 inline bool flow_takes_compress(const FlowShape& s)
 {
     const FlowPlan p = flow_compress_plan(s.d, s.k);
     if (!p.waves) return false;
+    if (flow_resident_shape(s.d, s.k)) 
+        return s.k % 4 != 0 && p.exact && (s.d <= 32 ? s.slices >= (s.bf16 ? 200000 : 1000000) : s.d == 64 && s.k > 16 && s.slices >= 500000);
     if (!s.bf16 && flow_too_small(s, p)) return false;
     if (s.d % 4) return true;
     // U over eight waves (f32 d = 400, k = 100 1.18, bf16 d = 500, k = 128 1.24); above 256 elements with bf16 storage or
@@ -246,6 +255,7 @@ inline bool flow_takes_decompress(const FlowShape& s)
     const FlowPlan p = flow_decompress_plan(s.d, s.k);
     const int d = s.d, k = s.k;
     if (!p.waves) return false;
+    if (flow_resident_shape(d, k)) return false;
     if (flow_too_small(s, p)) return false;
     if (d % 4) return true;
     const double each = flow_tiles_each(s, p);

@@ -269,3 +269,46 @@ def test_every_instance_with_several_tiles_per_work_group(d, k, blocks, dtype):
         gvq.gvq_set_option(0, 0)
         gvq.gvq_set_option(1, 0)
     b.close()
+
+
+@pytest.mark.parametrize("d,k,dtype,S", [(16, 1, "f32", 1_000_000), (16, 5, "f32", 1_000_003), (16, 15, "bf16", 200_000), (32, 3, "bf16", 200_001),
+                                         (32, 30, "f32", 1_000_001), (64, 17, "f32", 500_000), (64, 31, "bf16", 500_009), (16, 2, "bf16", 199_999)])
+@pytest.mark.parametrize("bases", [1, 7])
+def test_short_slices_with_ragged_comps(d, k, dtype, S, bases):
+    """Compress of many slices of 16, 32 or 64 elements whose comps are no whole words, against the register-resident kernels'
+    bounds-checked loop (option 2): whole gradients with a ragged tail, segments, the fused ring step.  Both add d exact products
+    in fp32: each is within d 2^-24 sum |u x| of the exact sum, and sum |u x| <= |x| for a unit column.  The bf16 kernels start from
+    U^T mu / N instead of centring: the mean adds its size to |x| there."""
+    gen = torch.Generator(device=DEV).manual_seed(d * k)
+    M = S * d - (d // 2 + 1)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = (torch.randn(M, generator=gen, device=DEV) + 0.5).to(tdt)
+    offs = [S * i // bases for i in range(bases + 1)]
+    b = gvq.Basis(M, d, k, offs if bases > 1 else None, dtype)
+    rng = np.random.default_rng(k)
+    b.import_(np.linalg.qr(rng.standard_normal((bases, d, k)))[0].astype(np.float32), rng.standard_normal((bases, d)).astype(np.float32))
+    first, count = S // 3 + 1, S // 2 + 5
+    part = torch.randn(S * k, generator=gen, device=DEV)
+    got = []
+    for mode in (0, 3):
+        y, z = torch.full((S * k,), 7.0, device=DEV), torch.full((S * k,), 7.0, device=DEV)
+        try:
+            gvq.gvq_set_option(2, mode)
+            b.compress(x, 3, y)
+            b.compress_segment(x, 3, first, count, part, z)
+        finally:
+            gvq.gvq_set_option(2, 0)
+        got.append((y.view(S, k), z.view(S, k)))
+    norm = torch.zeros(S * d, device=DEV)
+    norm[:M] = x.float().abs()
+    norm = norm.view(S, d).norm(dim=1, keepdim=True) + float(d) ** 0.5 * 2.0   # means of up to 4 or so, over three workers
+    tol = 2 * d * 2.0 ** -24 * norm
+    assert bool(((got[0][0] - got[1][0]).abs() <= tol).all())
+    rows = slice(first, first + count)
+    assert bool(((got[0][1] - got[1][1]).abs()[rows] <= tol[rows] + 2.0 ** -22 * (1 + part.view(S, k)[rows].abs())).all())
+    for y, z in got:
+        assert torch.equal(z[rows], y[rows] + part.view(S, k)[rows])
+        outside = torch.ones(S, dtype=torch.bool, device=DEV)
+        outside[rows] = False
+        assert bool((z[outside] == 7.0).all())
+    b.close()
