@@ -1610,7 +1610,10 @@ static int launch_compress_y(const gvq_basis* h, const CodecArgs& a, hipStream_t
     // elements, d = 64, k = 6 74 -> 48 us; d = 128 is best with two work-groups either way).
     int grid = streaming_grid<kern>(h, items, a.n_super || D == 128 ? fs.wg_per_cu : 0, true);
     CodecArgs b = a;
-    b.pace = pace_of(fs);
+    // A short launch has no steady state to pace: up to eight super-tiles a wave, unpaced (d = 64, k = 16, 4 / 7.6 / 15 M elements
+    // 7.3 / 10.4 / 16.7 -> 6.5 / 9.5 / 15.1 us, d = 128, k = 32, 7.6 / 15 / 30 M 13.5 / 20.3 / 31.9 -> 12.8 / 18.7 / 29.6; from 14
+    // a wave on d = 64 loses 3 %).
+    b.pace = gvq_opt_pace() < 0 && a.n_super <= (int64_t)8 * grid * WAVES_PER_WG ? 0 : pace_of(fs);
     b.run_tiles = run_length(h, a.n_super, grid, fs.many_run);
     b.rest_run = run_length(h, work_items(a) - a.n_super, grid);
     b.il = interleave_of(b, D >= 64 ? 64 : 1);   // steady state: d = 128 5.90 -> 5.99 TB/s, d = 64 6.09 -> 6.18, d = 32 5.43 -> 5.35
