@@ -262,10 +262,11 @@ const char* gvq_strerror(int status);
  *             3 = always the split, and never the kernels that keep U in registers (the default
  *             for fp32 gradients with one basis and d a multiple of 256; for A/B timing); any
  *             value but 0 also leaves out the kernels that move whole slices (gvq_flow.h, the default
- *             for most other shapes) in favour of the LDS-tiled ones;
+ *             for most other shapes, and for compress of many slices of 16, 32 or 64 elements when k is
+ *             no multiple of 4) in favour of the LDS-tiled or register-resident ones;
  *   option 3: bit mask that sends every tile of a kernel family through its bounds-checked general loop
- *             instead of the branch-free loop over whole tiles (1: fp32-pipe compress, 2: bf16-pipe
- *             compress, 4: decompress); results are identical, for A/B timing;
+ *             instead of the branch-free loop over whole tiles (1: fp32-pipe compress and monitor, 2: bf16-pipe
+ *             compress, 4: decompress); results are identical (the monitor's sum up to rounding), for A/B timing;
  *   option 4: pacing of the branch-free loop, -1 = each kernel's default: bit 0 = a wave waits for all its
  *             memory work before it parks the next tile, bit 1 = also after a tile's matrix products,
  *             bit 2 = the matrix products wait for the next tile's loads one by one;

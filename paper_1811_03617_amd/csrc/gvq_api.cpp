@@ -231,6 +231,12 @@ int gvq_fit_status(const gvq_basis_t* h, int* max_solves, void* stream)
 {
     if (!h) return GVQ_EINVAL;
     if (!h->has_cov) return GVQ_ENOTFIT;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing((hipStream_t)stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        GVQ_HIP(hipStreamSynchronize((hipStream_t)stream));   // refuses: there is nothing to wait for while a graph is recorded
+        return GVQ_EHIP;
+    }
     int* out = nullptr;   // of this call alone: callers may ask from several threads
     GVQ_HIP(hipHostMalloc((void**)&out, 2 * sizeof(int), hipHostMallocDefault));
     int rc = gvq_launch_fit_status(h, out, (hipStream_t)stream);
