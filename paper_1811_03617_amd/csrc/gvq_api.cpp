@@ -77,6 +77,7 @@ int gvq_basis_destroy(gvq_basis_t* h)
         if (pl.d_sup_basis) (void)hipFree(pl.d_sup_basis);
         if (pl.d_rest) (void)hipFree(pl.d_rest);
     }
+    if (h->h_notes) (void)hipHostFree(h->h_notes);
     free(h->h_offs);
     free(h->h_ltile);
     free(h->h_ftile);
@@ -165,6 +166,7 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
         TRY(hipMalloc((void**)&h->d_nsamp, sizeof(unsigned long long) * 2 * B));
         TRY(hipMalloc((void**)&h->d_solves, sizeof(int) * B));
         TRY(hipMalloc((void**)&h->d_ksel, sizeof(int) * B));
+        TRY(hipHostMalloc((void**)&h->h_notes, sizeof(unsigned long long), hipHostMallocDefault));
         if (gvq_loss_split_shape(h)) TRY(hipMalloc((void**)&h->d_Uls, sizeof(unsigned short) * gvq_loss_split_pack_halves(d)));
         // the same memory takes the sums of gvq_launch_loss_split
         TRY(hipMalloc((void**)&h->d_loss_slice, sizeof(float) * (size_t)(S > 2 * GVQ_LOSS_MAX_PARTS ? S : 2 * GVQ_LOSS_MAX_PARTS)));
@@ -237,19 +239,21 @@ int gvq_fit_status(const gvq_basis_t* h, int* max_solves, void* stream)
         GVQ_HIP(hipStreamSynchronize((hipStream_t)stream));   // refuses: there is nothing to wait for while a graph is recorded
         return GVQ_EHIP;
     }
-    int* out = nullptr;   // of this call alone: callers may ask from several threads
-    GVQ_HIP(hipHostMalloc((void**)&out, 2 * sizeof(int), hipHostMallocDefault));
-    int rc = gvq_launch_fit_status(h, out, (hipStream_t)stream);
+    // the kernel reads the handle's memory: it runs on the handle's device, whichever is current
+    int current = h->device;
+    GVQ_HIP(hipGetDevice(&current));
+    if (current != h->device) GVQ_HIP(hipSetDevice(h->device));
+    int rc = gvq_launch_fit_status(h, (hipStream_t)stream);
     if (rc == GVQ_OK) {
         const hipError_t e = hipStreamSynchronize((hipStream_t)stream);
         if (e != hipSuccess) rc = gvq_hip_fail(e, "hipStreamSynchronize");
     }
-    if (rc == GVQ_OK) {
-        if (max_solves) *max_solves = out[0];
-        rc = out[1] & 2 ? GVQ_ENONFINITE : out[1] & 1 ? GVQ_ENOCONV : GVQ_OK;
-    }
-    (void)hipHostFree(out);
-    return rc;
+    if (current != h->device) (void)hipSetDevice(current);
+    if (rc != GVQ_OK) return rc;
+    const unsigned long long word = *(const volatile unsigned long long*)h->h_notes;
+    if (max_solves) *max_solves = (int)(word & 0xffffffffu);
+    const unsigned int flags = (unsigned int)(word >> 32);
+    return flags & 2 ? GVQ_ENONFINITE : flags & 1 ? GVQ_ENOCONV : GVQ_OK;
 }
 
 int gvq_compress(const gvq_basis_t* h, const void* grad, int n_workers, float* comp_out, void* stream)

@@ -1211,8 +1211,9 @@ __global__ __launch_bounds__(256) void basis_out_kernel(const double* Z, size_t 
 }
 
 // What gvq_fit_status reports, into host memory: the most solves, whether any vector did not converge, whether any eigenvalue
-// is not finite.  (Copies of both arrays took 98 us for 26 bases of 768 eigenvalues.)
-__global__ __launch_bounds__(1024) void fit_status_kernel(const int* solves, int B, const double* eig, size_t n, int* out)
+// is not finite (the whole call 28 - 31 us, with copies of both arrays instead 38 - 48; 1 basis of 768 to 26 of 900 eigenvalues).
+__global__ __launch_bounds__(1024) void fit_status_kernel(const int* solves, int B, const double* eig, size_t n,
+                                                          unsigned long long* out)
 {
     __shared__ int most, flags;
     if (threadIdx.x == 0) most = flags = 0;
@@ -1229,13 +1230,13 @@ __global__ __launch_bounds__(1024) void fit_status_kernel(const int* solves, int
     if (mx) atomicMax(&most, mx);
     if (fl) atomicOr(&flags, fl);
     __syncthreads();
-    if (threadIdx.x == 0) { out[0] = most; out[1] = flags; }
+    if (threadIdx.x == 0) *out = (unsigned long long)(unsigned int)flags << 32 | (unsigned int)most;
 }
 
 // ======================================================================================
-int gvq_launch_fit_status(const gvq_basis* h, int* out, hipStream_t st)
+int gvq_launch_fit_status(const gvq_basis* h, hipStream_t st)
 {
-    hipLaunchKernelGGL(fit_status_kernel, dim3(1), dim3(1024), 0, st, h->d_solves, h->B, h->d_eig, (size_t)h->B * h->d, out);
+    hipLaunchKernelGGL(fit_status_kernel, dim3(1), dim3(1024), 0, st, h->d_solves, h->B, h->d_eig, (size_t)h->B * h->d, h->h_notes);
     GVQ_HIP(hipGetLastError());
     return GVQ_OK;
 }

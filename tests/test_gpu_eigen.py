@@ -218,3 +218,40 @@ def test_refreshes_on_several_streams_and_captured():
         assert np.max(np.abs(eig - alone[0][2])) <= 2e-15 * (d + 10) * eig[0, 0]
     for b in bases:
         b.close()
+
+
+class _Busy:
+    """A stream with a long, finite queue: copies that take about a quarter of a second."""
+
+    def __init__(self):
+        self.x = torch.empty(1 << 28, device=DEV)   # 1 GiB, about 0.35 ms a copy
+        self.y = torch.empty_like(self.x)
+        self.stream, self.done = torch.cuda.Stream(), torch.cuda.Event()
+
+    def start(self):
+        torch.cuda.synchronize()
+        with torch.cuda.stream(self.stream):
+            for _ in range(700):
+                self.y.copy_(self.x)
+
+    def end(self):
+        self.done.record(self.stream)
+
+
+def test_status_waits_for_its_own_stream_only():
+    """Another stream still has work when the answer is there (one of several streams: two may share a hardware queue)."""
+    x = torch.randn(64 * 500, device=DEV)
+    b = gvq.Basis(64 * 500, 64, 8)
+    b.fit([x])
+    solves = b.fit_status()
+    busy = _Busy()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    busy.start()
+    busy.end()
+    early = 0
+    for s in streams:
+        assert b.fit_status(stream=s.cuda_stream) == solves
+        early += not busy.done.query()
+    torch.cuda.synchronize()
+    assert early
+    b.close()
