@@ -173,6 +173,13 @@ __global__ __launch_bounds__(256) void cov_kernel(const double* mom_all, const u
 // rank-two update A - v w^T - w v^T, w = p - (tau/2)(p.v) v, p = tau A v.  Row r of the working matrix is
 // a.A + (r+1) n; the reflector of step i goes to row i-1, which nobody needs any more.
 
+// The update of one entry.  Written out, so that the compiler has nothing to contract: a column as a launch of its own and all of
+// them in one launch give the same bits.
+__device__ __forceinline__ double tri_update(double x, double vr, double wc, double wr, double vc)
+{
+    return fma(-vr, wc, fma(-wr, vc, x));
+}
+
 // One column of a matrix with more than 128 rows.  Every work-group repeats the O(n) part (the previous step's w, the
 // column, its reflector) and then takes eight rows: the rank-two update of the step before, in place, and their
 // entries of p for this step -- so a step is one launch, whose end is the only synchronisation it needs.  NE = number of
@@ -201,7 +208,8 @@ __global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
             x[u][q] = (r0 + u < n && c > i && c < n) ? cur[(size_t)(r0 + u) * n + c] : 0.0;
         }
 
-    // column i (row i, the matrix is symmetric) with the previous step's update; at most four entries per thread
+    // column i (row i, the matrix is symmetric) with the previous step's update; at most four entries per thread, always the
+    // same ones: tri_chain_kernel adds in this order too
     constexpr int NT = (NE + 3) / 4;
     double col[NT], v[NT], p[NT];
     double tau = 0.0, s = 0.0, pi = 0.0;
@@ -209,23 +217,24 @@ __global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
     if (i > 0) { tau = T[2 * a.t_ld + i - 1]; pi = p_old[i]; }
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
-        const int c = i + tid + 256 * u;
-        col[u] = c < n ? cur[(size_t)i * n + c] : 0.0;
-        v[u] = i > 0 && c < n ? v_old[c] : 0.0;
-        p[u] = i > 0 && c < n ? p_old[c] : 0.0;
+        const int c = tid + 256 * u;
+        const bool on = c >= i && c < n;
+        col[u] = on ? cur[(size_t)i * n + c] : 0.0;
+        v[u] = i > 0 && on ? v_old[c] : 0.0;
+        p[u] = i > 0 && on ? p_old[c] : 0.0;
         s = fma(p[u], v[u], s);
     }
     s = wave_sum(s);
     if (lane == 0) red[0][wave] = s;
     __syncthreads();
     s = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-    const double half = 0.5 * tau * s, wi = pi - half;   // v[i] of the previous step is 1
+    const double half = 0.5 * tau * s, wi = fma(-0.5 * tau, s, pi);   // v[i] of the previous step is 1
     double n2 = 0.0;
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
-        const int c = i + tid + 256 * u;
+        const int c = tid + 256 * u;
         const double w = fma(-half, v[u], p[u]);
-        if (i > 0) col[u] -= fma(v[u], wi, w);
+        col[u] -= fma(v[u], wi, w);
         if (c < n) { vp[c] = v[u]; wp[c] = w; }
         if (c > i + 1) n2 = fma(col[u], col[u], n2);
         if (c == i + 1) first = col[u];
@@ -240,8 +249,8 @@ __global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
     double* R = A + (size_t)i * n;   // row i-1 of the matrix
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
-        const int c = i + tid + 256 * u;
-        if (c >= n) continue;
+        const int c = tid + 256 * u;
+        if (c < i || c >= n) continue;
         const double h = c == i + 1 ? 1.0 : c > i ? col[u] * sc : 0.0;
         vn[c] = h;
         if (blockIdx.x == 0) {
@@ -260,8 +269,7 @@ __global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
         for (int q = 0; q < NE; ++q) {
             const int c = 64 * q + lane;
             if (c <= i || c >= n) continue;
-            double y = x[u][q];
-            if (i > 0) y -= fma(vr, wp[c], wr * vp[c]);
+            const double y = tri_update(x[u][q], vr, wp[c], wr, vp[c]);
             A[(size_t)(r + 1) * n + c] = y;
             dot = fma(y, vn[c], dot);
         }
@@ -379,13 +387,13 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
         __syncthreads();
         if (lost) break;   // uniform
         s = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-        const double half = 0.5 * tau * s, wi = i > 0 ? pi_s - half : 0.0;   // v[i] of the previous step is 1
+        const double half = 0.5 * tau * s, wi = i > 0 ? fma(-0.5 * tau, s, pi_s) : 0.0;   // v[i] of the previous step is 1
         double n2 = 0.0;
 #pragma unroll
         for (int u = 0; u < NT; ++u) {
             const int c = tid + 256 * u;
             const double w = fma(-half, v[u], p[u]);
-            if (i > 0) col[u] -= fma(v[u], wi, w);
+            col[u] -= fma(v[u], wi, w);
             if (c < NE * 64) {
                 cb[c] = c > i ? col[u] : 0.0;
                 wp[c] = w;
@@ -426,7 +434,7 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
             vr[u] = r == i + 1 ? 1.0 : cb[r] * sc;
 #pragma unroll
             for (int q = 0; q < NE; ++q) {
-                x[u][q] -= fma(vo, wl[q], wr * vl[q]);
+                x[u][q] = tri_update(x[u][q], vo, wl[q], wr, vl[q]);
                 dot[u] = fma(x[u][q], hl[q], dot[u]);
             }
             if (r == i + 1) {
