@@ -1301,11 +1301,25 @@ int gvq_launch_orthonormalise(const gvq_basis* h, double* Z, size_t Z_stride, in
     return GVQ_OK;
 }
 
+// Whether the stream may use every compute unit (hipExtStreamCreateWithCUMask gives it fewer).
+static bool whole_chip(const gvq_basis* h, hipStream_t st)
+{
+    uint32_t mask[32] = {0};
+    if (hipExtStreamGetCUMask(st, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    int units = 0;
+    for (uint32_t m : mask) units += __builtin_popcount(m);
+    return units >= h->num_cu;
+}
+
 // All columns up to the trailing block in one launch (*done), where every work-group (8 rows) has a compute unit to itself;
 // more matrices than that take turns, and a launch per column serves them all at once.  Work-groups that wait for each other
 // have to be on the chip together, so such launches of one process wait for one another, whatever their streams: two of
-// them, each half resident, would wait for ever.  A stream that is being captured keeps the launches per column: the graph may be
-// replayed beside anything.
+// them, each half resident, would wait for ever.  Two kinds of stream keep the launches per column: one that is being captured, as
+// the graph may be replayed beside anything, and one that may not use every compute unit, as work-groups are dealt to the eight
+// parts of the chip in turn, however many units of each the mask leaves.
 static int launch_chain(const gvq_basis* h, const EigenArgs& a, int steps, hipStream_t st, bool* done)
 {
     static std::mutex lock;
@@ -1317,6 +1331,7 @@ static int launch_chain(const gvq_basis* h, const EigenArgs& a, int steps, hipSt
         (void)hipGetLastError();
         return GVQ_OK;
     }
+    if (!whole_chip(h, st)) return GVQ_OK;
     hipLaunchKernelGGL(tri_chain_clear_kernel, dim3((unsigned)((8 * a.n + 255) / 256), h->B), dim3(256), 0, st, a.xchg, a.xchg_stride, 8 * a.n);
     GVQ_HIP(hipGetLastError());
     std::lock_guard<std::mutex> guard(lock);

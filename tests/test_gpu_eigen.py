@@ -2,6 +2,8 @@
 one-work-group tridiagonalisation (32, 64, 128), around the pieces of 64 that the long kernels hold per lane, odd sizes,
 few and all eigenvectors; repeated eigenvalues and null spaces; sample counts around the 16 x 16 products of the
 first-slice refresh.  Reference: numpy's symmetric eigensolver on the covariance that the library exports."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -240,6 +242,34 @@ def test_captured_refresh_has_the_bits_of_an_eager_one(d, k):
         for got, want in zip(b.export(), eager):
             assert np.array_equal(got, want)
     b.close()
+
+
+def _hip():
+    """The HIP runtime that PyTorch has loaded, for what PyTorch has no call for."""
+    torch.cuda.init()
+    with open("/proc/self/maps") as maps:
+        return ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+
+
+@pytest.mark.parametrize("d,k,B", [(300, 40, 6), (768, 96, 1), (1024, 5, 2)])
+@pytest.mark.parametrize("units", [(0xFFFFFFFF,) + (0,) * 7, (0x0000FFFF,) * 8, (0xFFFFFFFF,) * 7 + (0x7FFFFFFF,)])
+def test_refresh_on_a_stream_with_few_compute_units(d, k, B, units):
+    """The work-groups of a matrix that do not have the chip to themselves must not wait for each other."""
+    gen = torch.Generator(device=DEV).manual_seed(d)
+    x = torch.randn(B * (d + 9), d, generator=gen, device=DEV).reshape(-1)
+    b = gvq.Basis(x.numel(), d, k, [i * (d + 9) for i in range(B + 1)])
+    b.fit([x])
+    b.fit_status()
+    want = b.export()
+    hip, stream = _hip(), ctypes.c_void_p()
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), 8, (ctypes.c_uint32 * 8)(*units)) == 0
+    b.import_(np.zeros((B, d, k), np.float32), np.zeros((B, d), np.float32))
+    b.fit([x], stream=stream.value)
+    assert b.fit_status(stream=stream.value) >= 2
+    for got, w in zip(b.export(), want):
+        assert np.array_equal(got, w)
+    b.close()
+    assert hip.hipStreamDestroy(stream) == 0
 
 
 class _Busy:
