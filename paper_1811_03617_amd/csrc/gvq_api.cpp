@@ -17,6 +17,7 @@ static int g_long_mode = 0;
 static int g_no_fast = 0;
 static int g_pace = -1;
 static int g_interleave = 0;
+static int g_chain_polls = 0;
 
 int gvq_hip_fail(hipError_t e, const char* what)
 {
@@ -31,6 +32,7 @@ int gvq_opt_long_mode() { return g_long_mode; }
 int gvq_opt_no_fast() { return g_no_fast; }
 int gvq_opt_pace() { return g_pace; }
 int gvq_opt_interleave() { return g_interleave; }
+int gvq_opt_chain_polls() { return g_chain_polls; }
 
 static bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
@@ -62,6 +64,7 @@ int gvq_set_option(int option, int value)
     if (option == 3 && value >= 0 && value <= 7) { g_no_fast = value; return GVQ_OK; }
     if (option == 4 && value >= -1 && value <= 7) { g_pace = value; return GVQ_OK; }
     if (option == 5 && value >= 0 && value <= 4096) { g_interleave = value; return GVQ_OK; }
+    if (option == 6 && value >= 0 && value <= 1 << 22) { g_chain_polls = value; return GVQ_OK; }
     return GVQ_EINVAL;
 }
 
@@ -159,7 +162,7 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
         TRY(hipMalloc((void**)&h->d_eA, sizeof(double) * B * (d + 1) * d));
         TRY(hipMalloc((void**)&h->d_eT, sizeof(double) * B * 5 * d));
         TRY(hipMalloc((void**)&h->d_eZ, sizeof(double) * B * k * d));
-        if (d > GVQ_EIGEN_SMALL) TRY(hipMalloc((void**)&h->d_eX, sizeof(unsigned long long) * B * 8 * d));
+        if (d > GVQ_EIGEN_SMALL) TRY(hipMalloc((void**)&h->d_eX, sizeof(unsigned long long) * B * (8 * d + 8)));
         if (gvq_eigen_lu_doubles(d, k)) TRY(hipMalloc((void**)&h->d_eLU, sizeof(double) * B * gvq_eigen_lu_doubles(d, k)));
         TRY(hipMalloc((void**)&h->d_part, sizeof(double) * B * h->mom_part));
         TRY(hipMalloc((void**)&h->d_mom, sizeof(double) * B * W));

@@ -19,7 +19,7 @@ struct EigenArgs {
     int eig_ld;
     double* Z;                  // [B][k][n], Z_stride apart: eigenvectors
     size_t Z_stride;
-    unsigned long long* xchg;   // n > 128: [B][4][2 n], xchg_stride apart: what the work-groups of one matrix tell each other
+    unsigned long long* xchg;   // n > 128: [B][4][2 n], then a word, xchg_stride apart: what the work-groups of one matrix tell each other
     size_t xchg_stride;
     double* wy;                 // n > 128: [B][(n - 2) / 32 rounded up][32][32], wy_stride apart: T of each block of reflectors
     size_t wy_stride;

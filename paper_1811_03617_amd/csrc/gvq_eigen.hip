@@ -185,12 +185,15 @@ __device__ __forceinline__ double tri_update(double x, double vr, double wc, dou
 // entries of p for this step -- so a step is one launch, whose end is the only synchronisation it needs.  NE = number of
 // 64-column pieces of a row.  Bound by that chain (launch, two block-wide sums, one dot product: about 5 us a
 // column); its memory traffic is a few per cent of that.
-template <int NE>
-__global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
+template <int NE> struct TriShared {
+    double vp[NE * 64], wp[NE * 64], vn[NE * 64], red[2][4], first;
+};
+
+// ALL: by one work-group, which takes all the rows.
+template <int NE, bool ALL> __device__ __forceinline__ void tri_column(const EigenArgs& a, int i, TriShared<NE>& sh)
 {
-    __shared__ double vp[NE * 64], wp[NE * 64], vn[NE * 64], red[2][4], first;
+    double (&vp)[NE * 64] = sh.vp, (&wp)[NE * 64] = sh.wp, (&vn)[NE * 64] = sh.vn, (&red)[2][4] = sh.red, &first = sh.first;
     const int b = blockIdx.y, n = a.n, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (eig_skip(a.norm[b])) return;
     double* A = a.A + (size_t)b * a.A_stride;
     const double* cur = i == 0 ? a.src + (size_t)b * a.src_stride : A + n;   // the matrix before the pending update
     double* T = a.T + (size_t)b * 5 * a.t_ld;
@@ -198,15 +201,18 @@ __global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
     double* p_new = T + (size_t)(3 + (i & 1)) * a.t_ld;
 
     // this wave's two rows, requested first
-    const int r0 = i + 1 + (blockIdx.x * 4 + wave) * 2;
+    int r0 = i + 1 + (blockIdx.x * 4 + wave) * 2;
     double x[2][NE];
+    auto fetch = [&]() {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int q = 0; q < NE; ++q) {
-            const int c = 64 * q + lane;
-            x[u][q] = (r0 + u < n && c > i && c < n) ? cur[(size_t)(r0 + u) * n + c] : 0.0;
-        }
+            for (int q = 0; q < NE; ++q) {
+                const int c = 64 * q + lane;
+                x[u][q] = (r0 + u < n && c > i && c < n) ? cur[(size_t)(r0 + u) * n + c] : 0.0;
+            }
+    };
+    fetch();
 
     // column i (row i, the matrix is symmetric) with the previous step's update; at most four entries per thread, always the
     // same ones: tri_chain_kernel adds in this order too
@@ -259,23 +265,36 @@ __global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
         }
     }
     __syncthreads();
+    for (;;) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int r = r0 + u;
-        if (r >= n) continue;   // uniform over the wave
-        const double vr = vp[r], wr = wp[r];
-        double dot = 0.0;
+        for (int u = 0; u < 2; ++u) {
+            const int r = r0 + u;
+            if (r >= n) continue;   // uniform over the wave
+            const double vr = vp[r], wr = wp[r];
+            double dot = 0.0;
 #pragma unroll
-        for (int q = 0; q < NE; ++q) {
-            const int c = 64 * q + lane;
-            if (c <= i || c >= n) continue;
-            const double y = tri_update(x[u][q], vr, wp[c], wr, vp[c]);
-            A[(size_t)(r + 1) * n + c] = y;
-            dot = fma(y, vn[c], dot);
+            for (int q = 0; q < NE; ++q) {
+                const int c = 64 * q + lane;
+                if (c <= i || c >= n) continue;
+                const double y = tri_update(x[u][q], vr, wp[c], wr, vp[c]);
+                A[(size_t)(r + 1) * n + c] = y;
+                dot = fma(y, vn[c], dot);
+            }
+            dot = wave_sum(dot);
+            if (lane == 0) p_new[r] = t * dot;
         }
-        dot = wave_sum(dot);
-        if (lane == 0) p_new[r] = t * dot;
+        r0 += 8;
+        if (!ALL || r0 >= n) break;
+        fetch();
     }
+}
+
+template <int NE>
+__global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
+{
+    __shared__ TriShared<NE> sh;
+    if (eig_skip(a.norm[blockIdx.y])) return;
+    tri_column<NE, false>(a, i, sh);
 }
 
 // All of those steps in one launch, where the matrices' rows find a place in the registers of the chip at once (eight rows
@@ -289,10 +308,13 @@ __global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
 // still takes part is done with slot (i - 2) % 4; those that will write it in step i + 2 put the mark back at the end of step i,
 // and wait for that before they publish p of step i + 1, which every later reader of that slot has to see first.  (With three slots
 // the mark goes back within the step, and a step waited for it: 3.6 against 3.0 us.)  A work-group leaves when its rows are
-// reflected away, so nobody who no longer publishes still reads.  The wait is bounded: a work-group that gives up (never, as
-// long as the grid is resident) reports a solver that did not converge.
+// reflected away, so nobody who no longer publishes still reads.
+//
+// The wait is bounded (a poll takes about 0.7 us).  A work-group whose words do not come, because another process or a long kernel
+// keeps the others off the chip, gives up, says so behind the slots, and the rest stop too, at the latest when they look there;
+// tri_redo_kernel then does the matrix over, with one work-group that waits for nobody.
 #define TRI_CHAIN_MARK 0xFFFFFFFFFFFFFFFFull
-#define TRI_CHAIN_SPINS (1 << 22)
+#define TRI_CHAIN_POLLS (1 << 17)
 
 __global__ __launch_bounds__(256) void tri_chain_clear_kernel(unsigned long long* x, size_t stride, int n)
 {
@@ -315,7 +337,7 @@ __device__ __forceinline__ void chain_publish(unsigned long long* p, double v)
 }
 
 template <int NE>
-__global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
+__global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps, int polls)
 {
     constexpr int NT = (NE + 3) / 4;
     __shared__ double cb[NE * 64], wp[NE * 64], red[2][4], pi_s, first_s;
@@ -325,7 +347,7 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
     const double* src = a.src + (size_t)b * a.src_stride;
     double* A = a.A + (size_t)b * a.A_stride;
     double* T = a.T + (size_t)b * 5 * a.t_ld;
-    unsigned long long* X = a.xchg + (size_t)b * a.xchg_stride;   // [4][2 n]: p, row
+    unsigned long long* X = a.xchg + (size_t)b * a.xchg_stride;   // [4][2 n]: p, row; then the mark while nobody has given up
     const int r0 = (blockIdx.x * 4 + wave) * 2, r_last = blockIdx.x * 8 + 7;
     const bool writer = blockIdx.x == gridDim.x - 1;   // takes part to the end: it keeps the reflectors
 
@@ -341,8 +363,9 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
     }
 #pragma unroll
     for (int u = 0; u < NT; ++u) v[u] = 0.0;
-    if (tid == 0) lost = 0;
+    if (tid == 0) lost = chain_load(X + 8 * n) != TRI_CHAIN_MARK;
     __syncthreads();
+    if (lost) return;   // uniform: nobody polls, and sets it, before the barriers of step 0
 
     double tau = 0.0;   // of the step before
     bool gone = false;
@@ -372,7 +395,7 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
 #pragma unroll
                 for (int u = 0; u < NT; ++u) missing |= pw[u] == TRI_CHAIN_MARK || rw[u] == TRI_CHAIN_MARK;
                 if (!missing) break;
-                if (++spins > TRI_CHAIN_SPINS) { lost = 1; break; }
+                if (++spins >= polls || (spins % 64 == 0 && chain_load(X + 8 * n) != TRI_CHAIN_MARK)) { lost = 1; break; }
             }
 #pragma unroll
             for (int u = 0; u < NT; ++u) {
@@ -474,7 +497,7 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
         }
     }
     if (lost) {
-        if (tid == 0) atomicMax(a.solves + b, GVQ_NO_CONVERGENCE);
+        if (tid == 0) chain_store(X + 8 * n, 0ull);
         return;
     }
     if (gone) return;
@@ -486,6 +509,19 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps)
             const int r = r0 + u, c = 64 * q + lane;
             if (r >= steps && r < n && c >= steps && c < n) A[(size_t)(r + 1) * n + c] = x[u][q];
         }
+}
+
+// The matrices whose chain was given up (none, as a rule), from the start: the same operations in the same order, hence the same bits,
+// a column at a time by one work-group (d = 520 37 ms, 768 93, 1024 220).
+template <int NE>
+__global__ __launch_bounds__(256) void tri_redo_kernel(EigenArgs a, int steps)
+{
+    __shared__ TriShared<NE> sh;
+    if (eig_skip(a.norm[blockIdx.y]) || chain_load(a.xchg + (size_t)blockIdx.y * a.xchg_stride + 8 * a.n) == TRI_CHAIN_MARK) return;
+    for (int i = 0; i < steps; ++i) {
+        tri_column<NE, true>(a, i, sh);
+        __syncthreads();   // this column's rows and entries of p, before the next one reads them
+    }
 }
 
 // The whole matrix (n <= 128), or what is left of a larger one from row i0 on, in the registers of one work-group:
@@ -1273,7 +1309,10 @@ template <int NE> struct go_step {
     static void go(dim3 grid, EigenArgs a, int i, hipStream_t st) { hipLaunchKernelGGL((tri_step_kernel<NE>), grid, dim3(256), 0, st, a, i); }
 };
 template <int NE> struct go_chain {
-    static void go(dim3 grid, EigenArgs a, int steps, hipStream_t st) { hipLaunchKernelGGL((tri_chain_kernel<NE>), grid, dim3(256), 0, st, a, steps); }
+    static void go(dim3 grid, EigenArgs a, int steps, int polls, hipStream_t st) { hipLaunchKernelGGL((tri_chain_kernel<NE>), grid, dim3(256), 0, st, a, steps, polls); }
+};
+template <int NE> struct go_redo {
+    static void go(dim3 grid, EigenArgs a, int steps, hipStream_t st) { hipLaunchKernelGGL((tri_redo_kernel<NE>), grid, dim3(256), 0, st, a, steps); }
 };
 template <int NE> struct go_ortho {
     static void go(double* Z, size_t stride, int k, int n, int B, const unsigned long long* norm, hipStream_t st)
@@ -1332,15 +1371,17 @@ static int launch_chain(const gvq_basis* h, const EigenArgs& a, int steps, hipSt
         return GVQ_OK;
     }
     if (!whole_chip(h, st)) return GVQ_OK;
-    hipLaunchKernelGGL(tri_chain_clear_kernel, dim3((unsigned)((8 * a.n + 255) / 256), h->B), dim3(256), 0, st, a.xchg, a.xchg_stride, 8 * a.n);
+    hipLaunchKernelGGL(tri_chain_clear_kernel, dim3((unsigned)((8 * a.n + 1 + 255) / 256), h->B), dim3(256), 0, st, a.xchg, a.xchg_stride, 8 * a.n + 1);
     GVQ_HIP(hipGetLastError());
     std::lock_guard<std::mutex> guard(lock);
     hipEvent_t& ev = last[h->device];
     if (!ev) GVQ_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
     else GVQ_HIP(hipStreamWaitEvent(st, ev, 0));
-    by_long_pieces<go_chain>(a.n, dim3((unsigned)wgs, h->B), a, steps, st);
+    by_long_pieces<go_chain>(a.n, dim3((unsigned)wgs, h->B), a, steps, gvq_opt_chain_polls() > 0 ? gvq_opt_chain_polls() : TRI_CHAIN_POLLS, st);
     GVQ_HIP(hipGetLastError());
     GVQ_HIP(hipEventRecord(ev, st));
+    by_long_pieces<go_redo>(a.n, dim3(1, h->B), a, steps, st);
+    GVQ_HIP(hipGetLastError());
     *done = true;
     return GVQ_OK;
 }
@@ -1420,7 +1461,7 @@ EigenArgs gvq_eigen_args(const gvq_basis* h)
     a.eig = h->d_eig; a.eig_ld = h->d;
     a.Z = h->d_eZ; a.Z_stride = (size_t)h->k * d;
     a.wy = h->d_mom; a.wy_stride = d * d + d;   // the covariance is made: the moments are not needed any more
-    a.xchg = h->d_eX; a.xchg_stride = 8 * d;
+    a.xchg = h->d_eX; a.xchg_stride = 8 * d + 8;
     a.lu = h->d_eLU; a.lanes = 64; a.clamp = 0; a.solves = h->d_solves;
     return a;
 }

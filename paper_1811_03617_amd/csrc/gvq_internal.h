@@ -60,7 +60,7 @@ struct gvq_basis {
     double* d_eA = nullptr;     // eigensolver: [B][(d+1) d] matrix, then its reflectors (first-slice refresh: samples too)
     double* d_eT = nullptr;     // [B][5 d] tridiagonal matrix and work vectors
     double* d_eZ = nullptr;     // [B][k][d] eigenvectors
-    unsigned long long* d_eX = nullptr;   // d > GVQ_EIGEN_SMALL: [B][8 d] exchange between the work-groups of one matrix
+    unsigned long long* d_eX = nullptr;   // d > GVQ_EIGEN_SMALL: [B][8 d + 8] exchange between the work-groups of one matrix
     double* d_eLU = nullptr;    // d > GVQ_EIGEN_SMALL: factors of the inverse iteration
     int* d_solves = nullptr;    // [B] most solves any eigenvector took (0 = zero matrix), or GVQ_NO_CONVERGENCE
     int* d_ksel = nullptr;      // [B] result of the last gvq_select_k
@@ -115,6 +115,8 @@ int gvq_opt_no_fast();
 int gvq_opt_pace();
 // Super-tiles whose 1 KB rows interleave in the fast phase (CodecArgs::il), 0 = each kernel's default, 1 = none.
 int gvq_opt_interleave();
+// Polls of the one-launch tridiagonalisation before it gives up, 0 = its default.
+int gvq_opt_chain_polls();
 
 // Kernel launchers (each only enqueues on `st`; returns GVQ_OK or GVQ_EHIP).
 int gvq_launch_compress(const gvq_basis* h, const void* grad, int n_workers, int64_t first_slice,

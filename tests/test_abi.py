@@ -39,6 +39,8 @@ def test_strerror_and_option_checks():
     assert gvq.lib().gvq_set_option(5, 4097) == gvq.EINVAL
     assert gvq.lib().gvq_set_option(5, -1) == gvq.EINVAL
     assert gvq.lib().gvq_set_option(5, 0) == gvq.OK
+    assert gvq.lib().gvq_set_option(6, -1) == gvq.EINVAL
+    assert gvq.lib().gvq_set_option(6, 0) == gvq.OK
 
 
 @pytest.mark.parametrize("M,d,k,nb,offs", [

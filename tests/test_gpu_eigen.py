@@ -272,6 +272,42 @@ def test_refresh_on_a_stream_with_few_compute_units(d, k, B, units):
     assert hip.hipStreamDestroy(stream) == 0
 
 
+@pytest.mark.parametrize("d,k,B", [(129, 129, 1), (136, 9, 14), (257, 20, 3), (520, 24, 1), (768, 96, 1), (1024, 5, 2)])
+def test_refresh_whose_work_groups_stop_waiting(d, k, B):
+    """Option 6: the one launch gives up at the first word that has not arrived, and the columns are done over one by one: the
+    bits of the undisturbed refresh, many times its time (which shows that the launch did give up).  One basis is constant."""
+    gen = torch.Generator(device=DEV).manual_seed(d)
+    x = torch.randn(B, d + 9, d, generator=gen, device=DEV)
+    if B > 2:
+        x[1] = 0.5
+    x = x.reshape(-1)
+    b = gvq.Basis(x.numel(), d, k, [i * (d + 9) for i in range(B + 1)])
+
+    def refresh():
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        b.fit([x])
+        end.record()
+        solves = b.fit_status()
+        return solves, start.elapsed_time(end), b.export()
+
+    refresh()
+    solves, usual, want = refresh()
+    for polls in (1, 0):
+        try:
+            gvq.gvq_set_option(6, polls)
+            got = refresh()
+        finally:
+            gvq.gvq_set_option(6, 0)
+        print(d, B, polls, usual, got[1])
+        assert got[0] == solves
+        for a, w in zip(got[2], want):
+            assert np.array_equal(a, w)
+        if polls and d > 200:
+            assert got[1] > 2 * usual
+    b.close()
+
+
 class _Busy:
     """A stream with a long, finite queue: copies that take about a quarter of a second."""
 
