@@ -72,6 +72,7 @@ int gvq_basis_destroy(gvq_basis_t* h)
 {
     if (!h) return GVQ_OK;
     (void)hipDeviceSynchronize();
+    gvq_chain_forget(h);
     void* dev[] = {h->d_offs, h->d_tile_block, h->d_U, h->d_Upc, h->d_Upd, h->d_Upb, h->d_Uws, h->d_Umu, h->d_mu, h->d_eig, h->d_cov, h->d_eA, h->d_eT, h->d_eZ, h->d_eX, h->d_eLU, h->d_part, h->d_mom, h->d_nsamp, h->d_ltile, h->d_Ufc, h->d_Ufd, h->d_ftile, h->d_solves, h->d_ksel, h->d_Uls, h->d_loss_slice, h->d_loss_part};
     for (void* p : dev)
         if (p) (void)hipFree(p);
@@ -169,7 +170,8 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
         TRY(hipMalloc((void**)&h->d_nsamp, sizeof(unsigned long long) * 2 * B));
         TRY(hipMalloc((void**)&h->d_solves, sizeof(int) * B));
         TRY(hipMalloc((void**)&h->d_ksel, sizeof(int) * B));
-        TRY(hipHostMalloc((void**)&h->h_notes, sizeof(unsigned long long), hipHostMallocDefault));
+        TRY(hipHostMalloc((void**)&h->h_notes, 2 * sizeof(unsigned long long), hipHostMallocDefault));
+        h->h_notes[0] = h->h_notes[1] = 0;
         if (gvq_loss_split_shape(h)) TRY(hipMalloc((void**)&h->d_Uls, sizeof(unsigned short) * gvq_loss_split_pack_halves(d)));
         // the same memory takes the sums of gvq_launch_loss_split
         TRY(hipMalloc((void**)&h->d_loss_slice, sizeof(float) * (size_t)(S > 2 * GVQ_LOSS_MAX_PARTS ? S : 2 * GVQ_LOSS_MAX_PARTS)));

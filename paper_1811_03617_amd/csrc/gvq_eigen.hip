@@ -513,10 +513,12 @@ __global__ __launch_bounds__(256) void tri_chain_kernel(EigenArgs a, int steps, 
 
 // The matrices whose chain was given up (none, as a rule), from the start: the same operations in the same order, hence the same bits,
 // a column at a time by one work-group (d = 520 37 ms, 768 93, 1024 220).
+// The launch that waits inside is over when this one starts: `note` says so to the host.
 template <int NE>
-__global__ __launch_bounds__(256) void tri_redo_kernel(EigenArgs a, int steps)
+__global__ __launch_bounds__(256) void tri_redo_kernel(EigenArgs a, int steps, unsigned long long* note, unsigned long long ticket)
 {
     __shared__ TriShared<NE> sh;
+    if (blockIdx.y == 0 && threadIdx.x == 0) __hip_atomic_store(note, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (eig_skip(a.norm[blockIdx.y]) || chain_load(a.xchg + (size_t)blockIdx.y * a.xchg_stride + 8 * a.n) == TRI_CHAIN_MARK) return;
     for (int i = 0; i < steps; ++i) {
         tri_column<NE, true>(a, i, sh);
@@ -1312,7 +1314,10 @@ template <int NE> struct go_chain {
     static void go(dim3 grid, EigenArgs a, int steps, int polls, hipStream_t st) { hipLaunchKernelGGL((tri_chain_kernel<NE>), grid, dim3(256), 0, st, a, steps, polls); }
 };
 template <int NE> struct go_redo {
-    static void go(dim3 grid, EigenArgs a, int steps, hipStream_t st) { hipLaunchKernelGGL((tri_redo_kernel<NE>), grid, dim3(256), 0, st, a, steps); }
+    static void go(dim3 grid, EigenArgs a, int steps, unsigned long long* note, unsigned long long ticket, hipStream_t st)
+    {
+        hipLaunchKernelGGL((tri_redo_kernel<NE>), grid, dim3(256), 0, st, a, steps, note, ticket);
+    }
 };
 template <int NE> struct go_ortho {
     static void go(double* Z, size_t stride, int k, int n, int B, const unsigned long long* norm, hipStream_t st)
@@ -1353,16 +1358,32 @@ static bool whole_chip(const gvq_basis* h, hipStream_t st)
     return units >= h->num_cu;
 }
 
+// The last launch on a device whose work-groups wait for each other: it is over when its handle's note holds the ticket.
+struct ChainTurn {
+    const gvq_basis* owner = nullptr;
+    hipStream_t stream = nullptr;
+    unsigned long long ticket = 0;
+};
+static std::mutex g_chain_lock;
+static ChainTurn g_chain_last[GVQ_MAX_DEVICES];
+
+void gvq_chain_forget(const gvq_basis* h)
+{
+    std::lock_guard<std::mutex> guard(g_chain_lock);
+    for (ChainTurn& t : g_chain_last)
+        if (t.owner == h) t = ChainTurn();
+}
+
 // All columns up to the trailing block in one launch (*done), where every work-group (8 rows) has a compute unit to itself;
 // more matrices than that take turns, and a launch per column serves them all at once.  Work-groups that wait for each other
-// have to be on the chip together, so such launches of one process wait for one another, whatever their streams: two of
-// them, each half resident, would wait for ever.  Two kinds of stream keep the launches per column: one that is being captured, as
-// the graph may be replayed beside anything, and one that may not use every compute unit, as work-groups are dealt to the eight
-// parts of the chip in turn, however many units of each the mask leaves.
+// have to be on the chip together, so two such launches must not run side by side, each half resident.  A stream keeps its
+// own apart; while another stream's is queued or running, this refresh takes the launches per column, which wait for nobody
+// (an event between the streams would make it wait for all that the other stream had queued before).  So do two kinds of
+// stream: one that is being captured, as the graph may be replayed beside anything, and one that may not use every compute
+// unit, as work-groups are dealt to the eight parts of the chip in turn, however many units of each the mask leaves.
 static int launch_chain(const gvq_basis* h, const EigenArgs& a, int steps, hipStream_t st, bool* done)
 {
-    static std::mutex lock;
-    static hipEvent_t last[GVQ_MAX_DEVICES];
+    static unsigned long long tickets = 0;
     const int wgs = (a.n + 7) / 8;
     if ((int64_t)wgs * h->B > h->num_cu || h->device < 0 || h->device >= GVQ_MAX_DEVICES) return GVQ_OK;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -1371,16 +1392,16 @@ static int launch_chain(const gvq_basis* h, const EigenArgs& a, int steps, hipSt
         return GVQ_OK;
     }
     if (!whole_chip(h, st)) return GVQ_OK;
+    std::lock_guard<std::mutex> guard(g_chain_lock);
+    ChainTurn& last = g_chain_last[h->device];
+    const bool same = last.stream == st && st != hipStreamPerThread;   // that handle names another stream in each thread
+    if (last.owner && !same && ((const volatile unsigned long long*)last.owner->h_notes)[1] != last.ticket) return GVQ_OK;
     hipLaunchKernelGGL(tri_chain_clear_kernel, dim3((unsigned)((8 * a.n + 1 + 255) / 256), h->B), dim3(256), 0, st, a.xchg, a.xchg_stride, 8 * a.n + 1);
     GVQ_HIP(hipGetLastError());
-    std::lock_guard<std::mutex> guard(lock);
-    hipEvent_t& ev = last[h->device];
-    if (!ev) GVQ_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-    else GVQ_HIP(hipStreamWaitEvent(st, ev, 0));
     by_long_pieces<go_chain>(a.n, dim3((unsigned)wgs, h->B), a, steps, gvq_opt_chain_polls() > 0 ? gvq_opt_chain_polls() : TRI_CHAIN_POLLS, st);
     GVQ_HIP(hipGetLastError());
-    GVQ_HIP(hipEventRecord(ev, st));
-    by_long_pieces<go_redo>(a.n, dim3(1, h->B), a, steps, st);
+    last = ChainTurn{h, st, ++tickets};
+    by_long_pieces<go_redo>(a.n, dim3(1, h->B), a, steps, h->h_notes + 1, last.ticket, st);
     GVQ_HIP(hipGetLastError());
     *done = true;
     return GVQ_OK;

@@ -65,7 +65,8 @@ struct gvq_basis {
     int* d_solves = nullptr;    // [B] most solves any eigenvector took (0 = zero matrix), or GVQ_NO_CONVERGENCE
     int* d_ksel = nullptr;      // [B] result of the last gvq_select_k
     unsigned long long* h_notes = nullptr;  // pinned host memory that kernels write: [0] gvq_fit_status's answer in one word (calls
-                                            // that overlap on the same fit write the same one)
+                                            // that overlap on the same fit write the same one), [1] ticket of the last
+                                            // launch that waits inside (gvq_eigen.hip)
     float* d_loss_slice = nullptr;  // [S] per-slice squared residual of the last gvq_local_loss (gvq_monitor.hip: its sums)
     double* d_loss_part = nullptr;  // [B][loss_groups] partial sums of those
     int loss_groups = 1;
@@ -181,6 +182,7 @@ int gvq_launch_compress_ws(const gvq_basis* h, const void* grad, int n_workers, 
 size_t gvq_eigen_lu_doubles(int d, int k);   // doubles per basis of d_eLU
 // d_cov (made from d_mom first if from_moments) -> d_eig, d_U.
 int gvq_launch_eigen(const gvq_basis* h, bool from_moments, hipStream_t st);
+void gvq_chain_forget(const gvq_basis* h);   // before the handle goes: nothing of it is queued any more
 int gvq_launch_fit_status(const gvq_basis* h, hipStream_t st);   // -> h_notes[0]: most solves, 1 << 32 no convergence, 2 << 32 not finite
 bool gvq_sample_shape(int d, int L);         // first-slice refresh: gvq_launch_fit_samples takes it
 int gvq_launch_fit_samples(const gvq_basis* h, const void* const* grads, int L, hipStream_t st);

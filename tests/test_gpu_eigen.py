@@ -343,3 +343,34 @@ def test_status_waits_for_its_own_stream_only():
     torch.cuda.synchronize()
     assert early
     b.close()
+
+
+def test_refresh_does_not_wait_for_another_stream():
+    """A refresh above 128 elements that is queued behind long work on one stream does not hold up a refresh on another, nor the
+    next one on its own stream; all have the bits of one done alone."""
+    n, d, k = 5, 520, 24
+    gen = torch.Generator(device=DEV).manual_seed(6)
+    xs = [torch.randn(600 * d, generator=gen, device=DEV) for _ in range(n)]
+    bases = [gvq.Basis(600 * d, d, k) for _ in range(n)]
+    alone = []
+    for b, x in zip(bases, xs):
+        b.fit([x])
+        b.fit_status()
+        alone.append(b.export())
+    busy = _Busy()
+    streams = [torch.cuda.Stream() for _ in range(n - 2)]
+    busy.start()
+    for b, x in zip(bases[:2], xs):
+        b.fit([x], stream=busy.stream.cuda_stream)
+    busy.end()
+    early = 0
+    for b, x, s in zip(bases[2:], xs[2:], streams):   # several: two may share a hardware queue
+        b.fit([x], stream=s.cuda_stream)
+        assert b.fit_status(stream=s.cuda_stream) >= 2
+        early += not busy.done.query()
+    torch.cuda.synchronize()
+    assert early
+    for b, want in zip(bases, alone):
+        for got, w in zip(b.export(), want):
+            assert np.array_equal(got, w)
+        b.close()
