@@ -228,18 +228,46 @@ inline bool flow_too_small(const FlowShape& s, const FlowPlan& p)
 }
 
 // The register-resident kernels of gvq_codec.hip keep a shape of theirs whose comps are whole words.  Of the others, which go
-// through their bounds-checked loop, compress of many short slices comes here (60 M elements, there / here, us, f32 and bf16:
-// d = 16, k = 5 86 / 72 and 116 / 70; d = 32, k = 11 64 / 58 and 85 / 49; d = 64, k = 21 81 / 66 and 68 / 63); fewer slices (10 M elements f32:
-// d = 16 17 / 19, d = 32 13 / 15, d = 64 17 / 17; bf16 22 / 18, 16 / 13, 14 / 16), few comps at d = 64 (k = 6 f32 48 / 50, bf16
-// 33 / 43), d = 128 (k = 13 49 / 52) and decompress (d = 16, k = 5 72 / 78) do not.
+// through their bounds-checked loop, compress of many short slices comes here, with enough tiles (8192 elements) for every
+// work-group of the chip and, with several bases, enough of them per basis: each basis ends with a tile that is partly empty,
+// and a work-group loads U anew for it.  Here / there, 1 = level, 1 to 100 M elements, one basis down to 3000 elements per basis:
+//   d = 16: f32 from 16 M elements on 0.72 - 1.0, 6000 a basis 0.8 - 1.07, 3000 1.0 - 1.4, 8 M elements 1.07 - 1.2; bf16 from 16 M on
+//     0.55 - 0.99 down to 6000 a basis, 3000 k = 2 and 5 0.86 - 0.91, 11 and 15 1.0 - 1.25, 8 M elements 0.83 - 1.0 and 0.95 - 1.1;
+//   d = 32, k <= 16: f32 from 32 M on 0.85 - 0.97, 15000 a basis 0.92 - 0.95, 20000 0.95 - 1.07, 10000 1.06 - 1.16; bf16 from 16 M
+//     on 0.56 - 0.96 down to 20000 a basis, 6000 and 10000 0.74 - 1.1, 8 M elements one basis 0.85, several 1.07 - 1.3;
+//   d = 32, k > 16: f32 from 32 M on and bf16 from 6.4 M on 0.5 - 0.9 down to 6000 a basis, 3000 k = 22 1.0 - 1.1, 30 0.83 - 0.95;
+//   d = 64, from 32 M on: f32 k = 17 1.0 - 1.1, 19 to 29 0.7 - 0.99, 15000 a basis 0.85 - 0.91, 20000 0.85 - 1.08, 10000 1.0 - 1.25; bf16
+//     k = 17 and 19 1.0 - 1.25, 21 0.9 - 1.06 (from 48 M on 0.87 - 0.98), 26 and 29 0.75 - 0.97, 10000 a basis 1.02 - 1.16.
+// d = 128 (k = 13, 21: 0.96 - 1.5), fewer comps at d = 64 and decompress (d = 16, k = 5 78 / 72 us) stay there.
 inline bool flow_resident_shape(int d, int k) { return k <= 32 && (d == 16 || d == 32 || d == 64 || d == 128); }
+
+inline bool flow_takes_resident_compress(const FlowShape& s)
+{
+    double each, per_basis;   // fewest tiles per work-group, two on a unit, and per basis
+    if (s.d == 16) {
+        each = s.bf16 && s.k < 8 ? 1.9 : 3.8;
+        per_basis = s.bf16 && s.k < 8 ? 0.3 : 0.6;
+    } else if (s.d == 32 && s.k <= 16) {
+        each = !s.bf16 ? 7.6 : s.bases > 1 ? 3.8 : 1.5;
+        per_basis = s.bf16 ? 0.6 : 1.5;
+    } else if (s.d == 32) {
+        each = s.bf16 ? 1.5 : 7.6;
+        per_basis = s.k > 24 ? 0.3 : 0.6;
+    } else if (s.d == 64 && s.k > (s.bf16 ? 20 : 18)) {
+        each = s.bf16 && s.k <= 24 ? 11 : 7.6;
+        per_basis = 1.5;
+    } else {
+        return false;
+    }
+    const double tiles = (double)s.slices * s.d / 8192;
+    return s.k % 4 != 0 && tiles >= each * 2 * s.cus && (s.bases == 1 || tiles >= per_basis * s.bases);
+}
 
 inline bool flow_takes_compress(const FlowShape& s)
 {
     const FlowPlan p = flow_compress_plan(s.d, s.k);
     if (!p.waves) return false;
-    if (flow_resident_shape(s.d, s.k)) 
-        return s.k % 4 != 0 && p.exact && (s.d <= 32 ? s.slices >= (s.bf16 ? 200000 : 1000000) : s.d == 64 && s.k > 16 && s.slices >= 500000);
+    if (flow_resident_shape(s.d, s.k)) return p.exact && flow_takes_resident_compress(s);
     if (!s.bf16 && flow_too_small(s, p)) return false;
     if (s.d % 4) return true;
     // U over eight waves (f32 d = 400, k = 100 1.18, bf16 d = 500, k = 128 1.24); above 256 elements with bf16 storage or

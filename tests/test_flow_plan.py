@@ -194,3 +194,30 @@ int main()
     return bad;
 }
 """)
+
+
+def test_resident_shapes_with_ragged_comps(tmp_path):
+    """Which of them the whole-slice kernels take for compress: measured times of both on either side of every line."""
+    _run(tmp_path, r"""
+struct Case { int d, k; bool bf16; double million; int per_basis; bool here; };   // elements per basis, 0: one basis
+int main()
+{
+    const Case cases[] = {
+        {16, 5, false, 16.1, 0, true}, {16, 5, false, 12, 0, false}, {16, 5, false, 48, 6000, true}, {16, 5, false, 60, 3000, false},
+        {16, 11, true, 16.1, 6000, true}, {16, 11, true, 8, 0, false}, {16, 11, true, 60, 3000, false}, {16, 4, false, 60, 0, false},
+        {16, 2, true, 8.1, 0, true}, {16, 2, true, 4, 0, false}, {16, 5, true, 60, 3000, true}, {16, 5, true, 60, 1000, false},
+        {32, 11, false, 32.1, 0, true}, {32, 11, false, 16, 0, false}, {32, 11, false, 60, 15000, true}, {32, 11, false, 48, 10000, false},
+        {32, 11, true, 8, 0, true}, {32, 11, true, 8, 1000000, false}, {32, 11, true, 24, 6000, true}, {32, 3, true, 60, 3000, false},
+        {32, 30, false, 32.1, 3000, true}, {32, 30, true, 8, 0, true}, {32, 22, false, 100, 3000, false}, {32, 22, true, 48, 6000, true},
+        {64, 19, false, 32.1, 0, true}, {64, 17, false, 60, 0, false}, {64, 17, true, 60, 0, false}, {64, 21, true, 48, 0, true},
+        {64, 21, true, 32, 0, false}, {64, 29, true, 32.1, 15000, true}, {64, 29, true, 60, 3000, false}, {64, 29, false, 60, 10000, false},
+        {64, 30, true, 60, 0, false}, {128, 13, false, 60, 0, false}};
+    for (const Case& c : cases)
+        for (int cus : {256, 128}) {   // half the chip: half the size
+            const int64_t M = (int64_t)(c.million * 1e6) * cus / 256;
+            const int bases = c.per_basis ? (int)(M / c.per_basis) : 1;
+            if (flow_takes_compress(FlowShape{c.d, c.k, bases, c.bf16, M / c.d, cus}) != c.here) { printf("d %d k %d %g M\n", c.d, c.k, c.million); return 1; }
+        }
+    return 0;
+}
+""")
