@@ -841,11 +841,13 @@ static int launch_long(const gvq_basis* h, const LongArgs& a, int NT, hipStream_
 {
     const size_t lds = sizeof(f4) * 2 * 4 * NT * 64 + sizeof(float) * (size_t)a.nchunk * LC;
     static gvq_once_per_device once;
-    if (once.first(h->device)) {
+    const int rc = once.call(h->device, [&]() -> int {
         // the largest slice needs 8 KB NT + 4 KB: allow it once, for every later launch
         GVQ_HIP(hipFuncSetAttribute((const void*)KERN, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)(sizeof(f4) * 2 * 4 * NT * 64 + sizeof(float) * GVQ_MAX_D)));
-    }
+        return GVQ_OK;
+    });
+    if (rc != GVQ_OK) return rc;
     int per_cu = gvq_opt_wg_per_cu();
     if (per_cu <= 0) {
         // asked once per kernel and LDS size (the size changes with the slice length only)

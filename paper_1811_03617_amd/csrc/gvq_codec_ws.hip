@@ -645,8 +645,11 @@ template <auto KERN>
 static int launch_ws(const gvq_basis* h, const WsArgs& a, size_t lds, int nbuf, hipStream_t st)
 {
     static gvq_once_per_device once;   // per kernel
-    if (once.first(h->device))
+    const int rc = once.call(h->device, [&]() -> int {
         GVQ_HIP(hipFuncSetAttribute((const void*)KERN, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+        return GVQ_OK;
+    });
+    if (rc != GVQ_OK) return rc;
     int64_t grid = a.ntiles < h->num_cu ? a.ntiles : h->num_cu;   // one work-group per compute unit
     if (grid < 1) grid = 1;   // only the slices after the last whole tile
     hipLaunchKernelGGL(KERN, dim3((unsigned)grid), dim3(512), lds, st, a, nbuf);
@@ -710,9 +713,12 @@ static int launch_wsd(const gvq_basis* h, const WsdArgs& a, hipStream_t st)
     constexpr size_t lds = sizeof(float) * (2 * 16 * (D + WS_ROWPAD) + WSD_NY * 4 * 64 * ((16 * (8 * NKS + 1) + 63) / 64) + D);
     static_assert(lds <= 160 * 1024, "LDS");
     static gvq_once_per_device once;
-    if (once.first(h->device))
+    const int rc = once.call(h->device, [&]() -> int {
         GVQ_HIP(hipFuncSetAttribute((const void*)decompress_ws_kernel<STEPS, NKS, EXACT, OBF>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        return GVQ_OK;
+    });
+    if (rc != GVQ_OK) return rc;
     int64_t grid = a.ntiles < h->num_cu ? a.ntiles : h->num_cu;   // one work-group per compute unit
     if (grid < 1) grid = 1;
     hipLaunchKernelGGL((decompress_ws_kernel<STEPS, NKS, EXACT, OBF>), dim3((unsigned)grid), dim3(512), lds, st, a);

@@ -1433,18 +1433,23 @@ int gvq_launch_sym_eigen(const gvq_basis* h, EigenArgs a, bool ortho, hipStream_
     if (n <= GVQ_EIGEN_SMALL) {
         const size_t lds = sizeof(double) * 5 * n * 16;
         static gvq_once_per_device once;
-        if (once.first(h->device))
+        const int rc = once.call(h->device, [&]() -> int {
             GVQ_HIP(hipFuncSetAttribute((const void*)(inverse_kernel<16, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                         (int)(sizeof(double) * 5 * GVQ_EIGEN_SMALL * 16)));
+            return GVQ_OK;
+        });
+        if (rc != GVQ_OK) return rc;
         hipLaunchKernelGGL((inverse_kernel<16, true>), dim3((unsigned)((a.k + 15) / 16), B), dim3(64), lds, st, a);
     } else if (const int nv = n <= EIG_LDS4_ROWS ? 4 : 2; (int64_t)((a.k + nv - 1) / nv) * B <= h->num_cu) {
         static gvq_once_per_device once;
-        if (once.first(h->device)) {
+        const int rc = once.call(h->device, [&]() -> int {
             GVQ_HIP(hipFuncSetAttribute((const void*)(inverse_kernel<4, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                         (int)(sizeof(double) * 5 * EIG_LDS4_ROWS * 4)));
             GVQ_HIP(hipFuncSetAttribute((const void*)(inverse_kernel<2, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                         (int)(sizeof(double) * 5 * GVQ_MAX_D * 2)));
-        }
+            return GVQ_OK;
+        });
+        if (rc != GVQ_OK) return rc;
         const dim3 grid((unsigned)((a.k + nv - 1) / nv), B);
         if (nv == 4) hipLaunchKernelGGL((inverse_kernel<4, true>), grid, dim3(64), sizeof(double) * 5 * n * 4, st, a);
         else hipLaunchKernelGGL((inverse_kernel<2, true>), grid, dim3(64), sizeof(double) * 5 * n * 2, st, a);

@@ -468,8 +468,11 @@ int gvq_launch_moments(gvq_basis* h, const void* const* grads, int L, hipStream_
         const dim3 grid((unsigned)(a.np * a.chunks_diag + poff * a.chunks_off), (unsigned)h->B);
         static gvq_once_per_device once[4];
         auto launch = [&](auto kern, int lds) -> int {
-            if (once[(h->dtype == GVQ_BF16 ? 1 : 0) + (a.np > 1 ? 2 : 0)].first(h->device))
+            const int ready = once[(h->dtype == GVQ_BF16 ? 1 : 0) + (a.np > 1 ? 2 : 0)].call(h->device, [&]() -> int {
                 GVQ_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+                return GVQ_OK;
+            });
+            if (ready != GVQ_OK) return ready;
             for (int l0 = 0; l0 < L; l0 += GVQ_MAX_PTRS) {
                 a.L = L - l0 < GVQ_MAX_PTRS ? L - l0 : GVQ_MAX_PTRS;
                 for (int i = 0; i < a.L; ++i) a.grads.p[i] = grads[l0 + i];
