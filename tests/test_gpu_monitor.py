@@ -175,3 +175,75 @@ def test_local_loss_three_term_products_at_the_ends_of_the_range(scale):
         b.local_loss(torch.from_numpy(x).to(DEV).reshape(-1), 1, out)
         assert np.isnan(float(out))
     b.close()
+
+
+def _bf16_terms(v, nearest):
+    """fp32 numbers as three bf16 terms, each what the ones before leave, cut off or rounded to nearest even."""
+    terms, rest = [], v.astype(np.float32)
+    for _ in range(3):
+        bits = rest.view(np.uint32)
+        if nearest:
+            bits = bits + (0x7FFF + ((bits >> 16) & 1)).astype(np.uint32)
+        t = (bits & np.uint32(0xFFFF0000)).view(np.float32)
+        terms.append(t.astype(np.float64))
+        rest = rest - t
+    return terms
+
+
+def _emulated_residual(c, U, first=(), second=()):
+    """|c - U U^T c| with both products made of terms, i + j <= 2 but for the pairs named; sums in float64."""
+    def product(a, b, dropped):
+        return sum(a[i] @ b[j] for i in range(3) for j in range(3 - i) if (i, j) not in dropped)
+    u = _bf16_terms(U, True)
+    y = product(_bf16_terms(c, False), u, first).astype(np.float32)
+    return np.linalg.norm(c.astype(np.float64) - product(_bf16_terms(y, False), [t.T for t in u], second))
+
+
+@pytest.mark.parametrize("d,k", [(64, 17), (64, 32), (128, 17), (128, 21), (128, 32)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_local_loss_keeps_all_six_products(d, k, dtype):
+    """Slices that lie in the span of U but for the rounding of their elements: the residual is what the arithmetic leaves.  It is r + e,
+    e: the roundings of fp32 sums (6 d / 32 + 6 products of 32 terms each, at random: their root, 7 at most, times 2^-25),
+    of c = x - mu / N (2^-25 of |c| and |mu| / N each) and the products that are left out (3 * 2^-24 at most), so | |r + e| - |r| | <=
+    8 * 2^-24 |c|.  Leaving out any one of the six products of either contraction gives more, as the emulation shows here."""
+    rng = np.random.default_rng(d + k)
+    U = np.linalg.qr(rng.standard_normal((d, k)))[0].astype(np.float32)
+    U64 = U.astype(np.float64)
+    bound, worst, seen = 8 * 2.0 ** -24, 0.0, {}
+    for S in (5, 16, 37, 64 * 2048 // d, 131 * 2048 // d + 17, 3000 * 2048 // d + 1):
+        n = min(S, 400)
+        if dtype == "f32":
+            mu = rng.standard_normal(d).astype(np.float32)
+            x = (rng.standard_normal((n, k)) @ U64.T + mu / 3.0).astype(np.float32)
+        else:   # one slice; the mean makes up for its rounding to bf16
+            v = rng.standard_normal((1, k)) @ U64.T
+            x = (v.astype(np.float32).view(np.uint32) & np.uint32(0xFFFF0000)).view(np.float32)
+            mu = (3.0 * (x - v)).astype(np.float32)[0]
+        x = x[np.arange(S) % len(x)]
+        c = x[:n].astype(np.float64) - mu.astype(np.float64) / 3
+        times = np.bincount(np.arange(S) % n, minlength=n)
+        want = np.sqrt(times @ np.sum((c - (c @ U64) @ U64.T) ** 2, axis=1))
+        size = np.sqrt(times @ np.sum(c ** 2, axis=1))
+        b = gvq.Basis(S * d, d, k, None, dtype)
+        b.import_(U, mu)
+        g = torch.from_numpy(x.reshape(-1)).to(DEV).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+        out = torch.empty(1, device=DEV, dtype=torch.float64)
+        for mask in (0, 1):
+            try:
+                gvq.gvq_set_option(3, mask)
+                b.local_loss(g, 3, out)
+            finally:
+                gvq.gvq_set_option(3, 0)
+            err = abs(float(out) ** 0.5 - want) / size
+            worst = max(worst, err)
+            assert err <= bound, (S, mask, err * 2 ** 24)
+        b.close()
+        c32 = c.astype(np.float32)
+        r, size = np.linalg.norm(c - (c @ U64) @ U64.T), np.linalg.norm(c)
+        assert abs(_emulated_residual(c32, U) - r) <= bound * size / 4
+        for pair in ((0, 0), (0, 1), (1, 0), (1, 1), (0, 2), (2, 0)):
+            for which in ("first", "second"):
+                lost = abs(_emulated_residual(c32, U, **{which: (pair,)}) - r) / size
+                seen[which, pair] = max(seen.get((which, pair), 0.0), lost)
+    print(d, k, dtype, "worst", worst * 2 ** 24, "least lost", min(seen.values()) * 2 ** 24)
+    assert min(seen.values()) > bound

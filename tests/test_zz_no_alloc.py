@@ -47,6 +47,14 @@ def test_static_scratch_entry_point_matches_on_two_calls_in_a_row():
     _case(768 * 500 + 100, 768, 96, [0, 200, 501], "f32", 3, 3)
 
 
+@pytest.mark.parametrize("d,k", [(64, 17), (64, 32), (128, 21), (128, 32)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_static_scratch_entry_point_one_basis_many_comps(d, k, dtype):
+    """The kernels whose sums are float64: a gradient that fills the chip, then ones of a few slices, of one and of less."""
+    for i, M in enumerate((1500 * 2048 + 40, 16 * d + 5, d, 3)):
+        _case(M, d, k, None, dtype, 3, 10 + i)
+
+
 def test_static_scratch_entry_point_rejects_what_does_not_fit():
     import ctypes as C
     M, d, k = 2 * (gvq.STATIC_MAX_SLICES + 1), 2, 1
