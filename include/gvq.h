@@ -20,7 +20,8 @@
  *     aggregate and decompress only enqueue kernels on it and never synchronise the device;
  *     buffers must stay valid until that work has finished;
  *   - the library owns the handle and the scratch memory inside it (allocated by
- *     gvq_basis_create, released by gvq_basis_destroy) and nothing else;
+ *     gvq_basis_create, 16 bytes for d <= 128 by the first gvq_fit_status, released by
+ *     gvq_basis_destroy) and nothing else;
  *   - calls on one handle must not overlap in time on different streams;
  *   - the first launch of a kernel in a process asks the runtime once for its occupancy and,
  *     for some kernels, raises its LDS limit; these queries are not stream work, so call an

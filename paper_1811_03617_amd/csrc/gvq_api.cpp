@@ -5,6 +5,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <mutex>
 #include <new>
 
 #include "gvq_internal.h"
@@ -90,6 +91,16 @@ int gvq_basis_destroy(gvq_basis_t* h)
     return GVQ_OK;
 }
 
+// (13 us, a third of what the handle of a short-slice codec takes to create, which may never be fitted)
+static int alloc_notes(gvq_basis* h)
+{
+    unsigned long long* p = nullptr;
+    GVQ_HIP(hipHostMalloc((void**)&p, 2 * sizeof(unsigned long long), hipHostMallocDefault));
+    p[0] = p[1] = 0;
+    h->h_notes = p;
+    return GVQ_OK;
+}
+
 int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blocks,
                      const int64_t* offs, gvq_dtype_t dtype)
 {
@@ -170,8 +181,10 @@ int gvq_basis_create(gvq_basis_t** out, int64_t n_elems, int d, int k, int n_blo
         TRY(hipMalloc((void**)&h->d_nsamp, sizeof(unsigned long long) * 2 * B));
         TRY(hipMalloc((void**)&h->d_solves, sizeof(int) * B));
         TRY(hipMalloc((void**)&h->d_ksel, sizeof(int) * B));
-        TRY(hipHostMalloc((void**)&h->h_notes, 2 * sizeof(unsigned long long), hipHostMallocDefault));
-        h->h_notes[0] = h->h_notes[1] = 0;
+        if (d > GVQ_EIGEN_SMALL) {   // their fits write one of them; the others' first gvq_fit_status makes them
+            rc = alloc_notes(h);
+            if (rc != GVQ_OK) goto fail;
+        }
         if (gvq_loss_split_shape(h)) TRY(hipMalloc((void**)&h->d_Uls, sizeof(unsigned short) * gvq_loss_split_pack_halves(d)));
         // the same memory takes the sums of gvq_launch_loss_split
         TRY(hipMalloc((void**)&h->d_loss_slice, sizeof(float) * (size_t)(S > 2 * GVQ_LOSS_MAX_PARTS ? S : 2 * GVQ_LOSS_MAX_PARTS)));
@@ -248,7 +261,13 @@ int gvq_fit_status(const gvq_basis_t* h, int* max_solves, void* stream)
     int current = h->device;
     GVQ_HIP(hipGetDevice(&current));
     if (current != h->device) GVQ_HIP(hipSetDevice(h->device));
-    int rc = gvq_launch_fit_status(h, (hipStream_t)stream);
+    int rc = GVQ_OK;
+    {
+        static std::mutex lock;   // callers may ask from several threads
+        std::lock_guard<std::mutex> guard(lock);
+        if (!h->h_notes) rc = alloc_notes(const_cast<gvq_basis*>(h));
+    }
+    if (rc == GVQ_OK) rc = gvq_launch_fit_status(h, (hipStream_t)stream);
     if (rc == GVQ_OK) {
         const hipError_t e = hipStreamSynchronize((hipStream_t)stream);
         if (e != hipSuccess) rc = gvq_hip_fail(e, "hipStreamSynchronize");

