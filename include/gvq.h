@@ -275,7 +275,7 @@ const char* gvq_strerror(int status);
  *             loop whose 1 KB rows interleave, so that the waves running side by side sweep one compact
  *             window of memory row by row; 1 = none, at most 4096; results are identical;
  *   option 6: refresh with slices of more than 128 elements: how often a work-group looks for the others' results before it
- *             gives up and the reduction is done over without such waits (default 2^17, about 0.1 s); 1 = at the first miss;
+ *             gives up and the reduction is done over without such waits (default 2^19, 0.14 s); 1 = at the first miss;
  *             results are identical, for tests.
  * The options are plain process-wide variables read at launch time: set them while no other thread is
  * inside a libgvq call.  Returns GVQ_EINVAL for unknown options or values out of range.

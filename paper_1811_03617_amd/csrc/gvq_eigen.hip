@@ -310,11 +310,12 @@ __global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
 // the mark goes back within the step, and a step waited for it: 3.6 against 3.0 us.)  A work-group leaves when its rows are
 // reflected away, so nobody who no longer publishes still reads.
 //
-// The wait is bounded (a poll takes about 0.7 us).  A work-group whose words do not come, because another process or a long kernel
+// The wait is bounded: a poll takes 0.27 us, the bound 0.14 s, which is about what doing the matrix over takes, and longer than
+// most kernels that may hold up part of the grid.  A work-group whose words do not come, because another process or such a kernel
 // keeps the others off the chip, gives up, says so behind the slots, and the rest stop too, at the latest when they look there;
 // tri_redo_kernel then does the matrix over, with one work-group that waits for nobody.
 #define TRI_CHAIN_MARK 0xFFFFFFFFFFFFFFFFull
-#define TRI_CHAIN_POLLS (1 << 17)
+#define TRI_CHAIN_POLLS (1 << 19)
 
 __global__ __launch_bounds__(256) void tri_chain_clear_kernel(unsigned long long* x, size_t stride, int n)
 {
