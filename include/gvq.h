@@ -102,6 +102,10 @@ int64_t gvq_num_slices(const gvq_basis_t* h);
  * positive.  Results stay on the device inside the handle.  A basis whose range holds
  * no full slice gets mu = 0, eig = 0 and U = the first k unit vectors.
  * Asynchronous on `stream`; the handle counts as fitted once this returns GVQ_OK.
+ * Slices of more than 128 elements: the columns of the tridiagonal form come from one launch whose
+ * work-groups wait for each other, or from one launch per column (captured streams, streams with a
+ * CU mask, while another stream of the process has such a launch in its queue, more bases than the
+ * chip holds); the results are the same bits.
  */
 int gvq_fit_basis(gvq_basis_t* h, const void* const* grads, int L, void* stream);
 
@@ -190,8 +194,10 @@ int gvq_decompress_segment(const gvq_basis_t* h, const float* comp_sum, int64_t 
  * which a node watches to decide when the basis needs a refresh.  grad: device, M elements
  * of the handle's dtype; loss_out: device double [B] (8-byte aligned).  The tail slice is
  * projected zero-padded but only its real elements count.  The gradient is read once;
- * nothing else of its size is written.  fp32 arithmetic per slice, float64 sums over slices
- * in a fixed order.  Asynchronous on `stream`.
+ * nothing else of its size is written.  fp32 arithmetic per slice (with one basis, d = 64 or 128
+ * and 17 to 32 comps its products are made of three bf16 terms per number, which add up to it
+ * exactly; what is left out of a product is below 2^-24 of it), float64 sums over slices in a
+ * fixed order.  Asynchronous on `stream`.
  */
 int gvq_local_loss(const gvq_basis_t* h, const void* grad, int n_workers, double* loss_out,
                    void* stream);

@@ -1798,9 +1798,9 @@ int gvq_launch_decompress(const gvq_basis* h, const float* comp, int64_t first_s
     // (bf16 output of more than 128 comps cannot add up its column passes in place: the any-shape kernel below)
     if (gvq_long_shape(h->d, h->k) && !(h->k > 128 && odt == GVQ_BF16))
         return gvq_launch_decompress_long(h, comp, first_slice, n_slices, out, odt, st);
-    const bool bf = odt == GVQ_BF16;
     CodecArgs a = make_args(h, comp, out, 1, h->d_Upd);
     a.seg_begin = first_slice; a.seg_end = first_slice + n_slices;
+    const bool bf = odt == GVQ_BF16;
     if (gvq_mfma_shape(h->d, h->k)) {
         switch (h->d) {
         case 16: return bf ? launch_decompress_d<16, true>(h, a, st) : launch_decompress_d<16, false>(h, a, st);

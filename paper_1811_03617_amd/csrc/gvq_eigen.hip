@@ -2,8 +2,8 @@
 // and eigen vector s"), float64, any slice length and any number of bases side by side:
 //
 //   tridiagonal    A = Q T Q^T by Householder reflections.  Up to 128 rows one work-group holds the whole matrix in
-//                  its registers; a larger matrix is first cut down to its trailing 128 x 128 block by one launch
-//                  per column, spread over the chip.
+//                  its registers; a larger matrix is first cut down to its trailing 128 x 128 block by one launch over
+//                  the chip for all columns, or one per column.
 //   bisect         every eigenvalue of T by multisection on Sturm counts, a group of lanes per eigenvalue.
 //   inverse        the k wanted eigenvectors of T by inverse iteration from random vectors, one lane each.
 //   orthonormalise modified Gram-Schmidt over those k vectors (eigenvalues of the noise lie so close together that
@@ -12,7 +12,7 @@
 //   out            order, sign and conversion to the fp32 basis.
 //
 // It replaces Jacobi methods, which compute all d eigenvectors and need 12 - 14 sweeps over the matrix whatever k is:
-// d = 128 4.0 -> 0.42 ms, d = 768 (k = 96) 22 -> 5.3 ms.  What bounds it is the chain of dependent steps (d reflections,
+// d = 128 4.0 -> 0.39 ms, d = 768 (k = 96) 22 -> 3.0 ms.  What bounds it is the chain of dependent steps (d reflections,
 // each needing the whole of the one before), not arithmetic or memory.
 //
 // Every kernel returns at once for a basis whose matrix is zero (unit vectors, eigenvalues 0) or not finite
@@ -114,8 +114,8 @@ __device__ __forceinline__ double fast_sqrt(double x, double& inverse)
 }
 
 // The reflector that takes (x0, rest) to (beta, 0), n2 = |rest|^2: v = (1, rest * sc), H = I - t v v^T.  Every wave of a
-// work-group forms it, four to a SIMD, so what counts is the number of instructions: with the library's square root and
-// divisions a step of tri_small_kernel took 2.4 us, 2.2 with these.
+// work-group forms it for itself, so what counts is the number of instructions: with the library's square root and
+// divisions a step of tri_small_kernel, at four waves to a SIMD, took 2.4 us, 2.2 with these.
 __device__ __forceinline__ void reflector(double x0, double n2, double& beta, double& t, double& sc)
 {
     beta = x0; t = 0.0; sc = 0.0;
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(256) void tri_step_kernel(EigenArgs a, int i)
 // the step before and its own column: both are published as plain 64-bit words, and a word that still holds the mark
 // (all bits set, which no arithmetic on finite numbers gives) has not arrived.  Waiting for the words themselves takes one way
 // through memory per step, where a counter takes three (the data, the count, the data again) and the end of a launch about
-// five microseconds: d = 768 6.4 -> 3.0 us a column, 4.2 -> 1.94 ms for all of them.
+// five microseconds: d = 768 6.4 -> 2.9 us a column, 4.2 -> 1.85 ms for all of them.
 //
 // Slots: p of step i and row i + 1 go to slot i % 4.  Who has seen all of p of step i - 1 knows that every work-group which
 // still takes part is done with slot (i - 2) % 4; those that will write it in step i + 2 put the mark back at the end of step i,
@@ -926,7 +926,8 @@ __global__ __launch_bounds__(64) void inverse_kernel(EigenArgs a)
 // finished panel by panel, each in a launch of its own (FINISH), and after each the later panels shed their components along
 // it, a work-group each (SHED): the same operations in the same order (d = k = 1024 20.6 -> 2.8 ms; the whole refresh 29.4 -> 11.6, d = k = 512 6.4 -> 3.9).
 // A column's sums over the wave, four at a time, and its reciprocal square root are what a step waits for, and the finished
-// columns arrive while the one before them is worked through (d = 768, k = 96: 193 -> 158 us).
+// columns arrive while the one before them is worked through (d = 768, k = 96: 193 -> 158 us).  At NE = 16 ORTHO_ALL keeps 64 of
+// its registers in scratch for that, and gains all the same (d = 1024, k = 128: 392 -> 333 us; 26 bases of d = 900, k = 96 237 -> 212).
 enum OrthoPart { ORTHO_ALL, ORTHO_FINISH, ORTHO_SHED };
 template <int NE, OrthoPart PART>
 __global__ __launch_bounds__(512) void orthonormalise_kernel(double* Z, size_t Z_stride, int k, int n, int panel,

@@ -2,12 +2,12 @@
 // per slice y = U^T (x - mu/N), then |x - mu/N - U y|^2, summed over all slices.
 //
 // 4 d k flop per slice, twice what Eq. (2) needs, and on the fp32 matrix pipe they take longer than the gradient takes to
-// arrive (138 M elements, d = 128, k = 32: 113 against 90 us; 164 - 188 us measured, the products and the rest of a wave's
+// arrive (138 M elements, d = 128, k = 32: 113 against 90 us; 161 - 190 us measured, the products and the rest of a wave's
 // work hardly overlapped).  So both contractions run on v_mfma_f32_16x16x32_bf16, with every fp32 number as three bf16 terms
 // that add up to it exactly (x and y cut off at 8 bits, U rounded to nearest): of the nine products of two numbers the six
 // with i + j <= 4 are taken, what is left out is below 2^-24 of the product, and the large ones are added to the sum of the
 // small ones.  Six products take 100 matrix cycles where the fp32 pipe takes 256.  138 M elements, d = 128, k = 32, the whole call:
-// 183 -> 121 us (bf16 storage 158 -> 110; 60 M elements, d = 64, k = 24 78 -> 60), relative error against float64 over 18 draws of
+// 161 -> 118 - 124 us (its kernels in a trace 190 -> 121; bf16 storage 158 -> 110; 60 M elements, d = 64, k = 24 78 -> 60), relative error against float64 over 18 draws of
 // sizes and noise levels 1.7e-7 -> 1.6e-7 rms.  What bounds it now is a wave's own instructions: splitting, products and residuals of a tile
 // of 16 slices take 4000 cycles of a SIMD, of which the matrix pipe is busy 1700; the gradient alone would take 90 us.
 //
