@@ -95,7 +95,11 @@ int gvq_basis_destroy(gvq_basis_t* h)
 static int alloc_notes(gvq_basis* h)
 {
     unsigned long long* p = nullptr;
-    GVQ_HIP(hipHostMalloc((void**)&p, 2 * sizeof(unsigned long long), hipHostMallocDefault));
+    const hipError_t e = hipHostMalloc((void**)&p, 2 * sizeof(unsigned long long), hipHostMallocDefault);
+    if (e != hipSuccess) {
+        const int rc = gvq_hip_fail(e, "hipHostMalloc(notes)");
+        return e == hipErrorOutOfMemory ? GVQ_ENOMEM : rc;
+    }
     p[0] = p[1] = 0;
     h->h_notes = p;
     return GVQ_OK;
