@@ -7,7 +7,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgvq.so")
-SOURCES = ["gvq_api.cpp", "gvq_codec.hip", "gvq_codec_long.hip", "gvq_codec_ws.hip", "gvq_flow.hip", "gvq_flow_c_f32.hip", "gvq_flow_c_bf16.hip", "gvq_flow_d.hip", "gvq_fit.hip", "gvq_moments.hip", "gvq_eigen.hip", "gvq_sample.hip", "gvq_layout.hip", "gvq_monitor.hip"]
+SOURCES = ["gvq_api.cpp", "gvq_codec.hip", "gvq_codec_long.hip", "gvq_codec_ws.hip", "gvq_flow.hip", "gvq_flow_c_f32.hip", "gvq_flow_c_bf16.hip", "gvq_flow_d.hip", "gvq_fit.hip", "gvq_moments.hip", "gvq_moments_int.hip", "gvq_eigen.hip", "gvq_sample.hip", "gvq_layout.hip", "gvq_monitor.hip"]
 
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

@@ -55,6 +55,7 @@ struct gvq_basis {
     double* d_part = nullptr;   // moment partials: [B][mom_part]
     size_t mom_part = 0;        // doubles per basis
     int mom_diag = 1, mom_off = 0;   // sample chunks per panel, and per pair of different panels, of the moments kernel
+    int mom_idiag = 1, mom_ioff = 0; // ... and of the int8 moments kernel
     double* d_mom = nullptr;    // [B][d*d+d] reduced moments (sum x x^T, then sum x)
     unsigned long long* d_nsamp = nullptr;  // [B] sample slices the moment kernels of the last fit took in, counted by
                                 // them; then [B] largest |entry| of the decomposed matrix, as bits
@@ -136,6 +137,14 @@ bool gvq_bf16_pipe_shape(const gvq_basis* h);
 // Moments: chooses the sample chunks (`longest`: slices of the longest basis), returns the partials' doubles per basis.
 size_t gvq_moments_plan(gvq_basis* h, int64_t longest);
 int gvq_launch_moments(gvq_basis* h, const void* const* grads, int L, hipStream_t st);   // -> d_mom, d_nsamp
+// The same on the int8 matrix pipe (gvq_moments_int.hip): whether it can take the handle's slices, and takes a refresh from
+// L gradients.
+bool gvq_moments_int_shape(const gvq_basis* h);
+bool gvq_moments_int_takes(const gvq_basis* h, int L);
+size_t gvq_moments_int_plan(gvq_basis* h, int64_t longest);
+int gvq_launch_moments_int(gvq_basis* h, const void* const* grads, int L, hipStream_t st);
+// Partials -> d_mom.
+int gvq_launch_moments_reduce(const gvq_basis* h, int nt, int np, int pw, int chunks_diag, int chunks_off, hipStream_t st);
 bool gvq_long_shape(int d, int k);            // codec: the LDS-tiled MFMA kernels take this shape (d > 128, or any
                                               // shape with k <= 128 that the register-resident kernels do not)
 size_t gvq_long_pack_floats(int d, int k);    // floats per basis in either operand-order copy of U

@@ -1,6 +1,6 @@
 // Moments of the basis refresh (GradiVeQ Section 2, PCA paragraph after Eq. 4): per basis, sum x and sum x x^T over the
 // sample slices, in float64 (fp32 and bf16 inputs widen exactly and their products are exact in float64), for every
-// slice length up to GVQ_MAX_D.
+// slice length up to GVQ_MAX_D.  Many samples of slices longer than 64 elements: gvq_moments_int.hip.
 //
 // sum x x^T is a (d x n)(n x d) product with the samples as the contraction index, on v_mfma_f64_16x16x4_f64: A lane l =
 // (row l%16, step l/16), B lane l = (step l/16, column l%16), result register r of lane l = (row 4r + l/16, column l%16).
@@ -10,8 +10,7 @@
 // issues no vector instruction at all (9 products alone 585 cycles, with 72 v_fma_f32 in between 905): every conversion,
 // address and select is paid for in full.  So a work-group converts each number once, on its way into LDS, from where
 // its four waves read float64 operands that need nothing done to them, and a lane's addresses are a uniform pointer
-// plus an offset that never changes.  d = 128, 32 gradients of 138 M elements: 10.15 -> 10.0 ms; d = 768, 8 gradients:
-// 16.2 -> 14.7 ms (both converted each number in every wave that multiplied it); d = 24 and 16, 8 gradients of
+// plus an offset that never changes.  d = 24 and 16, 8 gradients of
 // 10 M elements, 0.98 -> 0.15 ms and 0.23 -> 0.12 ms with the sum over the partials.
 //
 // Where the rest of the matrix pipe's time goes at d = 128 (9 700 to 10 700 cycles per block of 32 samples for two
@@ -22,77 +21,12 @@
 // with itself (tile pairs T1 <= T2 only, the matrix is symmetric) or of two different panels (all NT^2 pairs).
 #include <math.h>
 
-#include <type_traits>
-#include <utility>
-
-#include "gvq_internal.h"
+#include "gvq_moments.h"
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 // a word of four numbers: slices of any length start anywhere, so it need not be aligned
 typedef unsigned int mw4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned short mh4 __attribute__((ext_vector_type(4), aligned(2)));
-
-// f(0) .. f(N - 1) with the index as a compile-time constant (which tiles a pair names decides which registers are used).
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_seq(F f, std::integer_sequence<int, I...>)
-{
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F> __device__ __forceinline__ void static_for(F f)
-{
-    static_for_seq(f, std::make_integer_sequence<int, N>{});
-}
-
-struct MomArgs {
-    gvq_ptrs grads;
-    int L;
-    const int64_t* offs;
-    int64_t M;
-    int d, np, pw;                // np panels of pw elements, the last one shorter
-    int chunks_diag, chunks_off;  // sample chunks of the two kinds of task
-    int accumulate;               // 0: overwrite the partials, 1: add to them
-    double* part;                 // [B][part_basis]: the diagonal tasks' partials, then the others'
-    size_t part_basis;
-    unsigned long long* nsamp;    // [B] += the sample slices this launch took in (counted by the tasks of panel 0)
-};
-
-// Words of four numbers: WORDS per row (sample) in LDS, RPS rows per 256 threads, four words per thread and block.
-// SPLIT: the tile pairs are shared out among the four waves, which then all read every sample; with few pairs each wave
-// has all of them and takes every fourth group of four samples.  Rows of an even number of tiles get one tile of
-// padding where all waves read them, so that the rows of a group start 32 banks apart.
-template <int NT, bool OFF> struct MomShape {
-    static constexpr bool SPLIT = OFF || NT >= 6;
-    static constexpr int NPAIR = OFF ? NT * NT : NT * (NT + 1) / 2;
-    static constexpr int TILES = OFF ? 2 * NT : NT;
-    static constexpr int U = 4;                                    // words per thread and block
-    static constexpr int WORDS = 4 * TILES, RPS = SPLIT ? 256 / WORDS : 256 / WORDS / 4 * 4, NS = U * RPS;
-    static constexpr int STRIDE = SPLIT ? 1 : 4, NGW = NS / 4 / STRIDE;   // groups of four samples per wave and block
-    static constexpr int NACC = SPLIT ? (NPAIR + 3) / 4 : NPAIR;
-    static constexpr int ROW = 16 * (SPLIT ? (TILES | 1) : TILES);
-    static constexpr int PART = NPAIR * 256 + (OFF ? 0 : 16 * NT);
-    static constexpr int BUF = NS * ROW;       // doubles per buffer
-    static constexpr int LDS = 2 * BUF * 8;    // bytes
-    static __host__ __device__ constexpr int row(int p)
-    {
-        if (OFF) return p / NT;
-        int t = 0;
-        while (p >= NT - t) { p -= NT - t; ++t; }
-        return t;
-    }
-    static __host__ __device__ constexpr int col(int p)   // tile index in the LDS row
-    {
-        if (OFF) return NT + p % NT;
-        int t = 0;
-        while (p >= NT - t) { p -= NT - t; ++t; }
-        return t + p;
-    }
-    static constexpr bool needs(int p0, int p1, int tile)   // one of the pairs p0 .. p1 - 1 has this tile
-    {
-        for (int p = p0; p < p1; ++p)
-            if (row(p) == tile || col(p) == tile) return true;
-        return false;
-    }
-};
 
 template <int NT, bool BF16, bool OFF, int WAVE>
 __device__ __forceinline__ void moments_task(const MomArgs& a, double* lds, int pa, int pb, int chunk, int chunks,
@@ -451,11 +385,29 @@ size_t gvq_moments_plan(gvq_basis* h, int64_t longest)
         basis = (size_t)np * h->mom_diag * Diag::PART + (size_t)poff * h->mom_off * Off::PART;
         return GVQ_OK;
     });
+    if (gvq_moments_int_shape(h)) {
+        const size_t other = gvq_moments_int_plan(h, longest);
+        if (other > basis) basis = other;
+    }
     return basis;
+}
+
+int gvq_launch_moments_reduce(const gvq_basis* h, int nt, int np, int pw, int chunks_diag, int chunks_off, hipStream_t st)
+{
+    return by_tiles(nt, [&](auto t) -> int {
+        constexpr int NT = decltype(t)::value;
+        const int width = np > 1 ? MomShape<NT, true>::PART : MomShape<NT, false>::PART;
+        hipLaunchKernelGGL((moments_reduce_kernel<NT>), dim3((unsigned)((width + 63) / 64), (unsigned)(np + np * (np - 1) / 2), (unsigned)h->B),
+                           dim3(chunks_diag > 16 || chunks_off > 16 ? 1024 : 64), 0, st, h->d_part, h->mom_part, h->d_mom, h->d,
+                           np, pw, chunks_diag, chunks_off);
+        GVQ_HIP(hipGetLastError());
+        return GVQ_OK;
+    });
 }
 
 int gvq_launch_moments(gvq_basis* h, const void* const* grads, int L, hipStream_t st)
 {
+    if (gvq_moments_int_takes(h, L)) return gvq_launch_moments_int(h, grads, L, st);
     MomArgs a;
     a.offs = h->d_offs; a.M = h->M; a.d = h->d; a.np = panels(h->d); a.pw = 16 * panel_tiles(h->d);
     a.chunks_diag = h->mom_diag; a.chunks_off = h->mom_off;
@@ -492,10 +444,6 @@ int gvq_launch_moments(gvq_basis* h, const void* const* grads, int L, hipStream_
             rc = bf ? launch(moments_kernel<NT, true, false>, Diag::LDS) : launch(moments_kernel<NT, false, false>, Diag::LDS);
         }
         if (rc != GVQ_OK) return rc;
-        const int width = a.np > 1 ? Off::PART : Diag::PART;
-        hipLaunchKernelGGL((moments_reduce_kernel<NT>), dim3((unsigned)((width + 63) / 64), (unsigned)(a.np + poff), (unsigned)h->B),
-                           dim3(a.chunks_diag > 16 || a.chunks_off > 16 ? 1024 : 64), 0, st, h->d_part, h->mom_part, h->d_mom, h->d, a.np, a.pw, a.chunks_diag, a.chunks_off);
-        GVQ_HIP(hipGetLastError());
-        return GVQ_OK;
+        return gvq_launch_moments_reduce(h, NT, a.np, a.pw, a.chunks_diag, a.chunks_off, st);
     });
 }

@@ -1,0 +1,109 @@
+"""Moments of the basis refresh from many samples (the int8 matrix pipe): the edges of its tiles and panels, blocks that end a
+basis or the gradient, scales that have to change on the way, whole numbers, numbers that are not finite."""
+import numpy as np
+import pytest
+
+from paper_1811_03617_amd import gvq
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _fit(grads, M, d, cuts, dtype):
+    b = gvq.Basis(M, d, 1, cuts, dtype)
+    b.fit([g.to(DEV) for g in grads])
+    C, n = b.export_cov()
+    mu = b.export()[1]
+    return b, C, n, mu
+
+
+def _check(C, n, mu, grads, M, d, cuts):
+    X = np.stack([g.to(torch.float64).numpy()[: M // d * d].reshape(-1, d) for g in grads])
+    for i, (lo, hi) in enumerate(zip(cuts[:-1], cuts[1:])):
+        x = X[:, lo:min(hi, M // d)].reshape(-1, d)
+        assert n[i] == x.shape[0]
+        m = x.mean(0)
+        # as float64 sums of n products: a number's digits and the products left out are off by less than 2^-46 of its
+        # column's largest, far below the n + 2 roundings that such a sum may have
+        bound = (max(n[i], 64) + 4) * 2.0 ** -53 * (np.abs(x).T @ np.abs(x) / n[i] + 2 * np.outer(np.abs(m), np.abs(m)))
+        assert np.all(np.abs(C[i] - (x.T @ x / n[i] - np.outer(m, m))) <= 2 * bound + 1e-300)
+        assert np.array_equal(C[i], C[i].T)
+        assert np.allclose(mu[i], m, rtol=1e-6, atol=1e-7 * np.abs(x).max())
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [65, 79, 80, 81, 96, 97, 100, 112, 113, 127, 128, 129, 160, 161, 192, 193, 250, 385, 768, 1024])
+def test_covariance_and_counts(d, dtype):
+    rng = np.random.default_rng(d)
+    L = 34 if d in (80, 128) else 5
+    slices = 16384 // L + 147
+    cuts = [0, slices - 75, slices - 74, slices] if d <= 300 else [0, slices]   # of one slice, and of a block and a few
+    M = slices * d - (1 if d % 3 else 0)
+    # columns of different size, samples that change their size on the way, columns that are zero at first or always
+    size = 10.0 ** rng.uniform(-6, 0, d)
+    grads = []
+    for _ in range(L):
+        x = rng.standard_normal((slices, d)) * size + 0.3 * size
+        x[slices // 3: slices // 2] *= 1e-5
+        x[slices // 2: slices // 2 + 200] = 0.0
+        x[slices // 2 + 200: slices // 2 + 300] *= 1e3
+        x[:100, 3] = 0.0
+        x[:, d // 2] = 0.0
+        grads.append(torch.from_numpy(x.reshape(-1)[:M].astype(np.float32)))
+    if dtype == "bf16":
+        grads = [g.to(torch.bfloat16) for g in grads]
+    b, C, n, mu = _fit(grads, M, d, cuts if len(cuts) > 2 else None, dtype)
+    b.close()
+    _check(C, n, mu, grads, M, d, cuts)
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -140, 2.0 ** -40, 1.0, 2.0 ** 40])
+@pytest.mark.parametrize("d", [80, 128, 144])
+def test_whole_numbers_are_exact(d, scale):
+    rng = np.random.default_rng(d)
+    L, slices = 3, 6000
+    M = slices * d
+    x = [rng.integers(-2000, 2001, M) for _ in range(L)]
+    b, C, n, mu = _fit([torch.from_numpy((v * np.float64(scale)).astype(np.float32)) for v in x], M, d, None, "f32")
+    b.close()
+    X = np.concatenate([v.reshape(-1, d) for v in x])
+    G, s = (X.T @ X).astype(np.float64), X.sum(0).astype(np.float64)   # below 2^53
+    N = float(len(X))
+    want = (G / N - np.outer(s / N, s / N)) * scale ** 2
+    # a division, a product and a difference of exact sums
+    assert np.all(np.abs(C[0] - want) <= 2.0 ** -51 * (G.max() / N + np.abs(np.outer(s, s)).max() / N ** 2) * scale ** 2)
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("d", [128, 160])
+def test_not_finite(d, bad):
+    rng = np.random.default_rng(d)
+    L, slices, column = 4, 5000, 17
+    M = slices * d
+    grads = [torch.from_numpy(rng.standard_normal(M).astype(np.float32)) for _ in range(L)]
+    clean = [g.clone() for g in grads]
+    grads[2][d * 1234 + column] = float(bad)
+    b, C, n, mu = _fit(grads, M, d, None, "f32")
+    with pytest.raises(gvq.GvqError) as e:
+        b.fit_status()
+    assert e.value.status == gvq.ENONFINITE
+    b.close()
+    assert not np.isfinite(C[0][column]).any() and not np.isfinite(mu[0][column])
+    keep = np.arange(d) != column
+    X = np.concatenate([g.to(torch.float64).numpy().reshape(-1, d) for g in clean])[:, keep]
+    m = X.mean(0)
+    assert np.allclose(C[0][np.ix_(keep, keep)], X.T @ X / len(X) - np.outer(m, m), rtol=0, atol=1e-12)
+
+
+def test_same_bits_twice():
+    rng = np.random.default_rng(3)
+    d, slices, L = 200, 9000, 3
+    grads = [torch.from_numpy(rng.standard_normal(slices * d).astype(np.float32)).to(DEV) for _ in range(L)]
+    b = gvq.Basis(slices * d, d, 4)
+    res = []
+    for _ in range(2):
+        b.fit(grads)
+        res.append(b.export_cov()[0])
+    b.close()
+    assert np.array_equal(res[0], res[1])
