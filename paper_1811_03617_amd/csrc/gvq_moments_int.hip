@@ -20,9 +20,9 @@
 // has products in flight, and its own products do not overlap with its own vector instructions.  Hence twelve waves, three a
 // SIMD, the most that have room for their share of the accumulators (seven levels a pair of tiles, 84 of 168 registers for
 // three pairs), of which one parks the next block before its products, the others behind them.  A block of 64 samples
-// of 128 elements takes 5000 cycles, 3400 of them products (eight waves 5300, all of them parking between their products 6400);
-// with the eigensolver 32 gradients of 138 M elements 10.07 -> 6.52 ms, 8 gradients of
-// d = 768 16.8 -> 13.1 ms.
+// of 128 elements takes 4820 cycles at 1.8 to 1.85 GHz, 3400 of them products (eight waves 5300, all of them parking between their products 6400);
+// with the eigensolver 32 gradients of 138 M elements 10.1 -> 6.37 ms, 8 gradients of
+// d = 768 16.9 -> 12.6 ms.
 #include <math.h>
 
 #include "gvq_moments.h"
@@ -64,7 +64,8 @@ template <int NT, bool OFF, int ND> struct IntShape {
         return o;
     }
     static constexpr Order order = make_order();
-    static constexpr int extra(int w) { return INT_WAVES - 1 - w < NPAIR % INT_WAVES ? 1 : 0; }
+    // of eight tiles with themselves, the waves that do not park take a pair from those that park first
+    static constexpr int extra(int w) { return (INT_WAVES - 1 - w < NPAIR % INT_WAVES ? 1 : 0) + (!OFF && NT == 8 ? (w < 4 ? -1 : w < 8 ? 0 : 1) : 0); }
     static constexpr int first(int w)
     {
         int p = 0;
@@ -169,27 +170,27 @@ __device__ __forceinline__ void int_task(const MomArgs& a, unsigned char* lds, i
 
     float x[16];
     int64_t left = nblk * a.L;   // blocks not yet requested
-    // The requested block: 64 slices from src on, of which only those from `skip` on and no more than `rows` count.  A block
-    // that ends a task's samples, or lies at the gradient's end, is read with its neighbours, so that every load is whole.
-    struct Block { uintptr_t src; int skip, rows; } req{0, 0, 0};
+    // A block: 64 slices from src on, of which only those from `skip` on and no more than `rows` count.  One that ends a task's
+    // samples, or lies at the gradient's end, is read with its neighbours, so that every load is whole.
+    struct Block { uintptr_t src; int skip, rows; } ahead{0, 0, 0};   // the one to request next
     const int step = d * ES, stride = INT_NS * step;
-    int64_t rows_left = 0;   // this task's samples of the gradient from the requested block on
+    int64_t rows_left = 0;   // this task's samples of the gradient from that block on
     int l = 0;
     unsigned long long taken = 0;
     auto next_block = [&]() {
         if (left == 0) return;   // the last block is requested again: loads stay unconditional
         --left;
         rows_left -= INT_NS;
-        req.src += stride;
+        ahead.src += stride;
         if (rows_left < INT_NS) {
             if (rows_left <= 0) {
-                req.src = (uintptr_t)a.grads.p[l++] + j0 * step;
+                ahead.src = (uintptr_t)a.grads.p[l++] + j0 * step;
                 rows_left = j1 - j0;
             }
-            req.rows = rows_left < INT_NS ? (int)rows_left : INT_NS;
+            ahead.rows = rows_left < INT_NS ? (int)rows_left : INT_NS;
             const int64_t past = j1 - rows_left - (full - INT_NS);   // slices that the block's 64 would reach past the last
-            req.skip = past > 0 ? (int)past : 0;
-            req.src -= req.skip * step;
+            ahead.skip = past > 0 ? (int)past : 0;
+            ahead.src -= ahead.skip * step;
         }
     };
     // Loads through a buffer resource: the rows' distances are uniform offsets, which a lane's address would have to add up.
@@ -342,8 +343,10 @@ __device__ __forceinline__ void int_task(const MomArgs& a, unsigned char* lds, i
     const unsigned char* mine = lds + lane * 16;
     int64_t todo = left;
     int flip = 0;
-    if (todo > 0) next_block();
-    Block parked_block = req;
+    next_block();
+    Block parked_block = ahead;   // in LDS
+    next_block();
+    Block req = ahead;            // in registers, or on its way
     next_block();
     bool forget = true;   // the columns' largest numbers so far
     while (todo > 0) {
@@ -363,16 +366,12 @@ __device__ __forceinline__ void int_task(const MomArgs& a, unsigned char* lds, i
             auto fetch_digit = [&](int g, int tile) {
                 return *(const i4*)(buf + g * Sh::PLANE + tile * 1024);
             };
-            auto fetch = [&](i4 (&o)[NB], int tile) {
-#pragma unroll
-                for (int g = 0; g < NB; ++g) o[g] = fetch_digit(g, tile);
-            };
             auto fetch_for = [&](auto ii, auto phase) {   // the tiles that change from a phase of pair i to the next
                 constexpr int I = decltype(ii)::value, PH = decltype(phase)::value;
                 constexpr auto before = Sh::slots(P0, P0 + NA, P0 + I, PH), now = Sh::slots(P0, P0 + NA, P0 + I, PH + 1);
-                static_for<INT_SLOTS>([&](auto qi) {
-                    constexpr int Q = decltype(qi)::value;
-                    if constexpr (now.t[Q] != before.t[Q]) fetch(op[Q], now.t[Q]);
+                static_for<NB * INT_SLOTS>([&](auto gi) {   // digit by digit: the first products need the first ones only
+                    constexpr int G = decltype(gi)::value / INT_SLOTS, Q = decltype(gi)::value % INT_SLOTS;
+                    if constexpr (now.t[Q] != before.t[Q]) op[Q][G] = fetch_digit(G, now.t[Q]);
                 });
             };
             // The two waves of a SIMD park at different times, one of them before its products and one behind: while one
@@ -385,18 +384,18 @@ __device__ __forceinline__ void int_task(const MomArgs& a, unsigned char* lds, i
             if (since > INT_FLUSH || (known & 1u) || forget) {
                 if (since > 1) break;   // with the scales just made all is well, or cannot be helped
             }
-            if (!OFF) {
-                taken += parked_block.rows;
-                if constexpr (PARKS) unsafeAtomicAdd(&sums[sum_at()], sums[4 * COLS + sum_at()]);
-            }
+            if (!OFF && WAVE == 0) taken += parked_block.rows;
             parked_block = req;
-            next_block();
+            req = ahead;
             auto park_next = [&]() {
                 if constexpr (PARKS) {
+                    double sum = 0.0;
+                    if (!OFF) sum = sums[4 * COLS + sum_at()];   // of the block that was parked last
                     mask(parked_block);
-                    // the next block as soon as registers are free; a panel with itself has none to spare for that
-                    park(next, [&](int q) { if (OFF) load_quad(q, req); });
-                    if (!OFF) load(req);
+                    // the next block as soon as registers are free; the late waves of a panel with itself have none to spare
+                    park(next, [&](int q) { if (OFF || EARLY) load_quad(q, req); });
+                    if (!OFF && !EARLY) load(req);
+                    if (!OFF) unsafeAtomicAdd(&sums[sum_at()], sum);
                 }
             };
             if constexpr (EARLY) {
@@ -404,6 +403,10 @@ __device__ __forceinline__ void int_task(const MomArgs& a, unsigned char* lds, i
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (NA > 0) fetch_for(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
             }
+            // Two panels: who parks behind its products goes first (6060 -> 5660 cycles a block).  A panel with itself has waves
+            // that do not park, and gains nothing (21 pairs of tiles lose 3 %).
+            constexpr int PRIORITY = !OFF || EARLY ? 0 : WAVE < 8 ? 2 : 1;
+            if constexpr (PRIORITY > 0) __builtin_amdgcn_s_setprio(PRIORITY);
             static_for<NA>([&](auto ii) {
                 constexpr int I = decltype(ii)::value;
                 __builtin_amdgcn_sched_barrier(0);
@@ -412,12 +415,18 @@ __device__ __forceinline__ void int_task(const MomArgs& a, unsigned char* lds, i
                 if constexpr (I > 0) fetch_for(ii, std::integral_constant<int, 0>{});
                 fetch_for(ii, std::integral_constant<int, 1>{});
                 __builtin_amdgcn_sched_barrier(0);
+                auto multiply = [&](int i, int j) {
+                    if (i + j < INT_LEVELS)
+                        acc[I][i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(op[A][i], op[B][j], acc[I][i + j], 0, 0, 0);
+                };
 #pragma unroll
-                for (int j = 0; j < NB; ++j)
+                for (int top = 0; top < NB; ++top) {   // in the order in which digits arrive
 #pragma unroll
-                    for (int i = 0; i < NB; ++i)
-                        if (i + j < INT_LEVELS)
-                            acc[I][i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(op[A][i], op[B][j], acc[I][i + j], 0, 0, 0);
+                    for (int i = 0; i < top; ++i) multiply(top, i);
+#pragma unroll
+                    for (int i = 0; i <= top; ++i) multiply(i, top);
+                }
+                if constexpr (PARKS && !EARLY && I == 0) next_block();   // scalar work, between products
                 if ((rare >> R | rare >> C) & 1u) {
 #pragma unroll
                     for (int g = NB; g < ND; ++g) {
@@ -433,9 +442,11 @@ __device__ __forceinline__ void int_task(const MomArgs& a, unsigned char* lds, i
                 }
             });
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (PRIORITY > 0) __builtin_amdgcn_s_setprio(0);
             if constexpr (!EARLY) park_next();
             --todo;
             if (todo == 0) break;
+            if constexpr (EARLY) next_block();
             exchange();   // also: everyone is done with this block's buffer
         }
         flush(acc);
@@ -535,7 +546,7 @@ bool gvq_moments_int_takes(const gvq_basis* h, int L)
 }
 
 // Sample chunks per task: as in gvq_moments_plan, with one work-group per compute unit and whole blocks of samples.  Cycles a
-// block measured: 5000 (36 pairs of tiles) and 3720 (21) for a panel with itself, 5740 (36) for two panels.
+// block measured: 4820 (36 pairs of tiles) and 3570 (21) for a panel with itself, 5660 (36) for two panels.
 size_t gvq_moments_int_plan(gvq_basis* h, int64_t longest)
 {
     const int np = int_panels(h->d), poff = np * (np - 1) / 2;
@@ -551,7 +562,7 @@ size_t gvq_moments_int_plan(gvq_basis* h, int64_t longest)
         double best = 0.0;
         for (int64_t c = 1; c <= most && c <= (int64_t)(2.0 * slots); ++c) {
             for (int64_t cd = poff ? (c + 1) / 2 : c; cd <= c; ++cd) {
-                const double td = task(2050 + 80 * Diag::NPAIR, cd), to = poff ? task(2850 + 80 * Off::NPAIR, c) : 0.0;
+                const double td = task(2100 + 75 * Diag::NPAIR, cd), to = poff ? task(2950 + 75 * Off::NPAIR, c) : 0.0;
                 const double tasks = (double)h->B * (np * cd + (poff ? poff * c : 0));
                 const double work = (double)h->B * (np * cd * td + (poff ? poff * c * to : 0.0));
                 const double longest_task = td > to ? td : to;
