@@ -57,7 +57,9 @@ __device__ __forceinline__ double hash_unit(unsigned int i, unsigned int j)
 EigenArgs gvq_eigen_args(const gvq_basis* h);
 // Eigenvalues and the k leading eigenvectors of B matrices; the vectors orthonormal to float64 precision if `ortho`,
 // else as the inverse iteration leaves them.
-int gvq_launch_sym_eigen(const gvq_basis* h, EigenArgs a, bool ortho, hipStream_t st);
+// Matrices of up to GVQ_EIGEN_SMALL rows: `side` is done along with them.
+struct SampleCov;
+int gvq_launch_sym_eigen(const gvq_basis* h, EigenArgs a, bool ortho, hipStream_t st, const SampleCov* side = nullptr);
 int gvq_launch_orthonormalise(const gvq_basis* h, double* Z, size_t Z_stride, int k, int n, hipStream_t st);
 // h->d_eZ (k columns of d) -> h->d_U, with order and sign settled.
 int gvq_launch_basis_out(const gvq_basis* h, hipStream_t st);

@@ -17,7 +17,7 @@
 //
 // Every kernel returns at once for a basis whose matrix is zero (unit vectors, eigenvalues 0) or not finite
 // (eigenvalues NaN, reported by gvq_fit_status), which the largest |entry| says (EigenArgs::norm).
-#include "gvq_eigen.h"
+#include "gvq_sample.h"
 
 #include <mutex>
 #include <type_traits>
@@ -534,9 +534,17 @@ __global__ __launch_bounds__(256) void tri_redo_kernel(EigenArgs a, int steps, u
 // instructions that every wave repeats and the two passes through LDS; hence R = 8 and one wave per SIMD above 64 rows (16 waves
 // of 4 x 4: d = 128 270 -> 245 us, 1000 bases 2450 -> 1960 for the whole refresh).  The matrix never leaves the
 // registers (in LDS, 128 x 128 doubles would take 1000 cycles to read once).
-template <int TJ, int R>
-__global__ __launch_bounds__(TJ * TJ) void tri_small_kernel(EigenArgs a, int i0)
+//
+// SIDE: the work-groups behind those of the `mats` matrices take a block of `side` per wave.  A refresh from first slices has one
+// matrix a work-group and needs its full covariances only when it is over: 26 bases of d = 768, L = 100 84 us as a launch of their own.
+template <int TJ, int R, bool SIDE>
+__global__ __launch_bounds__(TJ * TJ) void tri_small_kernel(EigenArgs a, int i0, int mats, SampleCov side)
 {
+    if (SIDE && (int)blockIdx.x >= mats) {
+        const int at = ((int)blockIdx.x - mats) * (TJ * TJ / 64) + (int)(threadIdx.x >> 6);
+        if (at < side.total) (void)sample_cov_block(side, at);
+        return;
+    }
     constexpr int N = R * TJ, PL = N > 64 ? N / 64 : 1;   // entries of a vector per lane
     __shared__ double colb[2][N], pb[N];
     const int b = blockIdx.x, n = a.n, nl = n - i0, tid = threadIdx.x, lane = tid & 63;
@@ -1409,7 +1417,7 @@ static int launch_chain(const gvq_basis* h, const EigenArgs& a, int steps, hipSt
     return GVQ_OK;
 }
 
-int gvq_launch_sym_eigen(const gvq_basis* h, EigenArgs a, bool ortho, hipStream_t st)
+int gvq_launch_sym_eigen(const gvq_basis* h, EigenArgs a, bool ortho, hipStream_t st, const SampleCov* side)
 {
     const int n = a.n, B = h->B, i0 = n > GVQ_EIGEN_SMALL ? n - GVQ_EIGEN_SMALL : 0;
     bool chain = false;
@@ -1421,9 +1429,15 @@ int gvq_launch_sym_eigen(const gvq_basis* h, EigenArgs a, bool ortho, hipStream_
         by_long_pieces<go_step>(n, dim3((unsigned)((n - 1 - i + 7) / 8), B), a, i, st);
         GVQ_HIP(hipGetLastError());
     }
-    if (n - i0 <= 32) hipLaunchKernelGGL((tri_small_kernel<8, 4>), dim3(B), dim3(64), 0, st, a, i0);
-    else if (n - i0 <= 64) hipLaunchKernelGGL((tri_small_kernel<16, 4>), dim3(B), dim3(256), 0, st, a, i0);
-    else hipLaunchKernelGGL((tri_small_kernel<16, 8>), dim3(B), dim3(256), 0, st, a, i0);
+    auto small = [&](auto kern, auto kern_side, int threads) {
+        const int per = threads / 64;
+        if (side) hipLaunchKernelGGL(kern_side, dim3((unsigned)(B + (side->total + per - 1) / per)), dim3(threads), 0, st, a, i0, B, *side);
+        else hipLaunchKernelGGL(kern, dim3(B), dim3(threads), 0, st, a, i0, B, SampleCov{});
+    };
+    if (side && i0 > 0) return GVQ_EINVAL;   // no caller does
+    if (n - i0 <= 32) small(tri_small_kernel<8, 4, false>, tri_small_kernel<8, 4, true>, 64);
+    else if (n - i0 <= 64) small(tri_small_kernel<16, 4, false>, tri_small_kernel<16, 4, true>, 256);
+    else small(tri_small_kernel<16, 8, false>, tri_small_kernel<16, 8, true>, 256);
     GVQ_HIP(hipGetLastError());
     // a wave per eigenvalue while that leaves the chip's 1024 SIMDs a handful each, fewer lanes for many small matrices (the
     // passes that more lanes spare are fewer than the lanes: 16 x 16, 4000 of them 69 us with 16 lanes, 36 with 4 and a wave each)

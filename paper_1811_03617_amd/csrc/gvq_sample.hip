@@ -5,12 +5,13 @@
 // of the L x L matrix K = Xc Xc^T / L: K v = lambda v  =>  C (Xc^T v) = lambda (Xc^T v).  With 2 L <= d the eigensolver
 // therefore runs on K, and the kept directions are Xc^T v, made orthonormal.  Directions beyond the rank of the data
 // (eigenvalue <= 1e-12 of the largest) are not determined by it: random vectors take their place and the same
-// orthonormalisation completes U.  C itself is formed for gvq_basis_export_cov only.
+// orthonormalisation completes U.  C itself is formed for gvq_basis_export_cov only, by compute units that the
+// tridiagonalisation of K leaves idle.
 //
 // One work-group per basis did all of this in one kernel before (26 bases, d = 768, k = 96, L = 100: 17.8 ms, and
 // 1.4 ms for the moments, which read two elements from memory per product); spread over the chip in products on the
 // fp64 matrix pipe the same refresh takes 0.8 ms.
-#include "gvq_eigen.h"
+#include "gvq_sample.h"
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
@@ -24,7 +25,6 @@ struct SampleArgs {
     size_t x_stride;
     double* K;             // [B][L][L], x_stride apart
     const double* V;       // [B][min(k, L)][L], x_stride apart: eigenvectors of K
-    double* cov;           // [B][d][d]
     float* mu;             // [B][d]
     double* Z;             // [B][k][d]
     const double* eig;     // [B][d]
@@ -39,31 +39,41 @@ __device__ __forceinline__ float load_elem(const void* g, bool bf16, int64_t idx
     return ((const float*)g)[idx];
 }
 
-// mu and the centred samples: 64 elements per work-group, its four waves a quarter of the samples each.
+// mu and the centred samples: 64 elements per work-group, its four waves a quarter of the samples each, which are read once
+// and together (26 bases of d = 768, L = 100: 30 -> 25 us against eight at a time, twice).
 __global__ __launch_bounds__(256) void centre_kernel(SampleArgs a)
 {
     __shared__ double part[4][64];
     const int b = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int e = blockIdx.x * 64 + lane;
     const int64_t j = a.offs[b];
-    const bool full = (j + 1) * a.d <= a.M, on = full && e < a.d;   // the first slice must be a full one
+    const bool full = (j + 1) * a.d <= a.M;   // the first slice must be a full one
     const int l0 = a.L * wave / 4, l1 = a.L * (wave + 1) / 4;
-    double s = 0.0;
-    if (on) {
-#pragma unroll 8
-        for (int l = l0; l < l1; ++l)
-            s += (double)load_elem(a.grads[l / GVQ_MAX_PTRS].p[l % GVQ_MAX_PTRS], a.bf16 != 0, j * a.d + e);
+    float v[GVQ_SAMPLE_MAX_L / 4];
+    const int64_t at = full ? j * a.d + (e < a.d ? e : a.d - 1) : 0;
+    static_assert(GVQ_SAMPLE_MAX_L / 4 == 32, "two halves of 16");
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        if (l0 + 16 * half >= l1) break;
+#pragma unroll
+        for (int i = 16 * half; i < 16 * half + 16; ++i) {
+            const int l = l0 + i < l1 ? l0 + i : l1 - 1;
+            v[i] = full ? load_elem(a.grads[l / GVQ_MAX_PTRS].p[l % GVQ_MAX_PTRS], a.bf16 != 0, at) : 0.f;
+        }
     }
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < GVQ_SAMPLE_MAX_L / 4; ++i)
+        if (l0 + i < l1) s += (double)v[i];
     part[wave][lane] = s;
     __syncthreads();
     // true division: identical samples then give exactly C = 0
     const double mean = ((part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane])) / (double)a.L;
     double* X = a.X + (size_t)b * a.x_stride;
     if (e < a.d) {
-#pragma unroll 8
-        for (int l = l0; l < l1; ++l)
-            X[(size_t)l * a.d + e] =
-                on ? (double)load_elem(a.grads[l / GVQ_MAX_PTRS].p[l % GVQ_MAX_PTRS], a.bf16 != 0, j * a.d + e) - mean : 0.0;
+#pragma unroll
+        for (int i = 0; i < GVQ_SAMPLE_MAX_L / 4; ++i)
+            if (l0 + i < l1) X[(size_t)(l0 + i) * a.d + e] = full ? (double)v[i] - mean : 0.0;
         if (wave == 0) a.mu[(size_t)b * a.d + e] = (float)mean;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -126,60 +136,10 @@ __global__ __launch_bounds__(256) void sample_gram_kernel(SampleArgs a)
 }
 
 // C = X^T X / L in 64 x 64 blocks, one wave each (and its mirror image).
-__global__ __launch_bounds__(64) void sample_cov_kernel(SampleArgs a, int want_norm)
+__global__ __launch_bounds__(64) void sample_cov_kernel(SampleCov c, unsigned long long* norm)
 {
-    const int b = blockIdx.y, lane = threadIdx.x, m = lane & 15, kk = lane >> 4, d = a.d;
-    const int ng = (d + 63) / 64;
-    int g1 = 0, rem = blockIdx.x;
-    while (rem >= ng - g1) { rem -= ng - g1; ++g1; }
-    const int g2 = g1 + rem;
-    const double* X = a.X + (size_t)b * a.x_stride;
-    d4 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-    double na[4], nb[4];
-    auto fetch = [&](int l) {   // one group of four samples ahead, from inside the array; zero past the last sample
-        const double* row = X + (size_t)(l + kk < a.L ? l + kk : a.L - 1) * d;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int e1 = 64 * g1 + 16 * t + m, e2 = 64 * g2 + 16 * t + m;
-            na[t] = row[e1 < d ? e1 : d - 1];
-            nb[t] = row[e2 < d ? e2 : d - 1];
-        }
-    };
-    fetch(0);
-    for (int l = 0; l < a.L; l += 4) {
-        double va[4], vb[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            va[t] = l + kk < a.L ? na[t] : 0.0;
-            vb[t] = nb[t];
-        }
-        fetch(l + 4);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[i], vb[j], acc[i][j], 0, 0, 0);
-    }
-    double* cov = a.cov + (size_t)b * d * d;
-    double big = 0.0, bad = 0.0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = 64 * g1 + 16 * i + 4 * r + kk, col = 64 * g2 + 16 * j + m;
-                if (row >= d || col >= d) continue;
-                const double v = acc[i][j][r] / (double)a.L;
-                cov[(size_t)row * d + col] = v;
-                if (g1 != g2) cov[(size_t)col * d + row] = v;
-                big = fmax(big, fabs(v));
-                if (v != v) bad = v;
-            }
-    if (want_norm) eig_norm_max(bad != bad ? bad : big, a.nsamp + a.B + b);
+    const double v = sample_cov_block(c, blockIdx.x);
+    eig_norm_max(v, norm + blockIdx.x / c.blocks);
 }
 
 // The raw directions X^T v (random numbers where the data determines none), 16 columns x 64 elements per wave.
@@ -248,15 +208,18 @@ int gvq_launch_fit_samples(const gvq_basis* h, const void* const* grads, int L, 
     double* work = h->d_eA + (size_t)L * d;       // K's work space: a spare row, then K
     a.K = work + L;
     a.V = work + (size_t)(L + 1) * L;
-    a.cov = h->d_cov; a.mu = h->d_mu; a.Z = h->d_eZ; a.eig = h->d_eig; a.nsamp = h->d_nsamp; a.B = B;
+    a.mu = h->d_mu; a.Z = h->d_eZ; a.eig = h->d_eig; a.nsamp = h->d_nsamp; a.B = B;
     a.solves = h->d_solves;
     const bool gram = gram_shape(d, L);
     hipLaunchKernelGGL(centre_kernel, dim3((unsigned)((d + 63) / 64), B), dim3(256), 0, st, a);
     GVQ_HIP(hipGetLastError());
-    const int ng = (d + 63) / 64;
-    hipLaunchKernelGGL(sample_cov_kernel, dim3((unsigned)(ng * (ng + 1) / 2), B), dim3(64), 0, st, a, gram ? 0 : 1);
-    GVQ_HIP(hipGetLastError());
-    if (!gram) return gvq_launch_eigen(h, false, st);
+    const int ng = (d + 63) / 64, blocks = ng * (ng + 1) / 2;
+    const SampleCov cov{a.X, a.x_stride, h->d_cov, L, d, blocks, B * blocks};
+    if (!gram) {
+        hipLaunchKernelGGL(sample_cov_kernel, dim3((unsigned)cov.total), dim3(64), 0, st, cov, a.nsamp + B);
+        GVQ_HIP(hipGetLastError());
+        return gvq_launch_eigen(h, false, st);
+    }
     const int nt = (L + 15) / 16;
     hipLaunchKernelGGL(sample_gram_kernel, dim3((unsigned)(nt * (nt + 1) / 2), B), dim3(256), 0, st, a);
     GVQ_HIP(hipGetLastError());
@@ -264,7 +227,7 @@ int gvq_launch_fit_samples(const gvq_basis* h, const void* const* grads, int L, 
     e.src = a.K; e.src_stride = e.A_stride;
     e.A = work;
     e.Z = const_cast<double*>(a.V); e.Z_stride = e.A_stride;
-    int rc = gvq_launch_sym_eigen(h, e, false, st);
+    int rc = gvq_launch_sym_eigen(h, e, false, st, &cov);
     if (rc != GVQ_OK) return rc;
     hipLaunchKernelGGL(sample_lift_kernel, dim3((unsigned)((d + 255) / 256), (unsigned)((k + 15) / 16), B), dim3(256), 0, st, a);
     GVQ_HIP(hipGetLastError());
