@@ -21,6 +21,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0  # MI355X published HBM3E bandwidth
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X published dense bf16 matrix rate
 FP64_MFMA_PEAK_TFLOPS = 78.6  # MI355X published fp64 matrix rate
+INT8_MFMA_PEAK_TOPS = 5000.0  # MI355X published dense int8 matrix rate
 
 
 def main():
@@ -284,19 +285,23 @@ def run_workload(name, args):
                      "traffic_source": None if traffic is None else
                      "profiles/hbm_traffic.json (rocprofv3 FETCH_SIZE/WRITE_SIZE runs, see profiles/*_hbm_traffic.md)"},
     }
-    # the basis refresh against its own roofline: d x d Gram sums on the fp64 matrix pipe (only the
-    # symmetric half of the 16 x 16 blocks is multiplied), input read once from HBM
+    # the basis refresh against its own roofline: d x d Gram sums (only the symmetric half of the 16 x 16 blocks is
+    # multiplied) on the fp64 matrix pipe, or above 64 elements as 22 (bf16 storage: 9) products of digits on the
+    # int8 one; input read once from HBM
     if not args.skip_fit:
         full = w.M // w.d
         blocks16 = (w.d + 15) // 16
         fit_flop = 2.0 * L * full * 256 * (blocks16 * (blocks16 + 1) // 2)
         fit_in_bytes = float(L) * w.M * es
-        mfma_s, hbm_s = fit_flop / (FP64_MFMA_PEAK_TFLOPS * 1e12), fit_in_bytes / (HBM_PEAK_GBS * 1e9)
+        digits = w.d > 64
+        fit_peak = INT8_MFMA_PEAK_TOPS if digits else FP64_MFMA_PEAK_TFLOPS
+        fit_flop *= (22 if w.dtype == "f32" else 9) if digits else 1
+        mfma_s, hbm_s = fit_flop / (fit_peak * 1e12), fit_in_bytes / (HBM_PEAK_GBS * 1e9)
         if mfma_s >= hbm_s:
             res["fit"]["roofline"] = {"bound": "mfma", "achieved": round(fit_flop / fit_ms / 1e9, 2),
-                                      "peak": FP64_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
-                                      "frac": round(fit_flop / fit_ms / 1e9 / FP64_MFMA_PEAK_TFLOPS, 4),
-                                      "note": "whole refresh (moments + eigensolver) against the moments' flop"}
+                                      "peak": fit_peak, "unit": "TOP/s (int8)" if digits else "TFLOP/s",
+                                      "frac": round(fit_flop / fit_ms / 1e9 / fit_peak, 4),
+                                      "note": "whole refresh (moments + eigensolver) against the moments' operations"}
         else:
             res["fit"]["roofline"] = {"bound": "hbm", "achieved": round(fit_in_bytes / fit_ms / 1e6, 1),
                                       "peak": HBM_PEAK_GBS, "unit": "GB/s",
