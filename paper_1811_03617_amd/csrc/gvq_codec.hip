@@ -119,12 +119,12 @@ __device__ __forceinline__ void compress_fast_phase(const CodecArgs& a, f4* lds)
     // takes rows j, j + a.il, j + 2 a.il, ... of them, so that the waves that run side by side read and write one
     // compact window row by row; the super-tiles past the last whole group keep their own NL consecutive rows.
     constexpr int ES = BF16 ? 2 : 4;
-    const int64_t n_il = (!MANY && a.il > 1) ? a.n_super / a.il * a.il : 0;
+    const int64_t n_il = (!MANY && a.il > 1) ? il_group(a.n_super, a.il) * a.il : 0;
     struct Where { int64_t in_byte, out_word; int rstride; };   // first input byte, first result word, rows between rows
     auto where = [&](int64_t p) {
         Where w;
         if (!MANY && p < n_il) {
-            const int64_t g = p / a.il, j = p - g * a.il;
+            const int64_t g = il_group(p, a.il), j = p - g * a.il;
             const int64_t row = g * a.il * NL + j;                    // from the first super-tile's start
             w.in_byte = a.sup_first * (int64_t)(TILE_SLICES * D * ES) + row * 1024;
             w.out_word = a.sup_first * (int64_t)(TILE_SLICES) * kc + row * orw;
@@ -636,12 +636,12 @@ __device__ __forceinline__ void compress_bf16_fast_phase(const CodecArgs& a, u4*
     u4 regs[NL];
     f4 prev[ACC ? NSO : 1];
     // Where super-tile p lies: see compress_fast_phase.
-    const int64_t n_il = (!MANY && a.il > 1) ? a.n_super / a.il * a.il : 0;
+    const int64_t n_il = (!MANY && a.il > 1) ? il_group(a.n_super, a.il) * a.il : 0;
     struct Where { int64_t in_byte, out_word; int rstride; };
     auto where = [&](int64_t p) {
         Where w;
         if (!MANY && p < n_il) {
-            const int64_t g = p / a.il, j = p - g * a.il;
+            const int64_t g = il_group(p, a.il), j = p - g * a.il;
             const int64_t row = g * a.il * NL + j;
             w.in_byte = a.sup_first * (int64_t)(TILE_SLICES * D * 2) + row * 1024;
             w.out_word = a.sup_first * (int64_t)(TILE_SLICES) * kc + row * orw;
@@ -964,12 +964,12 @@ __device__ __forceinline__ void decompress_fast_phase(const CodecArgs& a, f4* ld
     f4 y[NY];
     // Where super-tile p lies (see compress_fast_phase): its first output byte, first input word, rows between rows.
     constexpr int ES = OUT_BF16 ? 2 : 4;
-    const int64_t n_il = (!MANY && a.il > 1) ? a.n_super / a.il * a.il : 0;
+    const int64_t n_il = (!MANY && a.il > 1) ? il_group(a.n_super, a.il) * a.il : 0;
     struct Where { int64_t out_byte, in_word; int rstride; };
     auto where = [&](int64_t p) {
         Where w;
         if (!MANY && p < n_il) {
-            const int64_t g = p / a.il, j = p - g * a.il;
+            const int64_t g = il_group(p, a.il), j = p - g * a.il;
             const int64_t row = g * a.il * NS + j;
             w.out_byte = a.sup_first * (int64_t)(TILE_SLICES * D * ES) + row * 1024;
             w.in_word = a.sup_first * (int64_t)(TILE_SLICES) * kc + row * irw;

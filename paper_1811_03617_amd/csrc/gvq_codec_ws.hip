@@ -371,10 +371,10 @@ __global__ __launch_bounds__(512) void decompress_ws_kernel(WsdArgs a)
 
     // Slice `row` of tile `tile`, counted from a.first (see above); the tiles past the last whole group, and the
     // tail tile, keep 16 consecutive slices.
-    const int64_t n_il = a.ntiles / a.il * a.il;
+    const int64_t n_il = il_group(a.ntiles, a.il) * a.il;
     auto slice_of = [&](int64_t tile, int row) -> int64_t {
         if (tile >= n_il) return 16 * tile + row;
-        const int64_t g = tile / a.il, j = tile - g * a.il;
+        const int64_t g = il_group(tile, a.il), j = tile - g * a.il;
         return 16 * a.il * g + (int64_t)row * a.il + j;
     };
     // This wave's copies of a tile's y: the 64 words from 64 c on, c = w and w + 8 (the latter only exists for
