@@ -560,9 +560,13 @@ size_t gvq_moments_int_plan(gvq_basis* h, int64_t longest)
         };
         const int64_t most = (longest + INT_NS - 1) / INT_NS;
         double best = 0.0;
+        const int cycles_d = 2100 + 75 * Diag::NPAIR, cycles_o = 2950 + 75 * Off::NPAIR;
         for (int64_t c = 1; c <= most && c <= (int64_t)(2.0 * slots); ++c) {
-            for (int64_t cd = poff ? (c + 1) / 2 : c; cd <= c; ++cd) {
-                const double td = task(2100 + 75 * Diag::NPAIR, cd), to = poff ? task(2950 + 75 * Off::NPAIR, c) : 0.0;
+            // A panel with itself in as many chunks as make its tasks no longer than the others, or one fewer: 1,023 splits
+            // looked at where all of c/2 .. c are 66,048 (d = 160, 312,500 samples), for the same estimate within 0.2 %.
+            const int64_t even = poff ? (c * cycles_d + cycles_o - 1) / cycles_o : c;
+            for (int64_t cd = poff && even > 1 ? even - 1 : even; cd <= even; ++cd) {
+                const double td = task(cycles_d, cd), to = poff ? task(cycles_o, c) : 0.0;
                 const double tasks = (double)h->B * (np * cd + (poff ? poff * c : 0));
                 const double work = (double)h->B * (np * cd * td + (poff ? poff * c * to : 0.0));
                 const double longest_task = td > to ? td : to;
