@@ -26,15 +26,17 @@
 #include <math.h>
 
 #include "gvq_moments.h"
+#include "gvq_moments_place.h"
 
 typedef int i4 __attribute__((ext_vector_type(4)));
 
 #define INT_THREADS 768
 #define INT_WAVES 12
 #define INT_SLOTS 2
-#define INT_NS 64                    // samples per block
 #define INT_LEVELS 7
 #define INT_FLUSH 320                // blocks between flushes: 6 products of 2^14 a sample stay below 2^31 for 21845 samples
+
+static_assert(INT_MOST_D >= GVQ_MAX_D, "columns past a slice's end");
 
 template <int NT, bool OFF, int ND> struct IntShape {
     using Mom = MomShape<NT, OFF>;
@@ -153,18 +155,14 @@ __device__ __forceinline__ void int_task(const MomArgs& a, unsigned char* lds, i
     const int64_t j0 = lo + cnt * chunk / chunks, j1 = lo + cnt * (chunk + 1) / chunks;
     const int64_t nblk = (j1 - j0 + INT_NS - 1) / INT_NS;
 
-    // This thread's item in one word: from bit 14 on, where its first sample lies in a block's memory; below, where its first
-    // digits go in LDS, which also says its column and samples.  Columns past the slice's end are read past the buffer
-    // resource's, as zeros.
-    unsigned int place = 0u;
+    unsigned int place = 0u;   // this thread's item
     if constexpr (PARKS) {
         const int c = tid % COLS, q = tid / COLS;
         const int e = OFF && c >= 16 * NT ? pb * a.pw + c - 16 * NT : pa * a.pw + c;
-        const unsigned int from = e < d ? (unsigned int)((16 * q * d + e) * ES) : 0x3fffcu;
-        place = from << 14 | (unsigned int)((c >> 4) * 1024 + q * 256 + (c & 15) * 16);
+        place = int_place(int_from(e, q, d, ES), c, q);
     }
-    auto col_of = [](unsigned int p) { return (int)((p >> 10 & 15u) * 16 + (p >> 4 & 15u)); };
-    auto quarter_of = [](unsigned int p) { return (int)(p >> 8 & 3u); };
+    auto col_of = [](unsigned int p) { return int_place_column(p); };
+    auto quarter_of = [](unsigned int p) { return int_place_quarter(p); };
     // Hides a value's origin, so that what is made from it is not kept in registers from one block to the next.
     auto fresh = [](auto v) { asm("" : "+v"(v)); return v; };
 
@@ -199,7 +197,7 @@ __device__ __forceinline__ void int_task(const MomArgs& a, unsigned char* lds, i
     for (int i = 0; i < 8; ++i) row_at[i] = __builtin_amdgcn_readfirstlane(i * step);
     auto load_quad = [&](int q, const Block& k) {
         auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)k.src, 0, stride, 0x00027000);
-        const unsigned int at = (fresh(place) >> 14) + (q >= 2 ? 8u * step : 0u);
+        const unsigned int at = int_place_from(fresh(place)) + (q >= 2 ? 8u * step : 0u);
 #pragma unroll
         for (int i = 4 * q; i < 4 * q + 4; ++i) {
             if (BF16) x[i] = __uint_as_float((unsigned int)__builtin_amdgcn_raw_buffer_load_b16(rsrc, at, row_at[i & 7], 0) << 16);
@@ -254,7 +252,7 @@ __device__ __forceinline__ void int_task(const MomArgs& a, unsigned char* lds, i
             }
             then(q);
         }
-        unsigned char* o = buf + (fresh(place) & 0x3fffu);
+        unsigned char* o = buf + int_place_lds(fresh(place));
 #pragma unroll
         for (int g = 0; g < ND; ++g) *(i4*)(o + g * Sh::PLANE) = out4[g];
         const float limit = ldexpf(0.98f, BITS - 1 - fresh(by));   // 0x7f7f.. of 0x8000..: every byte's digit is at most 127
@@ -518,9 +516,6 @@ __global__ __launch_bounds__(INT_THREADS, 3) void moments_int_kernel(MomArgs a)
 }
 
 // ======================================================================================
-static int int_panels(int d) { const int t = (d + 15) / 16; return t <= 8 ? 1 : (t + 5) / 6; }
-static int int_tiles(int d) { const int np = int_panels(d); return ((d + 15) / 16 + np - 1) / np; }
-
 template <typename F> static int by_int_tiles(int nt, F f)
 {
     switch (nt) {
