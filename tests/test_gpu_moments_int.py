@@ -107,3 +107,61 @@ def test_same_bits_twice():
         res.append(b.export_cov()[0])
     b.close()
     assert np.array_equal(res[0], res[1])
+
+
+def _gram(x):
+    """sum x x^T: exact products, eight at a time in float64, the rest in long double."""
+    total = np.zeros((x.shape[1],) * 2, np.longdouble)
+    for i in range(0, len(x), 8):
+        total += x[i:i + 8].T @ x[i:i + 8]
+    return total
+
+
+def _tails(name, slices, d, rng):
+    x = rng.standard_normal((slices, d))
+    if name == "lognormal":
+        return np.exp(3.0 * x) * rng.choice([-1.0, 1.0], x.shape)
+    if name == "one_sided":
+        return np.exp(2.0 * x)
+    if name == "fourth_power":
+        return x ** 4
+    if name == "few_large":
+        return x * np.where(rng.random(x.shape) < 0.01, 1.0, 1e-3)
+    if name == "two_sizes":
+        return x * np.where(rng.random(x.shape) < 0.15, 1.0, 1e-6)
+    if name == "some_tiny":
+        return x * np.where(rng.random(x.shape) < 0.05, 1e-9, 1.0)
+    if name == "constant_outliers":   # every column one number, with one large one, in another sample each
+        x = np.repeat(np.abs(x[:1]) + 0.1, slices, 0)
+        x[rng.integers(0, slices, d), np.arange(d)] *= 1000.0
+        return x
+    if name == "sizes_change":        # by blocks of samples, in both directions
+        return x * 10.0 ** rng.uniform(-8, 0, slices // 64 + 1).repeat(64)[:slices, None]
+    assert name == "student"
+    return rng.standard_t(1.5, x.shape)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [65, 128, 192])
+@pytest.mark.parametrize("name", ["lognormal", "one_sided", "fourth_power", "few_large", "two_sizes", "some_tiny",
+                                  "constant_outliers", "sizes_change", "student"])
+def test_as_exact_products_summed_in_float64(name, d, dtype):
+    """Columns whose numbers differ in size by far more than a digit product holds: the sums have to be as good as float64 sums of
+    exact products, relative to the sum of the products' absolute values."""
+    rng = np.random.default_rng(d)
+    L, slices = 4, 4200
+    M = slices * d
+    grads = [torch.from_numpy(_tails(name, slices, d, rng).astype(np.float32).reshape(-1)) for _ in range(L)]
+    if dtype == "bf16":
+        grads = [g.to(torch.bfloat16) for g in grads]
+    b, C, n, mu = _fit(grads, M, d, None, dtype)
+    b.close()
+    x = np.concatenate([g.to(torch.float64).numpy().reshape(-1, d) for g in grads])
+    N = len(x)
+    assert n[0] == N
+    G, m = _gram(x) / N, x.astype(np.longdouble).sum(0) / N
+    most = np.abs(x).T @ np.abs(x) / N
+    # Roundings one after the other: a sum of a chunk's samples (65 of each gradient or fewer) has no more than 4 * 65 of them,
+    # that of the 65 chunks 65; the covariance is a quotient, a product and a difference behind it; 8 are the reference's.
+    bound = (4 * 65 + 65 + 4 + 8) * 2.0 ** -53 * most + 2.0 ** -50 * np.abs(np.outer(m, m))
+    assert np.all(np.abs(C[0] - (G - np.outer(m, m))) <= bound)
