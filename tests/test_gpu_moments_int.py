@@ -24,8 +24,8 @@ def _check(C, n, mu, grads, M, d, cuts):
         x = X[:, lo:min(hi, M // d)].reshape(-1, d)
         assert n[i] == x.shape[0]
         m = x.mean(0)
-        # as float64 sums of n products: a number's digits and the products left out are off by less than 2^-46 of its
-        # column's largest, far below the n + 2 roundings that such a sum may have
+        # as float64 sums of n products, with their n + 2 roundings at worst (test_every_digit and test_as_exact_products... look
+        # closer)
         bound = (max(n[i], 64) + 4) * 2.0 ** -53 * (np.abs(x).T @ np.abs(x) / n[i] + 2 * np.outer(np.abs(m), np.abs(m)))
         assert np.all(np.abs(C[i] - (x.T @ x / n[i] - np.outer(m, m))) <= 2 * bound + 1e-300)
         assert np.array_equal(C[i], C[i].T)
@@ -56,6 +56,72 @@ def test_covariance_and_counts(d, dtype):
     b, C, n, mu = _fit(grads, M, d, cuts if len(cuts) > 2 else None, dtype)
     b.close()
     _check(C, n, mu, grads, M, d, cuts)
+
+
+# Numbers whose digits are known: a column's room is four times its largest number P, so that in units of 2^-47 of the room P is
+# 2^45 and c = 100 (2^16 + 2^8) has 100 as its digits 3 and 4 (of 0 to 5), c + 100 as its digit 5 too.
+_P, _C = 2 ** 45, 100 * (2 ** 16 + 2 ** 8)
+
+
+def _digit_columns(d, slices, dtype):
+    """P in every eighth sample of a column and its small number in the others; the sample's sign takes turns, so that the mean is
+    0.  Returns the numbers (in units, float64) and sum x x^T over n samples of their kind as whole numbers, for multiples of 16."""
+    small = np.full(d, _C)
+    if dtype == "bf16":   # three digits hold nearly every number of a column: eight bits of digits 3 and 4, in few columns
+        small[:] = 2 ** 37
+        small[5::16] = 201 << 12
+    else:
+        small[5::16] += 100
+    t, col = np.arange(16)[:, None], np.arange(d)[None, :]
+    large = (t // 2 + col + col // 16) % 8 == 0   # elsewhere in the next columns, and in the next that have last digits
+    x = np.where(large, _P, small).astype(object) * np.where(t % 2 == 0, 1, -1)
+    gram = x.T.dot(x)
+    assert slices % 16 == 0 and not x.sum(0).any()
+    return np.tile(x.astype(np.float64), (slices // 16, 1)), gram * (slices // 16), small
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [65, 96, 112, 128, 144, 192])
+def test_every_digit(d, dtype):
+    """Every level of products that is to be there is: without the last one, or without the products of last digits, the sums are off by
+    ten times the bound and more."""
+    L, slices = 4, 4160
+    x, gram, small = _digit_columns(d, slices, dtype)
+    g = torch.from_numpy((x * 2.0 ** -45).astype(np.float32).reshape(-1))
+    if dtype == "bf16":
+        g = g.to(torch.bfloat16)
+    assert np.array_equal(g.to(torch.float64).numpy(), (x * 2.0 ** -45).reshape(-1))
+    b, C, n, mu = _fit([g] * L, slices * d, d, None, dtype)
+    b.close()
+    assert n[0] == L * slices and not mu.any()
+    # in units: the ninth level and those below it are left out, 2^(-78 + 94) for a product of two digits, five such products of 100 x 100
+    # and less at most, and 2^(-62 + 94) of every block and chunk where the eighth joins the seventh; then 2^-47 of the products'
+    # absolute values for roundings (a chunk's Horner steps, 65 chunks, the quotient)
+    left_out = slices * 5 * 1e4 * 2.0 ** 16 + (slices / 64 + 66) * 2.0 ** 32
+    most = np.abs(x).T @ np.abs(x)
+    off = np.abs((C[0] * 2.0 ** 90).astype(object) * slices - gram)
+    assert np.all(off.astype(np.float64) <= left_out + most * 2.0 ** -47)
+
+
+@pytest.mark.parametrize("d", [65, 128, 150])
+def test_sums_that_fill_an_int(d):
+    """More than a thousand blocks a task of digits -128: the sums of a level's products leave 32 bits unless they become float64 in
+    between."""
+    slices, L = 1 << 19, 32
+    t, col = np.arange(8)[:, None], np.arange(d)[None, :]
+    # -128 as digits 1, 2 and 3
+    x = np.where((t + 3 * col) % 8 == 0, 1.0, -(2.0 ** -6) * (1 + 2.0 ** -8 + 2.0 ** -16)) * np.ones((8, d))
+    g = torch.from_numpy(x.astype(np.float32)).to(DEV).repeat(slices // 8, 1).reshape(-1)
+    assert np.array_equal(x, x.astype(np.float32))
+    b = gvq.Basis(slices * d, d, 1, None, "f32")
+    b.fit([g] * L)
+    C, n = b.export_cov()
+    b.close()
+    m = x.mean(0)
+    want = x.T @ x / 8 - np.outer(m, m)
+    assert n[0] == slices * L
+    # a chunk's few sums, up to 256 chunks in sixteen sums of sixteen, the covariance's three operations
+    assert np.all(np.abs(C[0] - want) <= 2.0 ** -46 * (x.T @ x).max() / 8)
 
 
 @pytest.mark.parametrize("scale", [2.0 ** -140, 2.0 ** -40, 1.0, 2.0 ** 40])
