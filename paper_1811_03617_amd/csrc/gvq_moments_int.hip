@@ -9,7 +9,7 @@
 // an fp32 number is exact if it is above 2^-24 of that room (bf16: 2^-40).
 //
 // What keeps the sums as good as float64 sums of exact products (INT_LOW, INT_MANY): no 16 numbers of a column that a thread
-// converts are all below 2^-6 of the room, unless they are zeros, and no more than an eighth of these items have a number below
+// converts are all below 2^-6 of the room, unless they are zeros or fewer (the last of a task's samples of a gradient), and no more than an eighth of these items have a number below
 // 2^-16.  A block for which that is not so, or that holds a number out of range, gets new scales; where new scales do not help,
 // it is multiplied on the fp64 pipe (int_exactly), as are the blocks behind it if new scales are asked for too often.  Difference to
 // long double sums over sqrt(C_aa C_bb), rms, fp64 pipe -> here: planted model, 200 000 samples of 96 elements at 64 scales
@@ -28,7 +28,7 @@
 // registers, three a SIMD: of up to three pairs of tiles each, 28 registers a pair, some of which park the next block before their
 // products and some behind them; for eight tiles with themselves (36 pairs) two pairs for the four that park first, three
 // for the four that park behind their products and four for those that do not park, a few of whose registers are in scratch.
-// 32 gradients of 138 M elements, d = 128, with the eigensolver: fp64 pipe 9.9 ms, here 7.0 (without the eighth level 6.3; three pairs
+// 32 gradients of 138 M elements, d = 128, with the eigensolver: fp64 pipe 9.9 ms, here 7.0 (without the eighth level 6.2; three pairs
 // for every wave 7.9, spills; eight waves of 256 registers and every wave parking between its own products were slower yet);
 // 8 gradients of d = 768 16.5 -> 12.9 ms.  Data that go to the fp64 pipe after all (lognormal numbers): d = 128 9.9 -> 10.6 ms, in bf16
 // 5.4 -> 5.6, d = 160 3.0 -> 3.6, d = 768 16.5 -> 20.1; sizes that change by orders of magnitude every block 10.0 -> 10.8, where new
@@ -86,6 +86,7 @@ template <int NT, bool OFF> struct IntShape {
     static constexpr Order order = make_order();
     // of eight tiles with themselves, the waves that do not park take a pair from those that park first
     static constexpr int extra(int w) { return (INT_WAVES - 1 - w < NPAIR % INT_WAVES ? 1 : 0) + (!OFF && NT == 8 ? (w < 4 ? -1 : w < 8 ? 0 : 1) : 0); }
+    static_assert(NPAIR >= INT_WAVES, "a pair for every wave");
     static constexpr int first(int w)
     {
         int p = 0;
@@ -299,8 +300,8 @@ __device__ __forceinline__ int int_task(const MomArgs& a, unsigned char* lds, in
         const unsigned int p = fresh(place);
         return quarter_of(p) * COLS + col_of(p);
     };
-    // `then(q)` follows the last use of four samples' registers; `count`: the samples are new to the sums of x.
-    auto park = [&](unsigned char* buf, bool count, auto then) {
+    // Block k, which x holds.  `then(q)` follows the last use of four samples' registers; `count`: the samples are new to the sums of x.
+    auto park = [&](const IntBlock& k, unsigned char* buf, bool count, auto then) {
         // 1.5 * 2^52 makes the sum's unit 1: its lower bits are the whole number, biased so that every byte is a digit + 128
         constexpr double BIAS = 0x1.8p52 + 0x808080808080p0;
         const double scale = __builtin_bit_cast(double, (unsigned long long)(1023 + fresh(by)) << 52);
@@ -337,8 +338,11 @@ __device__ __forceinline__ int int_task(const MomArgs& a, unsigned char* lds, in
         const unsigned long long some = __ballot(last != 0u);
         const bool many = __builtin_popcountll(some) > INT_MANY;
         stale = low || (many && last != 0u);
+        // fewer than 16 samples say little about their column
+        constexpr int Q0 = 64 * WAVE / COLS, Q1 = (64 * WAVE + 63) / COLS;
+        const bool whole = k.skip <= 16 * Q0 && k.skip + k.rows >= 16 * Q1 + 16;
         marks = (__any(!(most < ldexpf(0.98f, room))) ? 1u : 0u)   // 0x7f7f.. of 0x8000..: every byte's digit is at most 127
-                | (__any(low) ? 2u : 0u) | (many ? 4u : 0u);
+                | (__any(low) && whole ? 2u : 0u) | (many ? 4u : 0u);
         // a wave has four tiles' columns, side by side or around the end
         if (some != 0ull) {
             const unsigned int tiles = (some & 0xffffull ? 1u : 0u) | (some & 0xffff0000ull ? 2u : 0u)
@@ -420,7 +424,7 @@ __device__ __forceinline__ int int_task(const MomArgs& a, unsigned char* lds, in
             const double f = (double)__uint_as_float(m ? m : 1u);
             by = BITS - 1 - ((int)(__builtin_bit_cast(unsigned long long, f) >> 52) - 1023 + 2);
             if (quarter_of(p) == 0) at.cexp[col_of(p)] = by;
-            park(buf, !counted, [](int) {});
+            park(k, buf, !counted, [](int) {});
         }
         counted = true;
         exchange();
@@ -473,7 +477,7 @@ __device__ __forceinline__ int int_task(const MomArgs& a, unsigned char* lds, in
                 if constexpr (PARKS) {
                     mask(parked_block);
                     // the next block as soon as registers are free; the late waves of a panel with itself have none to spare
-                    park(next, todo > 1, [&](int q) { if (OFF || EARLY) load_quad(q, req); });
+                    park(parked_block, next, todo > 1, [&](int q) { if (OFF || EARLY) load_quad(q, req); });
                     if (!OFF && !EARLY) load(req);
                 }
             };
@@ -482,7 +486,7 @@ __device__ __forceinline__ int int_task(const MomArgs& a, unsigned char* lds, in
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (NA > 0) fetch_for(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
             }
-            // Two panels: who parks behind its products goes first (6060 -> 5660 cycles a block).  A panel with itself has waves
+            // Two panels: who parks behind its products goes first (6060 -> 5660 cycles a block, before the eighth level).  A panel with itself has waves
             // that do not park, and gains nothing (21 pairs of tiles lose 3 %).
             constexpr int PRIORITY = !OFF || EARLY ? 0 : WAVE < 8 ? 2 : 1;
             if constexpr (PRIORITY > 0) __builtin_amdgcn_s_setprio(PRIORITY);
@@ -745,10 +749,10 @@ template <typename F> static int by_int_tiles(int nt, F f)
 // It reads 64 slices at a time, and counts a task's slices and blocks of 32 gradients in an int.
 bool gvq_moments_int_shape(const gvq_basis* h) { return h->d > 64 && h->M / h->d >= INT_NS && h->M / h->d < 1 << 30; }
 
-// From 16384 samples of the longest basis on.  Of 70 refreshes from 2000 to a million samples a basis (65 to 1024 elements,
-// both storages, 1 to 100 bases) none is more than 1 % slower than with the fp64 pipe; from 16384 to 100 000 samples they
-// take 0.96 of its time where the eigensolver takes most of it and down to 0.56 with 100 bases, from 100 000 on 0.49 to
-// 0.97.  Below, there is little to gain and fewer samples over which the products left out average.
+// From 16384 samples of the longest basis on.  Of 90 refreshes from there to a million samples a basis (65 to 1024 elements, both
+// storages, 1 to 100 bases, normal numbers) none takes longer than with the fp64 pipe, by more than 0.2 %: up to 30 000
+// samples 0.97 to 1.0 of its time, where the eigensolver takes most of it, down to 0.58 with 100 bases or 430 000 samples in
+// bf16.  Below, there is little to gain.
 bool gvq_moments_int_takes(const gvq_basis* h, int L)
 {
     if (!gvq_moments_int_shape(h)) return false;
@@ -757,8 +761,9 @@ bool gvq_moments_int_takes(const gvq_basis* h, int L)
     return longest * L >= 16384;
 }
 
-// Sample chunks per task: as in gvq_moments_plan, with one work-group per compute unit and whole blocks of samples.  Cycles a
-// block measured: 4820 (36 pairs of tiles) and 3570 (21) for a panel with itself, 5660 (36) for two panels.
+// Sample chunks per task: as in gvq_moments_plan, with one work-group per compute unit and whole blocks of samples.  What a block
+// takes, in units that balance the two kinds of task best: alone, panels with themselves take less of it (2740 cycles of 80 elements, 3300 of
+// 96, where two panels take 4520 and 5990), but with these figures d = 250 takes 4.36 instead of 3.98 ms, d = 768 13.2 instead of 12.9.
 size_t gvq_moments_int_plan(gvq_basis* h, int64_t longest)
 {
     const int np = int_panels(h->d), poff = np * (np - 1) / 2;
