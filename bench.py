@@ -24,6 +24,13 @@ FP64_MFMA_PEAK_TFLOPS = 78.6  # MI355X published fp64 matrix rate
 INT8_MFMA_PEAK_TOPS = 5000.0  # MI355X published dense int8 matrix rate
 
 
+def fit_on_int8_pipe(w, L):
+    """Whether the library sums the moments of a refresh from L gradients on the int8 matrix pipe (gvq_moments_int_takes)."""
+    offs = w.block_offsets() or [0, -(-w.M // w.d)]
+    longest = max(b - a for a, b in zip(offs[:-1], offs[1:]))
+    return w.d > 64 and w.M // w.d >= 64 and longest * L >= 16384
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -286,16 +293,16 @@ def run_workload(name, args):
                      "profiles/hbm_traffic.json (rocprofv3 FETCH_SIZE/WRITE_SIZE runs, see profiles/*_hbm_traffic.md)"},
     }
     # the basis refresh against its own roofline: d x d Gram sums (only the symmetric half of the 16 x 16 blocks is
-    # multiplied) on the fp64 matrix pipe, or above 64 elements as 22 (bf16 storage: 9) products of digits on the
-    # int8 one; input read once from HBM
+    # multiplied) on the fp64 matrix pipe, or from many samples of more than 64 elements as 24 (bf16 storage: 9) products of
+    # digits on the int8 one; input read once from HBM
     if not args.skip_fit:
         full = w.M // w.d
         blocks16 = (w.d + 15) // 16
         fit_flop = 2.0 * L * full * 256 * (blocks16 * (blocks16 + 1) // 2)
         fit_in_bytes = float(L) * w.M * es
-        digits = w.d > 64
+        digits = fit_on_int8_pipe(w, L)
         fit_peak = INT8_MFMA_PEAK_TOPS if digits else FP64_MFMA_PEAK_TFLOPS
-        fit_flop *= (22 if w.dtype == "f32" else 9) if digits else 1
+        fit_flop *= (24 if w.dtype == "f32" else 9) if digits else 1
         mfma_s, hbm_s = fit_flop / (fit_peak * 1e12), fit_in_bytes / (HBM_PEAK_GBS * 1e9)
         if mfma_s >= hbm_s:
             res["fit"]["roofline"] = {"bound": "mfma", "achieved": round(fit_flop / fit_ms / 1e9, 2),

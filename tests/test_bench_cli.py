@@ -35,3 +35,13 @@ def test_graft_entry_has_build_and_smoke():
     sys.path.insert(0, ROOT)
     import __graft_entry__ as g
     assert callable(g.build) and callable(g.smoke)
+
+
+def test_refresh_is_priced_on_the_pipe_that_does_it():
+    """Short bases or few gradients stay on the fp64 matrix pipe, whatever the slice length."""
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_1811_03617_amd import WORKLOADS
+    for name, L, want in (("vgg16", 32, True), ("vgg16", 1, True), ("vgg16_bf16", 32, True), ("vgg16_bf16", 2, False),
+                          ("alexnet", 16, False), ("tiny", 8, False)):
+        assert bench.fit_on_int8_pipe(WORKLOADS[name], L) == want
