@@ -21,7 +21,8 @@
 //
 // Digits come from float64: x * scale + 1.5 * 2^52 + 0x80..80 has them, plus 128 each, as its lower bytes (one conversion and one
 // v_fma_f64; with fp32 arithmetic alone it took seven instructions a number and the kernel a sixth longer).  The last digit
-// (bf16: the last three) is 0 in nearly every number: its products are made only for tiles of a block that have another one.
+// (bf16: the last three) is 0 in nearly every number: its products are made only for tiles of a block that have another one
+// (bf16: of the fourth digit, and rarer yet the last two apart: 139 bases of d = 128, 32 gradients 5.20 -> 5.04 ms).
 //
 // What bounds it: instruction issue.  A wave issues a vector instruction every 5 cycles, every 7.8 while another wave of its SIMD
 // has products in flight, and its own products do not overlap with its own vector instructions.  Hence twelve waves of 168
@@ -256,7 +257,7 @@ template <int NT, bool OFF> struct IntLds {
     unsigned int* colmax;   // [COLS]
     int* cexp;              // [COLS] x 2^cexp is what the digits hold
     // [2][16], a word per wave: 1 a number is out of its column's range, 2 an item's are all far below it, 4 too many items have
-    // last digits; from bit 4 on, the tiles whose last digits are not all zero
+    // last digits; from bit 3 on, the tiles whose first digit of those that are nearly always 0 is not, from bit 15 on, the others
     unsigned int* flags;
     double* sums;           // [4][COLS] of x
     __device__ __forceinline__ explicit IntLds(unsigned char* lds)
@@ -307,7 +308,7 @@ __device__ __forceinline__ int int_task(const MomArgs& a, unsigned char* lds, in
         const double scale = __builtin_bit_cast(double, (unsigned long long)(1023 + fresh(by)) << 52);
         double sum[2] = {0.0, 0.0};
         float most = 0.f;
-        unsigned int last = 0u;
+        unsigned int last = 0u, deep = 0u;
         i4 out4[ND];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -326,7 +327,8 @@ __device__ __forceinline__ int int_task(const MomArgs& a, unsigned char* lds, in
 #pragma unroll
             for (int g = 0; g < ND; ++g) {
                 out4[g][q] = (int)dig[g];
-                if (g >= NB) last |= dig[g];
+                if (g == NB) last |= dig[g];
+                if (g > NB) deep |= dig[g];
             }
             then(q);
         }
@@ -335,20 +337,24 @@ __device__ __forceinline__ int int_task(const MomArgs& a, unsigned char* lds, in
         for (int g = 0; g < ND; ++g) *(i4*)(o + g * Sh::PLANE) = out4[g];
         const int room = BITS - 1 - fresh(by);
         const bool low = most > 0.f && most < ldexpf(0.98f, room - INT_LOW);
-        const unsigned long long some = __ballot(last != 0u);
+        const unsigned long long some = __ballot((last | deep) != 0u);
         const bool many = __builtin_popcountll(some) > INT_MANY;
-        stale = low || (many && last != 0u);
+        stale = low || (many && (last | deep) != 0u);
         // fewer than 16 samples say little about their column
         constexpr int Q0 = 64 * WAVE / COLS, Q1 = (64 * WAVE + 63) / COLS;
         const bool whole = k.skip <= 16 * Q0 && k.skip + k.rows >= 16 * Q1 + 16;
         marks = (__any(!(most < ldexpf(0.98f, room))) ? 1u : 0u)   // 0x7f7f.. of 0x8000..: every byte's digit is at most 127
                 | (__any(low) && whole ? 2u : 0u) | (many ? 4u : 0u);
         // a wave has four tiles' columns, side by side or around the end
+        auto tiles = [](unsigned long long items) {
+            const unsigned int t = (items & 0xffffull ? 1u : 0u) | (items & 0xffff0000ull ? 2u : 0u)
+                                   | (items & 0xffff00000000ull ? 4u : 0u) | (items & 0xffff000000000000ull ? 8u : 0u);
+            const unsigned int at_tile = t << 64 * WAVE % COLS / 16;
+            return (at_tile | at_tile >> Sh::TILES) & ((1u << Sh::TILES) - 1u);
+        };
         if (some != 0ull) {
-            const unsigned int tiles = (some & 0xffffull ? 1u : 0u) | (some & 0xffff0000ull ? 2u : 0u)
-                                       | (some & 0xffff00000000ull ? 4u : 0u) | (some & 0xffff000000000000ull ? 8u : 0u);
-            const unsigned int at_tile = tiles << 64 * WAVE % COLS / 16;
-            marks |= ((at_tile | at_tile >> Sh::TILES) & ((1u << Sh::TILES) - 1u)) << 4;
+            marks |= tiles(__ballot(last != 0u)) << 3;
+            if constexpr (NB + 1 < ND) marks |= tiles(__ballot(deep != 0u)) << 15;
         }
         if (!OFF && count) unsafeAtomicAdd(&at.sums[sum_at()], sum[0] + sum[1]);
     };
@@ -468,7 +474,7 @@ __device__ __forceinline__ int int_task(const MomArgs& a, unsigned char* lds, in
             constexpr bool EARLY = WAVE < 4;
             if constexpr (!EARLY && NA > 0) fetch_for(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
             __builtin_amdgcn_sched_barrier(0);
-            const unsigned int known = findings(), rare = known >> 4;
+            const unsigned int known = findings(), rare = known >> 3, deep = known >> 15;
             if (since > INT_FLUSH || (known & 7u)) break;   // (not the first)
             if (!OFF && WAVE == 0) taken += parked_block.rows;
             parked_block = req;
@@ -519,20 +525,32 @@ __device__ __forceinline__ int int_task(const MomArgs& a, unsigned char* lds, in
                 if (NB == 5) add_rest();
                 if constexpr (PARKS && !EARLY && I == 0) next_block();   // scalar work, between products
                 if ((rare >> R | rare >> C) & 1u) {
-                    rest = i4{0, 0, 0, 0};
+                    if (NB + NB - 1 >= INT_LEVELS) rest = i4{0, 0, 0, 0};
+                    const i4 a_last = fetch_digit(NB, R);
 #pragma unroll
-                    for (int g = NB; g < ND; ++g) {
-                        const i4 a_last = fetch_digit(g, R);
+                    for (int i = 0; i < NB; ++i) product(a_last, NB, op[B][i], i);
+                    const i4 b_last = fetch_digit(NB, C);
+                    if (2 * NB < INT_LEVELS) product(a_last, NB, b_last, NB);
 #pragma unroll
-                        for (int i = 0; i < NB; ++i) product(a_last, g, op[B][i], i);
+                    for (int i = 0; i < NB; ++i) product(op[A][i], i, b_last, NB);
+                    if (NB + NB - 1 >= INT_LEVELS) add_rest();
+                }
+                if constexpr (NB + 1 < ND) {
+                    if ((deep >> R | deep >> C) & 1u) {
+                        rest = i4{0, 0, 0, 0};
 #pragma unroll
-                        for (int i = NB; i < ND; ++i)
-                            if (g + i <= INT_LEVELS) product(a_last, g, fetch_digit(i, C), i);
-                        const i4 b_last = fetch_digit(g, C);
+                        for (int g = NB + 1; g < ND; ++g) {
+                            const i4 a_last = fetch_digit(g, R);
 #pragma unroll
-                        for (int i = 0; i < NB; ++i) product(op[A][i], i, b_last, g);
+                            for (int i = 0; i < ND; ++i)
+                                if (g + i <= INT_LEVELS) product(a_last, g, i < NB ? op[B][i < NB ? i : 0] : fetch_digit(i, C), i);
+                            const i4 b_last = fetch_digit(g, C);
+#pragma unroll
+                            for (int i = 0; i <= NB; ++i)
+                                if (g + i <= INT_LEVELS) product(i < NB ? op[A][i < NB ? i : 0] : fetch_digit(i, R), i, b_last, g);
+                        }
+                        add_rest();
                     }
-                    add_rest();
                 }
             });
             __builtin_amdgcn_sched_barrier(0);
