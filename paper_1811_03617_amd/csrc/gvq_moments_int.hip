@@ -31,9 +31,10 @@
 // for the four that park behind their products and four for those that do not park, a few of whose registers are in scratch.
 // 32 gradients of 138 M elements, d = 128, with the eigensolver: fp64 pipe 9.9 ms, here 7.0 (without the eighth level 6.2; three pairs
 // for every wave 7.9, spills; eight waves of 256 registers and every wave parking between its own products were slower yet);
-// 8 gradients of d = 768 16.5 -> 12.9 ms.  Data that go to the fp64 pipe after all (lognormal numbers): d = 128 9.9 -> 10.6 ms, in bf16
-// 5.4 -> 5.6, d = 160 3.0 -> 3.6, d = 768 16.5 -> 20.1; sizes that change by orders of magnitude every block 10.0 -> 10.8, where new
-// scales every time took 17 to 22 ms.
+// 8 gradients of d = 768 16.5 -> 12.9 ms.  Data that go to the fp64 pipe after all take longer than
+// in its own kernel (60 M elements, 8 gradients, Student's t with three degrees of freedom, or lognormal with sigma = 1): d = 128 1.55 -> 1.64 ms, in
+// bf16 1.54 -> 1.61, d = 160 2.04 -> 2.36, d = 768 8.8 -> 10.1 (with twice as many tries of new scales 1.75, 1.70, 2.45 and 10.6); sizes that
+// change by orders of magnitude every block 1.56 -> 1.64, where new scales every time took twice as long.
 #include <math.h>
 
 #include "gvq_moments.h"
@@ -437,7 +438,8 @@ __device__ __forceinline__ int int_task(const MomArgs& a, unsigned char* lds, in
     };
     const unsigned char* mine = lds + lane * 16;
     int flip = 0;
-    bool all = true;      // no column's largest number so far is known
+    bool all = done == 0;     // no column's largest number so far is known
+    bool again = done > 0;    // they are, but may be of samples much larger than this block's; its columns then say so
     // New scales take as long as a block and a half, a block on the fp64 pipe as long as 1.4: not worth it for fewer than four blocks.
     int spent = 0;
     while (todo > 0) {
@@ -447,7 +449,12 @@ __device__ __forceinline__ int int_task(const MomArgs& a, unsigned char* lds, in
         // parked with the scales it had, is parked again
         refresh(parked_block, all, lds + flip * Sh::BUF);
         all = false;
-        if (findings() & 7u) break;   // nor do new scales fit
+        if (findings() & 7u) {
+            if (!again) break;   // nor do new scales fit
+            again = false;
+            continue;
+        }
+        again = false;
         if constexpr (PARKS) load(req);
         i4 acc[NA > 0 ? NA : 1][INT_LEVELS];
 #pragma unroll
@@ -679,7 +686,7 @@ __device__ __forceinline__ void int_exactly(const MomArgs& a, unsigned char* lds
 }
 
 // Blocks go to the fp64 pipe when digits will not do for one with scales of its own, or new scales are asked for too often: that one,
-// and while the ones behind it are no better twice as many each time, up to 256.
+// and while the ones behind it are no better eight times as many each time, up to 512.
 template <int NT, bool BF16, bool OFF>
 __device__ __forceinline__ void int_chunk(const MomArgs& a, unsigned char* lds, int pa, int pb, int chunk, int chunks, double* out)
 {
@@ -704,13 +711,13 @@ __device__ __forceinline__ void int_chunk(const MomArgs& a, unsigned char* lds, 
     unsigned int taken = 0u;   // samples, counted by the first wave
     for (int done = 0, spell = 1; done < total;) {
         const int before = done;
-        done = int_waves<NT, BF16, OFF>(a, lds, pa, pb, range, done, spell > 1 ? 8 : 32, out, taken);
+        done = int_waves<NT, BF16, OFF>(a, lds, pa, pb, range, done, spell > 1 ? 4 : 8, out, taken);
         if (done == total) break;
         if (done - before >= 32) spell = 1;
         const int n = spell < total - done ? spell : total - done;
         int_exactly<NT, BF16, OFF>(a, lds, pa, pb, range, done, n, out, taken);
         done += n;
-        spell = spell < 256 ? 2 * spell : 256;
+        spell = spell < 512 ? 8 * spell : 512;
     }
     if (total == 0 && !a.accumulate)
         for (int i = tid; i < Sh::NPAIR * 256; i += INT_THREADS) out[i] = 0.0;

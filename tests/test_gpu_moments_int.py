@@ -231,3 +231,42 @@ def test_as_exact_products_summed_in_float64(name, d, dtype):
     # that of the 65 chunks 65; the covariance is a quotient, a product and a difference behind it; 8 are the reference's.
     bound = (4 * 65 + 65 + 4 + 8) * 2.0 ** -53 * most + 2.0 ** -50 * np.abs(np.outer(m, m))
     assert np.all(np.abs(C[0] - (G - np.outer(m, m))) <= bound)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,B", [(65, 60), (112, 60), (128, 60), (161, 40), (250, 40)])
+def test_long_tasks_that_change_pipes(d, B, dtype):
+    """Bases of one chunk each, up to 300 blocks a task: heavy tails keep to the fp64 pipe for long, an outlier in every gradient takes
+    a block or a few there, sizes that shrink for good leave it again.  A block lost, taken twice or mixed up is off by 1e-3."""
+    rng = np.random.default_rng(d)
+    L, lens = 34, 480 + 9 * (np.arange(B) % 13)
+    cuts = [0] + [int(c) for c in lens.cumsum()]
+    M = cuts[-1] * d - 1   # the last slice is not whole
+    xs = []
+    for g in range(3):
+        x = rng.standard_normal((cuts[-1], d))
+        for i in range(B):
+            at = x[cuts[i]:cuts[i + 1]]
+            if i % 3 == 0:
+                at[:] = rng.standard_t(3, at.shape)
+            elif i % 3 == 1:
+                at[100 + 64 * g, d // 2] = 1e4
+            else:
+                at[200:] *= 1e-5 if g == 2 else 1.0
+        xs.append(torch.from_numpy(x.astype(np.float32).reshape(-1)[:M]))
+    if dtype == "bf16":
+        xs = [x.to(torch.bfloat16) for x in xs]
+    times = [20, 7, 7]   # the shrunken sizes come last
+    b, C, n, mu = _fit([x for x, t in zip(xs, times) for _ in range(t)], M, d, cuts, dtype)
+    b.close()
+    X = [x.to(torch.float64).numpy()[: M // d * d].reshape(-1, d) for x in xs]
+    for i, (lo, hi) in enumerate(zip(cuts[:-1], cuts[1:])):
+        own = [x[lo:min(hi, M // d)] for x in X]
+        assert n[i] == L * len(own[0])
+        total = sum(t * (x.T @ x) for t, x in zip(times, own)) / n[i]
+        most = sum(t * (np.abs(x).T @ np.abs(x)) for t, x in zip(times, own)) / n[i]
+        m = sum(t * x.sum(0) for t, x in zip(times, own)) / n[i]
+        # n roundings one after the other at worst, a few more for the covariance, as many again for the reference
+        bound = (2 * n[i] + 16) * 2.0 ** -53 * (most + 2 * np.outer(np.abs(m), np.abs(m)))
+        assert np.all(np.abs(C[i] - (total - np.outer(m, m))) <= bound)
+        assert np.allclose(mu[i], m, rtol=1e-6, atol=1e-7 * max(np.abs(x).max() for x in own))
