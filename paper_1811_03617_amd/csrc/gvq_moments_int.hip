@@ -31,10 +31,11 @@
 // for the four that park behind their products and four for those that do not park, a few of whose registers are in scratch.
 // 32 gradients of 138 M elements, d = 128, with the eigensolver: fp64 pipe 9.9 ms, here 7.0 (without the eighth level 6.2; three pairs
 // for every wave 7.9, spills; eight waves of 256 registers and every wave parking between its own products were slower yet);
-// 8 gradients of d = 768 16.5 -> 12.9 ms.  Data that go to the fp64 pipe after all take longer than
-// in its own kernel (60 M elements, 8 gradients, Student's t with three degrees of freedom, or lognormal with sigma = 1): d = 128 1.55 -> 1.64 ms, in
-// bf16 1.54 -> 1.61, d = 160 2.04 -> 2.36, d = 768 8.8 -> 10.1 (with twice as many tries of new scales 1.75, 1.70, 2.45 and 10.6); sizes that
-// change by orders of magnitude every block 1.56 -> 1.64, where new scales every time took twice as long.
+// 8 gradients of d = 768 16.5 -> 12.9 ms.  Data that go to the fp64 pipe after all take up to a
+// tenth longer than in its own kernel, whose tasks are cut finer (60 M elements, 8 gradients, Student's t with three degrees of freedom, or lognormal with
+// sigma = 1): d = 128 1.55 -> 1.58 ms, in bf16 1.54 -> 1.55, d = 160 2.04 -> 2.18, d = 768 8.8 -> 9.8 (with twice as many tries of
+// new scales, and blocks parked whole between two barriers, 1.75, 1.70, 2.45 and 10.6); sizes that change by orders of
+// magnitude every block 1.56 -> 1.57, where new scales every time took twice as long.
 #include <math.h>
 
 #include "gvq_moments.h"
@@ -221,12 +222,13 @@ __device__ __forceinline__ void int_load(float (&x)[16], const IntBlock& k, unsi
 #pragma unroll
     for (int q = 0; q < 4; ++q) int_load_quad<BF16, OFF>(x, q, k, place, step);
 }
+template <int I0 = 0, int I1 = 16>
 __device__ __forceinline__ void int_mask(float (&x)[16], const IntBlock& k, unsigned int place)   // samples that do not count become zeros
 {
     if (k.rows < INT_NS) {
         const int r = 16 * int_place_quarter(fresh(place)) - k.skip;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = (unsigned int)(r + i) < (unsigned int)k.rows ? x[i] : 0.f;
+        for (int i = I0; i < I1; ++i) x[i] = (unsigned int)(r + i) < (unsigned int)k.rows ? x[i] : 0.f;
     }
 }
 
@@ -594,7 +596,7 @@ __device__ __forceinline__ int int_waves(const MomArgs& a, unsigned char* lds, i
     }
 }
 
-// Blocks `done` to done + n on the fp64 pipe: 64 rows of float64 in LDS.  The first block's samples are in the sums of x.
+// Blocks `done` to done + n on the fp64 pipe: 32 rows of float64 in either half of the LDS.  The first block's samples are in the sums of x.
 template <int NT, bool BF16, bool OFF>
 __device__ __forceinline__ void int_exactly(const MomArgs& a, unsigned char* lds, int pa, int pb, const IntRange& range, int done, int n, double* out,
                                             unsigned int& taken)
@@ -623,55 +625,87 @@ __device__ __forceinline__ void int_exactly(const MomArgs& a, unsigned char* lds
         row[i] = 16 * r;
         col[i] = 16 * c;
     }
-    double* const rows = (double*)lds;
-    // samples s and s + 4 of eight side by side: a lane reads its operands of two products at once (a product leaves no vector
-    // instruction room beside it; one by one: 138 M elements, d = 128, 32 gradients 11.1 ms)
-    d2* const to = (d2*)rows + 8 * int_place_quarter(place) * Sh::ROW + int_place_column(place);
-    const d2* const from = (const d2*)rows + (lane >> 4) * Sh::ROW + (lane & 15);
+    // Half a block at a time, in turn in either half of the rows: every thread parks eight of its item's 16 samples for the next
+    // products while other waves multiply.  Samples s and s + 4 of eight side by side: a lane reads its operands of two products at once
+    // (a product leaves no vector instruction room beside it; one by one: 138 M elements, d = 128, 32 gradients 11.1 ms).
+    constexpr int HALF = INT_NS / 4 * Sh::ROW;   // pairs of doubles
+    d2* const rows = (d2*)lds;
+    d2* const to = rows + 4 * int_place_quarter(place) * Sh::ROW + int_place_column(place);
+    const d2* const from = rows + (lane >> 4) * Sh::ROW + (lane & 15);
     IntBlocks blocks(a, range, done, step);
     blocks.next(a, range, step);
     IntBlock block = blocks.ahead;
     float x[16];
+    double sum = 0.0;   // of this thread's samples, but the first block's
     if (parks) int_load<BF16, OFF>(x, block, place, step);
+    auto park = [&](auto half, const IntBlock& k, bool count) {
+        constexpr int H = decltype(half)::value;
+        int_mask<8 * H, 8 * H + 8>(x, k, place);
+        double part[2] = {0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int s = 8 * H + i;
+            const d2 v = {(double)x[s], (double)x[s + 4]};
+            to[H * HALF + i * Sh::ROW] = v;
+            part[0] += v[0];
+            part[1] += v[1];
+        }
+        if (!OFF && count) sum += part[0] + part[1];
+    };
+    auto load = [&](auto half, const IntBlock& k) {
+        constexpr int H = decltype(half)::value;
+        int_load_quad<BF16, OFF>(x, 2 * H, k, place, step);
+        int_load_quad<BF16, OFF>(x, 2 * H + 1, k, place, step);
+    };
+    constexpr std::integral_constant<int, 0> lower;
+    constexpr std::integral_constant<int, 1> upper;
     // two sums a pair, half as long: the work-groups of gvq_moments.hip, two a compute unit, have half as many samples
     d4 acc[NP][2];
 #pragma unroll
     for (int i = 0; i < NP; ++i) acc[i][0] = acc[i][1] = d4{0.0, 0.0, 0.0, 0.0};
-    for (int k = 0; k < n; ++k) {
-        if (parks) {
-            int_mask(x, block, place);
-            double sum[2] = {0.0, 0.0};
+    auto multiply = [&](auto half) {
+        auto pairs_of = [&](auto pairs) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int s = i < 4 ? i : i + 4;
-                const d2 v = {(double)x[s], (double)x[s + 4]};
-                to[i * Sh::ROW] = v;
-                sum[0] += v[0];
-                sum[1] += v[1];
-            }
-            if (!OFF && k > 0) unsafeAtomicAdd(&at.sums[int_place_quarter(place) * Sh::COLS + int_place_column(place)], sum[0] + sum[1]);
-        }
-        if (!OFF && wave == 0) taken += block.rows;
-        __syncthreads();
-        blocks.next(a, range, step);
-        block = blocks.ahead;
-        if (parks) int_load<BF16, OFF>(x, block, place, step);
-        auto multiply = [&](auto pairs) {
-#pragma unroll 4
-            for (int g = 0; g < INT_NS / 8; ++g) {
+            for (int g = 0; g < INT_NS / 16; ++g) {
 #pragma unroll
                 for (int i = 0; i < decltype(pairs)::value; ++i) {
                     if (i > 0) __builtin_amdgcn_sched_barrier(6);   // pair by pair: 10.6 -> 10.4 ms
-                    const d2 u = from[4 * g * Sh::ROW + row[i]], v = from[4 * g * Sh::ROW + col[i]];
+                    const d2* const at = from + decltype(half)::value * HALF + 4 * g * Sh::ROW;
+                    const d2 u = at[row[i]], v = at[col[i]];
                     acc[i][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[0], v[0], acc[i][0], 0, 0, 0);
                     acc[i][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[1], v[1], acc[i][1], 0, 0, 0);
                 }
             }
         };
-        if (MORE && more) multiply(std::integral_constant<int, NP>{});
-        else multiply(std::integral_constant<int, NF>{});
-        __syncthreads();   // everyone is done with the block's rows
+        if (MORE && more) pairs_of(std::integral_constant<int, NP>{});
+        else pairs_of(std::integral_constant<int, NF>{});
+    };
+    blocks.next(a, range, step);
+    IntBlock req = blocks.ahead;
+    if (parks) {
+        park(lower, block, false);
+        load(lower, req);
     }
+    __syncthreads();
+    for (int k = 0; k < n; ++k) {
+        if (parks) {
+            park(upper, block, k > 0);
+            load(upper, req);
+        }
+        multiply(lower);
+        if (!OFF && wave == 0) taken += block.rows;
+        block = req;
+        blocks.next(a, range, step);
+        req = blocks.ahead;
+        __syncthreads();   // the upper half is there, everyone is done with the lower one
+        if (parks) {
+            park(lower, block, k + 1 < n);
+            load(lower, req);
+        }
+        multiply(upper);
+        __syncthreads();
+    }
+    if (!OFF && parks) unsafeAtomicAdd(&at.sums[int_place_quarter(place) * Sh::COLS + int_place_column(place)], sum);
     const bool stored = a.accumulate != 0 || done > 0;
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
