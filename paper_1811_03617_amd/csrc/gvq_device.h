@@ -168,8 +168,8 @@ __device__ __forceinline__ int64_t grid_wave()
 __device__ __forceinline__ int64_t grid_waves() { return (int64_t)gridDim.x * WAVES_PER_WG; }
 
 // p / il for groups of il super-tiles: a shift for the powers of two that the kernels take by default (a 64-bit division is
-// 130 instructions, and a wave that waits for it has asked for nothing yet; decompress of 138 M bf16 elements 107.3 -> 105.4 us, a
-// step at d = 768, k = 96 1173 -> 1163, eight ring segments of 7.6 M elements 165.9 -> 164.9; the loss monitor gains nothing).
+// 130 instructions, and a wave that waits for it has asked for nothing yet; a step at d = 768, k = 96 1168 -> 1158 us; steps in bf16,
+// ring segments and the loss monitor are the same within what two runs differ).
 __device__ __forceinline__ int64_t il_group(int64_t p, int il)
 {
     return (il & (il - 1)) == 0 ? p >> __builtin_ctz(il) : p / il;
